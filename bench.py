@@ -412,7 +412,8 @@ def run_single(bisim, L, args, engine, mlp=None, trace=True):
         log(f"warmup {w}: #It={st.iterations} blocks={st.blocks} t_alg={st.t_alg_ms:.1f} ms")
     if engine == 0:  # what the automatic choice (cached tuner) resolved to, kept fixed
         engine, grid = h.run_config()
-        h.set_option(bisim.OPT_ENGINE, engine)
+        if getattr(args, "algorithm", 3) == 3:  # engine 3 takes Algorithm 2 only by itself
+            h.set_option(bisim.OPT_ENGINE, engine)
         h.set_option(bisim.OPT_GRID, grid)
         log(f"automatic engine choice: engine {engine}, {grid} workgroups")
     if engine == 2:  # sample ~200 iterations' phase kernels per step

@@ -144,24 +144,31 @@ const char* bisim_last_error(void);
 
 /*
  * bisim_set_option — per-handle settings.
- *   BISIM_OPT_ENGINE        0 = automatic (default: engine 2 for LTSs under
- *                           200,000 states, the learned policy, Algorithm 2,
- *                           traced or limited runs; otherwise the fastest of
- *                           engines 2 and 3 at a few grid sizes, timed on the
- *                           LTS's first 96 iterations once per device and size
- *                           class and cached in the file BISIM_TUNE_CACHE, else
+ *   BISIM_OPT_ENGINE        0 = automatic (default: engine 3 for Algorithm 3
+ *                           with the plain policy, and for Algorithm 2 up to
+ *                           16,384 states; engine 2 for the learned policy,
+ *                           traced, profiled or limited runs and states of
+ *                           more than 64 distinct actions; from 200,000 states
+ *                           on, engine 3's grid is timed on the LTS's first
+ *                           iterations once per device and size class and
+ *                           cached in the file BISIM_TUNE_CACHE, else
  *                           $HOME/.cache/bisim_tune.txt), 1 = one cooperative persistent
  *                           launch per fixpoint (grid barriers between
  *                           phases), 2 = one kernel per phase, launched in
  *                           batches with a device-side done flag, each
- *                           scanning all states, 3 = three kernels per
- *                           iteration over member lists (a refinable
+ *                           scanning all states, 3 = member lists (a refinable
  *                           partition): work per iteration follows the
  *                           splitter's members and in-transitions and the
- *                           states they touch, not n; Algorithm 3 with the
- *                           plain policy only (else BISIM_E_UNSUPPORTED at
- *                           coarsest_partition); about 96 more bytes of
- *                           device memory per state, allocated on first use.
+ *                           states they touch, not n; one workgroup carries
+ *                           out the run in rounds that decide many
+ *                           iterations at a time (those that split nothing),
+ *                           and three grid-wide kernels carry out the
+ *                           iterations of large splitters (every iteration of
+ *                           traced, counted and profiled runs); Algorithm 3
+ *                           with the plain policy only (else
+ *                           BISIM_E_UNSUPPORTED at coarsest_partition); about
+ *                           96 more bytes of device memory per state,
+ *                           allocated on first use.
  *   BISIM_OPT_COUNT_WORK    0 (default) or 1: engine 3 accumulates work totals
  *                           over the run (bisim_get_work).
  *   BISIM_OPT_FIRST_SPLITTER  -1 (default) or a block label of the

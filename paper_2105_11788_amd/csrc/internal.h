@@ -99,12 +99,16 @@ __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   return v;
 }
 
+// inclusive prefix sum over the wave: four shifts within the rows of 16 lanes
+// and two row broadcasts on the vector ALU (a shuffle costs an LDS round trip
+// per step)
 __device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    uint32_t t = (uint32_t)__shfl_up((int)v, d, kWave);
-    if ((int)lane() >= d) v += t;
-  }
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return v;
 }
 
@@ -305,6 +309,10 @@ bisim_status signature_run(bisim_lts* h, int32_t* block_id, bool hybrid);
 bisim_status lists_alloc(bisim_lts* h);
 bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals);
 void lists_free(bisim_lts* h);
+// the same engine by rounds of one workgroup (splitters that split nothing
+// decided ahead of their turn); rounds_apply says whether a run may take them
+bool rounds_apply(const bisim_lts* h);
+bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool rcpp);
 }  // namespace bisim
 
 struct bisim_mlp;

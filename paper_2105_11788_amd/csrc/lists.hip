@@ -34,6 +34,11 @@
 //                of Algorithm 3).  Marks, touched bits and counts are
 //                cleared.
 //
+// These three kernels carry out one iteration each time.  A run without a
+// trace, counters or kernel timing goes by rounds instead (k_rounds below,
+// rounds_dev.h): one workgroup decides many iterations at a time and asks for
+// the three kernels where a splitter is large.
+//
 // Every per-iteration set (touched states, listed segments, split states) is
 // a list built with wave-aggregated atomics, so no kernel scans anything of
 // size n.  Iterations are captured in a hipGraph of kGraphIters iterations
@@ -41,7 +46,7 @@
 // their position in the graph to) and replayed until the done flag is set.
 // The splitter sequence, the split counts and the partitions are those of
 // the other engines.  States with more than 64 actions use the mark-word
-// offsets of the preprocessing.
+// offsets of the preprocessing (and never the rounds).
 #include <hip/hip_ext.h>
 
 #include <cstring>
@@ -49,6 +54,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "rounds_dev.h"
 
 namespace bisim {
 namespace {
@@ -77,6 +83,8 @@ struct LArgs {
   uint64_t* sf;   // split states
   uint64_t* ub;   // unstable labels
   uint64_t* us;   // summary of ub
+  uint64_t *qb, *qs;  // rounds: unstable labels without a verdict and their summary (else null)
+  int gated;      // rounds: an iteration runs only when one was asked for (state.v[7])
   uint64_t* nlw;  // bids
   int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc;
   int32_t* tcn;  // per label: members first touched this iteration (0 between iterations)
@@ -129,6 +137,12 @@ __device__ __forceinline__ void set_unstable(const LArgs& a, uint32_t b) {
   const uint32_t w = b >> 6;
   const uint64_t old = atomicOr((unsigned long long*)&a.ub[w], 1ull << (b & 63));
   if (old == 0) atomicOr((unsigned long long*)&a.us[w >> 6], 1ull << (w & 63));
+  if (a.qb) label_set(a.qb, a.qs, b);
+}
+
+// nothing to do: the run is over, or no grid-wide iteration was asked for
+__device__ __forceinline__ bool idle(const LArgs& a, uint32_t done) {
+  return done || (a.gated && a.ctl->state.v[7] == 0);
 }
 
 __device__ __forceinline__ void count_work(const LArgs& a, uint32_t i, uint64_t v) {
@@ -172,7 +186,7 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   const bool lane_first = lane() < a.mpw && i_first < kWave;
   const uint32_t pf_lo = lane_first ? pc[4 + 2 * i_first] : 0u;
   const uint32_t pf_hi = lane_first ? pc[5 + 2 * i_first] : 0u;
-  if (done) return;
+  if (idle(a, done)) return;
   const bool over = k + 1 > a.iter_cap;
   if (C0 == kNone || over) {  // the final pass, or the iteration cap
     if (p.gtid == 0) {
@@ -334,7 +348,7 @@ __global__ void __launch_bounds__(kLT) k_l_compare(LArgs a, uint32_t kofs) {
   const uint32_t par = kofs & 1;
   const uint32_t nT = min(a.ctl->cntT[par].v[0], a.n);
   const uint32_t nL = a.ctl->cntC[par].v[0];
-  if (done) return;
+  if (idle(a, done)) return;
   const GPart p = gpart();
   const uint64_t epoch = (uint64_t)(k + 1) << 32;
   const uint32_t n = a.n;
@@ -515,7 +529,7 @@ __global__ void __launch_bounds__(kLT) k_l_split(LArgs a, uint32_t kofs) {
   const uint32_t nS = min(a.ctl->cntS[par].v[0], a.n);
   const uint32_t nT = min(a.ctl->cntT[par].v[0], a.n);
   const uint32_t C = a.ctl->state.v[3];
-  if (done) return;
+  if (idle(a, done)) return;
   const GPart p = gpart();
   if (p.gtid == 0) {
     a.ctl->cand[par].v[0] = kNone;  // the candidate slot of iteration k + 2
@@ -607,6 +621,68 @@ __global__ void k_l_zero_cnt(LArgs a) {
   for (uint32_t b = p.gtid; b < a.n; b += p.gthreads) a.cnt[b] = 0;
 }
 
+// ---------------------------------------------------------------------------
+// rounds: the loop by one workgroup (rounds_dev.h), until the run is over or
+// a splitter is large enough for the grid.  The three kernels above then
+// carry out that iteration, and the next launch goes on after it.
+// ---------------------------------------------------------------------------
+// Workgroup size: 1024 threads against 512 and 256, uniform LTS of 20k states
+// 30.6 / 34.8 / 37.2 ms, planted quotient of 1.03M states 336 / 366 / 447 ms
+// (a round's transitions are spread over all waves; its barriers cost less
+// than the loads they separate).
+constexpr int kRWG = 1024;
+constexpr uint32_t kSetupN = 16384;     // up to here the workgroup builds the member lists itself
+// A splitter whose marks fit neither the table nor LDS is the grid's: its
+// iteration takes about 32 us there (four launches), 40-112 us by the
+// workgroup, whose few waves wait for each transition's mark word in memory
+// (planted quotient of 1.03M states: 336 ms, with the workgroup taking up to
+// 8192 / 49152 transitions 444 / 937 ms).
+constexpr uint32_t kGridEdges = 2048;
+
+template <class MaskT, bool kBm>
+__global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, uint32_t* pf,
+                                                 const int32_t* start, uint32_t lds_bytes) {
+  extern __shared__ uint64_t lds[];
+  __shared__ RoundsShared<kRWG> sh;
+  const uint32_t done = ctl->state.v[1], entered = ctl->state.v[8];
+  const uint32_t it = ctl->state.v[6] + (ctl->state.v[7] ? 1u : 0u);
+  if (done) return;
+  uint32_t rc = kRoundsDone, C = kNone;
+  if (!entered) {
+    if (start) {
+      if (!rounds_setup<MaskT, kRWG>(a, sh, start, false)) rc = kRoundsBad;
+    } else {
+      const uint32_t nw = (a.n + 63u) >> 6, nsw = (nw + 63u) >> 6;
+      for (uint32_t q = threadIdx.x; q < nw; q += kRWG) a.qb[q] = a.ub[q];
+      for (uint32_t q = threadIdx.x; q < nsw; q += kRWG) a.qs[q] = a.us[q];
+      __syncthreads();
+    }
+  }
+  if (rc == kRoundsDone)
+    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it, C);
+  if (threadIdx.x != 0) return;
+  if (rc == kRoundsDone && sh.it > a.iter_cap) rc = kRoundsCap;
+  ctl->state.v[7] = 0;
+  ctl->state.v[8] = 1;
+  if (rc == kRoundsGrid) {
+    // one iteration with splitter C: counters and the prefetch slot as the
+    // mark kernel of an even launch position expects them
+    ctl->state.v[6] = sh.it - 1;  // the number of C's iteration
+    ctl->state.v[7] = 1;
+    ctl->cand[0].v[0] = C;
+    ctl->cand[1].v[0] = kNone;
+    ctl->cntT[0].v[0] = 0;
+    ctl->cntS[0].v[0] = 0;
+    ctl->cntC[0].v[0] = 0;
+    pf[3] = 0;
+    return;
+  }
+  ctl->state.v[0] = rc == kRoundsCap ? a.iter_cap + 1 : sh.it + 1;  // with the final pass
+  ctl->state.v[1] = 1;
+  if (rc == kRoundsCap) ctl->state.v[2] = 1;
+  if (rc == kRoundsBad) ctl->state.v[4] = 1;
+}
+
 template <class T>
 bisim_status lalloc(T** p, size_t count, hipStream_t s) {
   if (*p) return BISIM_OK;
@@ -649,14 +725,14 @@ bisim_status lists_alloc(bisim_lts* h) {
   return BISIM_OK;
 }
 
-// The iteration loop of engine 3; the common run initialisation has been
-// enqueued (block[] = the start partition, bitmaps, bids, control block).
-bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
+// the kernels' arguments, and the refinable partition of the start partition
+static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_totals, bool fill,
+                                LArgs& a) {
   BISIM_TRY(lists_alloc(h));
   hipStream_t st = h->stream;
   const uint32_t n = (uint32_t)h->n;
   bisim_lists& L = h->lists;
-  LArgs a{};
+  a = LArgs{};
   a.n = n;
   a.uniform = h->uniform;
   a.nwd = ((uint64_t)n + 63) / 64;
@@ -709,6 +785,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   a.trace_nsplit = h->trace_nsplit;
   a.trace_cap = (uint32_t)h->trace_cap;
 
+  if (!fill) return BISIM_OK;
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   int64_t gi = ((int64_t)n + kLT - 1) / kLT;
   gi = gi > cu * 8 ? cu * 8 : (gi < 1 ? 1 : gi);
@@ -722,7 +799,19 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   hipLaunchKernelGGL(k_l_fill, dim3((unsigned)gi), dim3(kLT), 0, st, a);
   hipLaunchKernelGGL(k_l_zero_cnt, dim3((unsigned)gi), dim3(kLT), 0, st, a);
   BISIM_TRY_HIP(hipGetLastError());
+  return BISIM_OK;
+}
 
+// The iteration loop of engine 3, one iteration at a time (traced, counted
+// and profiled runs, and what the rounds do not take); the common run
+// initialisation has been enqueued (block[] = the start partition, bitmaps,
+// bids, control block).
+bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
+  hipStream_t st = h->stream;
+  bisim_lists& L = h->lists;
+  LArgs a;
+  BISIM_TRY(lists_setup(h, cap, count_work_totals, true, a));
+  const int cu = h->num_cu > 0 ? h->num_cu : 1;
   const int grid = h->grid > 0 ? h->grid : cu * 8;
   h->run_grid = grid;
   const bool prof = h->profile_every > 0;
@@ -840,6 +929,106 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   else
     for (uint64_t& w : h->lists_work) w = 0;
   return BISIM_OK;
+}
+
+bool rounds_apply(const bisim_lts* h) {
+  return h->uniform && (uint32_t)h->n <= kRoundsMaxN && h->trace_cap == 0 &&
+         h->first_splitter < 0 && h->profile_every == 0 && !h->count_work;
+}
+
+template <class MaskT, bool kBm>
+static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* start, bool rcpp,
+                                  uint32_t cap, uint32_t lds_bytes) {
+  hipStream_t st = h->stream;
+  const uint32_t n = (uint32_t)h->n;
+  bisim_lists& L = h->lists;
+  RoundsArgs<MaskT> a{};
+  a.n = n;
+  a.iter_cap = cap;
+  a.rcpp = rcpp ? 1 : 0;
+  a.mean_deg = (uint32_t)(n ? (h->m + n - 1) / n : 1);
+  a.grid_edges = !rcpp && !start && h->m >= (int64_t)kGridEdges ? kGridEdges : 0;
+  a.in_ptr = h->in_ptr;
+  a.in_src = h->in_src;
+  a.in_ord = h->in_ord;
+  a.blk = h->block;
+  a.perm = L.perm;
+  a.pos = L.pos;
+  a.bs = L.bs;
+  a.be = L.be;
+  a.pin = L.pin;
+  a.mw = reinterpret_cast<MaskT*>(h->mw);
+  a.cnt = L.cnt;
+  a.fc = L.fc;
+  a.gc = L.gc;
+  a.nlb = h->nlw;
+  a.tmp64 = L.tmp64;
+  a.sf = h->sb;
+  a.ts = L.ts;
+  a.tb = L.tbk;
+  a.lb = L.lb;
+  a.llo = L.lo;
+  a.lsz = L.lh;
+  a.ss = L.ss;
+  a.sbk = L.sbk;
+  a.sr = L.sr;
+  a.sfi = L.sfi;
+  a.sne = L.sne;
+  a.sps = L.sps;
+  a.sse = L.sse;
+  a.ub = h->ub;
+  a.us = h->us;
+  a.qb = l.qb;
+  a.qs = l.qs;
+  const auto kern = k_rounds<MaskT, kBm>;
+  BISIM_TRY_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)lds_bytes));
+  const int cu = h->num_cu > 0 ? h->num_cu : 1;
+  const int grid = h->grid > 0 ? h->grid : cu * 4;
+  h->run_grid = a.grid_edges ? grid : 1;
+  hipLaunchKernelGGL(kern, dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start, lds_bytes);
+  BISIM_TRY_HIP(hipGetLastError());
+  uint64_t launched = 0;
+  for (uint32_t reps = 1;; reps = reps < 16 ? reps * 2 : reps) {
+    BISIM_TRY_HIP(hipMemcpyAsync(&h->ctl_host->state, &h->ctl->state, sizeof(Line),
+                                 hipMemcpyDeviceToHost, st));
+    BISIM_TRY_HIP(hipStreamSynchronize(st));
+    if (h->ctl_host->state.v[1] || launched > (uint64_t)cap + 1) return BISIM_OK;
+    for (uint32_t r = 0; r < reps; ++r) {
+      hipLaunchKernelGGL(k_l_mark, dim3(grid), dim3(kLT), 0, st, l, 0u);
+      hipLaunchKernelGGL(k_l_compare, dim3(grid), dim3(kLT), 0, st, l, 0u);
+      hipLaunchKernelGGL(k_l_split, dim3(grid), dim3(kLT), 0, st, l, 0u);
+      hipLaunchKernelGGL(kern, dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start,
+                         lds_bytes);
+    }
+    launched += reps;
+    BISIM_TRY_HIP(hipGetLastError());
+  }
+}
+
+// The run by rounds; the common run initialisation has been enqueued.
+bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool rcpp) {
+  LArgs l;
+  const uint32_t n = (uint32_t)h->n, nw = (n + 63) / 64;
+  const bool own = n <= kSetupN;
+  BISIM_TRY(lists_setup(h, cap, false, !own, l));
+  l.qb = h->lt;
+  l.qs = h->lt + nw;
+  l.gated = 1;
+  l.trace_cap = 0;
+  int lds_max = 0;
+  BISIM_TRY_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock,
+                                      h->device));
+  const uint32_t lds = (uint32_t)(lds_max - (int)sizeof(RoundsShared<kRWG>) - 64) & ~63u;
+  const bool bm =
+      rounds_bitmap_bytes(n) + split_bytes<kRWG>() + table_bytes<uint64_t>(4096) <= lds;
+  const int32_t* s0 = own ? start : nullptr;
+  for (uint64_t& w : h->lists_work) w = 0;
+  if (h->max_ranks <= 32)
+    return bm ? rounds_launch<uint32_t, true>(h, l, s0, rcpp, cap, lds)
+              : rounds_launch<uint32_t, false>(h, l, s0, rcpp, cap, lds);
+  return bm ? rounds_launch<uint64_t, true>(h, l, s0, rcpp, cap, lds)
+            : rounds_launch<uint64_t, false>(h, l, s0, rcpp, cap, lds);
 }
 
 void lists_free(bisim_lts* h) {

@@ -381,13 +381,14 @@ bisim_status count_labels(bisim_lts* h, const int32_t* block, int64_t* out) {
   return BISIM_OK;
 }
 
-static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id);
+static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id, bool chosen);
 
 namespace {
 // ---------------------------------------------------------------------------
 // automatic engine choice: a cached tuner over (engine, grid)
 // ---------------------------------------------------------------------------
-constexpr int32_t kTuneMinStates = 200000;  // smaller LTSs: per-phase kernels, no trials
+constexpr int32_t kTuneMinStates = 200000;  // smaller LTSs: no trials
+constexpr int32_t kRcppRoundsStates = 16384;
 constexpr int64_t kTuneIters = 96;          // iterations per trial
 
 std::string lts_tune_key(const bisim_lts* h) {
@@ -400,7 +401,7 @@ std::string lts_tune_key(const bisim_lts* h) {
   for (int64_t v = h->n; v > 1; v >>= 1) ++ln;
   for (int64_t v = h->m; v > 1; v >>= 1) ++lm;
   char buf[256];
-  snprintf(buf, sizeof buf, "lts_%s_cu%d_n%d_m%d_u%d", arch.c_str(), h->num_cu, ln, lm,
+  snprintf(buf, sizeof buf, "lts_rounds_%s_cu%d_n%d_m%d_u%d", arch.c_str(), h->num_cu, ln, lm,
            h->uniform);
   return buf;
 }
@@ -444,20 +445,32 @@ void lts_tune_store(const std::string& key, int engine, int grid, float us) {
 }
 }  // namespace
 
-// Engine and grid of an automatic run: the per-phase kernels for small LTSs
-// (and for the learned policy, Algorithm 2, traced runs and the
-// allocation-free entry point); otherwise the cached choice for this device
-// and size class, else the fastest of a few candidates timed on the first
-// kTuneIters iterations of this LTS (each timed twice, the second kept).
+// Engine and grid of an automatic run.  Engine 3 (rounds) for Algorithm 3
+// with the plain policy: it carries out one iteration where engine 2 carries
+// out eight, and is ahead from 5 states on (uniform LTS of 20k states: 35 ms
+// against 256 ms).  Engine 2 for the learned policy, traced, capped and
+// profiled runs, states of more than 64 actions, and the allocation-free
+// entry point, whose region does not hold the member lists.  Algorithm 2
+// takes the rounds while its mark words fit one workgroup's LDS; beyond, a
+// large splitter would need the grid, whose kernels run Algorithm 3 only.
+// From kTuneMinStates on the grid of the grid-wide iterations is the cached
+// choice for this device and size class, else the fastest of a few candidates
+// timed on the first kTuneIters iterations of this LTS (each timed twice, the
+// second kept).
 static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   *engine = 2;
   *grid = h->grid;
   const bool learned = h->policy == 1 && h->policy_w;
-  if (h->n < kTuneMinStates || learned || h->algorithm == 2 || h->trace_cap > 0 ||
-      h->first_splitter >= 0 || h->iter_limit > 0 || h->profile_every > 0 || arena_active() ||
-      h->start_override)
+  if (learned || h->iter_limit > 0 || arena_active() || !rounds_apply(h)) return BISIM_OK;
+  if (h->algorithm == 2) {
+    if (h->n <= kRcppRoundsStates) *engine = 3;
     return BISIM_OK;
+  }
+  if (h->n < kTuneMinStates || h->start_override) {
+    *engine = 3;
+    return BISIM_OK;
+  }
   const std::string key = lts_tune_key(h);
   int e = 0, g = 0;
   if (lts_tune_lookup(key, &e, &g)) {
@@ -468,7 +481,7 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   struct Cand {
     int engine, grid;
   };
-  const Cand cands[] = {{2, cu * 4}, {2, cu * 8}, {2, cu * 16}, {3, cu * 4}, {3, cu * 8}};
+  const Cand cands[] = {{3, cu * 4}, {3, cu * 8}};
   const int saved_engine = h->engine, saved_grid = h->grid;
   const int64_t saved_limit = h->iter_limit;
   float best = 1e30f;
@@ -480,7 +493,7 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
     h->iter_limit = kTuneIters;
     float us = 0.f;
     for (int rep = 0; rep < 2; ++rep) {
-      const bisim_status r = refine_run_impl(h, nullptr);
+      const bisim_status r = refine_run_impl(h, nullptr, true);
       if (r != BISIM_OK && r != BISIM_E_ITERCAP) {
         rc = r;
         break;
@@ -509,7 +522,7 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
 bisim_status refine_run(bisim_lts* h, int32_t* block_id) {
   if (h->engine != 0) {
     h->run_engine = h->engine;
-    return refine_run_impl(h, block_id);
+    return refine_run_impl(h, block_id, false);
   }
   int engine = 2, grid = 0;
   BISIM_TRY(choose_engine(h, &engine, &grid));
@@ -517,13 +530,14 @@ bisim_status refine_run(bisim_lts* h, int32_t* block_id) {
   h->engine = engine;
   h->grid = grid;
   h->run_engine = engine;
-  const bisim_status rc = refine_run_impl(h, block_id);
+  const bisim_status rc = refine_run_impl(h, block_id, true);
   h->engine = 0;
   h->grid = saved_grid;
   return rc;
 }
 
-static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id) {
+// chosen: the engine is this library's choice, not the caller's
+static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id, bool chosen) {
   hipStream_t st = h->stream;
   const int32_t n = h->n;
   const bool learned = h->policy == 1 && h->policy_w;
@@ -563,7 +577,7 @@ static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id) {
     first = (uint32_t)h->first_splitter;
   }
   const int engine = h->engine == 0 ? 2 : h->engine;  // per-phase kernels: the default
-  if (engine == 3 && (learned || rcpp)) {
+  if (engine == 3 && (learned || (rcpp && !chosen))) {
     set_error("coarsest_partition: the member-list engine runs Algorithm 3 with the plain "
               "splitter policy only");
     return BISIM_E_UNSUPPORTED;
@@ -578,7 +592,9 @@ static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id) {
   const size_t lds = learned ? mlp_lds_floats(kPolicyF) * sizeof(float) : 0;
   std::vector<uint32_t> sampled;
   std::vector<hipEvent_t> sample_start;
-  if (engine == 3) {
+  if (engine == 3 && rounds_apply(h)) {
+    BISIM_TRY(rounds_run(h, (uint32_t)cap, start, rcpp));
+  } else if (engine == 3) {
     BISIM_TRY(lists_loop(h, (uint32_t)cap, h->count_work != 0));
   } else if (engine == 1) {
     int per_cu = 0;

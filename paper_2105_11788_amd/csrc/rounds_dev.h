@@ -1,0 +1,1004 @@
+// The refinement loop of Algorithm 3 (section 4) by one workgroup, with the
+// iterations that split nothing decided ahead of their turn.
+//
+// An iteration picks the smallest unstable label C, and most of them split
+// nothing (about 85-95 % on the generated LTSs).  That verdict keeps: if no
+// block holds two states with different marks under C, then no refinement of
+// those blocks does either, so it stands until C itself loses a member.  A
+// round therefore takes the next labels that are unstable and have no verdict
+// (up to kCand, in label order), marks all of them side by side in one hash
+// table keyed by (candidate, source), and checks every touched block against
+// its leader.  Labels found stable lose their bit in Q (unstable, no verdict)
+// and keep their bit in U (unstable).  When the smallest label left in Q
+// splits something, every label of U before it is an iteration without a
+// split (counted, bit cleared), and its own iteration is carried out from the
+// marks the table already holds.  The splitter sequence, the partitions and
+// the iteration count are those of the lock-step loop.
+//
+// Why a workgroup and not the grid: an iteration is a chain of dependent
+// steps over a few hundred transitions.  A barrier costs well under 0.1 us in
+// a workgroup and 2.5-3 us as a kernel boundary, and with the verdicts taken
+// side by side one CU has enough lanes for a round's transitions.
+//
+// Bound: the chain of a round's dependent steps, about 9 us when something
+// splits (uniform LTS of 20k states, 3,464 rounds for 27,089 iterations):
+// candidates 1.6, members 1.1, transitions 1.8, comparison 1.1, verdicts 0.7,
+// split list 1.1, split 2.3 (four trips to the L2 and ten barriers among
+// them).  Against two grid-wide kernels per iteration: uniform LTS of 20k
+// states 252 -> 31 ms, Kripke structure of 1000 states 14.1 -> 3.4 ms, 25k
+// states with as many actions as transitions 151 -> 7.2 ms, planted quotient
+// of 1.03M states 748 -> 348 ms (load and read-back included).
+//
+// The partition is a refinable partition: perm lists the states block by
+// block, block b (a label, its smallest member) owns perm[bs[b] .. be[b]),
+// and pin[p] is the in-transition range of perm[p].  A split moves the
+// split-off states to the tail of the range.
+#pragma once
+
+#include <stdint.h>
+
+#include "internal.h"
+
+namespace bisim {
+
+constexpr uint32_t kCand = 32;       // candidates per round (at most a wave's lanes)
+constexpr uint32_t kKeyBits = 27;    // state bits of a table key
+constexpr uint32_t kRoundsMaxN = (1u << kKeyBits) - 1;  // so that no key is kNone
+constexpr uint32_t kListCap = 64;    // listed blocks kept in LDS
+constexpr uint32_t kScanU = 4;       // states or transitions in flight per thread
+// transitions per thread and round
+template <int WG>
+constexpr uint32_t edges_per_thread() { return WG >= 1024 ? 2 : 4; }
+// split states that are moved by the tables in LDS (one per thread)
+template <int WG>
+constexpr uint32_t small_split() { return WG < 256 ? WG : 256; }
+
+// results of rounds_loop
+constexpr uint32_t kRoundsDone = 0, kRoundsGrid = 1, kRoundsBad = 2, kRoundsCap = 3;
+
+// One instance; per-state arrays start at its first state, state ids in
+// in_src are shifted by s0.
+template <class MaskT>
+struct RoundsArgs {
+  uint32_t n, s0;
+  uint32_t iter_cap;
+  uint32_t rcpp;        // Algorithm 2: one mark per state, C not re-marked
+  uint32_t grid_edges;  // estimated in-transitions from which a splitter is left to the grid (0: never)
+  uint32_t mean_deg;    // mean in-degree, rounded up
+  const uint32_t* in_ptr;
+  const int32_t *in_src, *in_ord;
+  int32_t *blk, *perm, *pos, *bs, *be;
+  uint64_t* pin;
+  // used by splitters beyond the table, and by splits of more than WG states
+  MaskT* mw;                              // zero between iterations
+  int32_t *cnt, *fc, *gc;                 // zero between iterations
+  uint64_t *nlb, *tmp64, *sf;             // sf zero between iterations
+  int32_t *ts, *tb;                       // touched states and their blocks
+  int32_t *lb, *llo, *lsz;                // listed blocks and their ranges
+  int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;
+  // bitmaps over labels and their summaries (bit w set iff word w is not 0)
+  uint64_t *ub, *qb, *us, *qs;
+};
+
+template <int WG>
+struct RoundsShared {
+  uint32_t cand[kCand], cb[kCand], cpre[kCand], cend[kCand], unst[kCand];
+  uint32_t wsum[WG / kWave];
+  uint32_t mbeg[WG], mpre[WG];
+  uint8_t mc[WG];
+  int32_t ss[small_split<WG>()], sb[small_split<WG>()];  // the first split states and their blocks
+  uint32_t lb[kListCap], llo[kListCap], lsz[kListCap];   // the first listed blocks
+  uint32_t nc, np, mtot, csz0, nS, nL, nT, tctr, bad;
+  uint32_t it;  // iterations so far
+};
+
+template <class MaskT>
+__device__ __forceinline__ MaskT mask_or(MaskT* p, MaskT v);
+template <>
+__device__ __forceinline__ uint32_t mask_or<uint32_t>(uint32_t* p, uint32_t v) {
+  return atomicOr(p, v);
+}
+template <>
+__device__ __forceinline__ uint64_t mask_or<uint64_t>(uint64_t* p, uint64_t v) {
+  return atomicOr((unsigned long long*)p, (unsigned long long)v);
+}
+
+__device__ __forceinline__ uint32_t table_hash(uint32_t key, uint32_t shift) {
+  return (key * 2654435761u) >> shift;
+}
+// slot of key, inserted if absent (first: by this call).  The table is never
+// more than half full, so the probe ends.
+__device__ __forceinline__ uint32_t table_insert(uint32_t* tab, uint32_t mask, uint32_t shift,
+                                                 uint32_t key, bool& first) {
+  uint32_t h = table_hash(key, shift);
+  for (;;) {
+    const uint32_t old = atomicCAS(&tab[h], kNone, key);
+    first = old == kNone;
+    if (first || old == key) return h;
+    h = (h + 1) & mask;
+  }
+}
+// slot of key, kNone if absent
+__device__ __forceinline__ uint32_t table_find(const uint32_t* tab, uint32_t mask, uint32_t shift,
+                                               uint32_t key) {
+  uint32_t h = table_hash(key, shift);
+  for (;;) {
+    const uint32_t v = tab[h];
+    if (v == key) return h;
+    if (v == kNone) return kNone;
+    h = (h + 1) & mask;
+  }
+}
+
+// Append one entry per lane with pred (one atomic per wave); the entry's
+// index, kNone without pred.  Wave-uniform call.
+__device__ __forceinline__ uint32_t list_push(uint32_t* counter, bool pred) {
+  const uint64_t bal = __ballot(pred);
+  if (!bal) return kNone;
+  const int leader = __ffsll((unsigned long long)bal) - 1;
+  uint32_t base = 0;
+  if ((int)lane() == leader) base = atomicAdd(counter, (uint32_t)__popcll(bal));
+  base = (uint32_t)__shfl((int)base, leader, kWave);
+  return pred ? base + (uint32_t)__popcll(bal & ((1ull << lane()) - 1ull)) : kNone;
+}
+
+// entry i of the split list and of the list of blocks: in LDS, beyond its
+// capacity in global memory
+template <class A, class S>
+__device__ __forceinline__ void put_split(const A& a, S& sh, uint32_t cap, uint32_t i, int32_t s,
+                                          int32_t b) {
+  if (i < cap) {
+    sh.ss[i] = s;
+    sh.sb[i] = b;
+  } else {
+    a.ss[i] = s;
+    a.sbk[i] = b;
+  }
+}
+template <class A, class S>
+__device__ __forceinline__ void put_block(const A& a, S& sh, uint32_t i, uint32_t b, uint32_t lo,
+                                          uint32_t sz) {
+  if (i < kListCap) {
+    sh.lb[i] = b;
+    sh.llo[i] = lo;
+    sh.lsz[i] = sz;
+  } else {
+    a.lb[i] = (int32_t)b;
+    a.llo[i] = (int32_t)lo;
+    a.lsz[i] = (int32_t)sz;
+  }
+}
+
+// position of the r-th set bit of v (r < number of set bits)
+__device__ __forceinline__ uint32_t select_bit(uint64_t v, uint32_t r) {
+  uint32_t w = (uint32_t)v, p = 0;
+  const uint32_t c0 = (uint32_t)__popcll((unsigned long long)w);
+  if (r >= c0) {
+    r -= c0;
+    w = (uint32_t)(v >> 32);
+    p = 32;
+  }
+#pragma unroll
+  for (uint32_t step = 16; step >= 1; step >>= 1) {
+    const uint32_t c = (uint32_t)__popcll((unsigned long long)(w & ((1u << step) - 1u)));
+    if (r >= c) {
+      r -= c;
+      w >>= step;
+      p += step;
+    }
+  }
+  return p;
+}
+
+__device__ __forceinline__ void label_set(uint64_t* words, uint64_t* sum, uint32_t b) {
+  const uint32_t w = b >> 6;
+  const uint64_t old = atomicOr((unsigned long long*)&words[w], 1ull << (b & 63));
+  if (old == 0) atomicOr((unsigned long long*)&sum[w >> 6], 1ull << (w & 63));
+}
+// labels a and b join U and Q; the four words are updated side by side
+__device__ __forceinline__ void label_set2(uint64_t* U, uint64_t* US, uint64_t* Q, uint64_t* QS,
+                                           uint32_t a, uint32_t b) {
+  const uint32_t wa = a >> 6, wb = b >> 6;
+  const unsigned long long ba = 1ull << (a & 63), bb = 1ull << (b & 63);
+  const uint64_t ua = atomicOr((unsigned long long*)&U[wa], ba);
+  const uint64_t ub = atomicOr((unsigned long long*)&U[wb], bb);
+  const uint64_t qa = atomicOr((unsigned long long*)&Q[wa], ba);
+  const uint64_t qb = atomicOr((unsigned long long*)&Q[wb], bb);
+  if (ua == 0) atomicOr((unsigned long long*)&US[wa >> 6], 1ull << (wa & 63));
+  if (ub == 0) atomicOr((unsigned long long*)&US[wb >> 6], 1ull << (wb & 63));
+  if (qa == 0) atomicOr((unsigned long long*)&QS[wa >> 6], 1ull << (wa & 63));
+  if (qb == 0) atomicOr((unsigned long long*)&QS[wb >> 6], 1ull << (wb & 63));
+}
+__device__ __forceinline__ void label_clear(uint64_t* words, uint64_t* sum, uint32_t b) {
+  const uint32_t w = b >> 6;
+  const uint64_t bit = 1ull << (b & 63);
+  const uint64_t old = atomicAnd((unsigned long long*)&words[w], ~bit);
+  if ((old & ~bit) == 0)
+    atomicAnd((unsigned long long*)&sum[w >> 6], ~(1ull << (w & 63)));
+}
+
+// Lane l of the wave owns a run of v items (incl: inclusive scan over the
+// wave): the lane owning item e < total.
+__device__ __forceinline__ uint32_t wave_owner(uint32_t incl, uint32_t e) {
+  uint32_t j = 0;
+#pragma unroll
+  for (uint32_t step = 32; step >= 1; step >>= 1) {
+    const uint32_t probe = (uint32_t)__shfl((int)incl, (int)(j + step - 1), kWave);
+    if (probe <= e) j += step;
+  }
+  return j;
+}
+
+// bytes of the LDS region that the table takes for `slots` slots
+template <class MaskT>
+__host__ __device__ constexpr uint32_t table_bytes(uint32_t slots) {
+  return slots * (uint32_t)(4 + 4 + sizeof(MaskT));
+}
+// bytes of the tables of a split of up to small_split states: block table
+// (key, new label, split count, two counters, base of its staying states),
+// set of split states, staying states of the tails (state, position, range)
+template <int WG>
+__host__ __device__ constexpr uint32_t split_bytes() {
+  return small_split<WG>() * (2u * 24u + 2u * 4u + 16u);
+}
+constexpr uint32_t log2_u32(uint32_t v) { return v <= 1 ? 0 : 1 + log2_u32(v >> 1); }
+
+// Bit words of n labels plus summaries, twice (U and Q).
+__host__ __device__ inline uint32_t rounds_bitmap_bytes(uint32_t n) {
+  const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
+  return 16u * (nw + nsw);
+}
+
+// The set-up of a run by one workgroup: blk from start, member lists, ranges,
+// all labels unstable without verdict (global bitmaps), scratch zeroed.
+// Returns false if the partition is inconsistent (never expected).
+template <class MaskT, int WG>
+__device__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
+                             const int32_t* start, bool zero_mw) {
+  const uint32_t tid = threadIdx.x, wid = tid / kWave, n = a.n;
+  const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
+  for (uint32_t s = tid; s < n; s += WG) {
+    a.blk[s] = start[s] - (int32_t)a.s0;
+    a.cnt[s] = 0;
+    a.fc[s] = 0;
+    a.gc[s] = 0;
+    a.nlb[s] = 0;
+    if (zero_mw) a.mw[s] = 0;
+  }
+  for (uint32_t q = wid; q < nw; q += WG / kWave) {
+    const uint32_t s = (q << 6) + lane();
+    const uint64_t bits = __ballot(s < n && (uint32_t)(start[s < n ? s : 0] - (int32_t)a.s0) == s);
+    if (lane() == 0) {
+      a.ub[q] = bits;
+      a.qb[q] = bits;
+      a.sf[q] = 0;
+    }
+  }
+  if (tid == 0) sh.bad = 0;
+  __syncthreads();
+  for (uint32_t q = wid; q < nsw; q += WG / kWave) {
+    const uint32_t w = (q << 6) + lane();
+    const uint64_t bits = __ballot(w < nw && a.ub[w < nw ? w : 0] != 0);
+    if (lane() == 0) {
+      a.us[q] = bits;
+      a.qs[q] = bits;
+    }
+  }
+  for (uint32_t s = tid; s < n; s += WG) atomicAdd(&a.cnt[a.blk[s]], 1);
+  __syncthreads();
+  {  // block ranges: exclusive prefix sums of the sizes in label order
+    const uint32_t per = (n + WG - 1) / WG;
+    const uint32_t lo = min(n, tid * per), hi = min(n, lo + per);
+    uint32_t sum = 0;
+    for (uint32_t b = lo; b < hi; ++b) sum += (uint32_t)a.cnt[b];
+    const uint32_t incl = wave_incl_scan_u32(sum);
+    if (lane() == kWave - 1) sh.wsum[wid] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+    for (uint32_t q = 0; q < wid; ++q) run += sh.wsum[q];
+    for (uint32_t b = lo; b < hi; ++b) {
+      const uint32_t c = (uint32_t)a.cnt[b];
+      a.bs[b] = (int32_t)run;
+      a.be[b] = (int32_t)run;  // fill cursor, ends at the block's end
+      run += c;
+    }
+  }
+  __syncthreads();
+  for (uint32_t s = tid; s < n; s += WG) {
+    const uint32_t p = (uint32_t)atomicAdd(&a.be[a.blk[s]], 1);
+    if (p >= n) {  // cannot happen with consistent counts; report, never write
+      sh.bad = 1;
+      continue;
+    }
+    a.perm[p] = (int32_t)s;
+    a.pos[s] = (int32_t)p;
+    const uint32_t e0 = a.in_ptr[s];
+    a.pin[p] = ((uint64_t)e0 << 32) | (a.in_ptr[s + 1] - e0);
+  }
+  __syncthreads();
+  const bool ok = sh.bad == 0;
+  for (uint32_t s = tid; s < n; s += WG) a.cnt[s] = 0;
+  __syncthreads();
+  return ok;
+}
+
+// kBm: the bitmaps live in LDS during the loop (loaded from and stored back
+// to the global ones); else they stay in global memory.
+template <class MaskT, int WG, bool kBm>
+__device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
+                                                char* lds, uint32_t lds_bytes, uint32_t it0,
+                                                uint32_t& grid_C) {
+  constexpr uint32_t kWaves = WG / kWave;
+  const uint32_t tid = threadIdx.x, wid = tid / kWave;
+  const uint32_t n = a.n, s0 = a.s0;
+  const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
+
+  // ---- LDS: bitmaps, then the region of the table (and of the splits)
+  uint64_t *U = a.ub, *Q = a.qb, *US = a.us, *QS = a.qs;
+  char* region = lds;
+  uint32_t rbytes = lds_bytes;
+  if (kBm) {
+    U = reinterpret_cast<uint64_t*>(lds);
+    Q = U + nw;
+    US = Q + nw;
+    QS = US + nsw;
+    region = lds + 16u * (nw + nsw);
+    rbytes = lds_bytes - 16u * (nw + nsw);
+    for (uint32_t q = tid; q < nw; q += WG) {
+      U[q] = a.ub[q];
+      Q[q] = a.qb[q];
+    }
+    for (uint32_t q = tid; q < nsw; q += WG) {
+      US[q] = a.us[q];
+      QS[q] = a.qs[q];
+    }
+  }
+  // split tables (LDS that does not hold them: the global path), then the table
+  constexpr uint32_t kSmall = small_split<WG>(), kB = 2u * kSmall, kBShift = 32 - log2_u32(kB);
+  constexpr uint32_t EU = edges_per_thread<WG>();
+  const bool small_ok = split_bytes<WG>() + table_bytes<MaskT>(256) <= rbytes;
+  uint64_t* x_pin = reinterpret_cast<uint64_t*>(region);
+  uint32_t* x_u = reinterpret_cast<uint32_t*>(x_pin + kSmall);
+  uint32_t* x_q = x_u + kSmall;
+  uint32_t* b_key = x_q + kSmall;
+  uint32_t* b_nl = b_key + kB;
+  uint32_t* b_cnt = b_nl + kB;
+  uint32_t* b_fc = b_cnt + kB;
+  uint32_t* b_gc = b_fc + kB;
+  uint32_t* b_base = b_gc + kB;
+  uint32_t* s_set = b_base + kB;
+  if (small_ok) {
+    region += split_bytes<WG>();
+    rbytes -= split_bytes<WG>();
+    for (uint32_t q = tid; q < kB; q += WG) {  // empty between splits
+      b_key[q] = kNone;
+      b_nl[q] = kNone;
+      b_cnt[q] = 0;
+      b_fc[q] = 0;
+      b_gc[q] = 0;
+      s_set[q] = kNone;
+    }
+  }
+  uint32_t lg = 0;  // log2 of the table's slots; none below 32
+  while ((2u << lg) <= 2 * EU * WG && table_bytes<MaskT>(2u << lg) <= rbytes) ++lg;
+  const uint32_t slots = lg >= 5 ? 1u << lg : 0u;
+  const uint32_t tmask = slots - 1, tshift = 32 - lg;
+  const uint32_t ecap = slots / 2;
+  MaskT* t_mv = reinterpret_cast<MaskT*>(region);
+  uint32_t* t_key = reinterpret_cast<uint32_t*>(t_mv + slots);
+  uint32_t* t_cnt = t_key + slots;
+  const bool dense = (uint64_t)n * sizeof(MaskT) <= rbytes;  // mark words of a big splitter in LDS
+
+  if (tid == 0) {
+    sh.it = it0;
+    sh.bad = 0;
+  }
+  bool dirty = true;  // the region does not hold an empty table (workgroup-uniform)
+  uint32_t rc = kRoundsDone;
+  // candidates of the next round: after a split the next one is a few labels
+  // away (the mean gap is 4-12 iterations), so the rest would be marked for
+  // nothing; a round without a split is followed by a full one
+  uint32_t want = kCand;
+
+  for (;;) {
+    __syncthreads();
+    // ---- the next candidates: the smallest labels of Q, their ranges
+    if (wid == 0) {
+      // lane j: the j-th word of Q that is not 0, then the j-th label
+      uint32_t nword = 0, word = 0;
+      for (uint32_t q0 = 0; q0 < nsw && nword < want; q0 += kWave) {
+        const uint32_t q = q0 + lane();
+        const uint64_t sv = q < nsw ? QS[q] : 0ull;
+        if (__ballot(sv != 0) == 0) continue;
+        const uint32_t pc = (uint32_t)__popcll(sv);
+        const uint32_t incl = wave_incl_scan_u32(pc);
+        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        const uint32_t j = lane() - nword;
+        const uint32_t o = wave_owner(incl, min(j, total - 1));
+        const uint64_t v = (uint64_t)__shfl((unsigned long long)sv, (int)o, kWave);
+        const uint32_t before = (uint32_t)__shfl((int)(incl - pc), (int)o, kWave);
+        if (lane() >= nword && j < total) word = ((q0 + o) << 6) + select_bit(v, j - before);
+        nword += total;
+      }
+      uint32_t nc = 0, C = 0;
+      {
+        const uint64_t v = lane() < min(nword, want) ? Q[word] : 0ull;
+        const uint32_t pc = (uint32_t)__popcll(v);
+        const uint32_t incl = wave_incl_scan_u32(pc);
+        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        nc = min(total, want);
+        const uint32_t o = wave_owner(incl, min(lane(), total ? total - 1 : 0u));
+        const uint64_t w = (uint64_t)__shfl((unsigned long long)v, (int)o, kWave);
+        const uint32_t before = (uint32_t)__shfl((int)(incl - pc), (int)o, kWave);
+        const uint32_t cw = (uint32_t)__shfl((int)word, (int)o, kWave);
+        if (lane() < nc) C = (cw << 6) + select_bit(w, lane() - before);
+      }
+      uint32_t lo = 0, sz = 0;
+      if (lane() < nc) {
+        lo = (uint32_t)a.bs[C];
+        sz = (uint32_t)a.be[C] - lo;
+        if (lo > n || sz > n - lo) {  // never expected: report, visit nothing
+          sh.bad = 1;
+          lo = 0;
+          sz = 0;
+        }
+      }
+      const uint32_t mi = wave_incl_scan_u32(sz);
+      const uint64_t fit = __ballot(lane() < nc && mi <= (uint32_t)WG);
+      const uint32_t np = (uint32_t)__popcll(fit);  // sizes add up: a prefix of the lanes
+      if (lane() < kCand) {
+        sh.cand[lane()] = C;
+        sh.cb[lane()] = lo;
+        sh.cpre[lane()] = mi - sz;
+        sh.unst[lane()] = 0;
+      }
+      if (lane() == 0) {
+        sh.nc = nc;
+        sh.np = np;
+        sh.csz0 = sz;
+      }
+      if (np && lane() == np - 1) sh.mtot = mi;
+    } else if (tid == kWaves * kWave - 1) {
+      sh.nS = sh.nL = sh.nT = 0;
+      sh.tctr = 0;
+    }
+    if (dirty) {
+      for (uint32_t q = tid; q < slots; q += WG) {
+        t_mv[q] = 0;
+        t_key[q] = kNone;
+        t_cnt[q] = 0;
+      }
+      dirty = false;
+    }
+    __syncthreads();
+    const uint32_t nc = sh.nc;
+    if (sh.bad) {
+      rc = kRoundsBad;
+      break;
+    }
+    if (sh.it > a.iter_cap || (sh.it == a.iter_cap && nc)) {
+      rc = kRoundsCap;
+      break;
+    }
+    uint32_t np = sh.np;
+    const uint32_t mtot = np ? sh.mtot : 0u;
+    uint32_t E = 0;
+    if (np) {
+      // ---- members: one per thread, with its in-transition range
+      uint32_t beg = 0, deg = 0, c = 0;
+      if (tid < mtot) {
+#pragma unroll
+        for (uint32_t step = kCand / 2; step >= 1; step >>= 1)
+          if (c + step < np && sh.cpre[c + step] <= tid) c += step;
+        const uint64_t x = a.pin[sh.cb[c] + (tid - sh.cpre[c])];
+        beg = (uint32_t)(x >> 32);
+        deg = (uint32_t)x;
+      }
+      const uint32_t incl = wave_incl_scan_u32(deg);
+      if (lane() == kWave - 1) sh.wsum[wid] = incl;
+      __syncthreads();
+      uint32_t before = lane() < kWaves ? sh.wsum[lane()] : 0u;
+      before = wave_incl_scan_u32(lane() < wid ? before : 0u);
+      before = (uint32_t)__shfl((int)before, kWave - 1, kWave);
+      if (tid < mtot) {
+        sh.mbeg[tid] = beg;
+        sh.mpre[tid] = before + incl - deg;
+        sh.mc[tid] = (uint8_t)c;
+        // the last member of each candidate (a later one's first member
+        // follows, or the members end)
+        if (tid + 1 == mtot || (c + 1 < np && sh.cpre[c + 1] == tid + 1)) sh.cend[c] = before + incl;
+      }
+      __syncthreads();
+      // as many candidates as the table holds
+      const bool fits = lane() < np && sh.cend[lane()] <= ecap;
+      np = (uint32_t)__popcll(__ballot(fits));
+      E = np ? sh.cend[np - 1] : 0u;
+    }
+    const bool big = np == 0 && nc != 0;
+    uint32_t es[EU], eb[EU], ek[EU], sl[EU], ls[EU], lo[EU], sz[EU];
+    uint64_t split = 0;  // candidates that split something
+    if (np) {
+      // ---- transitions: insert (candidate, source), collect its marks
+      uint32_t eo[EU];
+      const uint32_t mtop = mtot > 1 ? 1u << (31 - __clz((int)(mtot - 1))) : 0u;
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        const uint32_t e = tid + u * WG;
+        sl[u] = kNone;
+        es[u] = kNone;
+        if (e < E) {
+          uint32_t j = 0;
+          for (uint32_t step = mtop; step >= 1; step >>= 1)
+            if (j + step < mtot && sh.mpre[j + step] <= e) j += step;
+          const uint32_t edge = sh.mbeg[j] + (e - sh.mpre[j]);
+          es[u] = (uint32_t)a.in_src[edge] - s0;
+          eo[u] = a.rcpp ? 0u : (uint32_t)a.in_ord[edge];
+          ek[u] = (uint32_t)sh.mc[j] << kKeyBits;
+        }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u)
+        if (es[u] != kNone) eb[u] = (uint32_t)a.blk[es[u]];
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        if (es[u] == kNone) continue;
+        bool first;
+        const uint32_t slot = table_insert(t_key, tmask, tshift, ek[u] | es[u], first);
+        mask_or<MaskT>(&t_mv[slot], (MaskT)1 << (eo[u] & (sizeof(MaskT) * 8 - 1)));
+        if (!first) continue;
+        sl[u] = slot;
+        if (eb[u] == es[u]) {
+          lo[u] = (uint32_t)a.bs[es[u]];
+          sz[u] = (uint32_t)a.be[es[u]] - lo[u];
+        }
+      }
+      __syncthreads();
+      // ---- every touched state against its leader (the leader of b is the
+      // state b); the touched members of a block counted at its leader
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        if (sl[u] == kNone) continue;
+        const uint32_t lead = eb[u] == es[u] ? sl[u]
+                                             : table_find(t_key, tmask, tshift, ek[u] | eb[u]);
+        ls[u] = lead;
+        if (lead != kNone) atomicAdd(&t_cnt[lead], 1u);
+        if (lead == kNone || t_mv[lead] != t_mv[sl[u]]) sh.unst[ek[u] >> kKeyBits] = 1;
+      }
+      __syncthreads();
+      // a touched leader with untouched members
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u)
+        if (sl[u] != kNone && eb[u] == es[u] && t_cnt[sl[u]] != sz[u])
+          sh.unst[ek[u] >> kKeyBits] = 1;
+      __syncthreads();
+      split = __ballot(lane() < np && sh.unst[lane() & (kCand - 1)] != 0);
+    }
+    const uint32_t f = split ? (uint32_t)(__ffsll((unsigned long long)split) - 1) : np;
+    // ---- verdicts, and the iterations that split nothing: every unstable
+    // label before the next one without a verdict
+    const bool turn = f < np || big;  // the iteration of C is carried out now
+    const uint32_t C = turn ? sh.cand[f < np ? f : 0] : 0u;
+    if (wid == 0 && ((lane() < np && !((split >> lane()) & 1ull)) || (turn && lane() == (f < np ? f : 0))))
+      label_clear(Q, QS, sh.cand[lane()]);
+    uint32_t limit = n;  // labels before it are taken, C's own iteration included
+    if (turn) limit = C + 1;
+    else if (np < nc) limit = sh.cand[np];
+    else if (nc == want) limit = sh.cand[want - 1] + 1;
+    {
+      uint32_t taken = 0;
+      const uint32_t wend = (limit + 63u) >> 6;
+      for (uint32_t w = tid; w < wend; w += WG) {
+        if (!kBm && !((US[w >> 6] >> (w & 63)) & 1ull)) continue;
+        uint64_t v = U[w];
+        if (!v) continue;
+        uint64_t keep = 0;
+        if (w == (limit >> 6)) keep = v & (~0ull << (limit & 63));
+        v &= ~keep;
+        if (!v) continue;
+        taken += (uint32_t)__popcll(v);
+        U[w] = keep;
+        if (!keep) atomicAnd((unsigned long long*)&US[w >> 6], ~(1ull << (w & 63)));
+      }
+      if (taken) atomicAdd(&sh.it, taken);
+    }
+    if (nc == 0) break;  // every unstable label had its verdict: the final pass follows
+    const auto clear_own = [&]() {  // this thread's slots of the table
+      if (np == 0) return;
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u)
+        if (sl[u] != kNone) {
+          t_mv[sl[u]] = 0;
+          t_key[sl[u]] = kNone;
+          t_cnt[sl[u]] = 0;
+        }
+    };
+    if (!turn) {
+      clear_own();
+      want = kCand;
+      continue;
+    }
+    want = kCand / 2;
+    // the members of the listed blocks that `is_split` says are split off
+    const auto members = [&](const auto& is_split) {
+      const uint32_t nL = sh.nL;
+      for (uint32_t j0 = 0; j0 < nL; j0 += kWave) {
+        const uint32_t j = j0 + lane();
+        uint32_t b = 0, l = 0, z = 0;
+        if (j < nL) {
+          b = j < kListCap ? sh.lb[j] : (uint32_t)a.lb[j];
+          l = j < kListCap ? sh.llo[j] : (uint32_t)a.llo[j];
+          z = j < kListCap ? sh.lsz[j] : (uint32_t)a.lsz[j];
+        }
+        const uint32_t incl = wave_incl_scan_u32(z);
+        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        for (uint32_t e0 = wid * kWave; e0 < total; e0 += WG) {
+          const uint32_t e = e0 + lane();
+          const uint32_t ee = min(e, total - 1);
+          const uint32_t o = wave_owner(incl, ee);
+          const uint32_t ob = (uint32_t)__shfl((int)b, (int)o, kWave);
+          const uint32_t ol = (uint32_t)__shfl((int)l, (int)o, kWave);
+          const uint32_t oi = (uint32_t)__shfl((int)(incl - z), (int)o, kWave);
+          uint32_t s = 0;
+          bool sp = false;
+          if (e < total) {
+            s = (uint32_t)a.perm[ol + (ee - oi)];
+            sp = is_split(s);
+          }
+          const uint32_t si = list_push(&sh.nS, sp);
+          if (sp) put_split(a, sh, kSmall, si, (int32_t)s, (int32_t)ob);
+        }
+      }
+    };
+    if (big) {
+      // ---- a splitter beyond the table: mark words per state
+      const uint32_t cb = sh.cb[0], csz = sh.csz0;
+      if (!dense && a.grid_edges && (uint64_t)csz * a.mean_deg >= a.grid_edges) {
+        grid_C = C;  // its iteration is counted already
+        rc = kRoundsGrid;
+        break;
+      }
+      if (dense) {
+        // mark words of all states in LDS.  Four members per thread are in
+        // flight; a member of many in-transitions is the whole wave's.
+        MaskT* mw = reinterpret_cast<MaskT*>(region);
+        for (uint32_t s = tid; s < n; s += WG) mw[s] = 0;
+        dirty = true;
+        __syncthreads();
+        const auto mark = [&](uint32_t s, uint32_t o) {
+          // a hub's transitions find its bit set: plain reads of one word do
+          // not serialise, atomics on it do
+          const MaskT bit = (MaskT)1 << (o & (sizeof(MaskT) * 8 - 1));
+          if (!(mw[s] & bit)) mask_or<MaskT>(&mw[s], bit);
+        };
+        for (uint32_t i0 = wid * kWave; i0 < csz; i0 += kScanU * WG) {
+          uint32_t beg[kScanU], deg[kScanU];
+          uint32_t most = 0;
+#pragma unroll
+          for (uint32_t u = 0; u < kScanU; ++u) {
+            const uint32_t i = i0 + u * WG + lane();
+            const uint64_t x = i < csz ? a.pin[cb + i] : 0ull;
+            beg[u] = (uint32_t)(x >> 32);
+            deg[u] = (uint32_t)x;
+          }
+#pragma unroll
+          for (uint32_t u = 0; u < kScanU; ++u) {
+            uint64_t hb = __ballot(deg[u] > 2 * kWave);
+            while (hb) {
+              const int o = __ffsll((unsigned long long)hb) - 1;
+              hb &= hb - 1;
+              const uint32_t ob = (uint32_t)__shfl((int)beg[u], o, kWave);
+              const uint32_t od = (uint32_t)__shfl((int)deg[u], o, kWave);
+              for (uint32_t e = lane(); e < od; e += kWave)
+                mark((uint32_t)a.in_src[ob + e] - s0, a.rcpp ? 0u : (uint32_t)a.in_ord[ob + e]);
+            }
+            if (deg[u] > 2 * kWave) deg[u] = 0;
+            most = max(most, deg[u]);
+          }
+          for (uint32_t e = 0; e < most; e += 2) {
+            uint32_t vs[2 * kScanU], vo[2 * kScanU];
+#pragma unroll
+            for (uint32_t u = 0; u < kScanU; ++u)
+#pragma unroll
+              for (uint32_t v = 0; v < 2; ++v) {
+                vs[2 * u + v] = kNone;
+                if (e + v < deg[u]) {
+                  vs[2 * u + v] = (uint32_t)a.in_src[beg[u] + e + v] - s0;
+                  vo[2 * u + v] = a.rcpp ? 0u : (uint32_t)a.in_ord[beg[u] + e + v];
+                }
+              }
+#pragma unroll
+            for (uint32_t v = 0; v < 2 * kScanU; ++v)
+              if (vs[v] != kNone) mark(vs[v], vo[v]);
+          }
+        }
+        __syncthreads();
+        // every state against its leader
+        for (uint32_t i0 = wid * kWave; i0 < n; i0 += kScanU * WG) {
+          uint32_t vb[kScanU];
+#pragma unroll
+          for (uint32_t u = 0; u < kScanU; ++u) {
+            const uint32_t s = i0 + u * WG + lane();
+            vb[u] = s < n ? (uint32_t)a.blk[s] : 0u;
+          }
+#pragma unroll
+          for (uint32_t u = 0; u < kScanU; ++u) {
+            const uint32_t s = i0 + u * WG + lane();
+            const bool sp = s < n && mw[s] != mw[vb[u]];
+            const uint32_t si = list_push(&sh.nS, sp);
+            if (sp) put_split(a, sh, kSmall, si, (int32_t)s, (int32_t)vb[u]);
+          }
+        }
+        __syncthreads();
+      } else {
+        // mark words in global memory, with a list of the touched states
+        MaskT* mw = a.mw;
+        __syncthreads();
+        for (uint32_t i0 = wid * kWave; i0 < csz; i0 += WG) {
+          const uint32_t i = i0 + lane();
+          uint32_t beg = 0, deg = 0;
+          if (i < csz) {
+            const uint64_t x = a.pin[cb + i];
+            beg = (uint32_t)(x >> 32);
+            deg = (uint32_t)x;
+          }
+          const uint32_t incl = wave_incl_scan_u32(deg);
+          const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+          for (uint32_t e0 = 0; e0 < total; e0 += kWave * kScanU) {
+            uint32_t vs[kScanU], vo[kScanU], vb[kScanU], vl[kScanU], vh[kScanU];
+            bool first[kScanU];
+#pragma unroll
+            for (uint32_t u = 0; u < kScanU; ++u) {
+              const uint32_t e = e0 + u * kWave + lane();
+              const uint32_t ee = min(e, total - 1);
+              const uint32_t j = wave_owner(incl, ee);
+              const uint32_t jb = (uint32_t)__shfl((int)beg, (int)j, kWave);
+              const uint32_t ji = (uint32_t)__shfl((int)(incl - deg), (int)j, kWave);
+              vs[u] = kNone;
+              if (e < total) {
+                const uint32_t edge = jb + (ee - ji);
+                vs[u] = (uint32_t)a.in_src[edge] - s0;
+                vo[u] = a.rcpp ? 0u : (uint32_t)a.in_ord[edge];
+              }
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kScanU; ++u) {
+              first[u] = false;
+              vb[u] = vl[u] = vh[u] = 0;
+              if (vs[u] == kNone) continue;
+              const MaskT bit = (MaskT)1 << (vo[u] & (sizeof(MaskT) * 8 - 1));
+              first[u] = mask_or<MaskT>(&mw[vs[u]], bit) == 0;
+              vb[u] = (uint32_t)a.blk[vs[u]];
+              vl[u] = (uint32_t)a.bs[vs[u]];
+              vh[u] = (uint32_t)a.be[vs[u]];
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kScanU; ++u) {
+              const uint32_t ti = list_push(&sh.nT, first[u]);
+              if (first[u]) {
+                a.ts[ti] = (int32_t)vs[u];
+                a.tb[ti] = (int32_t)vb[u];
+              }
+              // a touched leader of a one-state block has no untouched member
+              const bool lead = first[u] && vb[u] == vs[u] && vh[u] - vl[u] > 1;
+              const uint32_t li = list_push(&sh.nL, lead);
+              if (lead) put_block(a, sh, li, vs[u], vl[u], vh[u] - vl[u]);
+            }
+          }
+        }
+        __syncthreads();
+        const uint32_t nT = sh.nT;
+        for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG) {
+          const uint32_t i = i0 + lane();
+          int32_t s = 0, b = 0;
+          bool sp = false;
+          if (i < nT) {
+            s = a.ts[i];
+            b = a.tb[i];
+            sp = s != b && mw[s] != mw[b];
+          }
+          const uint32_t si = list_push(&sh.nS, sp);
+          if (sp) put_split(a, sh, kSmall, si, s, b);
+        }
+        members([&](uint32_t s) { return mw[s] == 0; });
+        __syncthreads();
+        for (uint32_t i = tid; i < nT; i += WG) mw[a.ts[i]] = 0;
+      }
+      if (sh.nS == 0) continue;
+    } else {
+      // ---- the split states of C from the table: touched states that differ
+      // from their leader, and the untouched members of blocks whose leader
+      // was touched
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f;
+        bool sp = false, part = false;
+        if (mine) {
+          if (es[u] == eb[u]) part = t_cnt[sl[u]] != sz[u];
+          else sp = ls[u] == kNone || t_mv[ls[u]] != t_mv[sl[u]];
+        }
+        const uint32_t si = list_push(&sh.nS, sp);
+        if (sp) put_split(a, sh, kSmall, si, (int32_t)es[u], (int32_t)eb[u]);
+        const uint32_t li = list_push(&sh.nL, part);
+        if (part) put_block(a, sh, li, eb[u], lo[u], sz[u]);
+      }
+      __syncthreads();
+      if (sh.nL) {  // workgroup-uniform
+        members([&](uint32_t s) {
+          return table_find(t_key, tmask, tshift, (f << kKeyBits) | s) == kNone;
+        });
+        __syncthreads();
+      }
+      clear_own();
+    }
+    // ---- split: the split part of each block goes to the tail of its range
+    // and takes its smallest member as label; front split states trade places
+    // with the staying states of the tail
+    const uint32_t nS = sh.nS;
+    if (tid == WG - 1 && !a.rcpp) label_set2(U, US, Q, QS, C, C);  // Algorithm 3 re-marks C
+    if (nS <= kSmall && small_ok) {
+      uint32_t s = 0, b = 0, ps = 0, blo = 0, bhi = 0, slot = 0, own = 0, r = 0;
+      const bool on = tid < nS;
+      if (on) {
+        s = (uint32_t)sh.ss[tid];
+        b = (uint32_t)sh.sb[tid];
+        ps = (uint32_t)a.pos[s];
+        blo = (uint32_t)a.bs[b];
+        bhi = (uint32_t)a.be[b];
+        bool first;
+        slot = table_insert(b_key, kB - 1, kBShift, b, first);
+        r = atomicAdd(&b_cnt[slot], 1u);
+        atomicMin(&b_nl[slot], s);
+        own = table_insert(s_set, kB - 1, kBShift, s, first);
+      }
+      __syncthreads();
+      uint32_t c = 0, ne = 0, q = 0, nl = 0, fi = kNone, us_ = 0;
+      uint64_t px = 0, pq = 0;
+      bool ok = false;
+      if (on) {
+        c = b_cnt[slot];
+        nl = b_nl[slot];
+        ne = bhi - c;
+        q = ne + r;
+        ok = bhi <= n && blo < ne && ne < bhi && ps >= blo && ps < bhi;  // else never expected
+        if (!ok) {
+          sh.bad = 1;
+        } else {
+          us_ = (uint32_t)a.perm[q];  // every tail position is examined once
+          pq = a.pin[q];
+          if (ps < ne) {
+            px = a.pin[ps];
+            fi = atomicAdd(&b_fc[slot], 1u);
+          }
+          if (r == 0) b_base[slot] = atomicAdd(&sh.tctr, c);
+          a.blk[s] = (int32_t)nl;
+        }
+      }
+      __syncthreads();
+      if (ok && table_find(s_set, kB - 1, kBShift, us_) == kNone) {
+        const uint32_t x = b_base[slot] + atomicAdd(&b_gc[slot], 1u);
+        if (x < kSmall) {
+          x_u[x] = us_;
+          x_q[x] = q;
+          x_pin[x] = pq;
+        } else {
+          sh.bad = 1;  // never expected
+        }
+      }
+      __syncthreads();
+      if (on) {  // the tables are empty again
+        b_key[slot] = kNone;
+        b_nl[slot] = kNone;
+        b_cnt[slot] = 0;
+        b_fc[slot] = 0;
+        b_gc[slot] = 0;
+        s_set[own] = kNone;
+      }
+      if (ok) {
+        if (fi != kNone) {
+          const uint32_t x = b_base[slot] + fi;
+          const uint32_t v = x_u[x], vq = x_q[x];
+          if (v < n && vq < n) {
+            a.perm[ps] = (int32_t)v;
+            a.pos[v] = (int32_t)ps;
+            a.pin[ps] = x_pin[x];
+            a.perm[vq] = (int32_t)s;
+            a.pos[s] = (int32_t)vq;
+            a.pin[vq] = px;
+          } else {
+            sh.bad = 1;  // never expected
+          }
+        }
+        if (s == nl) {  // the new leader: one thread per split block
+          a.bs[s] = (int32_t)ne;
+          a.be[s] = (int32_t)bhi;
+          a.be[b] = (int32_t)ne;
+          label_set2(U, US, Q, QS, b, s);
+        }
+      }
+    } else {
+      // more split states: the same through global arrays
+      const uint64_t epoch = (uint64_t)sh.it << 32;  // this iteration's number
+      for (uint32_t i = tid; i < nS; i += WG) {
+        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
+        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
+        atomicMax((unsigned long long*)&a.nlb[b],
+                  (unsigned long long)(epoch | (uint64_t)(kNone - (uint32_t)s)));
+        a.sr[i] = atomicAdd(&a.cnt[b], 1);
+        atomicOr((unsigned long long*)&a.sf[(uint32_t)s >> 6], 1ull << (s & 63));
+      }
+      __syncthreads();
+      for (uint32_t i = tid; i < nS; i += WG) {
+        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
+        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
+        const int32_t r = a.sr[i];
+        const int32_t e = a.be[b], l = a.bs[b], ps = a.pos[s], c = a.cnt[b];
+        const int32_t nl = (int32_t)(kNone - (uint32_t)a.nlb[b]);
+        const int32_t ne = e - c, q = ne + r;
+        int32_t fv = -1;
+        const bool ok = l >= 0 && l < ne && q < e && e <= (int32_t)n && ps >= l && ps < e;
+        if (ok) {
+          a.blk[s] = nl;
+          if (ps < ne) fv = atomicAdd(&a.fc[b], 1);
+          const int32_t u = a.perm[q];  // every tail position is examined once
+          if (!test_bit(a.sf, (uint32_t)u)) {
+            const int32_t j = atomicAdd(&a.gc[b], 1);
+            if (ne + j < e) a.tmp64[ne + j] = ((uint64_t)(uint32_t)u << 32) | (uint32_t)q;
+            else sh.bad = 1;  // never expected
+          }
+        } else {
+          sh.bad = 1;  // never expected: the entry does nothing
+        }
+        a.sfi[i] = fv;
+        a.sne[i] = ne;
+        a.sps[i] = ps;
+        a.sse[i] = (ok && nl == s) ? e : -1;
+      }
+      __syncthreads();
+      for (uint32_t i = tid; i < nS; i += WG) {
+        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
+        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
+        const int32_t fv = a.sfi[i], ne = a.sne[i], ps = a.sps[i], e = a.sse[i];
+        if (fv >= 0) {
+          const uint64_t x = a.tmp64[ne + fv];
+          const int32_t q = (int32_t)(uint32_t)x, u = (int32_t)(x >> 32);
+          if (q >= ne && q < (int32_t)n && u >= 0 && u < (int32_t)n) {
+            const uint64_t xq = a.pin[q], xp = a.pin[ps];
+            a.perm[ps] = u;
+            a.pos[u] = ps;
+            a.pin[ps] = xq;
+            a.perm[q] = s;
+            a.pos[s] = q;
+            a.pin[q] = xp;
+          } else {
+            sh.bad = 1;  // never expected
+          }
+        }
+        if (e >= 0) {  // the new leader: one thread per split block
+          a.bs[s] = ne;
+          a.be[s] = e;
+          a.be[b] = ne;
+          a.cnt[b] = 0;
+          a.fc[b] = 0;
+          a.gc[b] = 0;
+          label_set2(U, US, Q, QS, (uint32_t)b, (uint32_t)s);
+        }
+        atomicAnd((unsigned long long*)&a.sf[(uint32_t)s >> 6], ~(1ull << (s & 63)));
+      }
+    }
+  }
+  __syncthreads();
+  if (kBm) {
+    for (uint32_t q = tid; q < nw; q += WG) {
+      a.ub[q] = U[q];
+      a.qb[q] = Q[q];
+    }
+    for (uint32_t q = tid; q < nsw; q += WG) {
+      a.us[q] = US[q];
+      a.qs[q] = QS[q];
+    }
+    __syncthreads();
+  }
+  return rc;
+}
+
+}  // namespace bisim
