@@ -322,20 +322,24 @@ typedef struct bisim_batch bisim_batch;
 typedef struct {
   int64_t max_iterations;   /* largest per-instance #It */
   int64_t sum_iterations;   /* sum of per-instance #It */
-  int64_t lds_instances;    /* instances refined with LDS-resident state */
-  int64_t global_instances; /* instances refined with state in global memory */
+  int64_t lds_instances;    /* instances whose labels, marks, bids and bitmaps
+                               are within the LDS budget */
+  int64_t global_instances; /* the others */
   int32_t workgroup_size;   /* threads per workgroup used */
   int32_t grid;             /* workgroups launched */
   double t_pre_ms;          /* lts_batch_load device time */
   double t_alg_ms;          /* device time of the last coarsest_partition_batch */
   int64_t work[2][8];       /* work totals of the last run over all instances:
-                               [0] LDS-resident instances: iterations, splitter
-                               members, their in-transitions, touched states, -,
-                               split states, -, instances;
-                               [1] member-list instances: iterations, splitter
-                               members, their in-transitions, touched states,
-                               touched leaders listed, members of their blocks
-                               visited, split states, split blocks */
+                               [0] instances within the LDS budget: iterations,
+                               members of the labels marked, their in-transitions,
+                               touched (label, state) pairs, -, split states, -,
+                               instances;
+                               [1] the others: iterations, members of the labels
+                               marked, their in-transitions, touched (label, state)
+                               pairs, blocks listed for their untouched members,
+                               members of those visited, split states, split blocks
+                               (a label can be marked more than once before its
+                               iteration, and an iteration can need no marking) */
 } bisim_batch_stats;
 
 /*
@@ -376,11 +380,11 @@ void lts_batch_free(bisim_batch* b);
 
 /*
  * bisim_batch_set_option — per-batch settings.
- *   BISIM_BOPT_WG_SIZE     0 (default) or 256: the one size the kernel is built for.
+ *   BISIM_BOPT_WG_SIZE     0 (default: 512 threads) or 256.
  *   BISIM_BOPT_GRID        0 (default: autotuned) or a workgroup count.
  *   BISIM_BOPT_LDS_LIMIT   0 (default: the device's per-workgroup LDS) or a
- *                          smaller byte budget; instances whose state does
- *                          not fit are refined from global memory.
+ *                          smaller byte budget (what does not fit it is kept
+ *                          in global memory).
  *   BISIM_BOPT_TUNE        1 = re-run the autotuner on the next call even if
  *                          a cached choice exists.
  * Errors: BISIM_E_INVALID.

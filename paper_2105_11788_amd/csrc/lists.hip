@@ -658,8 +658,10 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
       __syncthreads();
     }
   }
+  RoundsWork work;
   if (rc == kRoundsDone)
-    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it, C);
+    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it, C,
+                                       work);
   if (threadIdx.x != 0) return;
   if (rc == kRoundsDone && sh.it > a.iter_cap) rc = kRoundsCap;
   ctl->state.v[7] = 0;

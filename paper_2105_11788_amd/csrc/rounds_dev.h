@@ -80,6 +80,15 @@ struct RoundsArgs {
   uint64_t *ub, *qb, *us, *qs;
 };
 
+// Work totals of a run, each thread's share (summed by the caller; what no
+// caller reads costs nothing).
+struct RoundsWork {
+  uint64_t members = 0, edges = 0;  // of the labels marked
+  uint64_t touched = 0;             // (label, source) pairs
+  uint64_t listed = 0, visits = 0;  // blocks with untouched members, and their members
+  uint64_t split = 0, blocks = 0;   // split states, new blocks
+};
+
 template <int WG>
 struct RoundsShared {
   uint32_t cand[kCand], cb[kCand], cpre[kCand], cend[kCand], unst[kCand];
@@ -253,8 +262,8 @@ __host__ __device__ inline uint32_t rounds_bitmap_bytes(uint32_t n) {
 // all labels unstable without verdict (global bitmaps), scratch zeroed.
 // Returns false if the partition is inconsistent (never expected).
 template <class MaskT, int WG>
-__device__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
-                             const int32_t* start, bool zero_mw) {
+__device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
+                                             const int32_t* start, bool zero_mw) {
   const uint32_t tid = threadIdx.x, wid = tid / kWave, n = a.n;
   const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
   for (uint32_t s = tid; s < n; s += WG) {
@@ -327,7 +336,7 @@ __device__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
 template <class MaskT, int WG, bool kBm>
 __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
                                                 char* lds, uint32_t lds_bytes, uint32_t it0,
-                                                uint32_t& grid_C) {
+                                                uint32_t& grid_C, RoundsWork& work) {
   constexpr uint32_t kWaves = WG / kWave;
   const uint32_t tid = threadIdx.x, wid = tid / kWave;
   const uint32_t n = a.n, s0 = a.s0;
@@ -513,6 +522,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       const bool fits = lane() < np && sh.cend[lane()] <= ecap;
       np = (uint32_t)__popcll(__ballot(fits));
       E = np ? sh.cend[np - 1] : 0u;
+      if (tid == 0 && np) {
+        work.members += np < sh.np ? sh.cpre[np] : mtot;
+        work.edges += E;
+      }
     }
     const bool big = np == 0 && nc != 0;
     uint32_t es[EU], eb[EU], ek[EU], sl[EU], ls[EU], lo[EU], sz[EU];
@@ -547,6 +560,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         mask_or<MaskT>(&t_mv[slot], (MaskT)1 << (eo[u] & (sizeof(MaskT) * 8 - 1)));
         if (!first) continue;
         sl[u] = slot;
+        work.touched += 1;
         if (eb[u] == es[u]) {
           lo[u] = (uint32_t)a.bs[es[u]];
           sz[u] = (uint32_t)a.be[es[u]] - lo[u];
@@ -621,6 +635,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     // the members of the listed blocks that `is_split` says are split off
     const auto members = [&](const auto& is_split) {
       const uint32_t nL = sh.nL;
+      if (tid == 0) work.listed += nL;
       for (uint32_t j0 = 0; j0 < nL; j0 += kWave) {
         const uint32_t j = j0 + lane();
         uint32_t b = 0, l = 0, z = 0;
@@ -642,6 +657,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           bool sp = false;
           if (e < total) {
             s = (uint32_t)a.perm[ol + (ee - oi)];
+            work.visits += 1;
             sp = is_split(s);
           }
           const uint32_t si = list_push(&sh.nS, sp);
@@ -657,6 +673,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         rc = kRoundsGrid;
         break;
       }
+      if (tid == 0) work.members += csz;
       if (dense) {
         // mark words of all states in LDS.  Four members per thread are in
         // flight; a member of many in-transitions is the whole wave's.
@@ -691,6 +708,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
               for (uint32_t e = lane(); e < od; e += kWave)
                 mark((uint32_t)a.in_src[ob + e] - s0, a.rcpp ? 0u : (uint32_t)a.in_ord[ob + e]);
             }
+            work.edges += deg[u];
             if (deg[u] > 2 * kWave) deg[u] = 0;
             most = max(most, deg[u]);
           }
@@ -743,6 +761,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           }
           const uint32_t incl = wave_incl_scan_u32(deg);
           const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+          work.edges += deg;
           for (uint32_t e0 = 0; e0 < total; e0 += kWave * kScanU) {
             uint32_t vs[kScanU], vo[kScanU], vb[kScanU], vl[kScanU], vh[kScanU];
             bool first[kScanU];
@@ -787,6 +806,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
         __syncthreads();
         const uint32_t nT = sh.nT;
+        if (tid == 0) work.touched += nT;
         for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG) {
           const uint32_t i = i0 + lane();
           int32_t s = 0, b = 0;
@@ -834,6 +854,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     // and takes its smallest member as label; front split states trade places
     // with the staying states of the tail
     const uint32_t nS = sh.nS;
+    if (tid == 0) work.split += nS;
     if (tid == WG - 1 && !a.rcpp) label_set2(U, US, Q, QS, C, C);  // Algorithm 3 re-marks C
     if (nS <= kSmall && small_ok) {
       uint32_t s = 0, b = 0, ps = 0, blo = 0, bhi = 0, slot = 0, own = 0, r = 0;
@@ -913,6 +934,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           a.be[s] = (int32_t)bhi;
           a.be[b] = (int32_t)ne;
           label_set2(U, US, Q, QS, b, s);
+          work.blocks += 1;
         }
       }
     } else {
@@ -981,6 +1003,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           a.fc[b] = 0;
           a.gc[b] = 0;
           label_set2(U, US, Q, QS, (uint32_t)b, (uint32_t)s);
+          work.blocks += 1;
         }
         atomicAnd((unsigned long long*)&a.sf[(uint32_t)s >> 6], ~(1ull << (s & 63)));
       }

@@ -111,3 +111,20 @@ def test_rounds_leave_large_splitters_to_the_grid(B, n, actions):
 def test_rounds_algorithm2(B, seed):
     check(B, gen.kripke_uniform(1000, 5000, seed=seed), algorithm=2, engines=(0,))
     check(B, gen.random_lts(700, 1500, 1, seed, init_blocks=3), algorithm=2, engines=(0,))
+
+
+@pytest.mark.parametrize("lds", [0, 2000, 30000, 70000])
+def test_batch_rounds_default_workgroup(B, lds):
+    """The batched kernel at its default workgroup size, from the whole LDS
+    down to a budget that holds neither the table nor the label bitmaps."""
+    insts = [CASES[c]() for c in ("n1", "n64", "kripke", "wide-marks", "chain", "fan-out", "hub",
+                                  "planted-2-actions", "no-transitions")]
+    with B.Batch(insts) as b:
+        b.set_option(B.BOPT_LDS_LIMIT, lds)
+        b.set_option(B.BOPT_GRID, 4)  # a workgroup takes several instances
+        out, its, st = b.run()
+        blocks = b.split(out.numpy())
+    assert st["workgroup_size"] == 512
+    for k, L in enumerate(insts):
+        ref = oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst, L.init)
+        assert (blocks[k] == ref["block"]).all() and its[k] == ref["iters"], (k, L.name)
