@@ -167,8 +167,9 @@ const char* bisim_last_error(void);
  *                           traced, counted and profiled runs); Algorithm 3
  *                           with the plain policy only (else
  *                           BISIM_E_UNSUPPORTED at coarsest_partition); about
- *                           96 more bytes of device memory per state,
- *                           allocated on first use.
+ *                           96 more bytes of device memory per state and, from
+ *                           8,192 transitions on, 8 per transition, allocated
+ *                           on first use.
  *   BISIM_OPT_COUNT_WORK    0 (default) or 1: engine 3 accumulates work totals
  *                           over the run (bisim_get_work).
  *   BISIM_OPT_FIRST_SPLITTER  -1 (default) or a block label of the
@@ -380,7 +381,8 @@ void lts_batch_free(bisim_batch* b);
 
 /*
  * bisim_batch_set_option — per-batch settings.
- *   BISIM_BOPT_WG_SIZE     0 (default: 512 threads) or 256.
+ *   BISIM_BOPT_WG_SIZE     0 (default: 1024 threads, or 256 where the autotuner
+ *                          measures that faster) or 256.
  *   BISIM_BOPT_GRID        0 (default: autotuned) or a workgroup count.
  *   BISIM_BOPT_LDS_LIMIT   0 (default: the device's per-workgroup LDS) or a
  *                          smaller byte budget (what does not fit it is kept

@@ -31,6 +31,7 @@
 struct bisim_batch {
   int32_t count = 0;
   int64_t N = 0, M = 0;
+  uint32_t n_max = 0;  // states of the largest instance
   int32_t Kmax = 1;
   hipStream_t stream = nullptr;
   hipStream_t own_stream = nullptr;
@@ -54,6 +55,7 @@ struct bisim_batch {
           *ob = nullptr, *nev = nullptr, *ltl = nullptr, *tlb = nullptr, *se = nullptr,
           *llo = nullptr, *lsz = nullptr;
   uint64_t *sf = nullptr, *us = nullptr, *tmp64 = nullptr, *pin = nullptr;
+  uint8_t* trk = nullptr;
   uint32_t* iters_d = nullptr;  // [count]
   uint32_t* ctl_d = nullptr;    // [0] queue head, [1] error
   unsigned long long* work_d = nullptr;  // [16] work totals per tier
@@ -96,6 +98,10 @@ struct BArgs {
   int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc, *tmp, *rk, *fi, *ob, *nev, *ltl, *tlb, *se, *llo,
       *lsz;
   uint64_t *sf, *us, *tmp64, *pin;
+  const uint32_t* __restrict__ out_ptr;  // transitions by source
+  const int32_t* __restrict__ out_dst;
+  const int32_t* __restrict__ out_ord;
+  uint8_t* trk;
   int32_t* out;
   uint32_t* iters;
   uint32_t* ctl;
@@ -111,12 +117,14 @@ __host__ __device__ inline uint64_t lds_need(uint32_t n) {
   return 8ull * 3 * nw + 8ull * n + ((sizeof(MaskT) * (uint64_t)n + 7) & ~7ull) + 4ull * n;
 }
 
-// Workgroup sizes: 512 threads unless the caller asks for 256.  A launch ends
-// with its slowest instance, whose rounds spread over more waves, and a CU
-// holds one such workgroup with the whole LDS (256 instances of up to 40k
-// states: 84 ms at 512 threads, 112 at 256, 108 at 1024; 48 of up to 200k:
-// 1,014 / 1,383 / 937 ms; 2048 of up to 2k: 4.2 / 4.5 / 5.2 ms).
-constexpr int kBatchWG = 512, kBatchWGOption = 256;
+// Workgroup sizes.  A launch ends with its slowest instance, whose rounds
+// spread over more waves at 1024 threads (one workgroup per CU with the whole
+// LDS); where instances are many and tiny, two or more workgroups of 256 per
+// CU are ahead.  At 1024 / 512 / 256 threads: 256 instances of up to 40k
+// states 88 / 92 / 112 ms, 48 of up to 200k 461 / 500 / 640, 2048 of up to 2k
+// 4.6 / 4.4 / 4.5, 8192 of up to 200 2.0 / 1.6 / 1.5.  The autotuner times
+// both; 256 is what the option names.
+constexpr int kBatchWG = 1024, kBatchWGOption = 256;
 
 template <int WG>
 struct Shared {
@@ -125,7 +133,10 @@ struct Shared {
   unsigned long long work[7];
 };
 
-template <class MaskT, int WG>
+// kBm: the label bitmaps of every instance fit the LDS budget beside the
+// tables (else they stay in global memory for all of them: a second copy of
+// the loop in one kernel spills registers).
+template <class MaskT, int WG, bool kBm>
 __global__ void __launch_bounds__(WG) k_batch(BArgs a) {
   extern __shared__ uint64_t lds[];
   __shared__ Shared<WG> sh;
@@ -134,10 +145,13 @@ __global__ void __launch_bounds__(WG) k_batch(BArgs a) {
     if (threadIdx.x == 0) sh.job = atomicAdd(&a.ctl[0], 1u);
     if (threadIdx.x < 7) sh.work[threadIdx.x] = 0;
     __syncthreads();
-    const uint32_t job = sh.job;
+    // scalars, so that the instance's pointers are scalars too (as vectors
+    // they cost over 100 registers and spilled)
+    const uint32_t job = uniform_u32(sh.job);
     if (job >= (uint32_t)a.count) break;
-    const int32_t k = a.order[job];
-    const uint32_t s0 = a.n_off[k], n = a.n_off[k + 1] - s0, b0 = a.bw_off[k];
+    const uint32_t k = uniform_u32((uint32_t)a.order[job]);
+    const uint32_t s0 = uniform_u32(a.n_off[k]), n = uniform_u32(a.n_off[k + 1]) - s0;
+    const uint32_t b0 = uniform_u32(a.bw_off[k]);
     RoundsArgs<MaskT> g{};
     g.n = n;
     g.s0 = s0;
@@ -174,14 +188,15 @@ __global__ void __launch_bounds__(WG) k_batch(BArgs a) {
     g.qb = a.qb + b0;
     g.us = a.us + b0;
     g.qs = a.qs + b0;
-    const bool bm =
-        rounds_bitmap_bytes(n) + split_bytes<WG>() + table_bytes<MaskT>(256) <= a.lds_bytes;
+    g.out_ptr = a.out_ptr + s0;
+    g.out_dst = a.out_dst;
+    g.out_ord = a.out_ord;
+    g.trk = a.trk + s0;
+    g.mean_deg = uniform_u32(n ? (a.in_ptr[s0 + n] - a.in_ptr[s0] + n - 1) / n : 1u);
     uint32_t rc = kRoundsBad, none = 0;
     RoundsWork w;
-    if (rounds_setup<MaskT, WG>(g, sh.r, a.pre_block + s0, true)) {
-      if (bm) rc = rounds_loop<MaskT, WG, true>(g, sh.r, base, a.lds_bytes, 0, none, w);
-      else rc = rounds_loop<MaskT, WG, false>(g, sh.r, base, a.lds_bytes, 0, none, w);
-    }
+    if (rounds_setup<MaskT, WG>(g, sh.r, a.pre_block + s0, true))
+      rc = rounds_loop<MaskT, WG, kBm>(g, sh.r, base, a.lds_bytes, 0, RoundsResume(), none, w);
     if (rc == kRoundsDone && sh.r.it > g.iter_cap) rc = kRoundsCap;
     for (uint32_t s = threadIdx.x; s < n; s += WG) a.out[s0 + s] = g.blk[s];
     const uint64_t t[7] = {w.members, w.edges, w.touched, w.listed, w.visits, w.split, w.blocks};
@@ -283,7 +298,7 @@ void free_batch(bisim_batch* b) {
                   b->pos,     b->bs,       b->be,      b->cnt, b->fc,      b->gc,    b->tmp,
                   b->rk,      b->fi,       b->ltl,     b->sf,  b->us,      b->ob,    b->nev,
                   b->tlb,     b->se,       b->tmp64,   b->work_d, b->llo, b->lsz,
-                  b->pin};
+                  b->pin,     b->trk};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (b->u) lts_destroy(b->u);
@@ -332,6 +347,10 @@ BArgs make_args(bisim_batch* b, int32_t* out) {
   a.pin = b->pin;
   a.sf = b->sf;
   a.us = b->us;
+  a.out_ptr = b->u->lists.out_ptr;
+  a.out_dst = b->u->lists.out_dst;
+  a.out_ord = b->u->lists.out_ord;
+  a.trk = b->trk;
   a.out = out;
   a.iters = b->iters_d;
   a.ctl = b->ctl_d;
@@ -340,23 +359,18 @@ BArgs make_args(bisim_batch* b, int32_t* out) {
   return a;
 }
 
-// allow dynamic LDS up to the device's per-workgroup maximum
-void allow_lds(bisim_batch* b) {
-  const void* fns[] = {
-      (const void*)k_batch<uint64_t, kBatchWG>, (const void*)k_batch<uint32_t, kBatchWG>,
-      (const void*)k_batch<uint64_t, kBatchWGOption>,
-      (const void*)k_batch<uint32_t, kBatchWGOption>};
-  for (const void* f : fns)
-    (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b->lds_max);
-  (void)hipGetLastError();
+// the kernel of a configuration: workgroup size, mark word and whether the
+// largest instance's label bitmaps fit the budget
+template <int WG>
+const void* kernel_for(const bisim_batch* b, int lds) {
+  const bool bm = rounds_bitmap_bytes(b->n_max) + split_bytes<WG>() +
+                      table_bytes<uint64_t>(256) <= (uint32_t)lds;
+  if (b->mask64)
+    return bm ? (const void*)k_batch<uint64_t, WG, true> : (const void*)k_batch<uint64_t, WG, false>;
+  return bm ? (const void*)k_batch<uint32_t, WG, true> : (const void*)k_batch<uint32_t, WG, false>;
 }
-
-const void* kernel_of(const bisim_batch* b, int wg) {
-  if (wg == kBatchWG)
-    return b->mask64 ? (const void*)k_batch<uint64_t, kBatchWG>
-                     : (const void*)k_batch<uint32_t, kBatchWG>;
-  return b->mask64 ? (const void*)k_batch<uint64_t, kBatchWGOption>
-                   : (const void*)k_batch<uint32_t, kBatchWGOption>;
+const void* kernel_of(const bisim_batch* b, int wg, int lds) {
+  return wg == kBatchWG ? kernel_for<kBatchWG>(b, lds) : kernel_for<kBatchWGOption>(b, lds);
 }
 
 bisim_status launch_once(bisim_batch* b, int32_t* out, int wg, int grid, int lds) {
@@ -368,7 +382,9 @@ bisim_status launch_once(bisim_batch* b, int32_t* out, int wg, int grid, int lds
     return BISIM_E_INVALID;
   }
   void* args[] = {&a};
-  BISIM_TRY_HIP(hipLaunchKernel(kernel_of(b, wg), dim3(grid), dim3(wg), args, lds, b->stream));
+  const void* f = kernel_of(b, wg, lds);
+  BISIM_TRY_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b->lds_max));
+  BISIM_TRY_HIP(hipLaunchKernel(f, dim3(grid), dim3(wg), args, lds, b->stream));
   BISIM_TRY_HIP(hipGetLastError());
   return BISIM_OK;
 }
@@ -376,7 +392,9 @@ bisim_status launch_once(bisim_batch* b, int32_t* out, int wg, int grid, int lds
 int max_resident(bisim_batch* b, int wg, int lds) {
   int per_cu = 0;
   if (wg != kBatchWG && wg != kBatchWGOption) return 0;
-  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_of(b, wg), wg, lds);
+  const void* f = kernel_of(b, wg, lds);
+  (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b->lds_max);
+  hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, wg, lds);
   if (e != hipSuccess || per_cu < 1) return 0;
   return per_cu * b->num_cu;
 }
@@ -438,27 +456,28 @@ void tune_store(const std::string& key, int wg, int grid, int lds, float ms) {
 // Autotuner: time each candidate (workgroup size, LDS budget, grid = as many
 // workgroups as stay resident) on the batch itself and keep the fastest.
 bisim_status autotune(bisim_batch* b, int32_t* out) {
-  const int wgs[] = {kBatchWG};
-  std::vector<int> budgets;
-  for (int l = b->lds_max; l >= 16384 && budgets.size() < 4; l /= 2) budgets.push_back(l);
+  const struct {
+    int wg, lds;
+  } cands[] = {{kBatchWG, b->lds_max},
+               {kBatchWGOption, b->lds_max / 2},
+               {kBatchWGOption, b->lds_max / 4}};
   float best = 1e30f;
   int bw = 0, bg = 0, bl = 0;
-  for (int wg : wgs) {
-    for (int lds : budgets) {
-      const int grid = max_resident(b, wg, lds);
-      if (grid < 1) continue;
-      BISIM_TRY_HIP(hipEventRecord(b->ev0, b->stream));
-      BISIM_TRY(launch_once(b, out, wg, grid, lds));
-      BISIM_TRY_HIP(hipEventRecord(b->ev1, b->stream));
-      BISIM_TRY_HIP(hipEventSynchronize(b->ev1));
-      float ms = 0;
-      BISIM_TRY_HIP(hipEventElapsedTime(&ms, b->ev0, b->ev1));
-      if (ms < best) {
-        best = ms;
-        bw = wg;
-        bg = grid;
-        bl = lds;
-      }
+  for (const auto& c : cands) {
+    const int wg = c.wg, lds = c.lds & ~63;
+    const int grid = max_resident(b, wg, lds);
+    if (grid < 1) continue;
+    BISIM_TRY_HIP(hipEventRecord(b->ev0, b->stream));
+    BISIM_TRY(launch_once(b, out, wg, grid, lds));
+    BISIM_TRY_HIP(hipEventRecord(b->ev1, b->stream));
+    BISIM_TRY_HIP(hipEventSynchronize(b->ev1));
+    float ms = 0;
+    BISIM_TRY_HIP(hipEventElapsedTime(&ms, b->ev0, b->ev1));
+    if (ms < best) {
+      best = ms;
+      bw = wg;
+      bg = grid;
+      bl = lds;
     }
   }
   if (!bw) {
@@ -496,12 +515,14 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
     return BISIM_E_INVALID;
   }
   int32_t Kmax = 1;
+  int64_t n_max = 0;
   for (int32_t k = 0; k < count; ++k) {
     if (n_off[k + 1] < n_off[k] || m_off[k + 1] < m_off[k] || num_actions[k] < 1) {
       set_error("lts_batch_load: offsets must be non-decreasing and num_actions >= 1");
       return BISIM_E_INVALID;
     }
     Kmax = std::max(Kmax, num_actions[k]);
+    n_max = std::max(n_max, n_off[k + 1] - n_off[k]);
   }
   const int64_t N = n_off[count], M = m_off[count];
   if (N >= 0x7FFFFFFF || M >= 0xFFFFFFFFll) {
@@ -518,6 +539,7 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
   b->N = N;
   b->M = M;
   b->Kmax = Kmax;
+  b->n_max = (uint32_t)n_max;
   b->n_off.assign(n_off, n_off + count + 1);
   bisim_status st = BISIM_OK;
   int32_t *gsrc = nullptr, *gdst = nullptr, *ginit = nullptr, *Kd = nullptr;
@@ -537,7 +559,6 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
       break;
     }
     b->lds_max = (b->lds_max - (int)sizeof(Shared<kBatchWG>) - 64) & ~63;
-    allow_lds(b);
     b->stream = hip_stream ? (hipStream_t)hip_stream : b->own_stream;
     hipStream_t s = b->stream;
     if (hipEventRecord(b->ev0, s) != hipSuccess) { st = BISIM_E_DEVICE; break; }
@@ -612,7 +633,8 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
         (st = dmalloc(&b->ob, (size_t)N)) || (st = dmalloc(&b->nev, (size_t)N)) ||
         (st = dmalloc(&b->us, BW)) || (st = dmalloc(&b->tlb, (size_t)N)) ||
         (st = dmalloc(&b->se, (size_t)N)) || (st = dmalloc(&b->tmp64, (size_t)N)) ||
-        (st = dmalloc(&b->pin, (size_t)N)) ||
+        (st = dmalloc(&b->pin, (size_t)N)) || (st = dmalloc(&b->trk, (size_t)N)) ||
+        (st = by_source(b->u)) ||
         (st = dmalloc(&b->llo, (size_t)N)) || (st = dmalloc(&b->lsz, (size_t)N)) ||
         (st = dmalloc(&b->iters_d, count)) || (st = dmalloc(&b->ctl_d, 2)) ||
         (st = dmalloc(&b->work_d, 16)))

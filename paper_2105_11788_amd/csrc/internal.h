@@ -165,6 +165,11 @@ struct bisim_lists {
   int32_t *ss = nullptr, *sbk = nullptr, *sr = nullptr, *sfi = nullptr, *sne = nullptr,
           *sps = nullptr, *sse = nullptr;
   uint64_t* work = nullptr;
+  // rounds: transitions by source, tracked labels
+  uint32_t* out_ptr = nullptr;
+  int32_t *out_dst = nullptr, *out_ord = nullptr;
+  uint8_t* trk = nullptr;
+  uint32_t* trk_save = nullptr;
   // the captured graph of a chunk of iterations and the arguments it holds
   hipGraphExec_t gexec = nullptr;
   unsigned char gargs[512] = {};
@@ -311,6 +316,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals);
 void lists_free(bisim_lts* h);
 // the same engine by rounds of one workgroup (splitters that split nothing
 // decided ahead of their turn); rounds_apply says whether a run may take them
+bisim_status by_source(bisim_lts* h);  // lists.out_ptr, out_dst, out_ord
 bool rounds_apply(const bisim_lts* h);
 bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool rcpp);
 }  // namespace bisim

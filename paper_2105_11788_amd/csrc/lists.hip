@@ -84,6 +84,7 @@ struct LArgs {
   uint64_t* ub;   // unstable labels
   uint64_t* us;   // summary of ub
   uint64_t *qb, *qs;  // rounds: unstable labels without a verdict and their summary (else null)
+  uint8_t* trk;   // rounds: per label, tracked (a block that splits here no longer is)
   int gated;      // rounds: an iteration runs only when one was asked for (state.v[7])
   uint64_t* nlw;  // bids
   int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc;
@@ -461,6 +462,9 @@ __device__ __forceinline__ void relabel_one(const LArgs& a, uint32_t i) {
   const int32_t e = a.be[b], c = a.cnt[b], pv = a.pos[s];
   const int32_t nl = (int32_t)(kNone - (uint32_t)nv);
   a.block[s] = nl;
+  // rounds: a split part with different marks (they are cleared by a kernel
+  // of its own then)
+  if (a.gated && marks_differ(a, s, nl)) a.ctl->state.v[9] = 1;
   const int32_t ne = e - c, q = ne + r;
   int32_t fv = -1, uv = -1;
   const bool ok = ne >= 0 && q >= ne && q < e && e <= (int32_t)n && pv >= 0 && pv < (int32_t)n;
@@ -512,6 +516,7 @@ __device__ __forceinline__ bool swap_one(const LArgs& a, uint32_t i, uint32_t& b
     a.cnt[b] = 0;
     a.fc[b] = 0;
     a.gc[b] = 0;
+    if (a.trk) a.trk[b] = 0;
     set_unstable(a, (uint32_t)b);
     set_unstable(a, (uint32_t)s);
     best = min(best, (uint32_t)b);
@@ -519,6 +524,21 @@ __device__ __forceinline__ bool swap_one(const LArgs& a, uint32_t i, uint32_t& b
   }
   atomicAnd((unsigned long long*)&a.sf[s >> 6], ~(1ull << (s & 63)));
   return lead;
+}
+
+// clear the marks, touched bits and touched counts of this iteration's
+// touched states
+__device__ __forceinline__ void clear_touched(const LArgs& a, uint32_t nT, const GPart& p) {
+  for (uint32_t i = p.gtid; i < nT; i += p.gthreads) {
+    const int32_t s = a.ts[i];
+    a.tcn[a.tbk[i]] = 0;  // every touched state of the block clears it
+    if (a.uniform) {
+      a.mw[s] = 0;
+    } else {
+      for (uint32_t w = a.woff[s]; w < a.woff[s + 1]; ++w) a.mw[w] = 0;
+    }
+    a.tb[s >> 6] = 0;  // every touched state of the word clears it
+  }
 }
 
 __global__ void __launch_bounds__(kLT) k_l_split(LArgs a, uint32_t kofs) {
@@ -564,18 +584,12 @@ __global__ void __launch_bounds__(kLT) k_l_split(LArgs a, uint32_t kofs) {
       count_work(a, 6, wave_sum_u64(leaders));
     }
   }
-  // clear the marks, touched bits and touched counts of this iteration's
-  // touched states
-  for (uint32_t i = p.gtid; i < nT; i += p.gthreads) {
-    const int32_t s = a.ts[i];
-    a.tcn[a.tbk[i]] = 0;  // every touched state of the block clears it
-    if (a.uniform) {
-      a.mw[s] = 0;
-    } else {
-      for (uint32_t w = a.woff[s]; w < a.woff[s + 1]; ++w) a.mw[w] = 0;
-    }
-    a.tb[s >> 6] = 0;  // every touched state of the word clears it
-  }
+  if (!a.gated) clear_touched(a, nT, p);
+}
+
+__global__ void __launch_bounds__(kLT) k_l_clear(LArgs a) {
+  if (idle(a, a.ctl->state.v[1])) return;
+  clear_touched(a, min(a.ctl->cntT[0].v[0], a.n), gpart());
 }
 
 // after a graph replay of `by` iterations: advance the iteration base
@@ -594,6 +608,7 @@ __global__ void k_l_zero(LArgs a) {
     a.fc[s] = 0;
     a.gc[s] = 0;
     a.tcn[s] = 0;
+    if (a.trk) a.trk[s] = 0;
   }
   if (p.gtid < 8) a.work[p.gtid] = 0;
   if (p.gtid < 2) a.pf[p.gtid * kPfWords + 3] = 0;
@@ -623,7 +638,7 @@ __global__ void k_l_zero_cnt(LArgs a) {
 
 // ---------------------------------------------------------------------------
 // rounds: the loop by one workgroup (rounds_dev.h), until the run is over or
-// a splitter is large enough for the grid.  The three kernels above then
+// a splitter is large enough for the grid.  The kernels above then
 // carry out that iteration, and the next launch goes on after it.
 // ---------------------------------------------------------------------------
 // Workgroup size: 1024 threads against 512 and 256, uniform LTS of 20k states
@@ -633,11 +648,14 @@ __global__ void k_l_zero_cnt(LArgs a) {
 constexpr int kRWG = 1024;
 constexpr uint32_t kSetupN = 16384;     // up to here the workgroup builds the member lists itself
 // A splitter whose marks fit neither the table nor LDS is the grid's: its
-// iteration takes about 32 us there (four launches), 40-112 us by the
+// iteration takes about 37 us there (five launches), 40-112 us by the
 // workgroup, whose few waves wait for each transition's mark word in memory
-// (planted quotient of 1.03M states: 336 ms, with the workgroup taking up to
-// 8192 / 49152 transitions 444 / 937 ms).
+// (planted quotient of 1.03M states before tracking: 336 ms, with the
+// workgroup taking up to 8192 / 49152 transitions 444 / 937 ms).
 constexpr uint32_t kGridEdges = 2048;
+// LTSs with fewer transitions have their mark words in LDS, where marking a
+// whole block costs little: their transitions are not laid out by source
+constexpr int64_t kTrackMinM = 65536;
 
 template <class MaskT, bool kBm>
 __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, uint32_t* pf,
@@ -646,6 +664,8 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
   __shared__ RoundsShared<kRWG> sh;
   const uint32_t done = ctl->state.v[1], entered = ctl->state.v[8];
   const uint32_t it = ctl->state.v[6] + (ctl->state.v[7] ? 1u : 0u);
+  RoundsResume resume;
+  if (ctl->state.v[7]) resume = {ctl->state.v[3], ctl->cntS[0].v[0], ctl->state.v[9]};
   if (done) return;
   uint32_t rc = kRoundsDone, C = kNone;
   if (!entered) {
@@ -660,8 +680,8 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
   }
   RoundsWork work;
   if (rc == kRoundsDone)
-    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it, C,
-                                       work);
+    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it,
+                                       resume, C, work);
   if (threadIdx.x != 0) return;
   if (rc == kRoundsDone && sh.it > a.iter_cap) rc = kRoundsCap;
   ctl->state.v[7] = 0;
@@ -671,6 +691,7 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
     // mark kernel of an even launch position expects them
     ctl->state.v[6] = sh.it - 1;  // the number of C's iteration
     ctl->state.v[7] = 1;
+    ctl->state.v[9] = 0;
     ctl->cand[0].v[0] = C;
     ctl->cand[1].v[0] = kNone;
     ctl->cntT[0].v[0] = 0;
@@ -683,6 +704,33 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
   ctl->state.v[1] = 1;
   if (rc == kRoundsCap) ctl->state.v[2] = 1;
   if (rc == kRoundsBad) ctl->state.v[4] = 1;
+}
+
+// transitions by source, from those by target
+__global__ void k_l_zero_u32(uint32_t* p, uint32_t n) {
+  const GPart g = gpart();
+  for (uint32_t i = g.gtid; i < n; i += g.gthreads) p[i] = 0;
+}
+__global__ void k_l_copy_u32(const uint32_t* __restrict__ from, uint32_t* __restrict__ to,
+                             uint32_t n) {
+  const GPart g = gpart();
+  for (uint32_t i = g.gtid; i < n; i += g.gthreads) to[i] = from[i];
+}
+__global__ void k_l_out_count(const int32_t* __restrict__ src, uint64_t m, uint32_t* cnt) {
+  const GPart g = gpart();
+  for (uint64_t i = g.gtid; i < m; i += g.gthreads) atomicAdd(&cnt[src[i]], 1u);
+}
+__global__ void k_l_out_fill(uint32_t n, const uint32_t* __restrict__ in_ptr,
+                             const int32_t* __restrict__ in_src, const int32_t* __restrict__ in_ord,
+                             uint32_t* cursor, int32_t* __restrict__ out_dst,
+                             int32_t* __restrict__ out_ord) {
+  const GPart g = gpart();
+  for (uint32_t t = g.gtid; t < n; t += g.gthreads)
+    for (uint32_t e = in_ptr[t]; e < in_ptr[t + 1]; ++e) {
+      const uint32_t q = atomicAdd(&cursor[in_src[e]], 1u);
+      out_dst[q] = (int32_t)t;
+      out_ord[q] = in_ord[e];
+    }
 }
 
 template <class T>
@@ -760,6 +808,7 @@ static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_tota
   a.pin = L.pin;
   a.pf = L.pf;
   a.tmp64 = L.tmp64;
+  a.trk = L.trk;
   a.lb = L.lb;
   a.lo = L.lo;
   a.lh = L.lh;
@@ -933,6 +982,38 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   return BISIM_OK;
 }
 
+// The transitions by source (target and action rank), from those by target.
+bisim_status by_source(bisim_lts* h) {
+  bisim_lists& L = h->lists;
+  if (L.out_ord) return BISIM_OK;  // the last one to be allocated
+  hipStream_t st = h->stream;
+  const size_t n = (size_t)h->n;
+  const int cu = h->num_cu > 0 ? h->num_cu : 1;
+  uint32_t* cur = nullptr;
+  BISIM_TRY(lalloc(&L.out_ptr, n + 1, st));
+  BISIM_TRY(lalloc(&L.out_dst, (size_t)h->m, st));
+  BISIM_TRY(lalloc(&cur, n, st));
+  int64_t g = (h->m + kLT - 1) / kLT;
+  g = g > cu * 32 ? cu * 32 : (g < 1 ? 1 : g);
+  int64_t gn = ((int64_t)n + kLT - 1) / kLT;
+  gn = gn > cu * 8 ? cu * 8 : (gn < 1 ? 1 : gn);
+  hipLaunchKernelGGL(k_l_zero_u32, dim3((unsigned)gn), dim3(kLT), 0, st, cur, (uint32_t)n);
+  hipLaunchKernelGGL(k_l_out_count, dim3((unsigned)g), dim3(kLT), 0, st, h->in_src,
+                     (uint64_t)h->m, cur);
+  bisim_status rc = exclusive_scan_u32(cur, L.out_ptr, (int64_t)n, st);
+  if (rc == BISIM_OK) rc = lalloc(&L.out_ord, (size_t)h->m, st);
+  if (rc == BISIM_OK) {
+    hipLaunchKernelGGL(k_l_copy_u32, dim3((unsigned)gn), dim3(kLT), 0, st, L.out_ptr, cur,
+                       (uint32_t)n);
+    hipLaunchKernelGGL(k_l_out_fill, dim3((unsigned)gn), dim3(kLT), 0, st, (uint32_t)n, h->in_ptr,
+                       h->in_src, h->in_ord, cur, L.out_dst, L.out_ord);
+  }
+  (void)dev_free(cur, st);
+  BISIM_TRY(rc);
+  BISIM_TRY_HIP(hipGetLastError());
+  return BISIM_OK;
+}
+
 bool rounds_apply(const bisim_lts* h) {
   return h->uniform && (uint32_t)h->n <= kRoundsMaxN && h->trace_cap == 0 &&
          h->first_splitter < 0 && h->profile_every == 0 && !h->count_work;
@@ -982,6 +1063,11 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.us = h->us;
   a.qb = l.qb;
   a.qs = l.qs;
+  a.out_ptr = L.out_ptr;
+  a.out_dst = L.out_dst;
+  a.out_ord = L.out_ord;
+  a.trk = L.trk;
+  a.trk_save = L.trk_save;
   const auto kern = k_rounds<MaskT, kBm>;
   BISIM_TRY_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds_bytes));
@@ -1000,6 +1086,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
       hipLaunchKernelGGL(k_l_mark, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_compare, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_split, dim3(grid), dim3(kLT), 0, st, l, 0u);
+      hipLaunchKernelGGL(k_l_clear, dim3(grid), dim3(kLT), 0, st, l);
       hipLaunchKernelGGL(kern, dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start,
                          lds_bytes);
     }
@@ -1013,6 +1100,12 @@ bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool r
   LArgs l;
   const uint32_t n = (uint32_t)h->n, nw = (n + 63) / 64;
   const bool own = n <= kSetupN;
+  bisim_lists& L = h->lists;
+  if (h->m >= kTrackMinM) {
+    BISIM_TRY(by_source(h));
+    BISIM_TRY(lalloc(&L.trk, n, h->stream));
+    BISIM_TRY(lalloc(&L.trk_save, kTrackSave, h->stream));
+  }
   BISIM_TRY(lists_setup(h, cap, false, !own, l));
   l.qb = h->lt;
   l.qs = h->lt + nw;
@@ -1040,7 +1133,7 @@ void lists_free(bisim_lts* h) {
     (void)hipStreamSynchronize(L.own);
     (void)hipStreamDestroy(L.own);
   }
-  void* ptrs[] = {L.perm, L.pos, L.bs,  L.be,  L.cnt, L.fc,  L.gc,  L.tmp64, L.lb, L.lo, L.lh, L.ts,
+  void* ptrs[] = {L.out_ptr, L.out_dst, L.out_ord, L.trk, L.trk_save, L.perm, L.pos, L.bs,  L.be,  L.cnt, L.fc,  L.gc,  L.tmp64, L.lb, L.lo, L.lh, L.ts,
                   L.tbk,  L.ss,  L.sbk, L.sr,  L.sfi, L.sne, L.sps, L.sse,   L.work, L.tcn,
                   L.pin,  L.pf};
   for (void* q : ptrs)

@@ -20,6 +20,19 @@
 // a workgroup and 2.5-3 us as a kernel boundary, and with the verdicts taken
 // side by side one CU has enough lanes for a round's transitions.
 //
+// A large block is marked again and again because single states leave it.
+// Such a label is tracked: the partition is known to be stable under a set B
+// of states that was the block (when it was last found stable, or after an
+// iteration of its own that left no block with two different marks), and the
+// states that have left since are listed.  Under the block as it is now, a
+// state's marks can differ from its marks under B only if it has a transition
+// to a listed state, so only those sources are visited; their outgoing
+// transitions tell which marks they lost, and two states of a block have equal
+// marks iff they lost the same ones.  The table then holds the lost marks in
+// place of the marks, and the rest of the round is the same.  (Uniform LTS of
+// 300k states 1,290 -> 929 ms, chain of 100k 2,640 -> 816, 48 instances of up
+// to 200k states in a batch 1,014 -> 500.)
+//
 // Bound: the chain of a round's dependent steps, about 9 us when something
 // splits (uniform LTS of 20k states, 3,464 rounds for 27,089 iterations):
 // candidates 1.6, members 1.1, transitions 1.8, comparison 1.1, verdicts 0.7,
@@ -44,11 +57,19 @@ namespace bisim {
 constexpr uint32_t kCand = 32;       // candidates per round (at most a wave's lanes)
 constexpr uint32_t kKeyBits = 27;    // state bits of a table key
 constexpr uint32_t kRoundsMaxN = (1u << kKeyBits) - 1;  // so that no key is kNone
+constexpr uint32_t kTracked = 64;    // labels tracked at a time
+constexpr uint32_t kLost = 64;       // states a tracked block can have lost
+// In-transitions from which a label is tracked: below, marking the whole block
+// costs a round no more than the visits of its lost states' sources (2.5 us).
+// While the mark words of all states fit LDS that is up to 8192 (3-4 us for
+// 5000; chain of 5000 states 40.4 ms untracked, 43.6 tracked from 384 on).
+constexpr uint32_t kTrackEdges = 384, kTrackEdgesDense = 8192;
+constexpr uint32_t kOutU = 8;        // outgoing transitions in flight per thread
 constexpr uint32_t kListCap = 64;    // listed blocks kept in LDS
 constexpr uint32_t kScanU = 4;       // states or transitions in flight per thread
 // transitions per thread and round
 template <int WG>
-constexpr uint32_t edges_per_thread() { return WG >= 1024 ? 2 : 4; }
+constexpr uint32_t edges_per_thread() { return WG >= 512 ? 2 : 4; }
 // split states that are moved by the tables in LDS (one per thread)
 template <int WG>
 constexpr uint32_t small_split() { return WG < 256 ? WG : 256; }
@@ -76,6 +97,12 @@ struct RoundsArgs {
   int32_t *ts, *tb;                       // touched states and their blocks
   int32_t *lb, *llo, *lsz;                // listed blocks and their ranges
   int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;
+  // transitions by source, and per label its entry among the tracked ones plus
+  // one (0: not tracked); null: no tracking
+  const uint32_t* out_ptr;
+  const int32_t *out_dst, *out_ord;
+  uint8_t* trk;
+  uint32_t* trk_save;  // [kTrackSave] between launches of one run (nullable)
   // bitmaps over labels and their summaries (bit w set iff word w is not 0)
   uint64_t *ub, *qb, *us, *qs;
 };
@@ -89,17 +116,36 @@ struct RoundsWork {
   uint64_t split = 0, blocks = 0;   // split states, new blocks
 };
 
+// What the grid did between two launches of one run: the iteration of `label`
+// (kNone: none), the split states it listed, and whether the split part of
+// some block holds different marks.
+struct RoundsResume {
+  uint32_t label = kNone, nS = 0, mixed = 0;
+};
+
 template <int WG>
 struct RoundsShared {
   uint32_t cand[kCand], cb[kCand], cpre[kCand], cend[kCand], unst[kCand];
+  uint32_t ctrk[kCand];  // tracked entry of the candidate plus one
+  uint32_t tn[kTracked], tlabel[kTracked];  // tracked labels: lost states, label
   uint32_t wsum[WG / kWave];
   uint32_t mbeg[WG], mpre[WG];
   uint8_t mc[WG];
   int32_t ss[small_split<WG>()], sb[small_split<WG>()];  // the first split states and their blocks
   uint32_t lb[kListCap], llo[kListCap], lsz[kListCap];   // the first listed blocks
-  uint32_t nc, np, mtot, csz0, nS, nL, nT, tctr, bad;
+  uint32_t nc, np, mtot, etot, csz0, nS, nL, nT, tctr, bad;
+  uint32_t inc;              // candidates visited through their lost states
+  uint32_t tnext;            // next tracked entry to take
+  uint32_t fent, ffresh;     // the splitter's entry plus one; taken in this round
+  uint32_t fold;             // lost states its entry already had
+  uint32_t mixed, nself;     // a split part with different marks; split states of C itself
   uint32_t it;  // iterations so far
 };
+
+// a value that is the same on every lane, as a scalar
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
 
 template <class MaskT>
 __device__ __forceinline__ MaskT mask_or(MaskT* p, MaskT v);
@@ -110,6 +156,12 @@ __device__ __forceinline__ uint32_t mask_or<uint32_t>(uint32_t* p, uint32_t v) {
 template <>
 __device__ __forceinline__ uint64_t mask_or<uint64_t>(uint64_t* p, uint64_t v) {
   return atomicOr((unsigned long long*)p, (unsigned long long)v);
+}
+
+template <class MaskT>
+__device__ __forceinline__ void mask_and(MaskT* p, MaskT v) {
+  if (sizeof(MaskT) == 4) atomicAnd((unsigned int*)p, (unsigned int)v);
+  else atomicAnd((unsigned long long*)p, (unsigned long long)v);
 }
 
 __device__ __forceinline__ uint32_t table_hash(uint32_t key, uint32_t shift) {
@@ -153,12 +205,13 @@ __device__ __forceinline__ uint32_t list_push(uint32_t* counter, bool pred) {
 
 // entry i of the split list and of the list of blocks: in LDS, beyond its
 // capacity in global memory
-template <class A, class S>
-__device__ __forceinline__ void put_split(const A& a, S& sh, uint32_t cap, uint32_t i, int32_t s,
-                                          int32_t b) {
+template <class A, class S, class M>
+__device__ __forceinline__ void put_split(const A& a, S& sh, M* marks, uint32_t cap, uint32_t i,
+                                          int32_t s, int32_t b, M mv) {
   if (i < cap) {
     sh.ss[i] = s;
     sh.sb[i] = b;
+    if (marks) marks[i] = mv;
   } else {
     a.ss[i] = s;
     a.sbk[i] = b;
@@ -245,11 +298,15 @@ __host__ __device__ constexpr uint32_t table_bytes(uint32_t slots) {
 }
 // bytes of the tables of a split of up to small_split states: block table
 // (key, new label, split count, two counters, base of its staying states),
-// set of split states, staying states of the tails (state, position, range)
+// set of split states, staying states of the tails (state, position, range),
+// marks of the split states and, per block, their union and intersection
 template <int WG>
 __host__ __device__ constexpr uint32_t split_bytes() {
-  return small_split<WG>() * (2u * 24u + 2u * 4u + 16u);
+  return small_split<WG>() * (2u * 24u + 2u * 4u + 16u + 5u * 8u);
 }
+// bytes of the tracked labels' lists
+constexpr uint32_t kTrackBytes = 4u * kTracked * kLost;
+constexpr uint32_t kTrackSave = kTracked * (2 + kLost) + 1;
 constexpr uint32_t log2_u32(uint32_t v) { return v <= 1 ? 0 : 1 + log2_u32(v >> 1); }
 
 // Bit words of n labels plus summaries, twice (U and Q).
@@ -272,6 +329,7 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
     a.fc[s] = 0;
     a.gc[s] = 0;
     a.nlb[s] = 0;
+    if (a.trk) a.trk[s] = 0;
     if (zero_mw) a.mw[s] = 0;
   }
   for (uint32_t q = wid; q < nw; q += WG / kWave) {
@@ -336,9 +394,10 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
 template <class MaskT, int WG, bool kBm>
 __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
                                                 char* lds, uint32_t lds_bytes, uint32_t it0,
-                                                uint32_t& grid_C, RoundsWork& work) {
+                                                const RoundsResume& resume, uint32_t& grid_C,
+                                                RoundsWork& work) {
   constexpr uint32_t kWaves = WG / kWave;
-  const uint32_t tid = threadIdx.x, wid = tid / kWave;
+  const uint32_t tid = threadIdx.x, wid = uniform_u32(tid / kWave);
   const uint32_t n = a.n, s0 = a.s0;
   const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
 
@@ -366,7 +425,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
   constexpr uint32_t kSmall = small_split<WG>(), kB = 2u * kSmall, kBShift = 32 - log2_u32(kB);
   constexpr uint32_t EU = edges_per_thread<WG>();
   const bool small_ok = split_bytes<WG>() + table_bytes<MaskT>(256) <= rbytes;
-  uint64_t* x_pin = reinterpret_cast<uint64_t*>(region);
+  MaskT* b_or = reinterpret_cast<MaskT*>(region);  // 8 bytes each are set aside
+  MaskT* b_and = b_or + kB;
+  MaskT* s_mv = small_ok ? b_and + kB : nullptr;
+  uint64_t* x_pin = reinterpret_cast<uint64_t*>(region + 5u * 8u * kSmall);
   uint32_t* x_u = reinterpret_cast<uint32_t*>(x_pin + kSmall);
   uint32_t* x_q = x_u + kSmall;
   uint32_t* b_key = x_q + kSmall;
@@ -386,7 +448,37 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       b_fc[q] = 0;
       b_gc[q] = 0;
       s_set[q] = kNone;
+      b_or[q] = 0;
+      b_and[q] = ~(MaskT)0;
     }
+  }
+  bool track = a.out_ptr && small_ok && kTrackBytes + table_bytes<MaskT>(1024) <= rbytes;
+  const uint32_t track_edges =
+      (uint64_t)n * sizeof(MaskT) <= rbytes - (track ? kTrackBytes : 0u) ? kTrackEdgesDense
+                                                                        : kTrackEdges;
+  if (track && track_edges == kTrackEdgesDense) {
+    // blocks only shrink: no tracking if none is large enough at the start
+    uint32_t most = 0;
+    for (uint32_t b = tid; b < n; b += WG)
+      if ((uint32_t)a.blk[b] == b) most = max(most, (uint32_t)(a.be[b] - a.bs[b]));
+    if (tid == 0) sh.nc = 0;
+    __syncthreads();
+    atomicMax(&sh.nc, most);
+    __syncthreads();
+    track = (uint64_t)sh.nc * a.mean_deg >= track_edges;
+    __syncthreads();
+  }
+  uint32_t* lost = reinterpret_cast<uint32_t*>(region);  // [kTracked][kLost]
+  if (track) {
+    region += kTrackBytes;
+    rbytes -= kTrackBytes;
+    const bool load = a.trk_save && resume.label != kNone;
+    for (uint32_t q = tid; q < kTracked; q += WG) {
+      sh.tlabel[q] = load ? a.trk_save[q] : kNone;
+      sh.tn[q] = load ? a.trk_save[kTracked + q] : 0u;
+    }
+    if (load)
+      for (uint32_t q = tid; q < kTracked * kLost; q += WG) lost[q] = a.trk_save[2 * kTracked + q];
   }
   uint32_t lg = 0;  // log2 of the table's slots; none below 32
   while ((2u << lg) <= 2 * EU * WG && table_bytes<MaskT>(2u << lg) <= rbytes) ++lg;
@@ -398,9 +490,34 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
   uint32_t* t_cnt = t_key + slots;
   const bool dense = (uint64_t)n * sizeof(MaskT) <= rbytes;  // mark words of a big splitter in LDS
 
+  // entry for label C, its lost states none (one lane per label)
+  const auto track_new = [&](uint32_t C) {
+    const uint32_t e = atomicAdd(&sh.tnext, 1u) % kTracked;
+    const uint32_t old = sh.tlabel[e];
+    if (old != kNone) a.trk[old] = 0;
+    sh.tlabel[e] = C;
+    sh.tn[e] = 0;
+    a.trk[C] = (uint8_t)(e + 1);
+    return e + 1;
+  };
+  // block b, tracked by entry e, loses state s
+  const auto track_lost = [&](uint32_t e, uint32_t b, uint32_t s) {
+    const uint32_t i = atomicAdd(&sh.tn[e], 1u);
+    if (i < kLost) lost[e * kLost + i] = s;
+    else a.trk[b] = 0;  // too many: no longer tracked
+  };
   if (tid == 0) {
     sh.it = it0;
     sh.bad = 0;
+    sh.tnext = track && a.trk_save && resume.label != kNone ? a.trk_save[kTracked * (2 + kLost)] : 0u;
+  }
+  if (track && resume.label != kNone && !resume.mixed) {  // workgroup-uniform
+    __syncthreads();
+    if (tid == 0) sh.fent = track_new(resume.label);
+    __syncthreads();
+    for (uint32_t i = tid; i < resume.nS; i += WG)
+      if ((uint32_t)a.sbk[i] == resume.label)
+        track_lost(sh.fent - 1, resume.label, (uint32_t)a.ss[i]);
   }
   bool dirty = true;  // the region does not hold an empty table (workgroup-uniform)
   uint32_t rc = kRoundsDone;
@@ -442,8 +559,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         const uint32_t cw = (uint32_t)__shfl((int)word, (int)o, kWave);
         if (lane() < nc) C = (cw << 6) + select_bit(w, lane() - before);
       }
-      uint32_t lo = 0, sz = 0;
+      uint32_t lo = 0, sz = 0, te = 0;
       if (lane() < nc) {
+        if (track) te = a.trk[C];
         lo = (uint32_t)a.bs[C];
         sz = (uint32_t)a.be[C] - lo;
         if (lo > n || sz > n - lo) {  // never expected: report, visit nothing
@@ -452,6 +570,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           sz = 0;
         }
       }
+      const uint32_t whole = sz;
+      const bool inc = te != 0 && sh.tn[te - 1] < sz;
+      if (inc) sz = sh.tn[te - 1];
+      const uint32_t incs = (uint32_t)__ballot(inc);
       const uint32_t mi = wave_incl_scan_u32(sz);
       const uint64_t fit = __ballot(lane() < nc && mi <= (uint32_t)WG);
       const uint32_t np = (uint32_t)__popcll(fit);  // sizes add up: a prefix of the lanes
@@ -460,16 +582,20 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         sh.cb[lane()] = lo;
         sh.cpre[lane()] = mi - sz;
         sh.unst[lane()] = 0;
+        sh.ctrk[lane()] = te;
+        sh.cend[lane()] = 0;
       }
       if (lane() == 0) {
         sh.nc = nc;
         sh.np = np;
-        sh.csz0 = sz;
+        sh.csz0 = whole;
+        sh.inc = incs;
       }
       if (np && lane() == np - 1) sh.mtot = mi;
     } else if (tid == kWaves * kWave - 1) {
       sh.nS = sh.nL = sh.nT = 0;
       sh.tctr = 0;
+      sh.fent = sh.ffresh = sh.mixed = sh.nself = 0;
     }
     if (dirty) {
       for (uint32_t q = tid; q < slots; q += WG) {
@@ -480,8 +606,8 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       dirty = false;
     }
     __syncthreads();
-    const uint32_t nc = sh.nc;
-    if (sh.bad) {
+    const uint32_t nc = uniform_u32(sh.nc);
+    if (uniform_u32(sh.bad)) {
       rc = kRoundsBad;
       break;
     }
@@ -489,8 +615,8 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       rc = kRoundsCap;
       break;
     }
-    uint32_t np = sh.np;
-    const uint32_t mtot = np ? sh.mtot : 0u;
+    uint32_t np = uniform_u32(sh.np);
+    const uint32_t mtot = np ? uniform_u32(sh.mtot) : 0u;
     uint32_t E = 0;
     if (np) {
       // ---- members: one per thread, with its in-transition range
@@ -499,9 +625,16 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
 #pragma unroll
         for (uint32_t step = kCand / 2; step >= 1; step >>= 1)
           if (c + step < np && sh.cpre[c + step] <= tid) c += step;
-        const uint64_t x = a.pin[sh.cb[c] + (tid - sh.cpre[c])];
-        beg = (uint32_t)(x >> 32);
-        deg = (uint32_t)x;
+        const uint32_t i = tid - sh.cpre[c];
+        if ((sh.inc >> c) & 1u) {
+          const uint32_t s = lost[(sh.ctrk[c] - 1) * kLost + i];
+          beg = a.in_ptr[s];
+          deg = a.in_ptr[s + 1] - beg;
+        } else {
+          const uint64_t x = a.pin[sh.cb[c] + i];
+          beg = (uint32_t)(x >> 32);
+          deg = (uint32_t)x;
+        }
       }
       const uint32_t incl = wave_incl_scan_u32(deg);
       if (lane() == kWave - 1) sh.wsum[wid] = incl;
@@ -517,11 +650,12 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         // follows, or the members end)
         if (tid + 1 == mtot || (c + 1 < np && sh.cpre[c + 1] == tid + 1)) sh.cend[c] = before + incl;
       }
+      if (tid == WG - 1) sh.etot = before + incl;
       __syncthreads();
-      // as many candidates as the table holds
-      const bool fits = lane() < np && sh.cend[lane()] <= ecap;
-      np = (uint32_t)__popcll(__ballot(fits));
-      E = np ? sh.cend[np - 1] : 0u;
+      // as many candidates as the table holds (one without members ends at 0)
+      const uint64_t over = __ballot(lane() < np && sh.cend[lane() & (kCand - 1)] > ecap);
+      if (over) np = (uint32_t)(__ffsll((unsigned long long)over) - 1);
+      E = uniform_u32(over ? (np ? sh.mpre[sh.cpre[np]] : 0u) : sh.etot);
       if (tid == 0 && np) {
         work.members += np < sh.np ? sh.cpre[np] : mtot;
         work.edges += E;
@@ -567,11 +701,73 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
       }
       __syncthreads();
+      const uint32_t incs = uniform_u32(sh.inc) & (np < 32 ? (1u << np) - 1u : ~0u);
+      if (incs) {  // workgroup-uniform
+        // sources of lost states: the marks that no other transition into the
+        // block still gives.  Long lists of outgoing transitions are searched
+        // by the whole wave, and only until every mark is found again.
+#pragma unroll
+        for (uint32_t u = 0; u < EU; ++u) {
+          const uint32_t c = es[u] != kNone ? ek[u] >> kKeyBits : 0u;
+          const bool need = sl[u] != kNone && ((incs >> c) & 1u);
+          if (__ballot(need) == 0) continue;
+          const MaskT had = need ? t_mv[sl[u]] : (MaskT)0;
+          const uint32_t label = sh.cand[c];
+          MaskT left = had;
+          uint32_t e = 0, end = 0;
+          if (need) {
+            e = a.out_ptr[es[u]];
+            end = a.out_ptr[es[u] + 1];
+          }
+          const uint32_t own = min(end, e + 4 * kOutU);
+          for (; e < own && left; e += kOutU) {
+            uint32_t vd[kOutU], vo[kOutU];
+#pragma unroll
+            for (uint32_t v = 0; v < kOutU; ++v) {
+              vd[v] = kNone;
+              if (e + v < own) {
+                vd[v] = (uint32_t)a.out_dst[e + v] - s0;
+                vo[v] = a.rcpp ? 0u : (uint32_t)a.out_ord[e + v];
+              }
+            }
+#pragma unroll
+            for (uint32_t v = 0; v < kOutU; ++v)
+              if (vd[v] != kNone) vd[v] = (uint32_t)a.blk[vd[v]];
+#pragma unroll
+            for (uint32_t v = 0; v < kOutU; ++v)
+              if (vd[v] == label) left &= ~((MaskT)1 << (vo[v] & (sizeof(MaskT) * 8 - 1)));
+          }
+          uint64_t more = __ballot(need && left != 0 && own < end);
+          while (more) {
+            const int o = __ffsll((unsigned long long)more) - 1;
+            more &= more - 1;
+            const uint32_t oe = (uint32_t)__shfl((int)end, o, kWave);
+            const uint32_t ol = (uint32_t)__shfl((int)label, o, kWave);
+            MaskT rest = (MaskT)__shfl((unsigned long long)left, o, kWave);
+            for (uint32_t x = (uint32_t)__shfl((int)own, o, kWave); x < oe && rest; x += kWave) {
+              MaskT got = 0;
+              if (x + lane() < oe) {
+                const uint32_t d = (uint32_t)a.out_dst[x + lane()] - s0;
+                const uint32_t r = a.rcpp ? 0u : (uint32_t)a.out_ord[x + lane()];
+                if ((uint32_t)a.blk[d] == ol) got = (MaskT)1 << (r & (sizeof(MaskT) * 8 - 1));
+              }
+#pragma unroll
+              for (int d = 32; d >= 1; d >>= 1)
+                got |= (MaskT)__shfl_xor((unsigned long long)got, d, kWave);
+              rest &= ~got;
+            }
+            if ((int)lane() == o) left = rest;
+          }
+          if (need) t_mv[sl[u]] = left;
+        }
+        __syncthreads();
+      }
       // ---- every touched state against its leader (the leader of b is the
       // state b); the touched members of a block counted at its leader
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
-        if (sl[u] == kNone) continue;
+        ls[u] = kNone;
+        if (sl[u] == kNone || t_mv[sl[u]] == 0) continue;  // not there, or no mark lost
         const uint32_t lead = eb[u] == es[u] ? sl[u]
                                              : table_find(t_key, tmask, tshift, ek[u] | eb[u]);
         ls[u] = lead;
@@ -582,7 +778,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       // a touched leader with untouched members
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u)
-        if (sl[u] != kNone && eb[u] == es[u] && t_cnt[sl[u]] != sz[u])
+        if (sl[u] != kNone && eb[u] == es[u] && t_mv[sl[u]] != 0 && t_cnt[sl[u]] != sz[u])
           sh.unst[ek[u] >> kKeyBits] = 1;
       __syncthreads();
       split = __ballot(lane() < np && sh.unst[lane() & (kCand - 1)] != 0);
@@ -591,9 +787,31 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     // ---- verdicts, and the iterations that split nothing: every unstable
     // label before the next one without a verdict
     const bool turn = f < np || big;  // the iteration of C is carried out now
-    const uint32_t C = turn ? sh.cand[f < np ? f : 0] : 0u;
+    const uint32_t C = uniform_u32(turn ? sh.cand[f < np ? f : 0] : 0u);
     if (wid == 0 && ((lane() < np && !((split >> lane()) & 1ull)) || (turn && lane() == (f < np ? f : 0))))
       label_clear(Q, QS, sh.cand[lane()]);
+    if (track && wid == 0) {
+      // a stable label is tracked from now on (its entry, if it has one,
+      // starts over); so is the splitter, should its split parts be uniform
+      const uint32_t l = lane() & (kCand - 1);
+      const bool mine = turn && lane() == (f < np ? f : 0);
+      const bool stable = lane() < np && !((split >> lane()) & 1ull);
+      uint32_t te = sh.ctrk[l];
+      bool fresh = false;
+      if (stable || mine) {
+        const bool inc = (sh.inc >> l) & 1u;
+        if (stable && te) sh.tn[te - 1] = 0;
+        if (!te && (big || (!inc && sh.cend[l] - sh.mpre[sh.cpre[l]] >= track_edges))) {
+          te = track_new(sh.cand[l]);
+          fresh = true;
+        }
+      }
+      if (mine) {
+        sh.fent = te;
+        sh.ffresh = fresh;
+        sh.fold = te && !fresh ? sh.tn[te - 1] : 0u;
+      }
+    }
     uint32_t limit = n;  // labels before it are taken, C's own iteration included
     if (turn) limit = C + 1;
     else if (np < nc) limit = sh.cand[np];
@@ -634,7 +852,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     want = kCand / 2;
     // the members of the listed blocks that `is_split` says are split off
     const auto members = [&](const auto& is_split) {
-      const uint32_t nL = sh.nL;
+      const uint32_t nL = uniform_u32(sh.nL);
       if (tid == 0) work.listed += nL;
       for (uint32_t j0 = 0; j0 < nL; j0 += kWave) {
         const uint32_t j = j0 + lane();
@@ -661,15 +879,16 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
             sp = is_split(s);
           }
           const uint32_t si = list_push(&sh.nS, sp);
-          if (sp) put_split(a, sh, kSmall, si, (int32_t)s, (int32_t)ob);
+          if (sp) put_split(a, sh, s_mv, kSmall, si, (int32_t)s, (int32_t)ob, (MaskT)0);
         }
       }
     };
     if (big) {
       // ---- a splitter beyond the table: mark words per state
-      const uint32_t cb = sh.cb[0], csz = sh.csz0;
+      const uint32_t cb = uniform_u32(sh.cb[0]), csz = uniform_u32(sh.csz0);
       if (!dense && a.grid_edges && (uint64_t)csz * a.mean_deg >= a.grid_edges) {
         grid_C = C;  // its iteration is counted already
+        if (tid == 0 && track && sh.ffresh) a.trk[C] = 0;
         rc = kRoundsGrid;
         break;
       }
@@ -743,7 +962,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
             const uint32_t s = i0 + u * WG + lane();
             const bool sp = s < n && mw[s] != mw[vb[u]];
             const uint32_t si = list_push(&sh.nS, sp);
-            if (sp) put_split(a, sh, kSmall, si, (int32_t)s, (int32_t)vb[u]);
+            if (sp) put_split(a, sh, s_mv, kSmall, si, (int32_t)s, (int32_t)vb[u], mw[s]);
           }
         }
         __syncthreads();
@@ -805,7 +1024,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           }
         }
         __syncthreads();
-        const uint32_t nT = sh.nT;
+        const uint32_t nT = uniform_u32(sh.nT);
         if (tid == 0) work.touched += nT;
         for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG) {
           const uint32_t i = i0 + lane();
@@ -817,34 +1036,38 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
             sp = s != b && mw[s] != mw[b];
           }
           const uint32_t si = list_push(&sh.nS, sp);
-          if (sp) put_split(a, sh, kSmall, si, s, b);
+          if (sp) put_split(a, sh, s_mv, kSmall, si, s, b, mw[s]);
         }
         members([&](uint32_t s) { return mw[s] == 0; });
         __syncthreads();
         for (uint32_t i = tid; i < nT; i += WG) mw[a.ts[i]] = 0;
       }
-      if (sh.nS == 0) continue;
+      if (sh.nS == 0) {  // stable: its entry starts over
+        if (tid == 0 && track) sh.tn[sh.fent - 1] = 0;
+        continue;
+      }
     } else {
       // ---- the split states of C from the table: touched states that differ
       // from their leader, and the untouched members of blocks whose leader
       // was touched
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
-        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f;
+        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && t_mv[sl[u]] != 0;
         bool sp = false, part = false;
         if (mine) {
           if (es[u] == eb[u]) part = t_cnt[sl[u]] != sz[u];
           else sp = ls[u] == kNone || t_mv[ls[u]] != t_mv[sl[u]];
         }
         const uint32_t si = list_push(&sh.nS, sp);
-        if (sp) put_split(a, sh, kSmall, si, (int32_t)es[u], (int32_t)eb[u]);
+        if (sp) put_split(a, sh, s_mv, kSmall, si, (int32_t)es[u], (int32_t)eb[u], t_mv[sl[u]]);
         const uint32_t li = list_push(&sh.nL, part);
         if (part) put_block(a, sh, li, eb[u], lo[u], sz[u]);
       }
       __syncthreads();
       if (sh.nL) {  // workgroup-uniform
         members([&](uint32_t s) {
-          return table_find(t_key, tmask, tshift, (f << kKeyBits) | s) == kNone;
+          const uint32_t x = table_find(t_key, tmask, tshift, (f << kKeyBits) | s);
+          return x == kNone || t_mv[x] == 0;
         });
         __syncthreads();
       }
@@ -853,11 +1076,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     // ---- split: the split part of each block goes to the tail of its range
     // and takes its smallest member as label; front split states trade places
     // with the staying states of the tail
-    const uint32_t nS = sh.nS;
+    const uint32_t nS = uniform_u32(sh.nS);
     if (tid == 0) work.split += nS;
-    if (tid == WG - 1 && !a.rcpp) label_set2(U, US, Q, QS, C, C);  // Algorithm 3 re-marks C
     if (nS <= kSmall && small_ok) {
-      uint32_t s = 0, b = 0, ps = 0, blo = 0, bhi = 0, slot = 0, own = 0, r = 0;
+      uint32_t s = 0, b = 0, ps = 0, blo = 0, bhi = 0, slot = 0, own = 0, r = 0, te = 0, self = 0;
       const bool on = tid < nS;
       if (on) {
         s = (uint32_t)sh.ss[tid];
@@ -865,11 +1087,17 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         ps = (uint32_t)a.pos[s];
         blo = (uint32_t)a.bs[b];
         bhi = (uint32_t)a.be[b];
+        if (track) te = a.trk[b];
         bool first;
         slot = table_insert(b_key, kB - 1, kBShift, b, first);
         r = atomicAdd(&b_cnt[slot], 1u);
         atomicMin(&b_nl[slot], s);
         own = table_insert(s_set, kB - 1, kBShift, s, first);
+        if (track) {
+          const MaskT mv = s_mv[tid];
+          mask_or<MaskT>(&b_or[slot], mv);
+          mask_and<MaskT>(&b_and[slot], mv);
+        }
       }
       __syncthreads();
       uint32_t c = 0, ne = 0, q = 0, nl = 0, fi = kNone, us_ = 0;
@@ -891,6 +1119,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
             fi = atomicAdd(&b_fc[slot], 1u);
           }
           if (r == 0) b_base[slot] = atomicAdd(&sh.tctr, c);
+          if (track && s == nl && b_or[slot] != b_and[slot]) sh.mixed = 1;
+          if (!track) self = 0;
+          else if (b == C) self = atomicAdd(&sh.nself, 1u);
+          else if (te) track_lost(te - 1, b, s);
           a.blk[s] = (int32_t)nl;
         }
       }
@@ -913,6 +1145,30 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         b_fc[slot] = 0;
         b_gc[slot] = 0;
         s_set[own] = kNone;
+        if (track) {
+          b_or[slot] = 0;
+          b_and[slot] = ~(MaskT)0;
+        }
+      }
+      // C's own entry: with uniform split parts the partition is stable under
+      // what C was, so its lost states are those of this iteration; else they
+      // join the earlier ones, and an entry taken in this round ends
+      const uint32_t fent = track ? sh.fent : 0u, mixed = sh.mixed, nself = sh.nself;
+      const bool ends = mixed && sh.ffresh;
+      const uint32_t had = mixed ? sh.fold : 0u;
+      if (on && b == C && fent && !ends && had + self < kLost)
+        lost[(fent - 1) * kLost + had + self] = s;
+      if (tid == WG - 1) {
+        if (fent) {
+          sh.tn[fent - 1] = had + nself;
+          if (ends || had + nself > kLost) a.trk[C] = 0;
+        }
+        if (!a.rcpp) {
+          // Algorithm 3 re-marks C; it needs a verdict if it changed (it is in
+          // Q then already) or a split part is not uniform
+          label_set(U, US, C);
+          if (mixed || !track) label_set(Q, QS, C);
+        }
       }
       if (ok) {
         if (fi != kNone) {
@@ -938,7 +1194,12 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
       }
     } else {
-      // more split states: the same through global arrays
+      // more split states: the same through global arrays, and the blocks that
+      // split are no longer tracked
+      if (tid == WG - 1) {
+        if (!a.rcpp) label_set2(U, US, Q, QS, C, C);
+        if (track) a.trk[C] = 0;
+      }
       const uint64_t epoch = (uint64_t)sh.it << 32;  // this iteration's number
       for (uint32_t i = tid; i < nS; i += WG) {
         const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
@@ -1002,6 +1263,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           a.cnt[b] = 0;
           a.fc[b] = 0;
           a.gc[b] = 0;
+          if (track) a.trk[b] = 0;
           label_set2(U, US, Q, QS, (uint32_t)b, (uint32_t)s);
           work.blocks += 1;
         }
@@ -1020,6 +1282,14 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       a.qs[q] = QS[q];
     }
     __syncthreads();
+  }
+  if (track && a.trk_save && rc == kRoundsGrid) {
+    for (uint32_t q = tid; q < kTracked; q += WG) {
+      a.trk_save[q] = sh.tlabel[q];
+      a.trk_save[kTracked + q] = sh.tn[q];
+    }
+    for (uint32_t q = tid; q < kTracked * kLost; q += WG) a.trk_save[2 * kTracked + q] = lost[q];
+    if (tid == 0) a.trk_save[kTracked * (2 + kLost)] = sh.tnext;
   }
   return rc;
 }

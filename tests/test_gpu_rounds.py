@@ -107,6 +107,35 @@ def test_rounds_leave_large_splitters_to_the_grid(B, n, actions):
         assert (blk == ks).all() and blocks == nb and its == ref[0][1]
 
 
+TRACKED = {
+    # large splitters that lose single states between their iterations
+    "uniform-2-actions": lambda: gen.uniform_lts(30000, 3.0, 2, 5),
+    "uniform-1-action-wide": lambda: gen.uniform_lts(9000, 12.0, 1, 6),
+    "chain": lambda: permuted(gen.chain_tail(40000), 7),
+    "fan-out": lambda: permuted(gen.fan_out(9000), 8),
+    "planted-2-actions": lambda: gen.planted_quotient(2500, 5.0, 2, seed=9),
+    # 64-bit marks: the mark words of 20k states do not fit LDS
+    "wide-marks": lambda: gen.uniform_zipf(20000, 60000, 40, seed=10),
+}
+
+
+@pytest.mark.parametrize("case", sorted(TRACKED))
+def test_rounds_track_large_splitters(B, case):
+    """Splitters of thousands of in-transitions are re-examined through the
+    states they lost; the lock-step engine gives the iteration count."""
+    L = TRACKED[case]()
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)
+    ref, _ = run(B, L, 2)
+    got, _ = run(B, L, 3)
+    with B.Batch([L, L]) as b:
+        b.set_option(B.BOPT_GRID, 2)
+        out, its, _ = b.run()
+        both = b.split(out.numpy())
+    for blk, n_it in [(x, i) for x, i, _ in got] + list(zip(both, its)):
+        assert (blk == ks).all() and n_it == ref[0][1]
+    assert got[0][2] == nb
+
+
 @pytest.mark.parametrize("seed", [1, 2])
 def test_rounds_algorithm2(B, seed):
     check(B, gen.kripke_uniform(1000, 5000, seed=seed), algorithm=2, engines=(0,))
@@ -124,7 +153,7 @@ def test_batch_rounds_default_workgroup(B, lds):
         b.set_option(B.BOPT_GRID, 4)  # a workgroup takes several instances
         out, its, st = b.run()
         blocks = b.split(out.numpy())
-    assert st["workgroup_size"] == 512
+    assert st["workgroup_size"] == 1024
     for k, L in enumerate(insts):
         ref = oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst, L.init)
         assert (blocks[k] == ref["block"]).all() and its[k] == ref["iters"], (k, L.name)
