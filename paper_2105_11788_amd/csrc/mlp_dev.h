@@ -108,12 +108,45 @@ __device__ __forceinline__ float mlp_forward_lanes(const MlpLds& L, int F, float
   return y + L.b3[0];
 }
 
-// Same, input row read from memory.
-__device__ __forceinline__ float mlp_row_forward(const MlpLds& L, int F, const float* xr,
-                                                 float* z1o, float* z2o) {
-  const int j = (int)lane();
-  const float xl = j < F ? xr[j] : 0.f;
-  return mlp_forward_lanes(L, F, xl, z1o, z2o);
+// Forward pass of one row per lane: the row's F features in x (already at
+// bf16 precision).  Every sum is taken in the order of mlp_forward_lanes (the
+// output's tree by a binary counter over the units in bit-reversed order), so
+// the two give the same bits.  64 rows take about 10 us of a wave, against 3
+// us for each by mlp_forward_lanes.
+template <int F>
+__device__ __forceinline__ float mlp_forward_rows(const MlpLds& L, const float (&x)[F]) {
+#pragma clang fp contract(off)
+  float h1[kMlpH];
+#pragma unroll
+  for (int j = 0; j < kMlpH; ++j) {
+    float z = L.b1[j];
+#pragma unroll
+    for (int f = 0; f < F; ++f) z = fmaf(L.W1T[f * kMlpH + j], x[f], z);
+    h1[j] = fmaxf(z, 0.f);
+  }
+  float part[6];  // part[d]: a finished subtree of 2^d units
+  float y = 0.f;
+  for (uint32_t q = 0; q < (uint32_t)kMlpH; ++q) {
+    const uint32_t j = __brev(q) >> 26;
+    const float* w = L.W2 + j * kMlpH;
+    float z = L.b2[j];
+#pragma unroll
+    for (int i = 0; i < kMlpH; ++i) z = fmaf(w[i], h1[i], z);
+    float v = L.w3[j] * fmaxf(z, 0.f);
+    bool open = true;
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      if (!open) continue;
+      if ((q >> d) & 1u) {
+        v = part[d] + v;
+      } else {
+        part[d] = v;
+        open = false;
+      }
+    }
+    y = v;  // the last unit closes the whole tree
+  }
+  return y + L.b3[0];
 }
 
 // Priority level of a predicted log(1 + blocks split): 16 levels of width 1/3.
