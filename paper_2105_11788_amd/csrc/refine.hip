@@ -51,6 +51,7 @@
 #include <cstdlib>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -233,6 +234,90 @@ __global__ void __launch_bounds__(kPT) k_persistent(Args a) {
       if (blockIdx.x == 0) phase_s(a, M, k & 1, k);
       if (!grid_barrier(a.ctl, gen)) break;
     }
+  }
+}
+
+// The learned policy by one workgroup (engine 1 with a grid of one): the same
+// phases with workgroup barriers between them, and, up to kLearnedWGStates,
+// on arrays in LDS (all but the transitions and the block features).  Bound by
+// the phases' chains of dependent steps: a Kripke structure of 1000 states
+// takes 8 us per iteration against 20 with four kernels (11 with the arrays in
+// global memory); the scans over all states make the kernels faster from about
+// 4000 states on.
+constexpr int kLW = 512;  // (1024 threads: the same time, with registers spilled)
+constexpr int32_t kLearnedWGStates = 2048;
+
+// bytes of the LDS arrays for n states, after the network's weights
+__host__ __device__ inline size_t learned_lds_bytes(size_t n) {
+  const size_t nwd = (n + 63) / 64, nsw = (nwd + 63) / 64, ntw = (nsw + 63) / 64;
+  return 8 * (2 * n + 4 * nwd + nsw + kLevels * (nwd + nsw + ntw)) + 4 * (7 * n) + 3 * n + 16 +
+         sizeof(Ctl) + 128;
+}
+
+__global__ void __launch_bounds__(kLW) k_learned_wg(Args g, uint32_t in_lds) {
+  extern __shared__ float sw[];
+  const MlpLds M = mlp_lds_layout(sw, kPolicyF);
+  mlp_stage(M, g.wbf, kPolicyF);
+  Args a = g;
+  const size_t n = (uint32_t)g.n, nwd = (n + 63) / 64, nsw = (nwd + 63) / 64, ntw = (nsw + 63) / 64;
+  if (in_lds) {
+    char* at = reinterpret_cast<char*>(M.end);
+    at += (128 - (uint32_t)(at - reinterpret_cast<char*>(sw)) % 128) % 128;
+    const auto place = [&](auto*& p, size_t count, bool copy) {
+      auto* to = reinterpret_cast<std::remove_reference_t<decltype(p)>>(at);
+      if (copy)
+        for (size_t i = threadIdx.x; i < count; i += kLW) to[i] = p[i];
+      p = to;
+      at += count * sizeof(*p);
+    };
+    uint32_t* ctl = reinterpret_cast<uint32_t*>(g.ctl);
+    place(ctl, sizeof(Ctl) / 4, true);
+    a.ctl = reinterpret_cast<Ctl*>(ctl);
+    if (a.uniform) place(a.mw, n, true);
+    place(a.nlw, n, true);
+    place(a.ub, nwd, true);
+    place(a.tb, nwd, true);
+    place(a.lt, nwd, true);
+    place(a.us, nsw, true);
+    place(a.lvb, kLevels * nwd, true);
+    place(a.lvs, kLevels * nsw, true);
+    place(a.lvt, kLevels * ntw, true);
+    place(a.block, n, true);
+    place(a.born, n, true);
+    place(a.used, n, true);
+    place(a.tlist, n, false);
+    place(a.slist, n, false);
+    place(a.chg, 2 * n, false);
+    place(a.lvl, n, true);
+    place(a.lvq, 2 * n + 1, false);
+  }
+  __syncthreads();
+  const Part p = part();
+  for (uint32_t k = 0;; ++k) {
+    const uint32_t C = head(a, k, p);
+    if (C == kNone) break;
+    phase_a_select<true>(a, k & 1, C, k, p);
+    phase_a_mark(a, k & 1, C, p);
+    __syncthreads();
+    phase_b(a, k & 1, k, p);
+    __syncthreads();
+    phase_c<true, true>(a, k & 1, k, C, p);
+    __syncthreads();
+    if (a.rescore && (k + 1) % a.rescore == 0) {
+      phase_f1(a, M, k + 1, p);
+      __syncthreads();
+      phase_f2(a, p);
+      __syncthreads();
+    }
+    phase_s(a, M, k & 1, k);
+    __syncthreads();
+  }
+  if (in_lds) {
+    __syncthreads();  // the final pass's control words
+    for (size_t i = threadIdx.x; i < n; i += kLW) g.block[i] = a.block[i];
+    const uint32_t* ctl = reinterpret_cast<const uint32_t*>(a.ctl);
+    for (size_t i = threadIdx.x; i < sizeof(Ctl) / 4; i += kLW)
+      reinterpret_cast<uint32_t*>(g.ctl)[i] = ctl[i];
   }
 }
 
@@ -462,6 +547,11 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   *engine = 2;
   *grid = h->grid;
   const bool learned = h->policy == 1 && h->policy_w;
+  if (learned && h->n <= kLearnedWGStates && h->grid == 0 && h->profile_every == 0) {
+    *engine = 1;
+    *grid = 1;
+    return BISIM_OK;
+  }
   if (learned || h->iter_limit > 0 || arena_active() || !rounds_apply(h)) return BISIM_OK;
   if (h->algorithm == 2) {
     if (h->n <= kRcppRoundsStates) *engine = 3;
@@ -596,6 +686,13 @@ static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id, bool chosen
     BISIM_TRY(rounds_run(h, (uint32_t)cap, start, rcpp));
   } else if (engine == 3) {
     BISIM_TRY(lists_loop(h, (uint32_t)cap, h->count_work != 0));
+  } else if (engine == 1 && learned && h->grid == 1) {
+    h->run_grid = 1;
+    const uint32_t in_lds = n <= kLearnedWGStates ? 1u : 0u;
+    const size_t shm = lds + (in_lds ? learned_lds_bytes((size_t)n) : 0);
+    BISIM_TRY_HIP(hipFuncSetAttribute((const void*)k_learned_wg,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
+    hipLaunchKernelGGL(k_learned_wg, dim3(1), dim3(kLW), shm, st, a, in_lds);
   } else if (engine == 1) {
     int per_cu = 0;
     if (learned)

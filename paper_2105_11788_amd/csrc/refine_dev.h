@@ -97,6 +97,28 @@ __device__ __forceinline__ uint32_t block_level(const Args& a, const MlpLds& M, 
   return score_level(mlp_forward_lanes(M, kPolicyF, x, &z1, &z2));
 }
 
+// one wave: the levels of the labels 64 w + (set bits of `bits`), each stored
+__device__ __forceinline__ void word_levels(const Args& a, const MlpLds& M, uint32_t w,
+                                            uint64_t bits, uint32_t kcur) {
+  if (__popcll(bits) < 4) {  // fewer labels than a pass of one per lane is worth
+    while (bits) {
+      const uint32_t b = (w << 6) + (uint32_t)(__ffsll((unsigned long long)bits) - 1);
+      bits &= bits - 1;
+      const uint32_t lv = block_level(a, M, b, kcur);
+      if (lane() == 0) a.lvl[b] = (uint8_t)lv;
+    }
+    return;
+  }
+  const bool on = (bits >> lane()) & 1ull;
+  const uint32_t b = on ? (w << 6) + lane()
+                        : (w << 6) + (uint32_t)(__ffsll((unsigned long long)bits) - 1);
+  float x[kPolicyF];
+#pragma unroll
+  for (int f = 0; f < kPolicyF; ++f) x[f] = bf16_rne(block_feature(a, b, f, kcur));
+  const uint32_t lv = score_level(mlp_forward_rows<kPolicyF>(M, x));
+  if (on) a.lvl[b] = (uint8_t)lv;
+}
+
 // ---- the level structure of the learned policy ----------------------------
 struct LvDims {
   uint32_t nwd, nsw, ntw;
@@ -1092,13 +1114,8 @@ __device__ void phase_f1(const Args& a, const MlpLds& M, uint32_t kcur, const Pa
   for (uint32_t i = p.gtid; i < kLevels * d.nsw; i += p.gthreads) a.lvs[i] = 0;
   for (uint32_t i = p.gtid; i < kLevels * d.ntw; i += p.gthreads) a.lvt[i] = 0;
   for (uint32_t w = p.gwave; w < d.nwd; w += p.gwaves) {
-    uint64_t bits = a.ub[w];
-    while (bits) {
-      const uint32_t b = (w << 6) + (uint32_t)(__ffsll((unsigned long long)bits) - 1);
-      bits &= bits - 1;
-      const uint32_t lv = block_level(a, M, b, kcur);
-      if (lane() == 0) a.lvl[b] = (uint8_t)lv;
-    }
+    const uint64_t bits = a.ub[w];
+    if (bits) word_levels(a, M, w, bits, kcur);
   }
 }
 __device__ void phase_f2(const Args& a, const Part& p) {
