@@ -17,19 +17,26 @@ void set_error(const char* fmt, ...) {
   va_end(ap);
 }
 
+// What loading takes of the handle's memory, temporaries included (the one-pass
+// preprocessing of many actions among them), and what the run state and the
+// member lists take: hints, so that a small LTS lives in one chunk.
+static size_t setup_bytes(int64_t n, int64_t m, int64_t K) {
+  size_t b = 16 * (size_t)m + 124 * (size_t)n + 8 * (size_t)K + 64 * 256;
+  if (K == 1) b += 4 * (size_t)n;
+  if (K > 64) b += 4 * (size_t)m + 64 * (size_t)n;
+  return b;
+}
+static size_t run_bytes(int64_t n, int64_t m) {
+  size_t b = 150 * (size_t)n + 96 * 256;
+  if (m >= 65536) b += 8 * (size_t)m;
+  return b;
+}
+
 static void free_handle(bisim_lts* h) {
   if (!h) return;
   hipStream_t s = h->stream;
   lists_free(h);
-  void* ptrs[] = {h->init_block, h->pre_block, h->nr_marks, h->in_ptr, h->in_src, h->in_ord, h->woff,
-                  h->block,     h->mw,       h->tb,     h->lt,     h->ub,     h->nlw,
-                  h->tlist,     h->slist,    h->ctl,    h->sfeat,  h->acc,    h->born,
-                  h->used,      h->chg,      h->us,     h->lvl,    h->lvb,    h->lvs,
-                  h->lvt,       h->lvq,      h->sb,     h->nlist};
-  for (void* p : ptrs)
-    if (p) (void)hipFreeAsync(p, s);
-  for (void* p : h->sig_buf)
-    if (p) (void)hipFreeAsync(p, s);
+  h->mem.release(s);
   (void)hipStreamSynchronize(s);
   if (h->ctl_host) (void)hipHostFree(h->ctl_host);
   if (h->ev0) (void)hipEventDestroy(h->ev0);
@@ -70,6 +77,10 @@ bisim_status load_into(bisim_lts* h, const int32_t* src, const int32_t* label,
     set_error("lts_load: no usable HIP device (%s)", hipGetErrorString(e));
     return BISIM_E_DEVICE;
   }
+  ChunkScope scope(h->mem);  // (an open ArenaScope comes first)
+  if (!arena_active())
+    h->mem.reserve(setup_bytes(h->n, h->m, h->K) + (with_run_state ? run_bytes(h->n, h->m) : 0),
+                   h->stream);
   BISIM_TRY_HIP(hipEventRecord(h->ev0, h->stream));
   BISIM_TRY(setup_load(h, src, label, dst, init_partition));
   if (with_run_state) BISIM_TRY(refine_alloc(h));
@@ -140,6 +151,7 @@ bisim_status coarsest_partition(bisim_lts* h, int32_t* block_id, bisim_stats* st
     set_error("coarsest_partition: NULL handle or output");
     return BISIM_E_INVALID;
   }
+  ChunkScope scope(h->mem);
   bisim_status rc = (h->algorithm == BISIM_ALGORITHM_SIGNATURE ||
                      h->algorithm == BISIM_ALGORITHM_HYBRID)
                         ? signature_run(h, block_id, h->algorithm == BISIM_ALGORITHM_HYBRID)

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "bisim.h"
 
 namespace bisim {
@@ -37,11 +39,47 @@ void set_error(const char* fmt, ...);
 // device memory of the library's buffers.  dev_alloc takes stream-ordered
 // memory (hipMallocAsync), or, while an ArenaScope is open on the calling
 // thread, a 256-byte aligned piece of the scope's region (bump allocation,
-// nothing is returned before the scope closes); dev_free releases the former
-// and ignores the latter.
+// nothing is returned before the scope closes), or, while a ChunkScope is
+// open, a piece of a handle's chunks; dev_free releases the first and ignores
+// the others (a chunk's last piece is taken back).
 // ---------------------------------------------------------------------------
 hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t dev_free(void* p, hipStream_t s);
+
+// The device memory of one handle: a few stream-ordered allocations that its
+// buffers, and the temporaries of its calls, are cut from.  An allocation of
+// its own for each of about 45 buffers took 9 us, and its release 9 more
+// (load and release of a 100-state LTS 870 us of 1,390 us with the run); a
+// chunk takes 75 us.  Released with the handle; used by one thread at a time,
+// as the handle is.
+class Chunks {
+ public:
+  // the next `bytes` bytes come from one chunk; without effect if no memory is
+  // left (requests are then allocated one by one)
+  void reserve(size_t bytes, hipStream_t s);
+  hipError_t alloc(void** p, size_t bytes, hipStream_t s);
+  bool holds(const void* p) const;
+  void take_back(const void* p);
+  void release(hipStream_t s);
+
+ private:
+  struct Chunk {
+    char* base;
+    size_t cap, used, last;  // last: start of the most recent piece
+  };
+  hipError_t add(size_t bytes, hipStream_t s);
+  std::vector<Chunk> chunks_;
+};
+class ChunkScope {
+ public:
+  explicit ChunkScope(Chunks& c);
+  ~ChunkScope();
+  ChunkScope(const ChunkScope&) = delete;
+  ChunkScope& operator=(const ChunkScope&) = delete;
+
+ private:
+  Chunks* outer_;
+};
 class ArenaScope {
  public:
   ArenaScope(char* base, size_t capacity);
@@ -178,6 +216,7 @@ struct bisim_lists {
 };
 
 struct bisim_lts {
+  bisim::Chunks mem;  // every device buffer of the handle
   int32_t n = 0;
   int64_t m = 0;
   int32_t K = 1;

@@ -986,6 +986,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
 bisim_status by_source(bisim_lts* h) {
   bisim_lists& L = h->lists;
   if (L.out_ord) return BISIM_OK;  // the last one to be allocated
+  ChunkScope scope(h->mem);
   hipStream_t st = h->stream;
   const size_t n = (size_t)h->n;
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
@@ -1133,11 +1134,6 @@ void lists_free(bisim_lts* h) {
     (void)hipStreamSynchronize(L.own);
     (void)hipStreamDestroy(L.own);
   }
-  void* ptrs[] = {L.out_ptr, L.out_dst, L.out_ord, L.trk, L.trk_save, L.perm, L.pos, L.bs,  L.be,  L.cnt, L.fc,  L.gc,  L.tmp64, L.lb, L.lo, L.lh, L.ts,
-                  L.tbk,  L.ss,  L.sbk, L.sr,  L.sfi, L.sne, L.sps, L.sse,   L.work, L.tcn,
-                  L.pin,  L.pf};
-  for (void* q : ptrs)
-    if (q) (void)dev_free(q, h->stream);
   L = bisim_lists{};
 }
 

@@ -957,6 +957,7 @@ bisim_status bisim_collect_training(bisim_lts* h, int64_t sample_every, int32_t 
     return BISIM_E_INVALID;
   }
   *rows = 0;
+  ChunkScope scope(h->mem);
   int lds_max = 0;
   BISIM_TRY_HIP(hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock,
                                       h->device));
@@ -978,7 +979,7 @@ bisim_status bisim_collect_training(bisim_lts* h, int64_t sample_every, int32_t 
   a.trace_work = nullptr;
   BISIM_TRY(refine_init(h, a, 0, false, true, h->pre_block));
   uint32_t* written = nullptr;
-  BISIM_TRY_HIP(hipMallocAsync((void**)&written, sizeof(uint32_t), st));
+  BISIM_TRY_HIP(dev_alloc((void**)&written, sizeof(uint32_t), st));
   int64_t r = 0;
   bisim_status rc = BISIM_OK;
   for (uint32_t k = 0;; ++k) {
@@ -1018,7 +1019,7 @@ bisim_status bisim_collect_training(bisim_lts* h, int64_t sample_every, int32_t 
       break;
     }
   }
-  (void)hipFreeAsync(written, st);
+  (void)dev_free(written, st);
   (void)hipStreamSynchronize(st);
   *rows = r;
   return rc;

@@ -394,7 +394,7 @@ struct Temps {
     return BISIM_OK;
   }
   ~Temps() {
-    for (void* p : ptrs) (void)dev_free(p, s);
+    for (size_t i = ptrs.size(); i-- > 0;) (void)dev_free(ptrs[i], s);
   }
 };
 }  // namespace

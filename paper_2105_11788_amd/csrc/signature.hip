@@ -444,10 +444,8 @@ struct Bufs {
     }
     const int i = k++;
     if (h->sig_bytes[i] < bytes) {
-      if (h->sig_buf[i]) (void)hipFreeAsync(h->sig_buf[i], h->stream);
-      h->sig_buf[i] = nullptr;
-      h->sig_bytes[i] = 0;
-      if (hipMallocAsync(&h->sig_buf[i], bytes, h->stream) != hipSuccess) {
+      h->sig_bytes[i] = 0;  // (the piece of a slot that grows stays with the handle)
+      if (dev_alloc(&h->sig_buf[i], bytes, h->stream) != hipSuccess) {
         h->sig_buf[i] = nullptr;
         set_error("signature refinement: out of device memory (%zu bytes)", bytes);
         return BISIM_E_NOMEM;
@@ -493,6 +491,11 @@ bisim_status signature_core(bisim_lts* h, int64_t stall, int32_t* out, int64_t* 
   uint32_t *out_ptr, *o_rn, *nbig, *pidx = nullptr, *perm = nullptr;
   uint64_t *key, *keys, *sig, *hk, *hks;
   unsigned long long* cnt;
+  if (!h->sig_buf[0]) {  // the first run's buffers in one piece
+    const size_t ts = n <= kHashMax ? 12 * (size_t)table_size(n) : 0;
+    const size_t t1 = radix_sort_temp_bytes(m, false), t2 = radix_sort_temp_bytes(n, true);
+    h->mem.reserve(20 * (size_t)m + 48 * (size_t)n + ts + (t1 > t2 ? t1 : t2) + 24 * 256, st);
+  }
   BISIM_TRY(b.get(&tgt, (size_t)m));
   BISIM_TRY(b.get(&blk, (size_t)n));
   BISIM_TRY(b.get(&nb, (size_t)n));

@@ -7,6 +7,53 @@
 namespace bisim {
 
 static thread_local ArenaScope* g_arena = nullptr;
+static thread_local Chunks* g_chunks = nullptr;
+
+static size_t piece_bytes(size_t bytes) { return ((bytes ? bytes : 1) + 255) & ~(size_t)255; }
+
+hipError_t Chunks::add(size_t bytes, hipStream_t s) {
+  void* p = nullptr;
+  const hipError_t e = hipMallocAsync(&p, bytes, s);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return e;
+  }
+  chunks_.push_back({(char*)p, bytes, 0, 0});
+  return hipSuccess;
+}
+void Chunks::reserve(size_t bytes, hipStream_t s) {
+  if (chunks_.empty() || chunks_.back().cap - chunks_.back().used < bytes)
+    (void)add(piece_bytes(bytes), s);
+}
+hipError_t Chunks::alloc(void** p, size_t bytes, hipStream_t s) {
+  const size_t need = piece_bytes(bytes);
+  if (chunks_.empty() || chunks_.back().cap - chunks_.back().used < need) {
+    // beyond what was reserved: pieces of 1 MiB for small requests
+    hipError_t e = need < (1u << 20) ? add(1u << 20, s) : hipErrorOutOfMemory;
+    if (e != hipSuccess) e = add(need, s);
+    if (e != hipSuccess) return e;
+  }
+  Chunk& c = chunks_.back();
+  c.last = c.used;
+  *p = c.base + c.used;
+  c.used += need;
+  return hipSuccess;
+}
+bool Chunks::holds(const void* p) const {
+  for (const Chunk& c : chunks_)
+    if ((const char*)p >= c.base && (const char*)p < c.base + c.cap) return true;
+  return false;
+}
+void Chunks::take_back(const void* p) {
+  for (Chunk& c : chunks_)
+    if (c.last < c.used && (const char*)p == c.base + c.last) c.used = c.last;
+}
+void Chunks::release(hipStream_t s) {
+  for (const Chunk& c : chunks_) (void)hipFreeAsync(c.base, s);
+  chunks_.clear();
+}
+ChunkScope::ChunkScope(Chunks& c) : outer_(g_chunks) { g_chunks = &c; }
+ChunkScope::~ChunkScope() { g_chunks = outer_; }
 
 ArenaScope::ArenaScope(char* base, size_t capacity) : base_(base), cap_(capacity), outer_(g_arena) {
   g_arena = this;
@@ -18,7 +65,7 @@ hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s) {
   *p = nullptr;
   if (bytes == 0) bytes = 1;
   ArenaScope* a = g_arena;
-  if (!a) return hipMallocAsync(p, bytes, s);
+  if (!a) return g_chunks ? g_chunks->alloc(p, bytes, s) : hipMallocAsync(p, bytes, s);
   const size_t at = (a->used_ + 255) & ~(size_t)255;
   if (at > a->cap_ || bytes > a->cap_ - at) return hipErrorOutOfMemory;
   *p = a->base_ + at;
@@ -30,6 +77,10 @@ hipError_t dev_free(void* p, hipStream_t s) {
   if (!p) return hipSuccess;
   for (ArenaScope* a = g_arena; a; a = a->outer_)
     if ((char*)p >= a->base_ && (char*)p < a->base_ + a->cap_) return hipSuccess;
+  if (g_chunks && g_chunks->holds(p)) {
+    g_chunks->take_back(p);
+    return hipSuccess;
+  }
   return hipFreeAsync(p, s);
 }
 
