@@ -21,7 +21,8 @@ void set_error(const char* fmt, ...) {
 // preprocessing of many actions among them), and what the run state and the
 // member lists take: hints, so that a small LTS lives in one chunk.
 static size_t setup_bytes(int64_t n, int64_t m, int64_t K) {
-  size_t b = 16 * (size_t)m + 124 * (size_t)n + 8 * (size_t)K + 64 * 256;
+  // (K <= 64: the table takes up to 48 bytes per state)
+  size_t b = (K <= 64 ? 9 : 17) * (size_t)m + 100 * (size_t)n + 8 * (size_t)K + 64 * 256;
   if (K == 1) b += 4 * (size_t)n;
   if (K > 64) b += 4 * (size_t)m + 64 * (size_t)n;
   return b;

@@ -231,6 +231,7 @@ struct bisim_lts {
   uint32_t* in_ptr = nullptr;    // [n+1] transitions grouped by target
   int32_t* in_src = nullptr;     // [m] source of each grouped transition
   int32_t* in_ord = nullptr;     // [m] its action's rank among the source's actions
+  uint8_t* in_lab8 = nullptr;    // [m] its label mod 8 (block features)
   uint32_t* woff = nullptr;      // [n+1] mark-word offsets (only when !uniform)
   int uniform = 1;               // every state has <= 64 actions: word index = state
   uint32_t max_out = 0;          // largest number of outgoing transitions of a state

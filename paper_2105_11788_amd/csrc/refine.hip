@@ -356,12 +356,41 @@ bisim_status refine_alloc(bisim_lts* h) {
   return BISIM_OK;
 }
 
+namespace {
+__global__ void k_zero_words(uint32_t* p, uint64_t count) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    p[i] = 0;
+}
+// outgoing / incoming transitions of every state by label mod 8 (block
+// features of the learned splitter policy are sums of these)
+__global__ void k_static_features(uint32_t n, const uint32_t* __restrict__ in_ptr,
+                                  const int32_t* __restrict__ in_src,
+                                  const uint8_t* __restrict__ in_lab8,
+                                  uint32_t* __restrict__ sfeat) {
+  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
+    for (uint32_t e = in_ptr[t]; e < in_ptr[t + 1]; ++e) {
+      const uint32_t q = in_lab8[e];
+      atomicAdd(&sfeat[(size_t)in_src[e] * 16 + q], 1u);
+      atomicAdd(&sfeat[(size_t)t * 16 + 8 + q], 1u);
+    }
+}
+}  // namespace
+
 // feature / policy state, allocated on first use
 bisim_status refine_alloc_features(bisim_lts* h) {
   if (h->acc) return BISIM_OK;
   const size_t n = (size_t)h->n;
   hipStream_t s = h->stream;
   const size_t nwd = (n + 63) / 64, nsw = (nwd + 63) / 64, ntw = (nsw + 63) / 64;
+  BISIM_TRY(dalloc(&h->sfeat, 16 * n, s));
+  const int64_t cu = h->num_cu > 0 ? h->num_cu : 1;
+  const int64_t g = std::min<int64_t>((16 * (int64_t)n + kT - 1) / kT, cu * 16);
+  hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
+                     h->sfeat, 16 * (uint64_t)n);
+  hipLaunchKernelGGL(k_static_features, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
+                     (uint32_t)n, h->in_ptr, h->in_src, h->in_lab8, h->sfeat);
+  BISIM_TRY_HIP(hipGetLastError());
   BISIM_TRY(dalloc(&h->acc, 17 * n, s));
   BISIM_TRY(dalloc(&h->born, n, s));
   BISIM_TRY(dalloc(&h->used, n, s));
