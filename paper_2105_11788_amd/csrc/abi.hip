@@ -29,7 +29,7 @@ static size_t setup_bytes(int64_t n, int64_t m, int64_t K) {
 }
 static size_t run_bytes(int64_t n, int64_t m) {
   size_t b = 150 * (size_t)n + 96 * 256;
-  if (m >= 65536) b += 8 * (size_t)m;
+  if (m >= 1024) b += 8 * (size_t)m;
   return b;
 }
 

@@ -58,6 +58,7 @@ struct bisim_batch {
   uint8_t* trk = nullptr;
   uint32_t* iters_d = nullptr;  // [count]
   uint32_t* ctl_d = nullptr;    // [0] queue head, [1] error
+  bisim::RoundsArgs<uint64_t>* args_d = nullptr;  // [count]
   unsigned long long* work_d = nullptr;  // [16] work totals per tier
   // options / tuning
   int opt_wg = 0, opt_grid = 0, opt_lds = 0, opt_retune = 0;
@@ -98,9 +99,8 @@ struct BArgs {
   int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc, *tmp, *rk, *fi, *ob, *nev, *ltl, *tlb, *se, *llo,
       *lsz;
   uint64_t *sf, *us, *tmp64, *pin;
-  const uint32_t* __restrict__ out_ptr;  // transitions by source
-  const int32_t* __restrict__ out_dst;
-  const int32_t* __restrict__ out_ord;
+  uint32_t* out_ptr;  // transitions by source
+  int32_t *out_dst, *out_ord;
   uint8_t* trk;
   int32_t* out;
   uint32_t* iters;
@@ -130,90 +130,42 @@ template <int WG>
 struct Shared {
   RoundsShared<WG> r;
   uint32_t job;
-  unsigned long long work[7];
 };
 
 // kBm: the label bitmaps of every instance fit the LDS budget beside the
 // tables (else they stay in global memory for all of them: a second copy of
 // the loop in one kernel spills registers).
 template <class MaskT, int WG, bool kBm>
-__global__ void __launch_bounds__(WG) k_batch(BArgs a) {
+__global__ void __launch_bounds__(WG) k_batch(BArgs a,
+                                                    const RoundsArgs<MaskT>* __restrict__ args) {
   extern __shared__ uint64_t lds[];
   __shared__ Shared<WG> sh;
   char* base = reinterpret_cast<char*>(lds);
   for (;;) {
     if (threadIdx.x == 0) sh.job = atomicAdd(&a.ctl[0], 1u);
-    if (threadIdx.x < 7) sh.work[threadIdx.x] = 0;
+    if (threadIdx.x < kWorkTotals) sh.r.work[threadIdx.x] = 0;
     __syncthreads();
-    // scalars, so that the instance's pointers are scalars too (as vectors
-    // they cost over 100 registers and spilled)
+    // the instance's pointers are read as scalars where they are needed
+    // (computed here they spilled: 60-120 bytes per thread)
     const uint32_t job = uniform_u32(sh.job);
     if (job >= (uint32_t)a.count) break;
     const uint32_t k = uniform_u32((uint32_t)a.order[job]);
-    const uint32_t s0 = uniform_u32(a.n_off[k]), n = uniform_u32(a.n_off[k + 1]) - s0;
-    const uint32_t b0 = uniform_u32(a.bw_off[k]);
-    RoundsArgs<MaskT> g{};
-    g.n = n;
-    g.s0 = s0;
-    g.iter_cap = 3u * n + 1u;
-    g.in_ptr = a.in_ptr + s0;
-    g.in_src = a.in_src;
-    g.in_ord = a.in_ord;
-    g.blk = a.blk + s0;
-    g.perm = a.perm + s0;
-    g.pos = a.pos + s0;
-    g.bs = a.bs + s0;
-    g.be = a.be + s0;
-    g.pin = a.pin + s0;
-    g.mw = reinterpret_cast<MaskT*>(a.mw) + s0;
-    g.cnt = a.cnt + s0;
-    g.fc = a.fc + s0;
-    g.gc = a.gc + s0;
-    g.nlb = a.nlb + s0;
-    g.tmp64 = a.tmp64 + s0;
-    g.sf = a.sf + b0;
-    g.ts = a.tl + s0;
-    g.tb = a.tlb + s0;
-    g.lb = a.ltl + s0;
-    g.llo = a.llo + s0;
-    g.lsz = a.lsz + s0;
-    g.ss = a.sl + s0;
-    g.sbk = a.ob + s0;
-    g.sr = a.rk + s0;
-    g.sfi = a.fi + s0;
-    g.sne = a.nev + s0;
-    g.sps = a.tmp + s0;
-    g.sse = a.se + s0;
-    g.ub = a.ub + b0;
-    g.qb = a.qb + b0;
-    g.us = a.us + b0;
-    g.qs = a.qs + b0;
-    g.out_ptr = a.out_ptr + s0;
-    g.out_dst = a.out_dst;
-    g.out_ord = a.out_ord;
-    g.trk = a.trk + s0;
-    g.mean_deg = uniform_u32(n ? (a.in_ptr[s0 + n] - a.in_ptr[s0] + n - 1) / n : 1u);
+    const RoundsArgs<MaskT> g = args[k];
+    const uint32_t s0 = g.s0, n = g.n;
     uint32_t rc = kRoundsBad, none = 0;
-    RoundsWork w;
+    RoundsResume resume;
+    resume.may_track = true;
     if (rounds_setup<MaskT, WG>(g, sh.r, a.pre_block + s0, true))
-      rc = rounds_loop<MaskT, WG, kBm>(g, sh.r, base, a.lds_bytes, 0, RoundsResume(), none, w);
+      rc = rounds_loop<MaskT, WG, kBm, kEither>(g, sh.r, base, a.lds_bytes, 0, resume, none);
     if (rc == kRoundsDone && sh.r.it > g.iter_cap) rc = kRoundsCap;
     for (uint32_t s = threadIdx.x; s < n; s += WG) a.out[s0 + s] = g.blk[s];
-    const uint64_t t[7] = {w.members, w.edges, w.touched, w.listed, w.visits, w.split, w.blocks};
-#pragma unroll
-    for (int i = 0; i < 7; ++i) {
-      uint64_t v = t[i];
-#pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) v += (uint64_t)__shfl_xor((unsigned long long)v, d, kWave);
-      if (lane() == 0 && v) atomicAdd(&sh.work[i], (unsigned long long)v);
-    }
     __syncthreads();
     if (threadIdx.x == 0) {
       const uint32_t its = sh.r.it + 1;  // with the final pass
       a.iters[k] = its;
       if (rc == kRoundsCap) atomicOr(&a.ctl[1], 1u);
       if (rc == kRoundsBad) atomicOr(&a.ctl[1], 2u);
-      const unsigned long long* x = sh.work;
+      const unsigned long long* x = sh.r.work;
       if (lds_need<MaskT>(n) <= a.lds_bytes) {
         const unsigned long long v[8] = {its, x[0], x[1], x[2], 0, x[5], 0, 1};
 #pragma unroll
@@ -226,6 +178,58 @@ __global__ void __launch_bounds__(WG) k_batch(BArgs a) {
     }
     __syncthreads();
   }
+}
+
+// The loop's arguments of every instance, once per batch (the mark words of
+// instances with 32-bit marks take the first half of their 64-bit ones).
+__global__ void k_batch_args(BArgs a, RoundsArgs<uint64_t>* __restrict__ out) {
+  const int32_t k = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (k >= a.count) return;
+  const uint32_t s0 = a.n_off[k], n = a.n_off[k + 1] - s0;
+  const uint32_t b0 = a.bw_off[k];
+  RoundsArgs<uint64_t> g{};
+  g.n = n;
+  g.s0 = s0;
+  g.iter_cap = 3u * n + 1u;
+  g.in_ptr = a.in_ptr + s0;
+  g.in_src = a.in_src;
+  g.in_ord = a.in_ord;
+  g.blk = a.blk + s0;
+  g.perm = a.perm + s0;
+  g.pos = a.pos + s0;
+  g.bs = a.bs + s0;
+  g.be = a.be + s0;
+  g.pin = a.pin + s0;
+  g.mw = reinterpret_cast<uint64_t*>(a.mw) + s0;
+  g.cnt = a.cnt + s0;
+  g.fc = a.fc + s0;
+  g.gc = a.gc + s0;
+  g.nlb = a.nlb + s0;
+  g.tmp64 = a.tmp64 + s0;
+  g.sf = a.sf + b0;
+  g.ts = a.tl + s0;
+  g.tb = a.tlb + s0;
+  g.lb = a.ltl + s0;
+  g.llo = a.llo + s0;
+  g.lsz = a.lsz + s0;
+  g.ss = a.sl + s0;
+  g.sbk = a.ob + s0;
+  g.sr = a.rk + s0;
+  g.sfi = a.fi + s0;
+  g.sne = a.nev + s0;
+  g.sps = a.tmp + s0;
+  g.sse = a.se + s0;
+  g.ub = a.ub + b0;
+  g.qb = a.qb + b0;
+  g.us = a.us + b0;
+  g.qs = a.qs + b0;
+  g.out_ptr = a.out_ptr + s0;
+  g.out_dst = a.out_dst;
+  g.out_ord = a.out_ord;
+  g.out_cur = nullptr;
+  g.trk = a.trk + s0;
+  g.mean_deg = n ? (a.in_ptr[s0 + n] - a.in_ptr[s0] + n - 1) / n : 1u;
+  out[k] = g;
 }
 
 __global__ void k_reset_queue(uint32_t* ctl, unsigned long long* work) {
@@ -298,7 +302,7 @@ void free_batch(bisim_batch* b) {
                   b->pos,     b->bs,       b->be,      b->cnt, b->fc,      b->gc,    b->tmp,
                   b->rk,      b->fi,       b->ltl,     b->sf,  b->us,      b->ob,    b->nev,
                   b->tlb,     b->se,       b->tmp64,   b->work_d, b->llo, b->lsz,
-                  b->pin,     b->trk};
+                  b->pin,     b->trk,      b->args_d};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (b->u) lts_destroy(b->u);
@@ -381,7 +385,8 @@ bisim_status launch_once(bisim_batch* b, int32_t* out, int wg, int grid, int lds
     set_error("batched kernel: workgroup size %d is not built", wg);
     return BISIM_E_INVALID;
   }
-  void* args[] = {&a};
+  const void* inst = b->args_d;  // (one layout for both mark words)
+  void* args[] = {&a, &inst};
   const void* f = kernel_of(b, wg, lds);
   BISIM_TRY_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b->lds_max));
   BISIM_TRY_HIP(hipLaunchKernel(f, dim3(grid), dim3(wg), args, lds, b->stream));
@@ -637,8 +642,15 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
         (st = by_source(b->u)) ||
         (st = dmalloc(&b->llo, (size_t)N)) || (st = dmalloc(&b->lsz, (size_t)N)) ||
         (st = dmalloc(&b->iters_d, count)) || (st = dmalloc(&b->ctl_d, 2)) ||
-        (st = dmalloc(&b->work_d, 16)))
+        (st = dmalloc(&b->work_d, 16)) || (st = dmalloc(&b->args_d, (size_t)count)))
       break;
+    if (count > 0)
+      hipLaunchKernelGGL(k_batch_args, dim3((unsigned)(count + 255) / 256), dim3(256), 0, s,
+                       make_args(b, nullptr), b->args_d);
+    if (hipGetLastError() != hipSuccess) {
+      st = BISIM_E_DEVICE;
+      break;
+    }
     float ms = 0;
     if (hipEventRecord(b->ev1, s) != hipSuccess || hipEventSynchronize(b->ev1) != hipSuccess ||
         hipEventElapsedTime(&ms, b->ev0, b->ev1) != hipSuccess) {

@@ -653,11 +653,16 @@ constexpr uint32_t kSetupN = 16384;     // up to here the workgroup builds the m
 // (planted quotient of 1.03M states before tracking: 336 ms, with the
 // workgroup taking up to 8192 / 49152 transitions 444 / 937 ms).
 constexpr uint32_t kGridEdges = 2048;
-// LTSs with fewer transitions have their mark words in LDS, where marking a
-// whole block costs little: their transitions are not laid out by source
-constexpr int64_t kTrackMinM = 65536;
+// LTSs with fewer transitions have no splitter worth tracking; up to the
+// second number the workgroup lays the transitions out by source itself, if
+// some block is large enough (10 us for 8000 transitions against 35 us for
+// the launches, which would be spent on every small LTS)
+constexpr int64_t kTrackMinM = kTrackEdgesDense, kOwnOutM = 65536;
 
-template <class MaskT, bool kBm>
+// state.v[10]: 0 without tracking so far, 1 with it, 2 no longer (the kernel
+// compiled for the other does nothing); state.v[11]: the transitions by source
+// are laid out
+template <class MaskT, bool kBm, bool kTrack>
 __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, uint32_t* pf,
                                                  const int32_t* start, uint32_t lds_bytes) {
   extern __shared__ uint64_t lds[];
@@ -665,8 +670,16 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
   const uint32_t done = ctl->state.v[1], entered = ctl->state.v[8];
   const uint32_t it = ctl->state.v[6] + (ctl->state.v[7] ? 1u : 0u);
   RoundsResume resume;
-  if (ctl->state.v[7]) resume = {ctl->state.v[3], ctl->cntS[0].v[0], ctl->state.v[9]};
-  if (done) return;
+  if (ctl->state.v[7]) {
+    resume.label = ctl->state.v[3];
+    resume.nS = ctl->cntS[0].v[0];
+    resume.mixed = ctl->state.v[9];
+  }
+  const uint32_t mode = ctl->state.v[10];
+  if (done || (mode == 1) != kTrack) return;
+  resume.may_track = mode == 0;
+  resume.nbig = ctl->state.v[12];
+  resume.lay_out = a.out_cur && ctl->state.v[11] == 0;
   uint32_t rc = kRoundsDone, C = kNone;
   if (!entered) {
     if (start) {
@@ -678,17 +691,23 @@ __global__ void __launch_bounds__(kRWG) k_rounds(RoundsArgs<MaskT> a, Ctl* ctl, 
       __syncthreads();
     }
   }
-  RoundsWork work;
   if (rc == kRoundsDone)
-    rc = rounds_loop<MaskT, kRWG, kBm>(a, sh, reinterpret_cast<char*>(lds), lds_bytes, it,
-                                       resume, C, work);
+    rc = rounds_loop<MaskT, kRWG, kBm, kTrack ? kTracking : kPlain>(
+        a, sh, reinterpret_cast<char*>(lds), lds_bytes, it, resume, C);
   if (threadIdx.x != 0) return;
   if (rc == kRoundsDone && sh.it > a.iter_cap) rc = kRoundsCap;
   ctl->state.v[7] = 0;
   ctl->state.v[8] = 1;
+  if (kTrack) ctl->state.v[11] = 1;
+  if (rc == kRoundsTrack) {
+    ctl->state.v[6] = sh.it;
+    ctl->state.v[10] = kTrack ? 2 : 1;
+    return;
+  }
   if (rc == kRoundsGrid) {
     // one iteration with splitter C: counters and the prefetch slot as the
     // mark kernel of an even launch position expects them
+    ctl->state.v[12] = sh.nbig;
     ctl->state.v[6] = sh.it - 1;  // the number of C's iteration
     ctl->state.v[7] = 1;
     ctl->state.v[9] = 0;
@@ -1067,22 +1086,35 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.out_ptr = L.out_ptr;
   a.out_dst = L.out_dst;
   a.out_ord = L.out_ord;
+  a.out_cur = L.out_ptr && h->m < kOwnOutM ? reinterpret_cast<uint32_t*>(L.tcn) : nullptr;
   a.trk = L.trk;
   a.trk_save = L.trk_save;
-  const auto kern = k_rounds<MaskT, kBm>;
-  BISIM_TRY_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)lds_bytes));
+  using Kernel = void (*)(RoundsArgs<MaskT>, Ctl*, uint32_t*, const int32_t*, uint32_t);
+  const Kernel kerns[2] = {k_rounds<MaskT, kBm, false>, k_rounds<MaskT, kBm, true>};
+  for (Kernel k : kerns)
+    BISIM_TRY_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      (int)lds_bytes));
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   const int grid = h->grid > 0 ? h->grid : cu * 4;
   h->run_grid = a.grid_edges ? grid : 1;
-  hipLaunchKernelGGL(kern, dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start, lds_bytes);
+  hipLaunchKernelGGL(kerns[0], dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start,
+                     lds_bytes);
   BISIM_TRY_HIP(hipGetLastError());
   uint64_t launched = 0;
-  for (uint32_t reps = 1;; reps = reps < 16 ? reps * 2 : reps) {
+  for (uint32_t reps = 1;;) {
     BISIM_TRY_HIP(hipMemcpyAsync(&h->ctl_host->state, &h->ctl->state, sizeof(Line),
                                  hipMemcpyDeviceToHost, st));
     BISIM_TRY_HIP(hipStreamSynchronize(st));
-    if (h->ctl_host->state.v[1] || launched > (uint64_t)cap + 1) return BISIM_OK;
+    const Line& now = h->ctl_host->state;
+    if (now.v[1] || launched > (uint64_t)cap + 16) return BISIM_OK;
+    const Kernel kern = kerns[now.v[10] == 1];
+    if (!now.v[7]) {  // nothing for the grid: the run changed to the other loop
+      hipLaunchKernelGGL(kern, dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start,
+                         lds_bytes);
+      launched += 1;
+      BISIM_TRY_HIP(hipGetLastError());
+      continue;
+    }
     for (uint32_t r = 0; r < reps; ++r) {
       hipLaunchKernelGGL(k_l_mark, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_compare, dim3(grid), dim3(kLT), 0, st, l, 0u);
@@ -1092,6 +1124,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
                          lds_bytes);
     }
     launched += reps;
+    reps = reps < 16 ? reps * 2 : reps;
     BISIM_TRY_HIP(hipGetLastError());
   }
 }
@@ -1103,7 +1136,13 @@ bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool r
   const bool own = n <= kSetupN;
   bisim_lists& L = h->lists;
   if (h->m >= kTrackMinM) {
-    BISIM_TRY(by_source(h));
+    if (h->m >= kOwnOutM) {
+      BISIM_TRY(by_source(h));
+    } else {
+      BISIM_TRY(lalloc(&L.out_ptr, (size_t)n + 1, h->stream));
+      BISIM_TRY(lalloc(&L.out_dst, (size_t)h->m, h->stream));
+      BISIM_TRY(lalloc(&L.out_ord, (size_t)h->m, h->stream));
+    }
     BISIM_TRY(lalloc(&L.trk, n, h->stream));
     BISIM_TRY(lalloc(&L.trk_save, kTrackSave, h->stream));
   }

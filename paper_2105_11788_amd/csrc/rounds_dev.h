@@ -31,16 +31,21 @@
 // marks iff they lost the same ones.  The table then holds the lost marks in
 // place of the marks, and the rest of the round is the same.  (Uniform LTS of
 // 300k states 1,290 -> 929 ms, chain of 100k 2,640 -> 816, 48 instances of up
-// to 200k states in a batch 1,014 -> 500.)
+// to 200k states in a batch 1,014 -> 500; with the shorter rounds 840, 660 and
+// 430.)
 //
-// Bound: the chain of a round's dependent steps, about 9 us when something
+// Bound: the chain of a round's dependent steps, about 7.5 us when something
 // splits (uniform LTS of 20k states, 3,464 rounds for 27,089 iterations):
-// candidates 1.6, members 1.1, transitions 1.8, comparison 1.1, verdicts 0.7,
-// split list 1.1, split 2.3 (four trips to the L2 and ten barriers among
-// them).  Against two grid-wide kernels per iteration: uniform LTS of 20k
-// states 252 -> 31 ms, Kripke structure of 1000 states 14.1 -> 3.4 ms, 25k
-// states with as many actions as transitions 151 -> 7.2 ms, planted quotient
-// of 1.03M states 748 -> 348 ms (load and read-back included).
+// members 1.0, transitions 1.3, comparison 1.0, verdicts 0.3, split list 0.9,
+// split 0.5 + 1.0, and the next round's candidates beside the moves 1.7.  A
+// trip to the L2 is about 0.2 of these, to LDS 0.06, and waves that have
+// nothing to do still take issue slots, so a step's loads are issued together,
+// searches are bit counts of start bitmaps, values that all lanes agree on go
+// through scalar registers, and sums over the workgroup are skipped while one
+// wave holds the members.  Against two grid-wide kernels per iteration: uniform
+// LTS of 20k states 232 -> 25 ms, Kripke structure of 1000 states 14.6 -> 2.2 ms,
+// 25k states with as many actions as transitions 134 -> 5.5 ms, planted quotient
+// of 1.03M states 746 -> 292 ms (load and read-back included).
 //
 // The partition is a refinable partition: perm lists the states block by
 // block, block b (a label, its smallest member) owns perm[bs[b] .. be[b]),
@@ -61,12 +66,25 @@ constexpr uint32_t kTracked = 64;    // labels tracked at a time
 constexpr uint32_t kLost = 64;       // states a tracked block can have lost
 // In-transitions from which a label is tracked: below, marking the whole block
 // costs a round no more than the visits of its lost states' sources (2.5 us).
-// While the mark words of all states fit LDS that is up to 8192 (3-4 us for
-// 5000; chain of 5000 states 40.4 ms untracked, 43.6 tracked from 384 on).
-constexpr uint32_t kTrackEdges = 384, kTrackEdgesDense = 8192;
-constexpr uint32_t kOutU = 8;        // outgoing transitions in flight per thread
+// While the mark words of all states fit LDS, marking a whole block is cheaper
+// (3 us and a table to clear for 5000 transitions) and the line lies higher
+// (chains of 1000 / 5000 / 15000 states: never tracked 7.9 / 41.5 / 189 ms,
+// from 1536 on 7.9 / 34.3 / 102).  It starts there once kTrackAfter whole
+// blocks were marked and stops when no block is as large: a round with tracking
+// costs 5-15 % more, which a large block that is hardly ever a splitter does
+// not repay.  For the same reason the loop is compiled with and without
+// tracking (product of 20,736 states 48.0 / 51.9 ms, 25k states with as many
+// actions as transitions 4.8 / 5.7), and a run changes from one to the other.
+constexpr uint32_t kTrackEdges = 384, kTrackEdgesDense = 1536;
+constexpr uint32_t kTrackAfter = 8;
+constexpr uint32_t kTrackLook = 256;  // rounds between two looks at the largest block
+// outgoing transitions in flight per thread (the batched kernel: as its
+// registers allow)
+template <class MaskT, int kMode, bool kBm>
+constexpr uint32_t out_u() { return kMode != 2 ? 8 : sizeof(MaskT) == 4 && kBm ? 6 : 2; }
 constexpr uint32_t kListCap = 64;    // listed blocks kept in LDS
-constexpr uint32_t kScanU = 4;       // states or transitions in flight per thread
+constexpr uint32_t kOwnBlock = 128;  // members up to which a wave takes a listed block alone
+constexpr uint32_t kScanU = 2;       // states or transitions in flight per thread
 // transitions per thread and round
 template <int WG>
 constexpr uint32_t edges_per_thread() { return WG >= 512 ? 2 : 4; }
@@ -76,6 +94,8 @@ constexpr uint32_t small_split() { return WG < 256 ? WG : 256; }
 
 // results of rounds_loop
 constexpr uint32_t kRoundsDone = 0, kRoundsGrid = 1, kRoundsBad = 2, kRoundsCap = 3;
+constexpr uint32_t kRoundsTrack = 4;  // go on in the loop with (or again without) tracking
+constexpr uint32_t kRoundsGo = 5;  // (inside: the next round)
 
 // One instance; per-state arrays start at its first state, state ids in
 // in_src are shifted by s0.
@@ -99,45 +119,65 @@ struct RoundsArgs {
   int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;
   // transitions by source, and per label its entry among the tracked ones plus
   // one (0: not tracked); null: no tracking
-  const uint32_t* out_ptr;
-  const int32_t *out_dst, *out_ord;
+  uint32_t* out_ptr;
+  int32_t *out_dst, *out_ord;
+  uint32_t* out_cur;   // [n], 0 when not in use: the workgroup lays them out, if it
+                       // tracks (null: they are there)
   uint8_t* trk;
   uint32_t* trk_save;  // [kTrackSave] between launches of one run (nullable)
   // bitmaps over labels and their summaries (bit w set iff word w is not 0)
   uint64_t *ub, *qb, *us, *qs;
 };
 
-// Work totals of a run, each thread's share (summed by the caller; what no
-// caller reads costs nothing).
-struct RoundsWork {
-  uint64_t members = 0, edges = 0;  // of the labels marked
-  uint64_t touched = 0;             // (label, source) pairs
-  uint64_t listed = 0, visits = 0;  // blocks with untouched members, and their members
-  uint64_t split = 0, blocks = 0;   // split states, new blocks
-};
+// Work totals of a run, in LDS (kEither only: the others' callers read none):
+// members and transitions of the labels marked, (label, source) pairs, blocks
+// with untouched members and their members, split states, new blocks.
+constexpr int kWMembers = 0, kWEdges = 1, kWTouched = 2, kWListed = 3, kWVisits = 4, kWSplit = 5,
+              kWBlocks = 6, kWorkTotals = 7;
 
 // What the grid did between two launches of one run: the iteration of `label`
 // (kNone: none), the split states it listed, and whether the split part of
 // some block holds different marks.
 struct RoundsResume {
   uint32_t label = kNone, nS = 0, mixed = 0;
+  uint32_t nbig = 0;       // whole blocks marked since the last look at the largest
+  bool may_track = false;  // the loop without tracking may end for it
+  bool lay_out = false;    // the transitions by source are to be laid out
 };
 
 template <int WG>
 struct RoundsShared {
   uint32_t cand[kCand], cb[kCand], cpre[kCand], cend[kCand], unst[kCand];
   uint32_t ctrk[kCand];  // tracked entry of the candidate plus one
+  uint32_t cbeg[kCand];  // its first transition of the round's (cend: past its last)
+  uint32_t wl[kWave];    // words of Q
+  // the candidates with members, in order: first member (and, after the last,
+  // their number), first position, candidate, tracked entry to visit plus one
+  uint32_t rfirst[kCand + 1], rb[kCand], rc[kCand], rtrk[kCand];
+  uint64_t cstarts[WG / kWave];  // bit i: member i is the first of a candidate
   uint32_t tn[kTracked], tlabel[kTracked];  // tracked labels: lost states, label
-  uint32_t wsum[WG / kWave];
+  uint32_t wsum[WG / kWave], wnz[WG / kWave];
+  // the members with in-transitions (mbeg, mpre, mc), and bit e: transition e
+  // of the round is the first of one
+  uint64_t starts[edges_per_thread<WG>() * WG / kWave];
+  unsigned long long work[kWorkTotals];
   uint32_t mbeg[WG], mpre[WG];
   uint8_t mc[WG];
   int32_t ss[small_split<WG>()], sb[small_split<WG>()];  // the first split states and their blocks
   uint32_t lb[kListCap], llo[kListCap], lsz[kListCap];   // the first listed blocks
-  uint32_t nc, np, mtot, etot, csz0, nS, nL, nT, tctr, bad;
+  uint32_t nc, np, mtot, etot, csz0, nT, tctr, bad;
+  union {
+    unsigned long long nSL;
+    struct {
+      uint32_t nS, nL;  // split states, listed blocks
+    };
+  };
   uint32_t inc;              // candidates visited through their lost states
   uint32_t tnext;            // next tracked entry to take
   uint32_t fent, ffresh;     // the splitter's entry plus one; taken in this round
   uint32_t fold;             // lost states its entry already had
+  uint32_t most;             // members of the largest block
+  uint32_t nbig;             // whole blocks marked, for the next launch
   uint32_t mixed, nself;     // a split part with different marks; split states of C itself
   uint32_t it;  // iterations so far
 };
@@ -145,6 +185,24 @@ struct RoundsShared {
 // a value that is the same on every lane, as a scalar
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+}
+
+// lane l's value (l the same on every lane), without a trip through the LDS unit
+__device__ __forceinline__ uint32_t lane_u32(uint32_t v, uint32_t l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)l);
+}
+__device__ __forceinline__ uint64_t lane_u64(uint64_t v, uint32_t l) {
+  return (uint64_t)lane_u32((uint32_t)(v >> 32), l) << 32 | lane_u32((uint32_t)v, l);
+}
+// set bits of v below this lane's position
+__device__ __forceinline__ uint32_t bits_below(uint64_t v) {
+  return (uint32_t)__builtin_amdgcn_mbcnt_hi(
+      (uint32_t)(v >> 32), (uint32_t)__builtin_amdgcn_mbcnt_lo((uint32_t)v, 0u));
+}
+// LDS writes of the wave's lanes before are seen by its lanes after
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 template <class MaskT>
@@ -199,8 +257,8 @@ __device__ __forceinline__ uint32_t list_push(uint32_t* counter, bool pred) {
   const int leader = __ffsll((unsigned long long)bal) - 1;
   uint32_t base = 0;
   if ((int)lane() == leader) base = atomicAdd(counter, (uint32_t)__popcll(bal));
-  base = (uint32_t)__shfl((int)base, leader, kWave);
-  return pred ? base + (uint32_t)__popcll(bal & ((1ull << lane()) - 1ull)) : kNone;
+  base = lane_u32(base, (uint32_t)leader);
+  return pred ? base + bits_below(bal) : kNone;
 }
 
 // entry i of the split list and of the list of blocks: in LDS, beyond its
@@ -231,25 +289,32 @@ __device__ __forceinline__ void put_block(const A& a, S& sh, uint32_t i, uint32_
   }
 }
 
-// position of the r-th set bit of v (r < number of set bits)
-__device__ __forceinline__ uint32_t select_bit(uint64_t v, uint32_t r) {
-  uint32_t w = (uint32_t)v, p = 0;
-  const uint32_t c0 = (uint32_t)__popcll((unsigned long long)w);
-  if (r >= c0) {
-    r -= c0;
-    w = (uint32_t)(v >> 32);
-    p = 32;
+// Lane l holds the set v of items 64 id .. 64 id + 63: the items of all lanes
+// in lane order to out[0 .. lim), one wave; their number (not capped).  A lane
+// writes its own items where it has few; of a lane with many, every lane of
+// the wave takes one (both are a few steps: of the latter there are at most
+// lim / 5).
+__device__ __forceinline__ uint32_t expand_bits(uint64_t v, uint32_t id, uint32_t* out,
+                                                uint32_t lim) {
+  constexpr uint32_t kFew = 4;
+  const uint32_t pc = (uint32_t)__popcll(v);
+  const uint32_t incl = wave_incl_scan_u32(pc);
+  const uint32_t total = lane_u32(incl, kWave - 1);
+  const uint32_t at = incl - pc;
+  uint64_t many = __ballot(pc > kFew && at < lim);
+  if (pc <= kFew) {
+    uint64_t x = v;
+    for (uint32_t k = at; x && k < lim; ++k, x &= x - 1)
+      out[k] = (id << 6) + (uint32_t)(__ffsll((unsigned long long)x) - 1);
   }
-#pragma unroll
-  for (uint32_t step = 16; step >= 1; step >>= 1) {
-    const uint32_t c = (uint32_t)__popcll((unsigned long long)(w & ((1u << step) - 1u)));
-    if (r >= c) {
-      r -= c;
-      w >>= step;
-      p += step;
-    }
+  while (many) {
+    const uint32_t o = (uint32_t)(__ffsll((unsigned long long)many) - 1);
+    many &= many - 1;
+    const uint64_t w = lane_u64(v, o);
+    const uint32_t k = lane_u32(at, o) + bits_below(w), i = lane_u32(id, o);
+    if (((w >> lane()) & 1ull) && k < lim) out[k] = (i << 6) + lane();
   }
-  return p;
+  return total;
 }
 
 __device__ __forceinline__ void label_set(uint64_t* words, uint64_t* sum, uint32_t b) {
@@ -389,17 +454,73 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
   return ok;
 }
 
+// The transitions by source, from those by target.
+template <class MaskT, int WG>
+__device__ __forceinline__ void rounds_by_source(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh) {
+  const uint32_t tid = threadIdx.x, wid = tid / kWave, n = a.n;
+  for (uint32_t s = tid; s < n; s += WG) a.out_cur[s] = 0;
+  __syncthreads();
+  for (uint32_t pass = 0; pass < 2; ++pass) {  // count, then place
+    // every in-transition of the states, a wave's 64 states at a time
+    for (uint32_t t0 = wid * kWave; t0 < n; t0 += WG) {
+      const uint32_t t = t0 + lane();
+      const uint32_t beg = t < n ? a.in_ptr[t] : 0u, deg = t < n ? a.in_ptr[t + 1] - beg : 0u;
+      const uint32_t incl = wave_incl_scan_u32(deg), total = lane_u32(incl, kWave - 1);
+      for (uint32_t e0 = 0; e0 < total; e0 += kWave) {
+        const uint32_t x = min(e0 + lane(), total - 1);
+        const uint32_t o = wave_owner(incl, x);
+        const uint32_t b = (uint32_t)__shfl((int)beg, (int)o, kWave);
+        const uint32_t y = (uint32_t)__shfl((int)(incl - deg), (int)o, kWave);
+        if (e0 + lane() >= total) continue;
+        const uint32_t e = b + (x - y);
+        const uint32_t q = atomicAdd(&a.out_cur[(uint32_t)a.in_src[e] - a.s0], 1u);
+        if (pass) {
+          a.out_dst[q] = (int32_t)(t0 + o + a.s0);
+          a.out_ord[q] = a.in_ord[e];
+        }
+      }
+    }
+    __syncthreads();
+    if (pass) break;
+    const uint32_t per = (n + WG - 1) / WG;
+    const uint32_t lo = min(n, tid * per), hi = min(n, lo + per);
+    uint32_t sum = 0;
+    for (uint32_t s = lo; s < hi; ++s) sum += a.out_cur[s];
+    const uint32_t incl = wave_incl_scan_u32(sum);
+    if (lane() == kWave - 1) sh.wsum[wid] = incl;
+    __syncthreads();
+    uint32_t run = incl - sum;
+    for (uint32_t q = 0; q < wid; ++q) run += sh.wsum[q];
+    for (uint32_t s = lo; s < hi; ++s) {
+      const uint32_t c = a.out_cur[s];
+      a.out_ptr[s] = run;
+      a.out_cur[s] = run;
+      run += c;
+    }
+    if (tid == WG - 1) a.out_ptr[n] = run;
+    __syncthreads();
+  }
+  for (uint32_t s = tid; s < n; s += WG) a.out_cur[s] = 0;
+  __syncthreads();
+}
+
 // kBm: the bitmaps live in LDS during the loop (loaded from and stored back
 // to the global ones); else they stay in global memory.
-template <class MaskT, int WG, bool kBm>
+// kMode: kPlain without tracked labels, kTracking with them, kEither the two in
+// one (the batched kernel, whose registers do not hold two loops).
+constexpr int kPlain = 0, kTracking = 1, kEither = 2;
+template <class MaskT, int WG, bool kBm, int kMode>
 __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, RoundsShared<WG>& sh,
                                                 char* lds, uint32_t lds_bytes, uint32_t it0,
-                                                const RoundsResume& resume, uint32_t& grid_C,
-                                                RoundsWork& work) {
+                                                const RoundsResume& resume, uint32_t& grid_C) {
   constexpr uint32_t kWaves = WG / kWave;
   const uint32_t tid = threadIdx.x, wid = uniform_u32(tid / kWave);
   const uint32_t n = a.n, s0 = a.s0;
   const uint32_t nw = (n + 63u) >> 6, nsw = (nw + 63u) >> 6;
+  // one lane adds v to a total
+  const auto count = [&](bool lead, int total, uint32_t v) {
+    if (kMode == kEither && lead) atomicAdd(&sh.work[total], (unsigned long long)v);
+  };
 
   // ---- LDS: bitmaps, then the region of the table (and of the splits)
   uint64_t *U = a.ub, *Q = a.qb, *US = a.us, *QS = a.qs;
@@ -421,9 +542,23 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       QS[q] = a.qs[q];
     }
   }
+  // labels x and y join U and Q (one after the other where the registers for
+  // eight addresses are not there)
+  const auto set2 = [&](uint32_t x, uint32_t y) {
+    if (kBm || kMode != kEither) {
+      label_set2(U, US, Q, QS, x, y);
+    } else {
+      label_set(U, US, x);
+      label_set(U, US, y);
+      label_set(Q, QS, x);
+      label_set(Q, QS, y);
+    }
+  };
   // split tables (LDS that does not hold them: the global path), then the table
   constexpr uint32_t kSmall = small_split<WG>(), kB = 2u * kSmall, kBShift = 32 - log2_u32(kB);
-  constexpr uint32_t EU = edges_per_thread<WG>();
+  constexpr uint32_t kOutU = out_u<MaskT, kMode, kBm>();
+  constexpr uint32_t EU = edges_per_thread<WG>(), kChunks = EU * WG / kWave;
+  static_assert(kChunks <= kWave && kWaves >= 2, "one chunk of transitions per lane");
   const bool small_ok = split_bytes<WG>() + table_bytes<MaskT>(256) <= rbytes;
   MaskT* b_or = reinterpret_cast<MaskT*>(region);  // 8 bytes each are set aside
   MaskT* b_and = b_or + kB;
@@ -452,24 +587,30 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       b_and[q] = ~(MaskT)0;
     }
   }
-  bool track = a.out_ptr && small_ok && kTrackBytes + table_bytes<MaskT>(1024) <= rbytes;
-  const uint32_t track_edges =
-      (uint64_t)n * sizeof(MaskT) <= rbytes - (track ? kTrackBytes : 0u) ? kTrackEdgesDense
-                                                                        : kTrackEdges;
-  if (track && track_edges == kTrackEdgesDense) {
-    // blocks only shrink: no tracking if none is large enough at the start
+  const bool can_track = a.out_ptr && small_ok && kTrackBytes + table_bytes<MaskT>(1024) <= rbytes;
+  const bool track_dense = can_track && (uint64_t)n * sizeof(MaskT) <= rbytes - kTrackBytes;
+  const uint32_t track_edges = track_dense ? kTrackEdgesDense : kTrackEdges;
+  // is some block large enough to be tracked?  (Blocks only shrink.)
+  const auto any_large = [&]() {
     uint32_t most = 0;
     for (uint32_t b = tid; b < n; b += WG)
       if ((uint32_t)a.blk[b] == b) most = max(most, (uint32_t)(a.be[b] - a.bs[b]));
-    if (tid == 0) sh.nc = 0;
+    if (tid == 0) sh.most = 0;
     __syncthreads();
-    atomicMax(&sh.nc, most);
+    atomicMax(&sh.most, most);
     __syncthreads();
-    track = (uint64_t)sh.nc * a.mean_deg >= track_edges;
-    __syncthreads();
+    return (uint64_t)uniform_u32(sh.most) * a.mean_deg >= track_edges;
+  };
+  bool track = kMode == kEither ? can_track && !track_dense : kMode == kTracking;
+  // mark words beyond LDS: a whole block costs tens of us, so tracking starts
+  // at once, unless the transitions by source would have to be laid out for it
+  if (kMode == kPlain && can_track && !track_dense && !a.out_cur && resume.may_track) {
+    if (tid == 0) sh.it = it0;
+    return kRoundsTrack;
   }
+  if (kMode == kTracking && resume.lay_out) rounds_by_source(a, sh);
   uint32_t* lost = reinterpret_cast<uint32_t*>(region);  // [kTracked][kLost]
-  if (track) {
+  if (kMode == kEither ? can_track : track) {
     region += kTrackBytes;
     rbytes -= kTrackBytes;
     const bool load = a.trk_save && resume.label != kNone;
@@ -520,172 +661,243 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         track_lost(sh.fent - 1, resume.label, (uint32_t)a.ss[i]);
   }
   bool dirty = true;  // the region does not hold an empty table (workgroup-uniform)
+  bool start = true;  // before the first round
   uint32_t rc = kRoundsDone;
   // candidates of the next round: after a split the next one is a few labels
   // away (the mean gap is 4-12 iterations), so the rest would be marked for
   // nothing; a round without a split is followed by a full one
   uint32_t want = kCand;
 
-  for (;;) {
-    __syncthreads();
-    // ---- the next candidates: the smallest labels of Q, their ranges
-    if (wid == 0) {
-      // lane j: the j-th word of Q that is not 0, then the j-th label
-      uint32_t nword = 0, word = 0;
-      for (uint32_t q0 = 0; q0 < nsw && nword < want; q0 += kWave) {
-        const uint32_t q = q0 + lane();
-        const uint64_t sv = q < nsw ? QS[q] : 0ull;
-        if (__ballot(sv != 0) == 0) continue;
-        const uint32_t pc = (uint32_t)__popcll(sv);
-        const uint32_t incl = wave_incl_scan_u32(pc);
-        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
-        const uint32_t j = lane() - nword;
-        const uint32_t o = wave_owner(incl, min(j, total - 1));
-        const uint64_t v = (uint64_t)__shfl((unsigned long long)sv, (int)o, kWave);
-        const uint32_t before = (uint32_t)__shfl((int)(incl - pc), (int)o, kWave);
-        if (lane() >= nword && j < total) word = ((q0 + o) << 6) + select_bit(v, j - before);
-        nword += total;
+  // ---- the next candidates, by the last wave (the first ones are busy with
+  // the split that may still be under way): the smallest labels of Q ...
+  const auto collect_labels = [&]() {
+    uint32_t nword = 0;
+    for (uint32_t q0 = 0; q0 < nsw && nword < want; q0 += kWave) {
+      const uint32_t q = q0 + lane();
+      const uint64_t sv = q < nsw ? QS[q] : 0ull;
+      if (__ballot(sv != 0) == 0) continue;
+      nword += expand_bits(sv, q, sh.wl + nword, want - nword);
+    }
+    nword = min(nword, want);
+    wave_sync();
+    const uint32_t word = lane() < nword ? sh.wl[lane()] : 0u;
+    const uint64_t v = lane() < nword ? Q[word] : 0ull;
+    return min(expand_bits(v, word, sh.cand, want), want);
+  };
+  // ... and their ranges
+  const auto collect_ranges = [&](uint32_t nc) {
+    if (lane() < kWaves) sh.cstarts[lane()] = 0;
+    wave_sync();
+    uint32_t lo = 0, sz = 0, te = 0;
+    if (lane() < nc) {
+      const uint32_t C = sh.cand[lane()];
+      if (track) te = a.trk[C];
+      lo = (uint32_t)a.bs[C];
+      sz = (uint32_t)a.be[C] - lo;
+      if (lo > n || sz > n - lo) {  // never expected: report, visit nothing
+        sh.bad = 1;
+        lo = 0;
+        sz = 0;
       }
-      uint32_t nc = 0, C = 0;
-      {
-        const uint64_t v = lane() < min(nword, want) ? Q[word] : 0ull;
-        const uint32_t pc = (uint32_t)__popcll(v);
-        const uint32_t incl = wave_incl_scan_u32(pc);
-        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
-        nc = min(total, want);
-        const uint32_t o = wave_owner(incl, min(lane(), total ? total - 1 : 0u));
-        const uint64_t w = (uint64_t)__shfl((unsigned long long)v, (int)o, kWave);
-        const uint32_t before = (uint32_t)__shfl((int)(incl - pc), (int)o, kWave);
-        const uint32_t cw = (uint32_t)__shfl((int)word, (int)o, kWave);
-        if (lane() < nc) C = (cw << 6) + select_bit(w, lane() - before);
-      }
-      uint32_t lo = 0, sz = 0, te = 0;
-      if (lane() < nc) {
-        if (track) te = a.trk[C];
-        lo = (uint32_t)a.bs[C];
-        sz = (uint32_t)a.be[C] - lo;
-        if (lo > n || sz > n - lo) {  // never expected: report, visit nothing
-          sh.bad = 1;
-          lo = 0;
-          sz = 0;
-        }
-      }
-      const uint32_t whole = sz;
-      const bool inc = te != 0 && sh.tn[te - 1] < sz;
-      if (inc) sz = sh.tn[te - 1];
-      const uint32_t incs = (uint32_t)__ballot(inc);
-      const uint32_t mi = wave_incl_scan_u32(sz);
-      const uint64_t fit = __ballot(lane() < nc && mi <= (uint32_t)WG);
-      const uint32_t np = (uint32_t)__popcll(fit);  // sizes add up: a prefix of the lanes
-      if (lane() < kCand) {
-        sh.cand[lane()] = C;
-        sh.cb[lane()] = lo;
-        sh.cpre[lane()] = mi - sz;
-        sh.unst[lane()] = 0;
-        sh.ctrk[lane()] = te;
-        sh.cend[lane()] = 0;
-      }
-      if (lane() == 0) {
-        sh.nc = nc;
-        sh.np = np;
-        sh.csz0 = whole;
-        sh.inc = incs;
-      }
-      if (np && lane() == np - 1) sh.mtot = mi;
-    } else if (tid == kWaves * kWave - 1) {
+    }
+    const uint32_t whole = sz;
+    const bool inc = te != 0 && sh.tn[te - 1] < sz;
+    if (inc) sz = sh.tn[te - 1];
+    const uint32_t incs = (uint32_t)__ballot(inc);
+    const uint32_t mi = wave_incl_scan_u32(sz);
+    const uint64_t fit = __ballot(lane() < nc && mi <= (uint32_t)WG);
+    const uint32_t np = (uint32_t)__popcll(fit);  // sizes add up: a prefix of the lanes
+    // the candidates with members, and bit i: member i is the first of one
+    const bool any = lane() < np && sz != 0;
+    const uint64_t some = __ballot(any);
+    const uint32_t r = bits_below(some), m0 = mi - sz;
+    if (any) {
+      sh.rfirst[r] = m0;
+      sh.rb[r] = lo;
+      sh.rc[r] = lane();
+      sh.rtrk[r] = inc ? te : 0u;
+      atomicOr((unsigned long long*)&sh.cstarts[m0 >> 6], 1ull << (m0 & 63));
+    }
+    if (np && lane() == np - 1) sh.rfirst[__popcll(some)] = mi;
+    if (lane() < kCand) {
+      sh.cb[lane()] = lo;
+      sh.cpre[lane()] = mi - sz;
+      sh.unst[lane()] = 0;
+      sh.ctrk[lane()] = te;
+      sh.cbeg[lane()] = 0;
+      sh.cend[lane()] = 0;
+    }
+    if (lane() == 0) {
+      sh.nc = nc;
+      sh.np = np;
+      sh.csz0 = whole;
+      sh.inc = incs;
+    }
+    if (np && lane() == np - 1) sh.mtot = mi;
+  };
+  const auto reset = [&]() {  // the first wave
+    if (tid == 0) {
       sh.nS = sh.nL = sh.nT = 0;
       sh.tctr = 0;
       sh.fent = sh.ffresh = sh.mixed = sh.nself = 0;
     }
-    if (dirty) {
-      for (uint32_t q = tid; q < slots; q += WG) {
-        t_mv[q] = 0;
-        t_key[q] = kNone;
-        t_cnt[q] = 0;
-      }
-      dirty = false;
-    }
+    if (tid < kChunks) sh.starts[tid] = 0;
+  };
+  uint32_t look = 0, nbig = resume.nbig;
+
+  // a split by the tables in LDS: this thread's split state
+  bool on = false, ok = false;  // there is one; its entries are consistent
+  uint32_t C = 0;               // the splitter
+  uint32_t s = 0, ps = 0, q = 0, at = 0, fi = kNone, other = 0, self = kNone;
+  uint64_t px = 0, pq = 0;
+  bool small = false;  // such a split is under way (workgroup-uniform)
+
+  // One round, up to the moves of a split by the tables in LDS.
+  const auto round = [&]() -> uint32_t {
     __syncthreads();
-    const uint32_t nc = uniform_u32(sh.nc);
-    if (uniform_u32(sh.bad)) {
-      rc = kRoundsBad;
-      break;
+    small = on = ok = false;
+    s = ps = q = at = other = 0;  // (so that no registers hold them meanwhile)
+    px = pq = 0;
+    fi = self = kNone;
+    if (can_track && __builtin_expect(track ? track_dense && ++look == kTrackLook
+                                            : nbig >= kTrackAfter && resume.may_track, 0)) {
+      look = 0;
+      nbig = 0;
+      if (any_large() != track) {
+        if (kMode != kEither) return kRoundsTrack;
+        track = !track;  // (entries that candidates already refer to stay valid)
+      }
     }
-    if (sh.it > a.iter_cap || (sh.it == a.iter_cap && nc)) {
-      rc = kRoundsCap;
-      break;
-    }
-    uint32_t np = uniform_u32(sh.np);
-    const uint32_t mtot = np ? uniform_u32(sh.mtot) : 0u;
+    // (loads that do not wait for one another: each is a trip of 0.06 us)
+    const uint32_t v_nc = sh.nc, v_np = sh.np, v_mtot = sh.mtot, v_inc = sh.inc, v_bad = sh.bad,
+                   v_it = sh.it;
+    const uint64_t v_cs = sh.cstarts[lane() & (kWaves - 1)];
+    const uint32_t nc = uniform_u32(v_nc);
+    uint32_t np = uniform_u32(v_np);
+    const uint32_t mtot = np ? uniform_u32(v_mtot) : 0u;
+    if (uniform_u32(v_bad)) return kRoundsBad;
+    if (v_it > a.iter_cap || (v_it == a.iter_cap && nc)) return kRoundsCap;
     uint32_t E = 0;
     if (np) {
-      // ---- members: one per thread, with its in-transition range
-      uint32_t beg = 0, deg = 0, c = 0;
-      if (tid < mtot) {
-#pragma unroll
-        for (uint32_t step = kCand / 2; step >= 1; step >>= 1)
-          if (c + step < np && sh.cpre[c + step] <= tid) c += step;
-        const uint32_t i = tid - sh.cpre[c];
-        if ((sh.inc >> c) & 1u) {
-          const uint32_t s = lost[(sh.ctrk[c] - 1) * kLost + i];
-          beg = a.in_ptr[s];
-          deg = a.in_ptr[s + 1] - beg;
-        } else {
-          const uint64_t x = a.pin[sh.cb[c] + i];
-          beg = (uint32_t)(x >> 32);
-          deg = (uint32_t)x;
+      // ---- members: one per thread, with its in-transition range; up to a
+      // wave of them need no sums over the workgroup
+      const bool one = mtot <= (uint32_t)kWave;
+      uint32_t beg = 0, deg = 0, c = 0, first = 0, next = 0, incl = 0;
+      uint64_t some = 0;
+      if (wid * kWave < mtot) {  // wave-uniform
+        // the last candidate whose members start at tid or before
+        const uint64_t own = lane_u64(v_cs, wid);
+        uint32_t k = bits_below(own) + (uint32_t)((own >> lane()) & 1ull) - 1u;
+        if (wid) {  // wave-uniform
+          const uint32_t pc = lane() < wid ? (uint32_t)__popcll(v_cs) : 0u;
+          k += lane_u32(wave_incl_scan_u32(pc), kWave - 1);
         }
+        if (tid < mtot) {
+          first = sh.rfirst[k];
+          next = sh.rfirst[k + 1];
+          c = sh.rc[k];
+          const uint32_t base = sh.rb[k], te = sh.rtrk[k];
+          const uint32_t i = tid - first;
+          if (te) {
+            const uint32_t s = lost[(te - 1) * kLost + i];
+            beg = a.in_ptr[s];
+            deg = a.in_ptr[s + 1] - beg;
+          } else {
+            const uint64_t x = a.pin[base + i];
+            beg = (uint32_t)(x >> 32);
+            deg = (uint32_t)x;
+          }
+        }
+        incl = wave_incl_scan_u32(deg);
+        some = __ballot(deg != 0);
       }
-      const uint32_t incl = wave_incl_scan_u32(deg);
-      if (lane() == kWave - 1) sh.wsum[wid] = incl;
-      __syncthreads();
-      uint32_t before = lane() < kWaves ? sh.wsum[lane()] : 0u;
-      before = wave_incl_scan_u32(lane() < wid ? before : 0u);
-      before = (uint32_t)__shfl((int)before, kWave - 1, kWave);
+      uint32_t before = 0, sbefore = 0;
+      if (!one) {
+        if (lane() == kWave - 1) {
+          sh.wsum[wid] = incl;
+          sh.wnz[wid] = (uint32_t)__popcll(some);
+        }
+        __syncthreads();
+        const bool lower = lane() < wid;
+        const uint32_t ws = lower ? sh.wsum[lane()] : 0u, wz = lower ? sh.wnz[lane()] : 0u;
+        before = lane_u32(wave_incl_scan_u32(ws), kWave - 1);
+        sbefore = lane_u32(wave_incl_scan_u32(wz), kWave - 1);
+      }
       if (tid < mtot) {
-        sh.mbeg[tid] = beg;
-        sh.mpre[tid] = before + incl - deg;
-        sh.mc[tid] = (uint8_t)c;
-        // the last member of each candidate (a later one's first member
-        // follows, or the members end)
-        if (tid + 1 == mtot || (c + 1 < np && sh.cpre[c + 1] == tid + 1)) sh.cend[c] = before + incl;
+        const uint32_t e0 = before + incl - deg;
+        if (deg) {
+          const uint32_t j = sbefore + bits_below(some);
+          sh.mbeg[j] = beg;
+          sh.mpre[j] = e0;
+          sh.mc[j] = (uint8_t)c;
+          if (e0 < EU * WG)
+            atomicOr((unsigned long long*)&sh.starts[e0 >> 6], 1ull << (e0 & 63));
+        }
+        if (tid == first) sh.cbeg[c] = e0;
+        if (tid + 1 == next) sh.cend[c] = before + incl;
       }
-      if (tid == WG - 1) sh.etot = before + incl;
+      if (tid == (one ? kWave : WG) - 1) sh.etot = before + incl;
       __syncthreads();
       // as many candidates as the table holds (one without members ends at 0)
-      const uint64_t over = __ballot(lane() < np && sh.cend[lane() & (kCand - 1)] > ecap);
-      if (over) np = (uint32_t)(__ffsll((unsigned long long)over) - 1);
-      E = uniform_u32(over ? (np ? sh.mpre[sh.cpre[np]] : 0u) : sh.etot);
+      const uint32_t ce = sh.cend[lane() & (kCand - 1)], etot = sh.etot;
+      const uint64_t over = __ballot(lane() < np && ce > ecap);
+      if (__builtin_expect(over != 0, 0)) {
+        np = (uint32_t)(__ffsll((unsigned long long)over) - 1);
+        const uint64_t part = __ballot(lane() < np && ce != 0);
+        E = part ? lane_u32(ce, 63u - (uint32_t)__builtin_clzll(part)) : 0u;
+      } else {
+        E = uniform_u32(etot);
+      }
       if (tid == 0 && np) {
-        work.members += np < sh.np ? sh.cpre[np] : mtot;
-        work.edges += E;
+        count(true, kWMembers, np < v_np ? sh.cpre[np] : mtot);
+        count(true, kWEdges, E);
       }
     }
     const bool big = np == 0 && nc != 0;
-    uint32_t es[EU], eb[EU], ek[EU], sl[EU], ls[EU], lo[EU], sz[EU];
+    uint32_t es[EU], eb[EU], ek[EU], sl[EU], lo[EU], sz[EU];
+    MaskT mv[EU], lmv[EU];  // a touched state's marks, its leader's
+    bool part[EU];          // it leads a block with untouched members
     uint64_t split = 0;  // candidates that split something
     if (np) {
       // ---- transitions: insert (candidate, source), collect its marks
       uint32_t eo[EU];
-      const uint32_t mtop = mtot > 1 ? 1u << (31 - __clz((int)(mtot - 1))) : 0u;
-#pragma unroll
-      for (uint32_t u = 0; u < EU; ++u) {
-        const uint32_t e = tid + u * WG;
-        sl[u] = kNone;
-        es[u] = kNone;
-        if (e < E) {
-          uint32_t j = 0;
-          for (uint32_t step = mtop; step >= 1; step >>= 1)
-            if (j + step < mtot && sh.mpre[j + step] <= e) j += step;
-          const uint32_t edge = sh.mbeg[j] + (e - sh.mpre[j]);
-          es[u] = (uint32_t)a.in_src[edge] - s0;
-          eo[u] = a.rcpp ? 0u : (uint32_t)a.in_ord[edge];
-          ek[u] = (uint32_t)sh.mc[j] << kKeyBits;
-        }
+      uint64_t st = 0;
+      uint32_t sbefore = 0;
+      if (wid * kWave < E) {  // wave-uniform
+        if (lane() < kChunks) st = sh.starts[lane()];
+        const uint32_t stn = (uint32_t)__popcll(st);
+        sbefore = wave_incl_scan_u32(stn) - stn;
       }
 #pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        const uint32_t e = tid + u * WG, chunk = wid + u * kWaves;
+        sl[u] = kNone;
+        es[u] = kNone;
+        if (chunk * kWave < E) {  // wave-uniform
+          // the last member that starts at e or before
+          const uint64_t own = lane_u64(st, chunk);
+          const uint32_t j = lane_u32(sbefore, chunk) + bits_below(own) +
+                             (uint32_t)((own >> lane()) & 1ull) - 1u;
+          if (e < E) {
+            const uint32_t edge = sh.mbeg[j] + (e - sh.mpre[j]);
+            es[u] = (uint32_t)a.in_src[edge] - s0;
+            eo[u] = a.rcpp ? 0u : (uint32_t)a.in_ord[edge];
+            ek[u] = (uint32_t)sh.mc[j] << kKeyBits;
+          }
+        }
+      }
+      // the range of the block that a source leads, beside its block while the
+      // round is latency-bound (should it lead none, the range is not used)
+      const bool wide = E > (uint32_t)WG;
+#pragma unroll
       for (uint32_t u = 0; u < EU; ++u)
-        if (es[u] != kNone) eb[u] = (uint32_t)a.blk[es[u]];
+        if (es[u] != kNone) {
+          eb[u] = (uint32_t)a.blk[es[u]];
+          if (!wide) {
+            lo[u] = (uint32_t)a.bs[es[u]];
+            sz[u] = (uint32_t)a.be[es[u]];
+          }
+        }
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
         if (es[u] == kNone) continue;
@@ -694,15 +906,23 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         mask_or<MaskT>(&t_mv[slot], (MaskT)1 << (eo[u] & (sizeof(MaskT) * 8 - 1)));
         if (!first) continue;
         sl[u] = slot;
-        work.touched += 1;
         if (eb[u] == es[u]) {
-          lo[u] = (uint32_t)a.bs[es[u]];
-          sz[u] = (uint32_t)a.be[es[u]] - lo[u];
+          if (wide) {
+            lo[u] = (uint32_t)a.bs[es[u]];
+            sz[u] = (uint32_t)a.be[es[u]];
+          }
+          sz[u] -= lo[u];
         }
       }
+      if (kMode == kEither && wid * kWave < E) {  // wave-uniform
+        uint32_t t = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < EU; ++u) t += (uint32_t)__popcll(__ballot(sl[u] != kNone));
+        count(lane() == 0, kWTouched, t);
+      }
       __syncthreads();
-      const uint32_t incs = uniform_u32(sh.inc) & (np < 32 ? (1u << np) - 1u : ~0u);
-      if (incs) {  // workgroup-uniform
+      const uint32_t incs = uniform_u32(v_inc) & (np < 32 ? (1u << np) - 1u : ~0u);
+      if (__builtin_expect(incs != 0, 0)) {  // workgroup-uniform
         // sources of lost states: the marks that no other transition into the
         // block still gives.  Long lists of outgoing transitions are searched
         // by the whole wave, and only until every mark is found again.
@@ -766,20 +986,25 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       // state b); the touched members of a block counted at its leader
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
-        ls[u] = kNone;
-        if (sl[u] == kNone || t_mv[sl[u]] == 0) continue;  // not there, or no mark lost
+        mv[u] = 0;
+        if (sl[u] == kNone) continue;
+        mv[u] = t_mv[sl[u]];
         const uint32_t lead = eb[u] == es[u] ? sl[u]
                                              : table_find(t_key, tmask, tshift, ek[u] | eb[u]);
-        ls[u] = lead;
+        if (mv[u] == 0) continue;  // no mark lost
+        lmv[u] = lead != kNone ? t_mv[lead] : (MaskT)0;
         if (lead != kNone) atomicAdd(&t_cnt[lead], 1u);
-        if (lead == kNone || t_mv[lead] != t_mv[sl[u]]) sh.unst[ek[u] >> kKeyBits] = 1;
+        if (lmv[u] != mv[u]) sh.unst[ek[u] >> kKeyBits] = 1;
       }
       __syncthreads();
       // a touched leader with untouched members
 #pragma unroll
-      for (uint32_t u = 0; u < EU; ++u)
-        if (sl[u] != kNone && eb[u] == es[u] && t_mv[sl[u]] != 0 && t_cnt[sl[u]] != sz[u])
-          sh.unst[ek[u] >> kKeyBits] = 1;
+      for (uint32_t u = 0; u < EU; ++u) {
+        part[u] = false;
+        if (mv[u] == 0 || eb[u] != es[u]) continue;
+        part[u] = t_cnt[sl[u]] != sz[u];
+        if (part[u]) sh.unst[ek[u] >> kKeyBits] = 1;
+      }
       __syncthreads();
       split = __ballot(lane() < np && sh.unst[lane() & (kCand - 1)] != 0);
     }
@@ -787,10 +1012,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     // ---- verdicts, and the iterations that split nothing: every unstable
     // label before the next one without a verdict
     const bool turn = f < np || big;  // the iteration of C is carried out now
-    const uint32_t C = uniform_u32(turn ? sh.cand[f < np ? f : 0] : 0u);
-    if (wid == 0 && ((lane() < np && !((split >> lane()) & 1ull)) || (turn && lane() == (f < np ? f : 0))))
+    C = uniform_u32(turn ? sh.cand[f < np ? f : 0] : 0u);
+    if (wid == kWaves - 1 && ((lane() < np && !((split >> lane()) & 1ull)) || (turn && lane() == (f < np ? f : 0))))
       label_clear(Q, QS, sh.cand[lane()]);
-    if (track && wid == 0) {
+    if (track && wid == kWaves - 1) {
       // a stable label is tracked from now on (its entry, if it has one,
       // starts over); so is the splitter, should its split parts be uniform
       const uint32_t l = lane() & (kCand - 1);
@@ -799,9 +1024,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       uint32_t te = sh.ctrk[l];
       bool fresh = false;
       if (stable || mine) {
-        const bool inc = (sh.inc >> l) & 1u;
+        const bool inc = (v_inc >> l) & 1u;
         if (stable && te) sh.tn[te - 1] = 0;
-        if (!te && (big || (!inc && sh.cend[l] - sh.mpre[sh.cpre[l]] >= track_edges))) {
+        if (!te && (big || (!inc && sh.cend[l] - sh.cbeg[l] >= track_edges))) {
           te = track_new(sh.cand[l]);
           fresh = true;
         }
@@ -819,7 +1044,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     {
       uint32_t taken = 0;
       const uint32_t wend = (limit + 63u) >> 6;
-      for (uint32_t w = tid; w < wend; w += WG) {
+      // (the last wave is at the verdicts: it takes the last words)
+      const uint32_t first = tid < WG - kWave ? WG - kWave - 1 - tid : tid;
+      for (uint32_t w = first; w < wend; w += WG) {
         if (!kBm && !((US[w >> 6] >> (w & 63)) & 1ull)) continue;
         uint64_t v = U[w];
         if (!v) continue;
@@ -833,7 +1060,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       }
       if (taken) atomicAdd(&sh.it, taken);
     }
-    if (nc == 0) break;  // every unstable label had its verdict: the final pass follows
+    if (nc == 0) return kRoundsDone;  // every unstable label had its verdict: the final pass follows
     const auto clear_own = [&]() {  // this thread's slots of the table
       if (np == 0) return;
 #pragma unroll
@@ -847,13 +1074,35 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     if (!turn) {
       clear_own();
       want = kCand;
-      continue;
+      return kRoundsGo;
     }
     want = kCand / 2;
     // the members of the listed blocks that `is_split` says are split off
     const auto members = [&](const auto& is_split) {
       const uint32_t nL = uniform_u32(sh.nL);
-      if (tid == 0) work.listed += nL;
+      count(tid == 0, kWListed, nL);
+      if (nL <= kWaves) {  // a block per wave, if all are small
+        const uint32_t z = lane() < nL ? sh.lsz[lane()] : 0u;
+        if (__ballot(z > kOwnBlock) == 0) {  // workgroup-uniform
+          if (wid < nL) {
+            const uint32_t b = uniform_u32(sh.lb[wid]), l = uniform_u32(sh.llo[wid]);
+            const uint32_t size = lane_u32(z, wid);
+            count(lane() == 0, kWVisits, size);
+            for (uint32_t e0 = 0; e0 < size; e0 += kWave) {
+              const uint32_t e = e0 + lane();
+              uint32_t s = 0;
+              bool sp = false;
+              if (e < size) {
+                s = (uint32_t)a.perm[l + e];
+                sp = is_split(s);
+              }
+              const uint32_t si = list_push(&sh.nS, sp);
+              if (sp) put_split(a, sh, s_mv, kSmall, si, (int32_t)s, (int32_t)b, (MaskT)0);
+            }
+          }
+          return;
+        }
+      }
       for (uint32_t j0 = 0; j0 < nL; j0 += kWave) {
         const uint32_t j = j0 + lane();
         uint32_t b = 0, l = 0, z = 0;
@@ -863,7 +1112,8 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           z = j < kListCap ? sh.lsz[j] : (uint32_t)a.lsz[j];
         }
         const uint32_t incl = wave_incl_scan_u32(z);
-        const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+        const uint32_t total = lane_u32(incl, kWave - 1);
+        count(tid == 0, kWVisits, total);
         for (uint32_t e0 = wid * kWave; e0 < total; e0 += WG) {
           const uint32_t e = e0 + lane();
           const uint32_t ee = min(e, total - 1);
@@ -875,7 +1125,6 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           bool sp = false;
           if (e < total) {
             s = (uint32_t)a.perm[ol + (ee - oi)];
-            work.visits += 1;
             sp = is_split(s);
           }
           const uint32_t si = list_push(&sh.nS, sp);
@@ -883,16 +1132,20 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
       }
     };
-    if (big) {
+    if (__builtin_expect(big, 0)) {
       // ---- a splitter beyond the table: mark words per state
+      ++nbig;
       const uint32_t cb = uniform_u32(sh.cb[0]), csz = uniform_u32(sh.csz0);
       if (!dense && a.grid_edges && (uint64_t)csz * a.mean_deg >= a.grid_edges) {
         grid_C = C;  // its iteration is counted already
-        if (tid == 0 && track && sh.ffresh) a.trk[C] = 0;
-        rc = kRoundsGrid;
-        break;
+        if (track && wid == kWaves - 1) {  // the wave that took the entry
+          wave_sync();
+          if (lane() == 0 && sh.ffresh) a.trk[C] = 0;
+        }
+        if (tid == 0) sh.nbig = nbig;
+        return kRoundsGrid;
       }
-      if (tid == 0) work.members += csz;
+      count(tid == 0, kWMembers, csz);
       if (dense) {
         // mark words of all states in LDS.  Four members per thread are in
         // flight; a member of many in-transitions is the whole wave's.
@@ -927,7 +1180,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
               for (uint32_t e = lane(); e < od; e += kWave)
                 mark((uint32_t)a.in_src[ob + e] - s0, a.rcpp ? 0u : (uint32_t)a.in_ord[ob + e]);
             }
-            work.edges += deg[u];
+            count(deg[u] != 0, kWEdges, deg[u]);
             if (deg[u] > 2 * kWave) deg[u] = 0;
             most = max(most, deg[u]);
           }
@@ -979,8 +1232,8 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
             deg = (uint32_t)x;
           }
           const uint32_t incl = wave_incl_scan_u32(deg);
-          const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
-          work.edges += deg;
+          const uint32_t total = lane_u32(incl, kWave - 1);
+          count(lane() == 0, kWEdges, total);
           for (uint32_t e0 = 0; e0 < total; e0 += kWave * kScanU) {
             uint32_t vs[kScanU], vo[kScanU], vb[kScanU], vl[kScanU], vh[kScanU];
             bool first[kScanU];
@@ -1025,7 +1278,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
         __syncthreads();
         const uint32_t nT = uniform_u32(sh.nT);
-        if (tid == 0) work.touched += nT;
+        count(tid == 0, kWTouched, nT);
         for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG) {
           const uint32_t i = i0 + lane();
           int32_t s = 0, b = 0;
@@ -1038,13 +1291,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           const uint32_t si = list_push(&sh.nS, sp);
           if (sp) put_split(a, sh, s_mv, kSmall, si, s, b, mw[s]);
         }
-        members([&](uint32_t s) { return mw[s] == 0; });
         __syncthreads();
-        for (uint32_t i = tid; i < nT; i += WG) mw[a.ts[i]] = 0;
-      }
-      if (sh.nS == 0) {  // stable: its entry starts over
-        if (tid == 0 && track) sh.tn[sh.fent - 1] = 0;
-        continue;
       }
     } else {
       // ---- the split states of C from the table: touched states that differ
@@ -1052,35 +1299,53 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       // was touched
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
-        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && t_mv[sl[u]] != 0;
-        bool sp = false, part = false;
-        if (mine) {
-          if (es[u] == eb[u]) part = t_cnt[sl[u]] != sz[u];
-          else sp = ls[u] == kNone || t_mv[ls[u]] != t_mv[sl[u]];
-        }
-        const uint32_t si = list_push(&sh.nS, sp);
-        if (sp) put_split(a, sh, s_mv, kSmall, si, (int32_t)es[u], (int32_t)eb[u], t_mv[sl[u]]);
-        const uint32_t li = list_push(&sh.nL, part);
-        if (part) put_block(a, sh, li, eb[u], lo[u], sz[u]);
+        if ((wid + u * kWaves) * kWave >= E) continue;  // wave-uniform
+        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && mv[u] != 0;
+        const bool sp = mine && es[u] != eb[u] && lmv[u] != mv[u];
+        const bool pt = mine && part[u];
+        const uint64_t sbal = __ballot(sp), pbal = __ballot(pt);
+        if ((sbal | pbal) == 0) continue;
+        unsigned long long base = 0;  // both lists by one atomic
+        if (lane() == 0)
+          base = atomicAdd(&sh.nSL, (unsigned long long)__popcll(pbal) << 32 |
+                                        (unsigned long long)__popcll(sbal));
+        base = lane_u64(base, 0);
+        if (sp)
+          put_split(a, sh, s_mv, kSmall, (uint32_t)base + bits_below(sbal), (int32_t)es[u],
+                    (int32_t)eb[u], mv[u]);
+        if (pt) put_block(a, sh, (uint32_t)(base >> 32) + bits_below(pbal), eb[u], lo[u], sz[u]);
       }
       __syncthreads();
-      if (sh.nL) {  // workgroup-uniform
-        members([&](uint32_t s) {
-          const uint32_t x = table_find(t_key, tmask, tshift, (f << kKeyBits) | s);
-          return x == kNone || t_mv[x] == 0;
-        });
-        __syncthreads();
+    }
+    if (sh.nL) {  // workgroup-uniform (none where all states were compared)
+      members([&](uint32_t t) {
+        if (big) return a.mw[t] == 0;
+        const uint32_t x = table_find(t_key, tmask, tshift, (f << kKeyBits) | t);
+        return x == kNone || t_mv[x] == 0;
+      });
+      __syncthreads();
+    }
+    if (__builtin_expect(big, 0)) {
+      if (!dense) {
+        const uint32_t nT = uniform_u32(sh.nT);
+        for (uint32_t i = tid; i < nT; i += WG) a.mw[a.ts[i]] = 0;
       }
+      if (sh.nS == 0) {  // stable: its entry starts over
+        if (tid == 0 && track) sh.tn[sh.fent - 1] = 0;
+        return kRoundsGo;
+      }
+    } else {
       clear_own();
     }
     // ---- split: the split part of each block goes to the tail of its range
     // and takes its smallest member as label; front split states trade places
     // with the staying states of the tail
     const uint32_t nS = uniform_u32(sh.nS);
-    if (tid == 0) work.split += nS;
-    if (nS <= kSmall && small_ok) {
-      uint32_t s = 0, b = 0, ps = 0, blo = 0, bhi = 0, slot = 0, own = 0, r = 0, te = 0, self = 0;
-      const bool on = tid < nS;
+    count(tid == 0, kWSplit, nS);
+    if (__builtin_expect(nS <= kSmall && small_ok, 1)) {
+      uint32_t b = 0, blo = 0, bhi = 0, r = 0, te = 0, slot = 0;
+      on = tid < nS;
+      small = true;
       if (on) {
         s = (uint32_t)sh.ss[tid];
         b = (uint32_t)sh.sb[tid];
@@ -1092,7 +1357,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         slot = table_insert(b_key, kB - 1, kBShift, b, first);
         r = atomicAdd(&b_cnt[slot], 1u);
         atomicMin(&b_nl[slot], s);
-        own = table_insert(s_set, kB - 1, kBShift, s, first);
+        at = slot | table_insert(s_set, kB - 1, kBShift, s, first) << 16;
         if (track) {
           const MaskT mv = s_mv[tid];
           mask_or<MaskT>(&b_or[slot], mv);
@@ -1100,104 +1365,47 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         }
       }
       __syncthreads();
-      uint32_t c = 0, ne = 0, q = 0, nl = 0, fi = kNone, us_ = 0;
-      uint64_t px = 0, pq = 0;
-      bool ok = false;
       if (on) {
-        c = b_cnt[slot];
-        nl = b_nl[slot];
-        ne = bhi - c;
+        const uint32_t c = b_cnt[slot], nl = b_nl[slot], ne = bhi - c;
         q = ne + r;
         ok = bhi <= n && blo < ne && ne < bhi && ps >= blo && ps < bhi;  // else never expected
         if (!ok) {
           sh.bad = 1;
         } else {
-          us_ = (uint32_t)a.perm[q];  // every tail position is examined once
+          other = (uint32_t)a.perm[q];  // every tail position is examined once
           pq = a.pin[q];
           if (ps < ne) {
             px = a.pin[ps];
             fi = atomicAdd(&b_fc[slot], 1u);
           }
           if (r == 0) b_base[slot] = atomicAdd(&sh.tctr, c);
-          if (track && s == nl && b_or[slot] != b_and[slot]) sh.mixed = 1;
-          if (!track) self = 0;
-          else if (b == C) self = atomicAdd(&sh.nself, 1u);
-          else if (te) track_lost(te - 1, b, s);
+          // Algorithm 3 re-marks C (below); it needs a verdict if it changed
+          // (it joins Q as a part then) or a split part is not uniform
+          if (track && s == nl && b_or[slot] != b_and[slot]) {
+            sh.mixed = 1;
+            if (!a.rcpp) label_set(Q, QS, C);
+          }
+          if (track && b == C) self = atomicAdd(&sh.nself, 1u);
+          else if (track && te) track_lost(te - 1, b, s);
           a.blk[s] = (int32_t)nl;
-        }
-      }
-      __syncthreads();
-      if (ok && table_find(s_set, kB - 1, kBShift, us_) == kNone) {
-        const uint32_t x = b_base[slot] + atomicAdd(&b_gc[slot], 1u);
-        if (x < kSmall) {
-          x_u[x] = us_;
-          x_q[x] = q;
-          x_pin[x] = pq;
-        } else {
-          sh.bad = 1;  // never expected
-        }
-      }
-      __syncthreads();
-      if (on) {  // the tables are empty again
-        b_key[slot] = kNone;
-        b_nl[slot] = kNone;
-        b_cnt[slot] = 0;
-        b_fc[slot] = 0;
-        b_gc[slot] = 0;
-        s_set[own] = kNone;
-        if (track) {
-          b_or[slot] = 0;
-          b_and[slot] = ~(MaskT)0;
-        }
-      }
-      // C's own entry: with uniform split parts the partition is stable under
-      // what C was, so its lost states are those of this iteration; else they
-      // join the earlier ones, and an entry taken in this round ends
-      const uint32_t fent = track ? sh.fent : 0u, mixed = sh.mixed, nself = sh.nself;
-      const bool ends = mixed && sh.ffresh;
-      const uint32_t had = mixed ? sh.fold : 0u;
-      if (on && b == C && fent && !ends && had + self < kLost)
-        lost[(fent - 1) * kLost + had + self] = s;
-      if (tid == WG - 1) {
-        if (fent) {
-          sh.tn[fent - 1] = had + nself;
-          if (ends || had + nself > kLost) a.trk[C] = 0;
-        }
-        if (!a.rcpp) {
-          // Algorithm 3 re-marks C; it needs a verdict if it changed (it is in
-          // Q then already) or a split part is not uniform
-          label_set(U, US, C);
-          if (mixed || !track) label_set(Q, QS, C);
-        }
-      }
-      if (ok) {
-        if (fi != kNone) {
-          const uint32_t x = b_base[slot] + fi;
-          const uint32_t v = x_u[x], vq = x_q[x];
-          if (v < n && vq < n) {
-            a.perm[ps] = (int32_t)v;
-            a.pos[v] = (int32_t)ps;
-            a.pin[ps] = x_pin[x];
-            a.perm[vq] = (int32_t)s;
-            a.pos[s] = (int32_t)vq;
-            a.pin[vq] = px;
-          } else {
-            sh.bad = 1;  // never expected
+          if (s == nl) {  // the new leader: one thread per split block
+            a.bs[s] = (int32_t)ne;
+            a.be[s] = (int32_t)bhi;
+            a.be[b] = (int32_t)ne;
+            set2(b, s);
+            count(true, kWBlocks, 1);
           }
         }
-        if (s == nl) {  // the new leader: one thread per split block
-          a.bs[s] = (int32_t)ne;
-          a.be[s] = (int32_t)bhi;
-          a.be[b] = (int32_t)ne;
-          label_set2(U, US, Q, QS, b, s);
-          work.blocks += 1;
-        }
+      }
+      if (tid == WG - 1 && !a.rcpp) {
+        label_set(U, US, C);
+        if (!track) label_set(Q, QS, C);
       }
     } else {
       // more split states: the same through global arrays, and the blocks that
       // split are no longer tracked
       if (tid == WG - 1) {
-        if (!a.rcpp) label_set2(U, US, Q, QS, C, C);
+        if (!a.rcpp) set2(C, C);
         if (track) a.trk[C] = 0;
       }
       const uint64_t epoch = (uint64_t)sh.it << 32;  // this iteration's number
@@ -1264,11 +1472,92 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           a.fc[b] = 0;
           a.gc[b] = 0;
           if (track) a.trk[b] = 0;
-          label_set2(U, US, Q, QS, (uint32_t)b, (uint32_t)s);
-          work.blocks += 1;
+          set2((uint32_t)b, (uint32_t)s);
+          count(true, kWBlocks, 1);
         }
         atomicAnd((unsigned long long*)&a.sf[(uint32_t)s >> 6], ~(1ull << (s & 63)));
       }
+    }
+    return kRoundsGo;
+  };
+
+  for (;;) {
+    if (!start) {
+      rc = round();
+      if (rc != kRoundsGo) break;
+    }
+    start = false;
+    // The candidates of the next round, by the last wave; after a split by the
+    // tables in LDS, whose labels, ranges and tracked entries are final behind
+    // this barrier, beside the moves.
+    __syncthreads();
+    const uint32_t slot = at & 0xFFFFu;  // of the block, and of the state in the set
+    if (small) {
+      if (ok && table_find(s_set, kB - 1, kBShift, other) == kNone) {
+        const uint32_t x = b_base[slot] + atomicAdd(&b_gc[slot], 1u);
+        if (x < kSmall) {
+          x_u[x] = other;
+          x_q[x] = q;
+          x_pin[x] = pq;
+        } else {
+          sh.bad = 1;  // never expected
+        }
+      }
+      // C's own entry: with uniform split parts the partition is stable under
+      // what C was, so its lost states are those of this iteration; else they
+      // join the earlier ones, and an entry taken in this round ends
+      if (track) {
+        const uint32_t fent = sh.fent, mixed = sh.mixed, nself = sh.nself;
+        const bool ends = mixed && sh.ffresh;
+        const uint32_t had = mixed ? sh.fold : 0u;
+        if (self != kNone && fent && !ends && had + self < kLost)
+          lost[(fent - 1) * kLost + had + self] = s;
+        if (tid == WG - 1 && fent) {
+          sh.tn[fent - 1] = had + nself;
+          if (ends || had + nself > kLost) a.trk[C] = 0;
+        }
+      }
+    }
+    uint32_t next_nc = 0;
+    if (wid == kWaves - 1) next_nc = collect_labels();
+    if (small) {
+      __syncthreads();
+      if (on) {  // the tables are empty again
+        b_key[slot] = kNone;
+        b_nl[slot] = kNone;
+        b_cnt[slot] = 0;
+        b_fc[slot] = 0;
+        b_gc[slot] = 0;
+        s_set[at >> 16] = kNone;
+        if (track) {
+          b_or[slot] = 0;
+          b_and[slot] = ~(MaskT)0;
+        }
+      }
+      if (ok && fi != kNone) {
+        const uint32_t x = b_base[slot] + fi;
+        const uint32_t v = x_u[x], vq = x_q[x];
+        if (v < n && vq < n) {
+          a.perm[ps] = (int32_t)v;
+          a.pos[v] = (int32_t)ps;
+          a.pin[ps] = x_pin[x];
+          a.perm[vq] = (int32_t)s;
+          a.pos[s] = (int32_t)vq;
+          a.pin[vq] = px;
+        } else {
+          sh.bad = 1;  // never expected
+        }
+      }
+    }
+    if (wid == kWaves - 1) collect_ranges(next_nc);
+    else if (wid == 0) reset();
+    if (__builtin_expect(dirty, 0)) {
+      for (uint32_t i = tid; i < slots; i += WG) {
+        t_mv[i] = 0;
+        t_key[i] = kNone;
+        t_cnt[i] = 0;
+      }
+      dirty = false;
     }
   }
   __syncthreads();

@@ -114,6 +114,11 @@ TRACKED = {
     "chain": lambda: permuted(gen.chain_tail(40000), 7),
     "fan-out": lambda: permuted(gen.fan_out(9000), 8),
     "planted-2-actions": lambda: gen.planted_quotient(2500, 5.0, 2, seed=9),
+    # tracking starts after some whole blocks were marked: mark words in LDS
+    # (and stops again), and beyond LDS with few transitions
+    "chain-in-lds": lambda: permuted(gen.chain_tail(12000), 11),
+    "uniform-in-lds": lambda: gen.uniform_lts(14000, 5.0, 1, 12),
+    "uniform-few-transitions": lambda: gen.uniform_lts(28000, 2.2, 1, 13),
     # 64-bit marks: the mark words of 20k states do not fit LDS
     "wide-marks": lambda: gen.uniform_zipf(20000, 60000, 40, seed=10),
 }
