@@ -22,7 +22,7 @@ void set_error(const char* fmt, ...) {
 // member lists take: hints, so that a small LTS lives in one chunk.
 static size_t setup_bytes(int64_t n, int64_t m, int64_t K) {
   // (K <= 64: the table takes up to 48 bytes per state)
-  size_t b = (K <= 64 ? 9 : 17) * (size_t)m + 100 * (size_t)n + 8 * (size_t)K + 64 * 256;
+  size_t b = (K <= 64 ? 8 : 17) * (size_t)m + 104 * (size_t)n + 8 * (size_t)K + 64 * 256;
   if (K == 1) b += 4 * (size_t)n;
   if (K > 64) b += 4 * (size_t)m + 64 * (size_t)n;
   return b;

@@ -231,10 +231,12 @@ struct bisim_lts {
   uint32_t* in_ptr = nullptr;    // [n+1] transitions grouped by target
   int32_t* in_src = nullptr;     // [m] source of each grouped transition
   int32_t* in_ord = nullptr;     // [m] its action's rank among the source's actions
-  uint8_t* in_lab8 = nullptr;    // [m] its label mod 8 (block features)
+  uint8_t* in_lab8 = nullptr;    // [m] its label mod 8 (block features), or
+  uint64_t* act_mask = nullptr;  // [n] the set of outgoing actions (at most 64 actions)
   uint32_t* woff = nullptr;      // [n+1] mark-word offsets (only when !uniform)
   int uniform = 1;               // every state has <= 64 actions: word index = state
   uint32_t max_out = 0;          // largest number of outgoing transitions of a state
+  bool max_out_known = true;     // false: counted by the first run that asks
   bool one_pass = false;         // pi_pre and the action ranks came from the one-pass kernels
   uint32_t max_ranks = 0;        // largest number of distinct actions of a state
   uint64_t nwords = 0;

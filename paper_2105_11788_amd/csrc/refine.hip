@@ -366,16 +366,63 @@ __global__ void k_zero_words(uint32_t* p, uint64_t count) {
 // features of the learned splitter policy are sums of these)
 __global__ void k_static_features(uint32_t n, const uint32_t* __restrict__ in_ptr,
                                   const int32_t* __restrict__ in_src,
+                                  const int32_t* __restrict__ in_ord,
                                   const uint8_t* __restrict__ in_lab8,
+                                  const uint64_t* __restrict__ act_mask,
                                   uint32_t* __restrict__ sfeat) {
   for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
     for (uint32_t e = in_ptr[t]; e < in_ptr[t + 1]; ++e) {
-      const uint32_t q = in_lab8[e];
+      uint32_t q = 0;
+      if (act_mask) {  // the label is the rank-th action of the source
+        uint64_t v = act_mask[in_src[e]];
+        for (int32_t r = in_ord[e]; r > 0; --r) v &= v - 1;
+        q = (uint32_t)(__ffsll((unsigned long long)v) - 1) & 7u;
+      } else {
+        q = in_lab8[e];
+      }
       atomicAdd(&sfeat[(size_t)in_src[e] * 16 + q], 1u);
       atomicAdd(&sfeat[(size_t)t * 16 + 8 + q], 1u);
     }
 }
 }  // namespace
+
+namespace {
+__global__ void k_out_degrees(const int32_t* __restrict__ in_src, uint64_t m,
+                              uint32_t* __restrict__ deg) {
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    atomicAdd(&deg[in_src[i]], 1u);
+}
+__global__ void k_max_degree(const uint32_t* __restrict__ deg, uint32_t n, uint32_t* out) {
+  uint32_t v = 0;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (uint64_t)gridDim.x * blockDim.x)
+    v = max(v, deg[i]);
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, kWave));
+  if (lane() == 0) atomicMax(out, v);
+}
+}  // namespace
+
+// the largest out-degree (engines 1 and 2 combine the marks of hubs), where
+// loading did not count it
+static bisim_status know_max_out(bisim_lts* h) {
+  if (h->max_out_known) return BISIM_OK;
+  const size_t n = (size_t)h->n;
+  hipStream_t s = h->stream;
+  uint32_t* deg = nullptr;  // [n], then the maximum
+  BISIM_TRY(dalloc(&deg, n + 1, s));
+  const unsigned g = (unsigned)(h->num_cu > 0 ? h->num_cu : 1) * 8;
+  hipLaunchKernelGGL(k_zero_words, dim3(g), dim3(kT), 0, s, deg, (uint64_t)n + 1);
+  hipLaunchKernelGGL(k_out_degrees, dim3(g), dim3(kT), 0, s, h->in_src, (uint64_t)h->m, deg);
+  hipLaunchKernelGGL(k_max_degree, dim3(g), dim3(kT), 0, s, deg, (uint32_t)n, deg + n);
+  BISIM_TRY_HIP(hipGetLastError());
+  BISIM_TRY_HIP(hipMemcpyAsync(&h->max_out, deg + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+  BISIM_TRY_HIP(hipStreamSynchronize(s));
+  (void)dev_free(deg, s);
+  h->max_out_known = true;
+  return BISIM_OK;
+}
 
 // feature / policy state, allocated on first use
 bisim_status refine_alloc_features(bisim_lts* h) {
@@ -389,7 +436,7 @@ bisim_status refine_alloc_features(bisim_lts* h) {
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
                      h->sfeat, 16 * (uint64_t)n);
   hipLaunchKernelGGL(k_static_features, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
-                     (uint32_t)n, h->in_ptr, h->in_src, h->in_lab8, h->sfeat);
+                     (uint32_t)n, h->in_ptr, h->in_src, h->in_ord, h->in_lab8, h->act_mask, h->sfeat);
   BISIM_TRY_HIP(hipGetLastError());
   BISIM_TRY(dalloc(&h->acc, 17 * n, s));
   BISIM_TRY(dalloc(&h->born, n, s));
@@ -702,6 +749,7 @@ static bisim_status refine_run_impl(bisim_lts* h, int32_t* block_id, bool chosen
     return BISIM_E_UNSUPPORTED;
   }
   if (learned) BISIM_TRY(refine_alloc_features(h));
+  if (engine != 3 && !(engine == 1 && learned && h->grid == 1)) BISIM_TRY(know_max_out(h));
   Args a = make_args(h, (uint32_t)cap, learned, learned);
   a.rcpp = rcpp ? 1u : 0u;
   BISIM_TRY(refine_init(h, a, first, learned, learned, start));
@@ -1000,6 +1048,7 @@ bisim_status bisim_collect_training(bisim_lts* h, int64_t sample_every, int32_t 
                             (int)lds);
   (void)hipGetLastError();
   BISIM_TRY(refine_alloc_features(h));
+  BISIM_TRY(know_max_out(h));
   int64_t cap_it = 3 * (int64_t)h->n - h->pre_blocks + 1;
   if (cap_it < 1) cap_it = 1;
   Args a = make_args(h, (uint32_t)cap_it, false, true);

@@ -376,41 +376,42 @@ __global__ void k_in_scatter(const int32_t* __restrict__ src, const int32_t* __r
 // whose entries keep their smallest state; every state is then compared with
 // its group's leader, so a collision is detected (the rounds run then).
 //
-// Bound by the atomics of the transition pass (three per transition) and, for
-// small LTSs, by the launches.  Load and refinement together: 100 states, 300
+// Bound by the atomics of the transition pass (two per transition) and the
+// scattered writes of the grouping by target, and for small LTSs by the
+// launches.  So the labels are not carried along (the masks are kept, and give
+// the label of a rank), and out-degrees are counted only for a run that asks
+// (2M states, 16.4M transitions: k_m_edges 1.85 -> 1.23 and k_m_scatter 1.84
+// -> 1.45 ms).  Load and refinement together: 100 states, 300
 // transitions 0.72 -> 0.50 ms; signature refinement of 250k states, 2M
-// transitions 12.4 -> 9.2 ms.
+// transitions 12.4 -> 8.3 ms.
 // ---------------------------------------------------------------------------
 struct MaskStats {
   uint32_t err;        // 1: out of range, 2: a collision, 4: a full table (never expected)
   uint32_t max_ranks;  // distinct actions of a state
   uint32_t blocks;
-  uint32_t max_out;
   unsigned long long marks;
 };
 
 __global__ void k_m_zero(int32_t n, uint32_t cap, uint64_t* __restrict__ mask,
-                         uint32_t* __restrict__ indeg, uint32_t* __restrict__ outdeg,
-                         uint32_t* __restrict__ newl, unsigned long long* __restrict__ keys,
+                         uint32_t* __restrict__ indeg, uint32_t* __restrict__ newl, unsigned long long* __restrict__ keys,
                          uint32_t* __restrict__ minst, MaskStats* st) {
   GSTRIDE(s, (int64_t)n) {
     mask[s] = 0;
     indeg[s] = 0;
-    outdeg[s] = 0;
     if (newl) newl[s] = kNone;
   }
   GSTRIDE(q, (int64_t)cap) {
     keys[q] = 0;
     minst[q] = kNone;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *st = MaskStats{0, 0, 0, 0, 0};
+  if (blockIdx.x == 0 && threadIdx.x == 0) *st = MaskStats{0, 0, 0, 0};
 }
 
 __global__ void k_m_edges(const int32_t* __restrict__ src, const int32_t* __restrict__ lab,
                           const int32_t* __restrict__ dst, int64_t m, int32_t n, int32_t K,
                           const int32_t* __restrict__ init, uint64_t* __restrict__ mask,
-                          uint32_t* __restrict__ indeg, uint32_t* __restrict__ outdeg,
-                          uint32_t* __restrict__ newl, MaskStats* st) {
+                          uint32_t* __restrict__ indeg, uint32_t* __restrict__ newl,
+                          MaskStats* st) {
   bool bad = false;
   GSTRIDE(i, m) {
     const uint32_t s = (uint32_t)src[i], d = (uint32_t)dst[i], l = (uint32_t)lab[i];
@@ -419,7 +420,6 @@ __global__ void k_m_edges(const int32_t* __restrict__ src, const int32_t* __rest
       continue;
     }
     atomicOr((unsigned long long*)&mask[s], 1ull << l);
-    atomicAdd(&outdeg[s], 1u);
     atomicAdd(&indeg[d], 1u);
   }
   if (init) {
@@ -492,19 +492,18 @@ __global__ void k_m_group(int32_t n, const int32_t* __restrict__ init,
 __global__ void __launch_bounds__(kT) k_m_label(int32_t n, const int32_t* __restrict__ init,
                                                 const uint32_t* __restrict__ newl,
                                                 const uint64_t* __restrict__ mask,
-                                                const uint32_t* __restrict__ outdeg,
                                                 const uint32_t* __restrict__ minst,
                                                 const uint32_t* __restrict__ slot,
                                                 int32_t* __restrict__ block,
                                                 int32_t* __restrict__ nr_marks,
                                                 int32_t* __restrict__ pi0_out, MaskStats* st) {
-  __shared__ uint32_t sh[3];
+  __shared__ uint32_t sh[2];
   __shared__ unsigned long long shm;
   if (st->err & 5u) return;
-  if (threadIdx.x < 3) sh[threadIdx.x] = 0;
+  if (threadIdx.x < 2) sh[threadIdx.x] = 0;
   if (threadIdx.x == 0) shm = 0;
   __syncthreads();
-  uint32_t mr = 0, nb = 0, mo = 0;
+  uint32_t mr = 0, nb = 0;
   unsigned long long marks = 0;
   bool bad = false;
   GSTRIDE(s, (int64_t)n) {
@@ -518,19 +517,16 @@ __global__ void __launch_bounds__(kT) k_m_label(int32_t n, const int32_t* __rest
     mr = max(mr, c);
     marks += c;
     nb += l == (uint32_t)s;
-    mo = max(mo, outdeg[s]);
   }
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) {
     mr = max(mr, (uint32_t)__shfl_xor((int)mr, d, kWave));
-    mo = max(mo, (uint32_t)__shfl_xor((int)mo, d, kWave));
     nb += (uint32_t)__shfl_xor((int)nb, d, kWave);
     marks += (unsigned long long)__shfl_xor((long long)marks, d, kWave);
   }
   if (lane() == 0) {
     atomicMax(&sh[0], mr);
     atomicAdd(&sh[1], nb);
-    atomicMax(&sh[2], mo);
     atomicAdd(&shm, marks);
   }
   if (bad) atomicOr(&st->err, 2u);
@@ -538,7 +534,6 @@ __global__ void __launch_bounds__(kT) k_m_label(int32_t n, const int32_t* __rest
   if (threadIdx.x == 0) {
     atomicMax(&st->max_ranks, sh[0]);
     atomicAdd(&st->blocks, sh[1]);
-    atomicMax(&st->max_out, sh[2]);
     atomicAdd(&st->marks, shm);
   }
 }
@@ -549,14 +544,13 @@ __global__ void k_m_scatter(const int32_t* __restrict__ src, const int32_t* __re
                             const uint64_t* __restrict__ mask,
                             const uint32_t* __restrict__ in_ptr, uint32_t* __restrict__ indeg,
                             int32_t* __restrict__ in_src, int32_t* __restrict__ in_ord,
-                            uint8_t* __restrict__ in_lab8, const MaskStats* st) {
+                            const MaskStats* st) {
   if (st->err & 5u) return;
   GSTRIDE(i, m) {
     const int32_t d = dst[i], s = src[i], l = lab[i];
     const uint32_t p = in_ptr[d] + atomicSub(&indeg[d], 1u) - 1u;
     in_src[p] = s;
     in_ord[p] = (int32_t)__popcll(mask[s] & ((1ull << l) - 1ull));
-    in_lab8[p] = (uint8_t)(l & 7);
   }
 }
 
@@ -599,19 +593,17 @@ static bisim_status setup_masks(bisim_lts* h, const int32_t* src, const int32_t*
   BISIM_TRY(dalloc(&h->in_ptr, (size_t)n + 1, st));
   BISIM_TRY(dalloc(&h->in_src, (size_t)m, st));
   BISIM_TRY(dalloc(&h->in_ord, (size_t)m, st));
-  BISIM_TRY(dalloc(&h->in_lab8, (size_t)m, st));
+  BISIM_TRY(dalloc(&h->act_mask, (size_t)n, st));
   if (h->K == 1) BISIM_TRY(dalloc(&h->init_block, (size_t)n, st));
   Temps tmp;
   tmp.s = st;
   uint32_t cap = 64;
   while (cap < 2u * (uint32_t)n) cap <<= 1;
-  uint64_t* mask;
-  uint32_t *indeg, *outdeg, *newl = nullptr, *minst, *slot;
+  uint64_t* mask = h->act_mask;
+  uint32_t *indeg, *newl = nullptr, *minst, *slot;
   unsigned long long* keys;
   MaskStats* sd;
-  BISIM_TRY(tmp.get(&mask, (size_t)n));
   BISIM_TRY(tmp.get(&indeg, (size_t)n));
-  BISIM_TRY(tmp.get(&outdeg, (size_t)n));
   if (init) BISIM_TRY(tmp.get(&newl, (size_t)n));
   BISIM_TRY(tmp.get(&keys, (size_t)cap));
   BISIM_TRY(tmp.get(&minst, (size_t)cap));
@@ -622,19 +614,19 @@ static bisim_status setup_masks(bisim_lts* h, const int32_t* src, const int32_t*
   const uint64_t key_mask = (collide && collide[0] == '1') ? 0ull : ~0ull;
   const unsigned gn = grid_for(n, cu);
   hipLaunchKernelGGL(k_m_zero, dim3(grid_for(cap, cu)), dim3(kT), 0, st, n, cap, mask, indeg,
-                     outdeg, newl, keys, minst, sd);
+                     newl, keys, minst, sd);
   hipLaunchKernelGGL(k_m_edges, dim3(grid_for(m > n ? m : n, cu)), dim3(kT), 0, st, src, lab, dst,
-                     m, n, h->K, init, mask, indeg, outdeg, newl, sd);
+                     m, n, h->K, init, mask, indeg, newl, sd);
   hipLaunchKernelGGL(k_m_group, dim3(gn), dim3(kT), 0, st, n, init, newl, mask, keys, minst,
                      cap - 1, slot, key_mask, sd);
   hipLaunchKernelGGL(k_m_label, dim3(gn < (unsigned)cu * 4 ? gn : (unsigned)cu * 4), dim3(kT), 0,
-                     st, n, init, newl, mask, outdeg, minst, slot, h->pre_block, h->nr_marks,
+                     st, n, init, newl, mask, minst, slot, h->pre_block, h->nr_marks,
                      h->init_block, sd);
   BISIM_TRY_HIP(hipGetLastError());
   BISIM_TRY(exclusive_scan_u32(indeg, h->in_ptr, n, st));
   if (m > 0)
     hipLaunchKernelGGL(k_m_scatter, dim3(grid_for(m, cu)), dim3(kT), 0, st, src, lab, dst, m, mask,
-                       h->in_ptr, indeg, h->in_src, h->in_ord, h->in_lab8, sd);
+                       h->in_ptr, indeg, h->in_src, h->in_ord, sd);
   BISIM_TRY_HIP(hipGetLastError());
   MaskStats sh{};
   BISIM_TRY_HIP(hipMemcpyAsync(&sh, sd, sizeof(sh), hipMemcpyDeviceToHost, st));
@@ -645,13 +637,15 @@ static bisim_status setup_masks(bisim_lts* h, const int32_t* src, const int32_t*
     return BISIM_E_RANGE;
   }
   *done = sh.err == 0;
+  if (!*done) h->act_mask = nullptr;  // (its memory goes with the handle's)
   h->one_pass = false;
   h->pre_blocks = sh.blocks;
   h->mark_length = (int64_t)sh.marks;
   h->uniform = 1;
   h->max_ranks = sh.max_ranks;
   h->nwords = (uint64_t)n;
-  h->max_out = sh.max_out;
+  h->max_out = 0;
+  h->max_out_known = !*done;  // (the rounds count it)
   return BISIM_OK;
 }
 
