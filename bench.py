@@ -437,8 +437,9 @@ def run_single(bisim, L, args, engine, mlp=None, trace=True):
         res["phase_ms"], res["phase_samples"] = h.phase_times()
         h.set_option(bisim.OPT_PROFILE_EVERY, 0)
     elif engine == 3:
-        # the timed runs replay captured graphs; kernel durations come from one
-        # more run launched kernel by kernel with end events (~200 sampled
+        # the timed runs go by rounds (one workgroup decides many iterations at
+        # a time); durations of the grid-wide kernels come from one more run in
+        # lock step, launched kernel by kernel with end events (~200 sampled
         # iterations); that run's fixpoint time is reported beside them
         h.set_option(bisim.OPT_PROFILE_EVERY, max(1, st.iterations // 200))
         t1 = time.perf_counter()
@@ -500,9 +501,11 @@ def form_plain(bisim, gen, args):
                                         "samples": int(r["phase_samples"][i])}
                      for i in range(3)}
         per_phase["work_totals"] = r["work_totals"]
-        per_phase["timing"] = ("kernel durations from a run launched kernel by kernel "
-                               f"({r['eager_ms_per_step']:.1f} ms to the fixpoint); the timed "
-                               "runs replay captured graphs of 32 iterations")
+        per_phase["timing"] = ("kernel durations and bytes of the lock-step loop, from a run "
+                               f"launched kernel by kernel ({r['eager_ms_per_step']:.1f} ms to "
+                               "the fixpoint); the timed runs go by rounds: one workgroup "
+                               "(k_rounds), bound by its chain of dependent steps, and the "
+                               "grid-wide kernels for large splitters only")
     elif eng == 1:
         pb = phase_bytes(L.n, r["work"], r["nsplit"])
         mb = method_bytes(L.n, L.m, st.mark_length, r["work"], r["nsplit"])
@@ -700,7 +703,8 @@ def form_batched(bisim, gen, args):
                     "bytes_definition": "bytes the batched kernel moves per launch: the byte "
                                         "model of its global loads, stores and atomics "
                                         "(bench.py batch_bytes) times its work totals per "
-                                        "tier; LDS-resident state counts nothing",
+                                        "tier (splitters marked, also those decided ahead of "
+                                        "their turn); LDS-resident state counts nothing",
                     "kernel_ms": kern_ms,
                     "measured_copy_GBs": copy_gbs,
                     "work_totals": {"lds_tier": st["work"][0], "member_list_tier": st["work"][1]},

@@ -146,9 +146,11 @@ const char* bisim_last_error(void);
  * bisim_set_option — per-handle settings.
  *   BISIM_OPT_ENGINE        0 = automatic (default: engine 3 for Algorithm 3
  *                           with the plain policy, and for Algorithm 2 up to
- *                           16,384 states; engine 2 for the learned policy,
- *                           traced, profiled or limited runs and states of
- *                           more than 64 distinct actions; from 200,000 states
+ *                           16,384 states; for the learned policy engine 1
+ *                           with one workgroup up to 2,048 states (arrays in
+ *                           LDS) and engine 2 above; engine 2 for traced,
+ *                           profiled or limited runs and states of more than
+ *                           64 distinct actions; from 200,000 states
  *                           on, engine 3's grid is timed on the LTS's first
  *                           iterations once per device and size class and
  *                           cached in the file BISIM_TUNE_CACHE, else
@@ -168,7 +170,7 @@ const char* bisim_last_error(void);
  *                           with the plain policy only (else
  *                           BISIM_E_UNSUPPORTED at coarsest_partition); about
  *                           96 more bytes of device memory per state and, from
- *                           8,192 transitions on, 8 per transition, allocated
+ *                           1,536 transitions on, 8 per transition, allocated
  *                           on first use.
  *   BISIM_OPT_COUNT_WORK    0 (default) or 1: engine 3 accumulates work totals
  *                           over the run (bisim_get_work).

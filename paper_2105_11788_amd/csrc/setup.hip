@@ -382,7 +382,7 @@ __global__ void k_in_scatter(const int32_t* __restrict__ src, const int32_t* __r
 // the label of a rank), and out-degrees are counted only for a run that asks
 // (2M states, 16.4M transitions: k_m_edges 1.85 -> 1.23 and k_m_scatter 1.84
 // -> 1.45 ms).  Load and refinement together: 100 states, 300
-// transitions 0.72 -> 0.50 ms; signature refinement of 250k states, 2M
+// transitions 0.72 -> 0.50 ms; signature refinement of 2M states, 16.4M
 // transitions 12.4 -> 8.3 ms.
 // ---------------------------------------------------------------------------
 struct MaskStats {
