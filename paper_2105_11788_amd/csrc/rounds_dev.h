@@ -701,7 +701,8 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       }
     }
     const uint32_t whole = sz;
-    const bool inc = te != 0 && sh.tn[te - 1] < sz;
+    // (a longer list ends the tracking; never read past it all the same)
+    const bool inc = te != 0 && sh.tn[te - 1] < min(sz, kLost + 1);
     if (inc) sz = sh.tn[te - 1];
     const uint32_t incs = (uint32_t)__ballot(inc);
     const uint32_t mi = wave_incl_scan_u32(sz);
@@ -1031,7 +1032,11 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           fresh = true;
         }
       }
+      // A lane above may have been given the splitter's own entry: it is that
+      // label's now, and the splitter has none.
+      wave_sync();
       if (mine) {
+        if (te && sh.tlabel[te - 1] != C) te = 0;
         sh.fent = te;
         sh.ffresh = fresh;
         sh.fold = te && !fresh ? sh.tn[te - 1] : 0u;

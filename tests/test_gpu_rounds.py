@@ -141,6 +141,30 @@ def test_rounds_track_large_splitters(B, case):
     assert got[0][2] == nb
 
 
+# more blocks of hundreds of in-transitions than labels are tracked at a time
+MANY_LARGE = {
+    "propositions": lambda: gen.random_lts(50000, 200000, 2, 21, init_blocks=150),
+    "propositions-wide-marks": lambda: gen.random_lts(40000, 160000, 40, 22, init_blocks=100),
+    "product": lambda: permuted(gen.sync_product(4, 14, seed=23), 24),
+}
+
+
+@pytest.mark.parametrize("case", sorted(MANY_LARGE))
+def test_rounds_reuse_tracked_entries(B, case):
+    """The entries of tracked labels turn over while their labels split; the
+    lock-step engine gives the iteration count."""
+    L = MANY_LARGE[case]()
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst, L.init)
+    ref, _ = run(B, L, 2)
+    got, _ = run(B, L, 3)
+    with B.Batch([L]) as b:
+        out, its, _ = b.run()
+        batched = b.split(out.numpy())[0]
+    for blk, n_it in [(x, i) for x, i, _ in got] + [(batched, its[0])]:
+        assert (blk == ks).all() and n_it == ref[0][1]
+    assert got[0][2] == nb
+
+
 @pytest.mark.parametrize("seed", [1, 2])
 def test_rounds_algorithm2(B, seed):
     check(B, gen.kripke_uniform(1000, 5000, seed=seed), algorithm=2, engines=(0,))

@@ -1,0 +1,88 @@
+"""The rounds of one workgroup (rounds_dev.h), compiled for the host and run
+lane by lane against the lock-step oracle.  Constants are lowered so that the
+borders they draw lie within small LTSs; whole numbers, no tolerance."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2105_11788_amd import gen
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2105_11788_amd", "csrc")
+P = ctypes.c_void_p
+
+
+class Run(ctypes.Structure):
+    _fields_ = [("n", ctypes.c_int32), ("m", ctypes.c_int32), ("K", ctypes.c_int32),
+                ("start", P), ("in_ptr", P), ("in_src", P), ("in_ord", P),
+                ("out_ptr", P), ("out_dst", P), ("out_ord", P),
+                ("rcpp", ctypes.c_int32), ("lds_bytes", ctypes.c_int32),
+                ("bitmaps_in_lds", ctypes.c_int32), ("either", ctypes.c_int32),
+                ("seed", ctypes.c_uint32), ("block", P), ("iterations", P)]
+
+
+def compiled(folder, constants):
+    """The model with some of the header's constants replaced."""
+    text = open(os.path.join(CSRC, "rounds_dev.h")).read()
+    for name, (was, now) in constants.items():
+        assert text.count(f"{name} = {was}") == 1, name
+        text = text.replace(f"{name} = {was}", f"{name} = {now}")
+    open(os.path.join(folder, "rounds_dev.h"), "w").write(text)
+    for f in ("internal.h", "rounds_model.cpp"):
+        shutil.copy(os.path.join(HERE, "host_model", f), folder)
+    so = os.path.join(folder, "model.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-w",
+                           "-I", str(folder), os.path.join(folder, "rounds_model.cpp"), "-o", so])
+    return ctypes.CDLL(so)
+
+
+def run(lib, L, lds=60000, either=False, track=True, bitmaps=True, seed=1):
+    pre = oracle.preprocess(L.n, L.K, L.src, L.lab, L.dst, L.init)
+
+    def grouped(by, other):
+        order = np.argsort(pre[by], kind="stable")
+        ptr = np.searchsorted(pre[by][order], np.arange(L.n + 1)).astype(np.uint32)
+        return [ptr] + [np.ascontiguousarray(pre[x][order]) for x in (other, "order")]
+
+    arrays = ([pre["pre_block"].copy()] + grouped("s_dst", "s_src") + grouped("s_src", "s_dst"))
+    block, its = np.empty(L.n, np.int32), np.zeros(1, np.int64)
+    p = [a.ctypes.data_as(P) for a in arrays]
+    if not track:
+        p[4:] = [None] * 3
+    r = Run(L.n, L.m, L.K, *p, 0, lds, bitmaps, either, seed,
+            block.ctypes.data_as(P), its.ctypes.data_as(P))
+    assert lib.model_run(ctypes.byref(r)) == 0
+    return block, int(its[0])
+
+
+def check(lib, L, **options):
+    ref = oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst, L.init)
+    block, its = run(lib, L, **options)
+    assert (block == ref["block"]).all() and its == ref["iters"], (L.name, options, its,
+                                                                   ref["iters"])
+
+
+@pytest.fixture(scope="module")
+def few_entries(tmp_path_factory):
+    """As many tracked labels as candidates, tracked from the first round and
+    from few transitions on, so that entries turn over all the time."""
+    return compiled(tmp_path_factory.mktemp("few"), {
+        "kCand": ("32", "8"), "kTracked": ("64", "8"), "kTrackEdges": ("384", "3"),
+        "kTrackEdgesDense": ("1536", "3"), "kTrackAfter": ("8", "0")})
+
+
+# schedules of the lanes under which the splitter's lost states were written
+# into the label that had been given its entry (other iteration counts)
+@pytest.mark.parametrize("either,lds,seed", [
+    (True, 29000, 759097991), (True, 29000, 801935232), (True, 29000, 718905886),
+    (True, 33000, 422976252), (True, 33000, 220949275), (True, 33000, 848167431),
+    (True, 60000, 669684967), (True, 60000, 373683345),
+    (False, 29000, 320150180), (False, 60000, 758017750), (False, 60000, 21045789)])
+def test_tracked_entry_of_the_splitter_is_taken(few_entries, either, lds, seed):
+    """A stable label can be given the entry of the splitter of the same round."""
+    check(few_entries, gen.sync_product(3, 8, seed=826946041), lds=lds, either=either, seed=seed)
