@@ -623,7 +623,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
   }
   uint32_t lg = 0;  // log2 of the table's slots; none below 32
   while ((2u << lg) <= 2 * EU * WG && table_bytes<MaskT>(2u << lg) <= rbytes) ++lg;
-  const uint32_t slots = lg >= 5 ? 1u << lg : 0u;
+  // more states than a key has bits for (in a batch): no table, so every
+  // splitter with in-transitions is marked by words per state
+  const uint32_t slots = lg >= 5 && n <= kRoundsMaxN ? 1u << lg : 0u;
   const uint32_t tmask = slots - 1, tshift = 32 - lg;
   const uint32_t ecap = slots / 2;
   MaskT* t_mv = reinterpret_cast<MaskT*>(region);

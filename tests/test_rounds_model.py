@@ -86,3 +86,18 @@ def few_entries(tmp_path_factory):
 def test_tracked_entry_of_the_splitter_is_taken(few_entries, either, lds, seed):
     """A stable label can be given the entry of the splitter of the same round."""
     check(few_entries, gen.sync_product(3, 8, seed=826946041), lds=lds, either=either, seed=seed)
+
+
+@pytest.fixture(scope="module")
+def short_keys(tmp_path_factory):
+    """Table keys with 6 bits for the state: 63 states at most have them."""
+    return compiled(tmp_path_factory.mktemp("keys"), {"kKeyBits": ("27", "6")})
+
+
+@pytest.mark.parametrize("track", [False, True])
+@pytest.mark.parametrize("n", [62, 63, 64, 65, 200])
+def test_more_states_than_table_keys(short_keys, n, track):
+    """A batch takes instances of more states than a table key has bits for."""
+    for seed in range(3):
+        L = gen.random_lts(n, 3 * n, 2, seed, init_blocks=3)
+        check(short_keys, L, either=True, track=track, seed=seed)
