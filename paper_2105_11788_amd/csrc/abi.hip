@@ -17,20 +17,21 @@ void set_error(const char* fmt, ...) {
   va_end(ap);
 }
 
-// What loading takes of the handle's memory, temporaries included (the one-pass
-// preprocessing of many actions among them), and what the run state and the
-// member lists take: hints, so that a small LTS lives in one chunk.
-static size_t setup_bytes(int64_t n, int64_t m, int64_t K) {
-  // (K <= 64: the table takes up to 48 bytes per state)
-  size_t b = (K <= 64 ? 8 : 17) * (size_t)m + 104 * (size_t)n + 8 * (size_t)K + 64 * 256;
-  if (K == 1) b += 4 * (size_t)n;
-  if (K > 64) b += 4 * (size_t)m + 64 * (size_t)n;
-  return b;
-}
-static size_t run_bytes(int64_t n, int64_t m) {
-  size_t b = 150 * (size_t)n + 96 * 256;
-  if (m >= 1024) b += 8 * (size_t)m;
-  return b;
+// What a handle's memory has to hold, as hints, so that a small LTS lives in
+// one chunk: what loading leaves; its temporaries (with at most 64 actions a
+// table of up to 48 bytes per state, else those of the one-pass
+// preprocessing); and what takes their place later: the run state and the
+// member lists, or for a batch the transitions by source.  Temporaries that
+// are larger than that by more than kTempsApart take memory of their own,
+// which loading returns (another chunk is 75 us).
+constexpr size_t kTempsApart = 4u << 20;
+static void reserve_handle(bisim_lts* h, bool with_run_state) {
+  const size_t n = (size_t)h->n, m = (size_t)h->m, k = (size_t)h->K;
+  const size_t keep = (h->K <= 64 ? 8 : 9) * m + 24 * n + 96 * 256;
+  const size_t temps = h->K <= 64 ? 64 * n : 12 * m + 104 * n + 12 * k;
+  const size_t run = (m >= 1024 ? 8 * m : 0) + (with_run_state ? 150 : 8) * n;
+  h->temps_apart = temps > run + kTempsApart ? temps : 0;
+  h->mem.reserve(keep + (temps < run || h->temps_apart ? run : temps), h->stream);
 }
 
 static void free_handle(bisim_lts* h) {
@@ -79,9 +80,7 @@ bisim_status load_into(bisim_lts* h, const int32_t* src, const int32_t* label,
     return BISIM_E_DEVICE;
   }
   ChunkScope scope(h->mem);  // (an open ArenaScope comes first)
-  if (!arena_active())
-    h->mem.reserve(setup_bytes(h->n, h->m, h->K) + (with_run_state ? run_bytes(h->n, h->m) : 0),
-                   h->stream);
+  if (!arena_active()) reserve_handle(h, with_run_state);
   BISIM_TRY_HIP(hipEventRecord(h->ev0, h->stream));
   BISIM_TRY(setup_load(h, src, label, dst, init_partition));
   if (with_run_state) BISIM_TRY(refine_alloc(h));

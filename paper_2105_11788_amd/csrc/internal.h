@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "bisim.h"
+#include "pieces.h"
 
 namespace bisim {
 
@@ -40,8 +41,8 @@ void set_error(const char* fmt, ...);
 // memory (hipMallocAsync), or, while an ArenaScope is open on the calling
 // thread, a 256-byte aligned piece of the scope's region (bump allocation,
 // nothing is returned before the scope closes), or, while a ChunkScope is
-// open, a piece of a handle's chunks; dev_free releases the first and ignores
-// the others (a chunk's last piece is taken back).
+// open, a piece of a handle's chunks; dev_free releases the first, ignores the
+// second and gives the piece back to its chunk.
 // ---------------------------------------------------------------------------
 hipError_t dev_alloc(void** p, size_t bytes, hipStream_t s);
 hipError_t dev_free(void* p, hipStream_t s);
@@ -54,20 +55,22 @@ hipError_t dev_free(void* p, hipStream_t s);
 // as the handle is.
 class Chunks {
  public:
-  // the next `bytes` bytes come from one chunk; without effect if no memory is
-  // left (requests are then allocated one by one)
+  // a chunk with room for `bytes` more; without effect if no memory is left
+  // (requests are then allocated one by one)
   void reserve(size_t bytes, hipStream_t s);
   hipError_t alloc(void** p, size_t bytes, hipStream_t s);
-  bool holds(const void* p) const;
-  void take_back(const void* p);
+  // false if p is not of these chunks
+  bool give_back(const void* p);
   void release(hipStream_t s);
 
  private:
   struct Chunk {
     char* base;
-    size_t cap, used, last;  // last: start of the most recent piece
+    size_t capacity;
+    Pieces pieces;
   };
   hipError_t add(size_t bytes, hipStream_t s);
+  bool cut(void** p, size_t need);
   std::vector<Chunk> chunks_;
 };
 class ChunkScope {
@@ -206,6 +209,7 @@ struct bisim_lists {
   // rounds: transitions by source, tracked labels
   uint32_t* out_ptr = nullptr;
   int32_t *out_dst = nullptr, *out_ord = nullptr;
+  bool out_laid = false;  // by by_source (else the rounds lay them out themselves)
   uint8_t* trk = nullptr;
   uint32_t* trk_save = nullptr;
   // the captured graph of a chunk of iterations and the arguments it holds
@@ -217,6 +221,7 @@ struct bisim_lists {
 
 struct bisim_lts {
   bisim::Chunks mem;  // every device buffer of the handle
+  size_t temps_apart = 0;  // bytes of loading's temporaries, if not cut from mem
   int32_t n = 0;
   int64_t m = 0;
   int32_t K = 1;

@@ -1016,7 +1016,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
 // The transitions by source (target and action rank), from those by target.
 bisim_status by_source(bisim_lts* h) {
   bisim_lists& L = h->lists;
-  if (L.out_ord) return BISIM_OK;  // the last one to be allocated
+  if (L.out_laid) return BISIM_OK;
   ChunkScope scope(h->mem);
   hipStream_t st = h->stream;
   const size_t n = (size_t)h->n;
@@ -1024,6 +1024,7 @@ bisim_status by_source(bisim_lts* h) {
   uint32_t* cur = nullptr;
   BISIM_TRY(lalloc(&L.out_ptr, n + 1, st));
   BISIM_TRY(lalloc(&L.out_dst, (size_t)h->m, st));
+  BISIM_TRY(lalloc(&L.out_ord, (size_t)h->m, st));
   BISIM_TRY(lalloc(&cur, n, st));
   int64_t g = (h->m + kLT - 1) / kLT;
   g = g > cu * 32 ? cu * 32 : (g < 1 ? 1 : g);
@@ -1032,8 +1033,7 @@ bisim_status by_source(bisim_lts* h) {
   hipLaunchKernelGGL(k_l_zero_u32, dim3((unsigned)gn), dim3(kLT), 0, st, cur, (uint32_t)n);
   hipLaunchKernelGGL(k_l_out_count, dim3((unsigned)g), dim3(kLT), 0, st, h->in_src,
                      (uint64_t)h->m, cur);
-  bisim_status rc = exclusive_scan_u32(cur, L.out_ptr, (int64_t)n, st);
-  if (rc == BISIM_OK) rc = lalloc(&L.out_ord, (size_t)h->m, st);
+  const bisim_status rc = exclusive_scan_u32(cur, L.out_ptr, (int64_t)n, st);
   if (rc == BISIM_OK) {
     hipLaunchKernelGGL(k_l_copy_u32, dim3((unsigned)gn), dim3(kLT), 0, st, L.out_ptr, cur,
                        (uint32_t)n);
@@ -1043,6 +1043,7 @@ bisim_status by_source(bisim_lts* h) {
   (void)dev_free(cur, st);
   BISIM_TRY(rc);
   BISIM_TRY_HIP(hipGetLastError());
+  L.out_laid = true;
   return BISIM_OK;
 }
 

@@ -565,18 +565,32 @@ bisim_status dalloc(T** p, size_t count, hipStream_t s) {
   return BISIM_OK;
 }
 
-struct Temps {
-  hipStream_t s = nullptr;
-  std::vector<void*> ptrs;
+// Temporaries of loading, given back with the object.
+class Temps {
+ public:
+  explicit Temps(bisim_lts* h) : stream_(h->stream), apart_(h->temps_apart && !arena_active()) {
+    if (apart_) own_.reserve(h->temps_apart, stream_);
+  }
   template <class T>
   bisim_status get(T** p, size_t count) {
-    BISIM_TRY(dalloc(p, count, s));
-    if (!arena_active()) ptrs.push_back((void*)*p);  // arena memory is never freed singly
+    if (apart_) {
+      ChunkScope scope(own_);
+      return dalloc(p, count, stream_);
+    }
+    BISIM_TRY(dalloc(p, count, stream_));
+    if (!arena_active()) ptrs_.push_back((void*)*p);  // arena memory is never freed singly
     return BISIM_OK;
   }
   ~Temps() {
-    for (size_t i = ptrs.size(); i-- > 0;) (void)dev_free(ptrs[i], s);
+    own_.release(stream_);
+    for (void* p : ptrs_) (void)dev_free(p, stream_);
   }
+
+ private:
+  hipStream_t stream_;
+  bool apart_;
+  Chunks own_;
+  std::vector<void*> ptrs_;
 };
 }  // namespace
 
@@ -595,8 +609,7 @@ static bisim_status setup_masks(bisim_lts* h, const int32_t* src, const int32_t*
   BISIM_TRY(dalloc(&h->in_ord, (size_t)m, st));
   BISIM_TRY(dalloc(&h->act_mask, (size_t)n, st));
   if (h->K == 1) BISIM_TRY(dalloc(&h->init_block, (size_t)n, st));
-  Temps tmp;
-  tmp.s = st;
+  Temps tmp(h);
   uint32_t cap = 64;
   while (cap < 2u * (uint32_t)n) cap <<= 1;
   uint64_t* mask = h->act_mask;
@@ -661,8 +674,7 @@ bisim_status setup_load(bisim_lts* h, const int32_t* src, const int32_t* lab,
   const int32_t K = h->K;
   hipStream_t st = h->stream;
   const int cu = h->num_cu;
-  Temps tmp;
-  tmp.s = st;
+  Temps tmp(h);
 
   // 1. validation
   uint32_t* err;
@@ -689,6 +701,9 @@ bisim_status setup_load(bisim_lts* h, const int32_t* src, const int32_t* lab,
   // labels mod 8 for the block features (not kept by the allocation-free
   // entry point, which runs the plain policy)
   if (!h->in_lab8 && !arena_active()) BISIM_TRY(dalloc(&h->in_lab8, (size_t)m, st));
+  // mark-word offsets, should a state have more than 64 actions (cut before
+  // the temporaries, whose place is used again)
+  if (K > 64 && !arena_active()) BISIM_TRY(dalloc(&h->woff, (size_t)n + 1, st));
 
   int32_t* ord;
   uint32_t *lab_cnt, *lab_ptr, *cursor, *idx, *newl, *red;
@@ -844,10 +859,12 @@ bisim_status setup_load(bisim_lts* h, const int32_t* src, const int32_t* lab,
   h->max_ranks = red_h[0];
   if (h->uniform) {
     h->nwords = (uint64_t)n;
+    (void)dev_free(h->woff, st);
+    h->woff = nullptr;
   } else {
     uint32_t* words;
     BISIM_TRY(tmp.get(&words, (size_t)n));
-    BISIM_TRY(dalloc(&h->woff, (size_t)n + 1, st));
+    if (!h->woff) BISIM_TRY(dalloc(&h->woff, (size_t)n + 1, st));
     hipLaunchKernelGGL(k_words, dim3(gn), dim3(kT), 0, st, n, h->nr_marks, words);
     BISIM_TRY(exclusive_scan_u32(words, h->woff, n, st));
     uint32_t nw = 0;

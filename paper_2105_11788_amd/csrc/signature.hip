@@ -444,7 +444,9 @@ struct Bufs {
     }
     const int i = k++;
     if (h->sig_bytes[i] < bytes) {
-      h->sig_bytes[i] = 0;  // (the piece of a slot that grows stays with the handle)
+      (void)dev_free(h->sig_buf[i], h->stream);
+      h->sig_buf[i] = nullptr;
+      h->sig_bytes[i] = 0;
       if (dev_alloc(&h->sig_buf[i], bytes, h->stream) != hipSuccess) {
         h->sig_buf[i] = nullptr;
         set_error("signature refinement: out of device memory (%zu bytes)", bytes);

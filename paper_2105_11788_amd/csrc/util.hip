@@ -18,35 +18,48 @@ hipError_t Chunks::add(size_t bytes, hipStream_t s) {
     (void)hipGetLastError();
     return e;
   }
-  chunks_.push_back({(char*)p, bytes, 0, 0});
-  return hipSuccess;
-}
-void Chunks::reserve(size_t bytes, hipStream_t s) {
-  if (chunks_.empty() || chunks_.back().cap - chunks_.back().used < bytes)
-    (void)add(piece_bytes(bytes), s);
-}
-hipError_t Chunks::alloc(void** p, size_t bytes, hipStream_t s) {
-  const size_t need = piece_bytes(bytes);
-  if (chunks_.empty() || chunks_.back().cap - chunks_.back().used < need) {
-    // beyond what was reserved: pieces of 1 MiB for small requests
-    hipError_t e = need < (1u << 20) ? add(1u << 20, s) : hipErrorOutOfMemory;
-    if (e != hipSuccess) e = add(need, s);
-    if (e != hipSuccess) return e;
+  try {
+    chunks_.push_back({(char*)p, bytes, Pieces(bytes)});
+  } catch (...) {  // no host memory for the list
+    (void)hipFreeAsync(p, s);
+    return hipErrorOutOfMemory;
   }
-  Chunk& c = chunks_.back();
-  c.last = c.used;
-  *p = c.base + c.used;
-  c.used += need;
   return hipSuccess;
 }
-bool Chunks::holds(const void* p) const {
-  for (const Chunk& c : chunks_)
-    if ((const char*)p >= c.base && (const char*)p < c.base + c.cap) return true;
+// the newest chunk with room takes the piece (a chunk's rest is not lost when
+// a larger request has opened another)
+bool Chunks::cut(void** p, size_t need) {
+  size_t at = 0;
+  for (size_t i = chunks_.size(); i-- > 0;)
+    if (chunks_[i].pieces.cut(need, &at)) {
+      *p = chunks_[i].base + at;
+      return true;
+    }
   return false;
 }
-void Chunks::take_back(const void* p) {
+void Chunks::reserve(size_t bytes, hipStream_t s) {
+  for (const Chunk& c : chunks_)
+    if (c.capacity - c.pieces.used() >= bytes) return;
+  (void)add(piece_bytes(bytes), s);
+}
+hipError_t Chunks::alloc(void** p, size_t bytes, hipStream_t s) try {
+  const size_t need = piece_bytes(bytes);
+  if (cut(p, need)) return hipSuccess;
+  // beyond what was reserved: 1 MiB at a time for small requests
+  hipError_t e = need < (1u << 20) ? add(1u << 20, s) : hipErrorOutOfMemory;
+  if (e != hipSuccess) e = add(need, s);
+  if (e != hipSuccess) return e;
+  return cut(p, need) ? hipSuccess : hipErrorOutOfMemory;
+} catch (...) {
+  return hipErrorOutOfMemory;
+}
+bool Chunks::give_back(const void* p) {
   for (Chunk& c : chunks_)
-    if (c.last < c.used && (const char*)p == c.base + c.last) c.used = c.last;
+    if ((const char*)p >= c.base && (const char*)p < c.base + c.capacity) {
+      c.pieces.give_back((size_t)((const char*)p - c.base));
+      return true;
+    }
+  return false;
 }
 void Chunks::release(hipStream_t s) {
   for (const Chunk& c : chunks_) (void)hipFreeAsync(c.base, s);
@@ -77,10 +90,7 @@ hipError_t dev_free(void* p, hipStream_t s) {
   if (!p) return hipSuccess;
   for (ArenaScope* a = g_arena; a; a = a->outer_)
     if ((char*)p >= a->base_ && (char*)p < a->base_ + a->cap_) return hipSuccess;
-  if (g_chunks && g_chunks->holds(p)) {
-    g_chunks->take_back(p);
-    return hipSuccess;
-  }
+  if (g_chunks && g_chunks->give_back(p)) return hipSuccess;
   return hipFreeAsync(p, s);
 }
 
