@@ -171,7 +171,12 @@ const char* bisim_last_error(void);
  *                           BISIM_E_UNSUPPORTED at coarsest_partition); about
  *                           96 more bytes of device memory per state and, from
  *                           1,536 transitions on, 8 per transition, allocated
- *                           on first use.
+ *                           on first use.  Without the memory for the latter
+ *                           it goes on without them; without the former an
+ *                           automatic run takes engine 2, which needs none
+ *                           (test hook: with the environment variable
+ *                           BISIM_HANDLE_LIMIT=<bytes> a handle's memory is
+ *                           bounded).
  *   BISIM_OPT_COUNT_WORK    0 (default) or 1: engine 3 accumulates work totals
  *                           over the run (bisim_get_work).
  *   BISIM_OPT_FIRST_SPLITTER  -1 (default) or a block label of the

@@ -223,7 +223,7 @@ __global__ void k_batch_args(BArgs a, RoundsArgs<uint64_t>* __restrict__ out) {
   g.qb = a.qb + b0;
   g.us = a.us + b0;
   g.qs = a.qs + b0;
-  g.out_ptr = a.out_ptr + s0;
+  g.out_ptr = a.out_ptr ? a.out_ptr + s0 : nullptr;
   g.out_dst = a.out_dst;
   g.out_ord = a.out_ord;
   g.out_cur = nullptr;
@@ -639,11 +639,16 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
         (st = dmalloc(&b->us, BW)) || (st = dmalloc(&b->tlb, (size_t)N)) ||
         (st = dmalloc(&b->se, (size_t)N)) || (st = dmalloc(&b->tmp64, (size_t)N)) ||
         (st = dmalloc(&b->pin, (size_t)N)) || (st = dmalloc(&b->trk, (size_t)N)) ||
-        (st = by_source(b->u)) ||
         (st = dmalloc(&b->llo, (size_t)N)) || (st = dmalloc(&b->lsz, (size_t)N)) ||
         (st = dmalloc(&b->iters_d, count)) || (st = dmalloc(&b->ctl_d, 2)) ||
         (st = dmalloc(&b->work_d, 16)) || (st = dmalloc(&b->args_d, (size_t)count)))
       break;
+    st = by_source(b->u);
+    if (st == BISIM_E_NOMEM) {  // no label is tracked then
+      clear_error();
+      st = BISIM_OK;
+    }
+    if (st != BISIM_OK) break;
     if (count > 0)
       hipLaunchKernelGGL(k_batch_args, dim3((unsigned)(count + 255) / 256), dim3(256), 0, s,
                        make_args(b, nullptr), b->args_d);

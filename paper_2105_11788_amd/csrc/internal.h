@@ -281,6 +281,7 @@ struct bisim_lts {
 
   // block features and the learned splitter policy
   uint32_t* sfeat = nullptr;  // [n][16] out/in transitions of each state by label mod 8
+  bool features = false;      // sfeat and the arrays of the policy below are there
   uint32_t* acc = nullptr;    // [n][17] per block label: size, out[8], in[8]
   uint32_t* born = nullptr;   // [n] iteration the block was created / last split
   uint32_t* used = nullptr;   // [n] iteration the block was last the splitter
@@ -361,9 +362,10 @@ bisim_status signature_run(bisim_lts* h, int32_t* block_id, bool hybrid);
 bisim_status lists_alloc(bisim_lts* h);
 bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals);
 void lists_free(bisim_lts* h);
+void lists_drop(bisim_lts* h);  // gives its buffers back (a later run allocates them again)
 // the same engine by rounds of one workgroup (splitters that split nothing
 // decided ahead of their turn); rounds_apply says whether a run may take them
-bisim_status by_source(bisim_lts* h);  // lists.out_ptr, out_dst, out_ord
+bisim_status by_source(bisim_lts* h);  // lists.out_ptr, out_dst, out_ord (optional)
 bool rounds_apply(const bisim_lts* h);
 bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool rcpp);
 }  // namespace bisim

@@ -806,6 +806,35 @@ bisim_status lists_alloc(bisim_lts* h) {
   return BISIM_OK;
 }
 
+template <size_t kCount>
+static void give_back(bisim_lts* h, void** const (&ptrs)[kCount]) {
+  for (void** p : ptrs) {
+    (void)dev_free(*p, h->stream);
+    *p = nullptr;
+  }
+}
+
+static void out_drop(bisim_lts* h) {
+  bisim_lists& L = h->lists;
+  void** const ptrs[] = {(void**)&L.out_ptr, (void**)&L.out_dst, (void**)&L.out_ord};
+  give_back(h, ptrs);
+  L.out_laid = false;
+}
+
+// gives back the buffers of this engine, whichever there are
+void lists_drop(bisim_lts* h) {
+  bisim_lists& L = h->lists;
+  void** const ptrs[] = {
+      (void**)&L.perm, (void**)&L.pos, (void**)&L.bs,    (void**)&L.be,  (void**)&L.cnt,
+      (void**)&L.fc,   (void**)&L.gc,  (void**)&L.tcn,   (void**)&L.pin, (void**)&L.pf,
+      (void**)&L.lb,   (void**)&L.lo,  (void**)&L.tmp64, (void**)&L.lh,  (void**)&L.ts,
+      (void**)&L.tbk,  (void**)&L.ss,  (void**)&L.sbk,   (void**)&L.sr,  (void**)&L.sfi,
+      (void**)&L.sne,  (void**)&L.sps, (void**)&L.sse,   (void**)&L.work, (void**)&L.trk,
+      (void**)&L.trk_save};
+  give_back(h, ptrs);
+  out_drop(h);
+}
+
 // the kernels' arguments, and the refinable partition of the start partition
 static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_totals, bool fill,
                                 LArgs& a) {
@@ -1013,7 +1042,17 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   return BISIM_OK;
 }
 
+static bisim_status out_alloc(bisim_lts* h) {
+  bisim_lists& L = h->lists;
+  bisim_status rc = lalloc(&L.out_ptr, (size_t)h->n + 1, h->stream);
+  if (rc == BISIM_OK) rc = lalloc(&L.out_dst, (size_t)h->m, h->stream);
+  if (rc == BISIM_OK) rc = lalloc(&L.out_ord, (size_t)h->m, h->stream);
+  if (rc != BISIM_OK) out_drop(h);
+  return rc;
+}
+
 // The transitions by source (target and action rank), from those by target.
+// BISIM_E_NOMEM leaves none of them.
 bisim_status by_source(bisim_lts* h) {
   bisim_lists& L = h->lists;
   if (L.out_laid) return BISIM_OK;
@@ -1022,10 +1061,12 @@ bisim_status by_source(bisim_lts* h) {
   const size_t n = (size_t)h->n;
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   uint32_t* cur = nullptr;
-  BISIM_TRY(lalloc(&L.out_ptr, n + 1, st));
-  BISIM_TRY(lalloc(&L.out_dst, (size_t)h->m, st));
-  BISIM_TRY(lalloc(&L.out_ord, (size_t)h->m, st));
-  BISIM_TRY(lalloc(&cur, n, st));
+  BISIM_TRY(out_alloc(h));
+  bisim_status rc = lalloc(&cur, n, st);
+  if (rc != BISIM_OK) {
+    out_drop(h);
+    return rc;
+  }
   int64_t g = (h->m + kLT - 1) / kLT;
   g = g > cu * 32 ? cu * 32 : (g < 1 ? 1 : g);
   int64_t gn = ((int64_t)n + kLT - 1) / kLT;
@@ -1033,7 +1074,7 @@ bisim_status by_source(bisim_lts* h) {
   hipLaunchKernelGGL(k_l_zero_u32, dim3((unsigned)gn), dim3(kLT), 0, st, cur, (uint32_t)n);
   hipLaunchKernelGGL(k_l_out_count, dim3((unsigned)g), dim3(kLT), 0, st, h->in_src,
                      (uint64_t)h->m, cur);
-  const bisim_status rc = exclusive_scan_u32(cur, L.out_ptr, (int64_t)n, st);
+  rc = exclusive_scan_u32(cur, L.out_ptr, (int64_t)n, st);
   if (rc == BISIM_OK) {
     hipLaunchKernelGGL(k_l_copy_u32, dim3((unsigned)gn), dim3(kLT), 0, st, L.out_ptr, cur,
                        (uint32_t)n);
@@ -1041,7 +1082,10 @@ bisim_status by_source(bisim_lts* h) {
                        h->in_src, h->in_ord, cur, L.out_dst, L.out_ord);
   }
   (void)dev_free(cur, st);
-  BISIM_TRY(rc);
+  if (rc != BISIM_OK) {
+    out_drop(h);
+    return rc;
+  }
   BISIM_TRY_HIP(hipGetLastError());
   L.out_laid = true;
   return BISIM_OK;
@@ -1148,16 +1192,14 @@ bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool r
   const uint32_t n = (uint32_t)h->n, nw = (n + 63) / 64;
   const bool own = n <= kSetupN;
   bisim_lists& L = h->lists;
+  BISIM_TRY(lists_alloc(h));
   if (h->m >= kTrackMinM) {
-    if (h->m >= kOwnOutM) {
-      BISIM_TRY(by_source(h));
-    } else {
-      BISIM_TRY(lalloc(&L.out_ptr, (size_t)n + 1, h->stream));
-      BISIM_TRY(lalloc(&L.out_dst, (size_t)h->m, h->stream));
-      BISIM_TRY(lalloc(&L.out_ord, (size_t)h->m, h->stream));
-    }
-    BISIM_TRY(lalloc(&L.trk, n, h->stream));
-    BISIM_TRY(lalloc(&L.trk_save, kTrackSave, h->stream));
+    // (without the memory for it the rounds go without tracking)
+    bisim_status rc = lalloc(&L.trk, n, h->stream);
+    if (rc == BISIM_OK) rc = lalloc(&L.trk_save, kTrackSave, h->stream);
+    if (rc == BISIM_OK) rc = h->m >= kOwnOutM ? by_source(h) : out_alloc(h);
+    if (rc == BISIM_E_NOMEM) clear_error();
+    else BISIM_TRY(rc);
   }
   BISIM_TRY(lists_setup(h, cap, false, !own, l));
   l.qb = h->lt;

@@ -411,7 +411,10 @@ static bisim_status know_max_out(bisim_lts* h) {
   const size_t n = (size_t)h->n;
   hipStream_t s = h->stream;
   uint32_t* deg = nullptr;  // [n], then the maximum
-  BISIM_TRY(dalloc(&deg, n + 1, s));
+  if (dalloc(&deg, n + 1, s) != BISIM_OK) {  // (a choice of kernels: go on without)
+    clear_error();
+    return BISIM_OK;
+  }
   const unsigned g = (unsigned)(h->num_cu > 0 ? h->num_cu : 1) * 8;
   hipLaunchKernelGGL(k_zero_words, dim3(g), dim3(kT), 0, s, deg, (uint64_t)n + 1);
   hipLaunchKernelGGL(k_out_degrees, dim3(g), dim3(kT), 0, s, h->in_src, (uint64_t)h->m, deg);
@@ -426,11 +429,22 @@ static bisim_status know_max_out(bisim_lts* h) {
 
 // feature / policy state, allocated on first use
 bisim_status refine_alloc_features(bisim_lts* h) {
-  if (h->acc) return BISIM_OK;
+  if (h->features) return BISIM_OK;
   const size_t n = (size_t)h->n;
   hipStream_t s = h->stream;
   const size_t nwd = (n + 63) / 64, nsw = (nwd + 63) / 64, ntw = (nsw + 63) / 64;
-  BISIM_TRY(dalloc(&h->sfeat, 16 * n, s));
+  // (those that a run before allocated, before it ran out of memory, are there)
+  const auto need = [&](auto** p, size_t count) { return *p ? BISIM_OK : dalloc(p, count, s); };
+  BISIM_TRY(need(&h->sfeat, 16 * n));
+  BISIM_TRY(need(&h->acc, 17 * n));
+  BISIM_TRY(need(&h->born, n));
+  BISIM_TRY(need(&h->used, n));
+  BISIM_TRY(need(&h->chg, 2 * n));
+  BISIM_TRY(need(&h->lvl, n));
+  BISIM_TRY(need(&h->lvb, kLevels * nwd));
+  BISIM_TRY(need(&h->lvs, kLevels * nsw));
+  BISIM_TRY(need(&h->lvt, kLevels * ntw));
+  BISIM_TRY(need(&h->lvq, 2 * n + 1));
   const int64_t cu = h->num_cu > 0 ? h->num_cu : 1;
   const int64_t g = std::min<int64_t>((16 * (int64_t)n + kT - 1) / kT, cu * 16);
   hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
@@ -438,15 +452,7 @@ bisim_status refine_alloc_features(bisim_lts* h) {
   hipLaunchKernelGGL(k_static_features, dim3((unsigned)std::max<int64_t>(g, 1)), dim3(kT), 0, s,
                      (uint32_t)n, h->in_ptr, h->in_src, h->in_ord, h->in_lab8, h->act_mask, h->sfeat);
   BISIM_TRY_HIP(hipGetLastError());
-  BISIM_TRY(dalloc(&h->acc, 17 * n, s));
-  BISIM_TRY(dalloc(&h->born, n, s));
-  BISIM_TRY(dalloc(&h->used, n, s));
-  BISIM_TRY(dalloc(&h->chg, 2 * n, s));
-  BISIM_TRY(dalloc(&h->lvl, n, s));
-  BISIM_TRY(dalloc(&h->lvb, kLevels * nwd, s));
-  BISIM_TRY(dalloc(&h->lvs, kLevels * nsw, s));
-  BISIM_TRY(dalloc(&h->lvt, kLevels * ntw, s));
-  BISIM_TRY(dalloc(&h->lvq, 2 * n + 1, s));
+  h->features = true;
   return BISIM_OK;
 }
 
@@ -677,6 +683,11 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   h->engine = saved_engine;
   h->grid = saved_grid;
   h->iter_limit = saved_limit;
+  if (rc == BISIM_E_NOMEM) {  // no room for the member lists: engine 2, nothing stored
+    clear_error();
+    lists_drop(h);
+    return BISIM_OK;
+  }
   if (rc != BISIM_OK) return rc;
   clear_error();
   lts_tune_store(key, be, bg, best);
@@ -696,7 +707,14 @@ bisim_status refine_run(bisim_lts* h, int32_t* block_id) {
   h->engine = engine;
   h->grid = grid;
   h->run_engine = engine;
-  const bisim_status rc = refine_run_impl(h, block_id, true);
+  bisim_status rc = refine_run_impl(h, block_id, true);
+  if (rc == BISIM_E_NOMEM && engine == 3) {  // engine 2 needs no member lists
+    clear_error();
+    lists_drop(h);
+    h->engine = h->run_engine = 2;
+    h->grid = saved_grid;
+    rc = refine_run_impl(h, block_id, true);
+  }
   h->engine = 0;
   h->grid = saved_grid;
   return rc;

@@ -85,13 +85,21 @@ bisim_status exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t count
   // tiles >= 2: the recursion below runs on ceil(count / kTile) < count values
   uint32_t* sums = nullptr;
   uint32_t* offs = nullptr;
-  BISIM_TRY_HIP(dev_alloc((void**)&sums, sizeof(uint32_t) * tiles, stream));
-  BISIM_TRY_HIP(dev_alloc((void**)&offs, sizeof(uint32_t) * (tiles + 1), stream));
+  if (dev_alloc((void**)&sums, sizeof(uint32_t) * tiles, stream) != hipSuccess ||
+      dev_alloc((void**)&offs, sizeof(uint32_t) * (tiles + 1), stream) != hipSuccess) {
+    (void)dev_free(sums, stream);
+    set_error("out of device memory (a prefix sum of %lld values)", (long long)count);
+    return BISIM_E_NOMEM;
+  }
   hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)tiles), dim3(kThreads), 0, stream, in, out, sums,
                      count);
   BISIM_TRY_HIP(hipGetLastError());
   bisim_status st = exclusive_scan_u32(sums, offs, tiles, stream);
-  if (st != BISIM_OK) return st;
+  if (st != BISIM_OK) {
+    (void)dev_free(offs, stream);
+    (void)dev_free(sums, stream);
+    return st;
+  }
   hipLaunchKernelGGL(k_scan_add, dim3((unsigned)tiles), dim3(kThreads), 0, stream, out, offs,
                      count);
   BISIM_TRY_HIP(hipGetLastError());

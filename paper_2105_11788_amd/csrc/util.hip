@@ -2,6 +2,8 @@
 // region for the allocation-free entry point) and a measurement helper: a
 // plain streaming copy, used to measure the bandwidth the device actually
 // sustains and to calibrate memory-traffic counters.
+#include <cstdlib>
+
 #include "internal.h"
 
 namespace bisim {
@@ -12,6 +14,12 @@ static thread_local Chunks* g_chunks = nullptr;
 static size_t piece_bytes(size_t bytes) { return ((bytes ? bytes : 1) + 255) & ~(size_t)255; }
 
 hipError_t Chunks::add(size_t bytes, hipStream_t s) {
+  // test hook: BISIM_HANDLE_LIMIT=<bytes> bounds the chunks of one handle
+  if (const char* limit = getenv("BISIM_HANDLE_LIMIT")) {
+    size_t held = 0;
+    for (const Chunk& c : chunks_) held += c.capacity;
+    if (held + bytes > strtoull(limit, nullptr, 10)) return hipErrorOutOfMemory;
+  }
   void* p = nullptr;
   const hipError_t e = hipMallocAsync(&p, bytes, s);
   if (e != hipSuccess) {

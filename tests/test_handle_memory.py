@@ -110,3 +110,69 @@ def test_load_leaves_no_temporaries(actions):
         extra = 16 * L.m // 64 if actions == 200 else 0  # mark words beyond one per state
         assert pool_bytes(B) - before <= 174 * L.n + 17 * L.m + extra + (2 << 20)
     assert pool_bytes(B) == before
+
+
+@pytest.mark.gpu
+def test_runs_within_less_memory(monkeypatch, tmp_path):
+    """What fits is run: without the layout that tracks large splitters, and
+    without the member lists (by the engine that needs none), down to what
+    loading takes.  Loads may fail, automatic runs never do."""
+    from paper_2105_11788_amd import bisim as B, gen
+    import oracle
+    monkeypatch.setenv("BISIM_TUNE_CACHE", str(tmp_path / "tune.txt"))
+    L = gen.planted_quotient(1500, 4.0, 3, seed=5)
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)
+    dev = [B.DeviceArray.from_numpy(a, np.int32) for a in (L.src, L.lab, L.dst)]
+    seen, its = [], set()
+    for limit in range(1 << 20, 12 << 20, 1 << 18):
+        monkeypatch.setenv("BISIM_HANDLE_LIMIT", str(limit))
+        try:
+            h = B.LTS(*dev, L.n, L.K, None)
+        except B.BisimError as e:
+            assert e.status == B.E_NOMEM and not seen
+            continue
+        with h:
+            for _ in range(2):
+                out, st = h.run()
+                assert (out.numpy() == ks).all() and st.blocks == nb
+                its.add(st.iterations)
+            seen.append(h.run_config()[0])
+            h.set_option(B.OPT_ENGINE, 3)
+            if seen[-1] == 3:
+                h.run()
+            else:
+                with pytest.raises(B.BisimError) as e:
+                    h.run()
+                assert e.value.status == B.E_NOMEM
+                h.set_option(B.OPT_ENGINE, 0)  # the handle stays usable
+                assert (h.run()[0].numpy() == ks).all()
+    assert len(its) == 1 and seen == sorted(seen) and {2, 3} <= set(seen)
+
+
+@pytest.mark.gpu
+def test_batch_within_less_memory(monkeypatch):
+    from paper_2105_11788_amd import bisim as B, gen
+    import oracle
+    insts = [gen.planted_quotient(300, 30.0, 3, seed=s) for s in (1, 2)]
+    refs = [oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst) for L in insts]
+    ran = failed = 0
+    for limit in range(1 << 20, 12 << 20, 1 << 18):
+        monkeypatch.setenv("BISIM_HANDLE_LIMIT", str(limit))
+        try:
+            b = B.Batch(insts)
+        except B.BisimError as e:
+            assert e.status == B.E_NOMEM and not ran
+            failed += 1
+            continue
+        with b:
+            b.set_option(B.BOPT_GRID, 2)
+            out, its, _ = b.run()
+            for x, n_it, r in zip(b.split(out.numpy()), its, refs):
+                assert (x == r["block"]).all() and n_it == r["iters"]
+            ran += 1
+    # what a load takes and leaves, a chunk and a step of the limit for rounding;
+    # the layout by source would be 8 bytes per transition more
+    n, m = sum(L.n for L in insts), sum(L.m for L in insts)
+    print(f"n {n} m {m}: loads from {(1 << 20) + failed * (1 << 18)} on", flush=True)
+    assert ran and 8 * m > 2 << 20
+    assert (1 << 20) + failed * (1 << 18) <= 8 * m + 88 * n + (1 << 20) + (1 << 18)
