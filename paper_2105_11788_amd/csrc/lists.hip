@@ -53,6 +53,7 @@
 #include <new>
 #include <vector>
 
+#include "grouped_dev.h"
 #include "internal.h"
 #include "rounds_dev.h"
 
@@ -756,12 +757,11 @@ __global__ void k_l_out_fill(uint32_t n, const uint32_t* __restrict__ in_ptr,
                              uint32_t* cursor, int32_t* __restrict__ out_dst,
                              int32_t* __restrict__ out_ord) {
   const GPart g = gpart();
-  for (uint32_t t = g.gtid; t < n; t += g.gthreads)
-    for (uint32_t e = in_ptr[t]; e < in_ptr[t + 1]; ++e) {
-      const uint32_t q = atomicAdd(&cursor[in_src[e]], 1u);
-      out_dst[q] = (int32_t)t;
-      out_ord[q] = in_ord[e];
-    }
+  each_in_transition(n, in_ptr, g.gwave, g.gwaves, [&](uint32_t t, uint32_t e) {
+    const uint32_t q = atomicAdd(&cursor[in_src[e]], 1u);
+    out_dst[q] = (int32_t)t;
+    out_ord[q] = in_ord[e];
+  });
 }
 
 template <class T>
@@ -1078,7 +1078,7 @@ bisim_status by_source(bisim_lts* h) {
   if (rc == BISIM_OK) {
     hipLaunchKernelGGL(k_l_copy_u32, dim3((unsigned)gn), dim3(kLT), 0, st, L.out_ptr, cur,
                        (uint32_t)n);
-    hipLaunchKernelGGL(k_l_out_fill, dim3((unsigned)gn), dim3(kLT), 0, st, (uint32_t)n, h->in_ptr,
+    hipLaunchKernelGGL(k_l_out_fill, dim3((unsigned)g), dim3(kLT), 0, st, (uint32_t)n, h->in_ptr,
                        h->in_src, h->in_ord, cur, L.out_dst, L.out_ord);
   }
   (void)dev_free(cur, st);

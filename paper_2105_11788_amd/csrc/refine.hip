@@ -54,6 +54,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "grouped_dev.h"
 #include "internal.h"
 #include "mlp_dev.h"
 #include "refine_dev.h"
@@ -370,19 +371,20 @@ __global__ void k_static_features(uint32_t n, const uint32_t* __restrict__ in_pt
                                   const uint8_t* __restrict__ in_lab8,
                                   const uint64_t* __restrict__ act_mask,
                                   uint32_t* __restrict__ sfeat) {
-  for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-    for (uint32_t e = in_ptr[t]; e < in_ptr[t + 1]; ++e) {
-      uint32_t q = 0;
-      if (act_mask) {  // the label is the rank-th action of the source
-        uint64_t v = act_mask[in_src[e]];
-        for (int32_t r = in_ord[e]; r > 0; --r) v &= v - 1;
-        q = (uint32_t)(__ffsll((unsigned long long)v) - 1) & 7u;
-      } else {
-        q = in_lab8[e];
-      }
-      atomicAdd(&sfeat[(size_t)in_src[e] * 16 + q], 1u);
-      atomicAdd(&sfeat[(size_t)t * 16 + 8 + q], 1u);
+  const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
+  const uint32_t waves = gridDim.x * blockDim.x / kWave;
+  each_in_transition(n, in_ptr, wave, waves, [&](uint32_t t, uint32_t e) {
+    uint32_t q = 0;
+    if (act_mask) {  // the label is the rank-th action of the source
+      uint64_t v = act_mask[in_src[e]];
+      for (int32_t r = in_ord[e]; r > 0; --r) v &= v - 1;
+      q = (uint32_t)(__ffsll((unsigned long long)v) - 1) & 7u;
+    } else {
+      q = in_lab8[e];
     }
+    atomicAdd(&sfeat[(size_t)in_src[e] * 16 + q], 1u);
+    atomicAdd(&sfeat[(size_t)t * 16 + 8 + q], 1u);
+  });
 }
 }  // namespace
 

@@ -1,0 +1,68 @@
+"""States of very many in-transitions (sinks): results equal the oracle's, and
+what is laid out once per handle is spread over transitions, not targets.  One
+lane that walks a million transitions takes 0.4 s; the bounds leave
+the layout 50 ms, a hundred times what its bytes take."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2105_11788_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2105_11788_amd import bisim
+    return bisim
+
+
+def sink(n, actions):
+    """Every state but the sink has a transition of each action to it."""
+    src = np.repeat(np.arange(1, n), actions)
+    return gen.LTS(n, actions, src, np.tile(np.arange(actions), n - 1), np.zeros(src.size, int))
+
+
+def timed(f):
+    t = time.perf_counter()
+    r = f()
+    return r, (time.perf_counter() - t) * 1e3
+
+
+def first_and_next(B, L, learned=False):
+    dev = [B.DeviceArray.from_numpy(a, np.int32) for a in (L.src, L.lab, L.dst)]
+    out = B.DeviceArray(L.n, np.int32)
+    with B.LTS(*dev, L.n, L.K, None) as h:
+        w = B.MLP(B.POLICY_FEATURES, seed=1) if learned else None
+        if learned:
+            B.set_splitter_policy(h, B.POLICY_LEARNED, w)
+        (_, st), first = timed(lambda: h.run(out))
+        _, later = timed(lambda: h.run(out))
+        return out.numpy(), st, first, later
+
+
+def test_sink_first_run(B):
+    first_and_next(B, sink(100, 2))  # (the kernels are loaded)
+    first_and_next(B, sink(100, 2), learned=True)
+    L = sink(100_001, 10)
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)
+    for learned in (False, True):
+        got, st, first, later = first_and_next(B, L, learned)
+        print(f"[sink] learned {learned}: first {first:.1f} ms, next {later:.1f}", flush=True)
+        assert (got == ks).all() and st.blocks == nb
+        assert first < later + 50
+
+
+def test_sink_batch_load(B):
+    L = sink(100_001, 10)
+    small = gen.kripke_uniform(100, 500, seed=1)
+    B.Batch([small]).close()
+    with B.Batch([L, small]) as b:
+        b.set_option(B.BOPT_GRID, 2)
+        out, its, st = b.run()
+        got = b.split(out.numpy())
+    print(f"[sink] batch load {st['t_pre_ms']:.1f} ms", flush=True)
+    assert (got[0] == oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)[0]).all()
+    assert st["t_pre_ms"] < 100  # (23 ms of them the load's atomics at the sink)

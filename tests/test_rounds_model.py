@@ -26,18 +26,18 @@ class Run(ctypes.Structure):
                 ("seed", ctypes.c_uint32), ("block", P), ("iterations", P)]
 
 
-def compiled(folder, constants):
+def compiled(folder, constants, header="rounds_dev.h", model="rounds_model.cpp"):
     """The model with some of the header's constants replaced."""
-    text = open(os.path.join(CSRC, "rounds_dev.h")).read()
+    text = open(os.path.join(CSRC, header)).read()
     for name, (was, now) in constants.items():
         assert text.count(f"{name} = {was}") == 1, name
         text = text.replace(f"{name} = {was}", f"{name} = {now}")
-    open(os.path.join(folder, "rounds_dev.h"), "w").write(text)
-    for f in ("internal.h", "rounds_model.cpp"):
+    open(os.path.join(folder, header), "w").write(text)
+    for f in ("internal.h", model):
         shutil.copy(os.path.join(HERE, "host_model", f), folder)
     so = os.path.join(folder, "model.so")
     subprocess.check_call(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-w",
-                           "-I", str(folder), os.path.join(folder, "rounds_model.cpp"), "-o", so])
+                           "-I", str(folder), os.path.join(folder, model), "-o", so])
     return ctypes.CDLL(so)
 
 
@@ -101,3 +101,30 @@ def test_more_states_than_table_keys(short_keys, n, track):
     for seed in range(3):
         L = gen.random_lts(n, 3 * n, 2, seed, init_blocks=3)
         check(short_keys, L, either=True, track=track, seed=seed)
+
+
+@pytest.fixture(scope="module")
+def grouped(tmp_path_factory):
+    return compiled(tmp_path_factory.mktemp("grouped"), {}, "grouped_dev.h", "grouped_model.cpp")
+
+
+# in-degrees: none at all, one state, hubs of several runs of transitions first
+# and last, states without any before, between and after, runs that just fit
+GROUPS = {
+    "none": [0, 0, 0], "one": [1], "hub": [3000], "hub-first": [2000, 1, 1], "hub-last": [1, 0, 1500],
+    "sparse": [0] * 400 + [1] + [0] * 300 + [2, 0, 1] + [0] * 500, "even": [1] * 1024,
+    "run": [512, 0, 512, 1], "mixed": [k * 37 % 11 * (k % 3) for k in range(700)] + [900, 0, 0, 5],
+}
+
+
+@pytest.mark.parametrize("waves", [1, 3])
+@pytest.mark.parametrize("case", sorted(GROUPS))
+def test_each_in_transition_once(grouped, case, waves):
+    degree = np.array(GROUPS[case], np.uint32)
+    ptr = np.concatenate([[0], np.cumsum(degree)]).astype(np.uint32)
+    m = int(ptr[-1])
+    target, visits = np.full(max(m, 1), 77, np.uint32), np.zeros(max(m, 1), np.uint32)
+    grouped.visit(len(degree), ptr.ctypes.data_as(P), waves, target.ctypes.data_as(P),
+                  visits.ctypes.data_as(P))
+    assert (visits[:m] == 1).all() and visits[m:].sum() == 0
+    assert (target[:m] == np.repeat(np.arange(len(degree)), degree)).all()
