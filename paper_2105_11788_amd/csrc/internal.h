@@ -212,6 +212,8 @@ struct bisim_lists {
   bool out_laid = false;  // by by_source (else the rounds lay them out themselves)
   uint8_t* trk = nullptr;
   uint32_t* trk_save = nullptr;
+  uint32_t* hubs = nullptr;  // states of very many in-transitions
+  bool hubs_known = false;
   // the captured graph of a chunk of iterations and the arguments it holds
   hipGraphExec_t gexec = nullptr;
   unsigned char gargs[512] = {};

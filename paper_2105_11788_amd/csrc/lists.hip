@@ -69,6 +69,10 @@ static_assert(kGraphIters % 2 == 0, "the iteration parity is the launch position
 // edge << 32 | count) of its first kWave members
 constexpr uint32_t kPfWords = 4u + 2u * kWave;
 constexpr int kPhases = 3;  // kernels per iteration
+// states of so many in-transitions are marked by the whole grid if there are
+// at most kHubCap of them (with more, waves have about as much each)
+constexpr uint32_t kHubDegree = 4096, kHubCap = 1024;
+constexpr uint32_t kManyMembers = 8192;
 
 struct LArgs {
   uint32_t n;
@@ -96,6 +100,7 @@ struct LArgs {
   int32_t *lb, *lo, *lh;  // listed segments: block, first and end position
   uint32_t lcap;
   uint32_t mpw;  // splitter members per wave and step of the mark kernel
+  uint32_t* hubs;  // [1 + kHubCap] number of states of kHubDegree in-transitions, and these
   int32_t *ts, *tbk;  // touched states and their blocks
   int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;  // split states (by list index)
   uint64_t* work;  // [8] totals when counting
@@ -188,6 +193,7 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   const bool lane_first = lane() < a.mpw && i_first < kWave;
   const uint32_t pf_lo = lane_first ? pc[4 + 2 * i_first] : 0u;
   const uint32_t pf_hi = lane_first ? pc[5 + 2 * i_first] : 0u;
+  const uint32_t hubs = a.hubs[0] <= kHubCap ? a.hubs[0] : 0u;  // (too many: as other members)
   if (idle(a, done)) return;
   const bool over = k + 1 > a.iter_cap;
   if (C0 == kNone || over) {  // the final pass, or the iteration cap
@@ -251,6 +257,70 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   if (p.gtid == 0 && a.count) {
     atomicAdd((unsigned long long*)&a.work[0], (unsigned long long)csz);
   }
+  // one transition per lane with `valid`: mark its source's slot and touch it
+  // (wave-uniform call).  A large splitter's transitions often give a mark
+  // that is there already (100k states, 200 transitions each: 5.9 ms an
+  // iteration): it is read first, and whoever set it has touched the source.
+  const bool many = csz >= kManyMembers;
+  const auto visit = [&](bool valid, uint32_t edge) {
+    bool first = false, lead = false;
+    int32_t s = 0, b = 0, o = 0;
+    uint32_t lo_ = 0, hi_ = 0;
+    if (valid) {
+      s = a.in_src[edge];
+      o = a.in_ord[edge];
+      if (many) valid = !((*mword(a, s, o) >> (o & 63)) & 1ull);
+    }
+    if (many && __ballot(valid) == 0) return;
+    if (valid) {
+      // the source's block and, in case it leads that block, the block's
+      // range are loaded beside the atomics (one round trip, not three)
+      b = a.block[s];
+      lo_ = (uint32_t)a.bs[s];
+      hi_ = (uint32_t)a.be[s];
+      atomicOr((unsigned long long*)mword(a, s, o), 1ull << (o & 63));
+      const uint64_t tbit = 1ull << (s & 63);
+      const uint64_t old = atomicOr((unsigned long long*)&a.tb[s >> 6], (unsigned long long)tbit);
+      first = !(old & tbit);
+      // a touched leader of a one-state block has no untouched member
+      lead = first && b == s && hi_ > lo_ + 1 && hi_ <= a.n;
+    }
+    if (first) atomicAdd(&a.tcn[b], 1);
+    // list entries for first touches and for the listed block's member
+    // segments (each with its absolute position range): both wave-aggregated
+    // reservations are issued before either result is used
+    const uint64_t tbal = __ballot(first);
+    count_work(a, 2, (uint64_t)__popcll(tbal));
+    const uint32_t nseg = lead ? (hi_ - lo_ + kSeg - 1) / kSeg : 0u;
+    const uint32_t sincl = wave_incl_scan_u32(nseg);
+    const uint32_t stot = (uint32_t)__shfl((int)sincl, kWave - 1, kWave);
+    count_work(a, 3, stot);
+    const uint32_t tcnt = (uint32_t)__popcll(tbal);
+    uint32_t tbase = 0, sbase = 0;
+    if (lane() == 0 && (tcnt | stot) != 0) {
+      // one lane, both atomics in flight before either result is waited
+      // for; the lane-dependent (always 0) slot keeps the compiler from
+      // rewriting each into a wave-wide reduction with its own wait
+      const uint32_t z = lane();
+      tbase = atomicAdd(&a.ctl->cntT[par].v[z], tcnt);
+      sbase = atomicAdd(&a.ctl->cntC[par].v[z], stot);
+    }
+    tbase = (uint32_t)__shfl((int)tbase, 0, kWave);
+    const uint32_t ti = tbase + (uint32_t)__popcll(tbal & ((1ull << lane()) - 1ull));
+    if (first && ti < a.n) {
+      a.ts[ti] = s;
+      a.tbk[ti] = b;
+    }
+    if (stot) {
+      const uint32_t base = (uint32_t)__shfl((int)sbase, 0, kWave) + sincl - nseg;
+      for (uint32_t q = 0; q < nseg; ++q) {
+        if (base + q >= a.lcap) break;  // never expected (capacity covers every block)
+        a.lb[base + q] = s;
+        a.lo[base + q] = (int32_t)(lo_ + q * kSeg);
+        a.lh[base + q] = (int32_t)min(hi_, lo_ + (q + 1) * kSeg);
+      }
+    }
+  };
   // a.mpw members per wave and step (about 64 / the mean in-degree), so that
   // a wave's in-transitions mostly fit one round of its 64 lanes
   for (uint32_t i0 = p.gwave * a.mpw; i0 < csz; i0 += p.gwaves * a.mpw) {
@@ -266,6 +336,7 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
         beg = (uint32_t)(x >> 32);
         deg = (uint32_t)x;
       }
+      if (hubs && deg >= kHubDegree) deg = 0;  // every wave's, below
     }
     const uint32_t incl = wave_incl_scan_u32(deg);
     const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
@@ -274,69 +345,25 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
       const uint32_t e = e0 + lane();
       const bool valid = e < total;
       const uint32_t ee = valid ? e : total - 1;
-      uint32_t j = 0;
-#pragma unroll
-      for (uint32_t step = 32; step >= 1; step >>= 1) {
-        const uint32_t probe = (uint32_t)__shfl((int)incl, (int)(j + step - 1), kWave);
-        if (probe <= ee) j += step;
-      }
+      const uint32_t j = wave_owner(incl, ee);
       const uint32_t jb = (uint32_t)__shfl((int)beg, (int)j, kWave);
       const uint32_t ji = (uint32_t)__shfl((int)incl, (int)j, kWave);
       const uint32_t jd = (uint32_t)__shfl((int)deg, (int)j, kWave);
-      bool first = false, lead = false;
-      int32_t s = 0, b = 0;
-      uint32_t lo_ = 0, hi_ = 0;
-      if (valid) {
-        const uint32_t edge = jb + (ee - (ji - jd));
-        s = a.in_src[edge];
-        const int32_t o = a.in_ord[edge];
-        // the source's block and, in case it leads that block, the block's
-        // range are loaded beside the atomics (one round trip, not three)
-        b = a.block[s];
-        lo_ = (uint32_t)a.bs[s];
-        hi_ = (uint32_t)a.be[s];
-        atomicOr((unsigned long long*)mword(a, s, o), 1ull << (o & 63));
-        const uint64_t tbit = 1ull << (s & 63);
-        const uint64_t old = atomicOr((unsigned long long*)&a.tb[s >> 6], (unsigned long long)tbit);
-        first = !(old & tbit);
-        if (first) atomicAdd(&a.tcn[b], 1);
-        // a touched leader of a one-state block has no untouched member
-        lead = first && b == s && hi_ > lo_ + 1 && hi_ <= a.n;
-      }
-      // list entries for first touches and for the listed block's member
-      // segments (each with its absolute position range): both wave-aggregated
-      // reservations are issued before either result is used
-      const uint64_t tbal = __ballot(first);
-      count_work(a, 2, (uint64_t)__popcll(tbal));
-      const uint32_t nseg = lead ? (hi_ - lo_ + kSeg - 1) / kSeg : 0u;
-      const uint32_t sincl = wave_incl_scan_u32(nseg);
-      const uint32_t stot = (uint32_t)__shfl((int)sincl, kWave - 1, kWave);
-      count_work(a, 3, stot);
-      const uint32_t tcnt = (uint32_t)__popcll(tbal);
-      uint32_t tbase = 0, sbase = 0;
-      if (lane() == 0 && (tcnt | stot) != 0) {
-        // one lane, both atomics in flight before either result is waited
-        // for; the lane-dependent (always 0) slot keeps the compiler from
-        // rewriting each into a wave-wide reduction with its own wait
-        const uint32_t z = lane();
-        tbase = atomicAdd(&a.ctl->cntT[par].v[z], tcnt);
-        sbase = atomicAdd(&a.ctl->cntC[par].v[z], stot);
-      }
-      tbase = (uint32_t)__shfl((int)tbase, 0, kWave);
-      const uint32_t ti = tbase + (uint32_t)__popcll(tbal & ((1ull << lane()) - 1ull));
-      if (first && ti < a.n) {
-        a.ts[ti] = s;
-        a.tbk[ti] = b;
-      }
-      if (stot) {
-        const uint32_t base = (uint32_t)__shfl((int)sbase, 0, kWave) + sincl - nseg;
-        for (uint32_t q = 0; q < nseg; ++q) {
-          if (base + q >= a.lcap) break;  // never expected (capacity covers every block)
-          a.lb[base + q] = s;
-          a.lo[base + q] = (int32_t)(lo_ + q * kSeg);
-          a.lh[base + q] = (int32_t)min(hi_, lo_ + (q + 1) * kSeg);
-        }
-      }
+      visit(valid, jb + (ee - (ji - jd)));
+    }
+  }
+  // the hubs of C: their transitions over all waves (by the wave that has the
+  // member, 64 at a time, a sink of 1M in-transitions took 21 ms)
+  for (uint32_t h0 = 0; h0 < hubs; h0 += kWave) {
+    const uint32_t h = h0 + lane() < hubs ? a.hubs[1 + h0 + lane()] : kNone;
+    uint64_t mine = __ballot(h != kNone && (uint32_t)a.block[h != kNone ? h : 0] == C);
+    while (mine) {
+      const uint32_t s = lane_u32(h, (uint32_t)(__ffsll((unsigned long long)mine) - 1));
+      mine &= mine - 1;
+      const uint32_t beg = a.in_ptr[s], deg = a.in_ptr[s + 1] - beg;
+      if (p.gwave == 0) count_work(a, 1, deg);
+      for (uint64_t e0 = (uint64_t)p.gwave * kWave; e0 < deg; e0 += (uint64_t)p.gwaves * kWave)
+        visit(e0 + lane() < deg, beg + (uint32_t)min(e0 + lane(), (uint64_t)deg - 1));
     }
   }
 }
@@ -644,6 +671,15 @@ __global__ void k_l_fill(LArgs a) {
     }
   }
 }
+// states of very many in-transitions, once per handle (hubs[0] starts at 0)
+__global__ void k_l_hubs(LArgs a) {
+  const GPart p = gpart();
+  for (uint32_t s = p.gtid; s < a.n; s += p.gthreads)
+    if (a.in_ptr[s + 1] - a.in_ptr[s] >= kHubDegree) {
+      const uint32_t i = atomicAdd(&a.hubs[0], 1u);
+      if (i < kHubCap) a.hubs[1 + i] = s;
+    }
+}
 __global__ void k_l_zero_cnt(LArgs a) {
   const GPart p = gpart();
   for (uint32_t b = p.gtid; b < a.n; b += p.gthreads) a.cnt[b] = 0;
@@ -803,6 +839,7 @@ bisim_status lists_alloc(bisim_lts* h) {
   int32_t** lists[] = {&L.ts, &L.tbk, &L.ss, &L.sbk, &L.sr, &L.sfi, &L.sne, &L.sps, &L.sse};
   for (int32_t** q : lists) BISIM_TRY(lalloc(q, n, s));
   BISIM_TRY(lalloc(&L.work, 8, s));
+  BISIM_TRY(lalloc(&L.hubs, 1 + kHubCap, s));
   return BISIM_OK;
 }
 
@@ -830,9 +867,10 @@ void lists_drop(bisim_lts* h) {
       (void**)&L.lb,   (void**)&L.lo,  (void**)&L.tmp64, (void**)&L.lh,  (void**)&L.ts,
       (void**)&L.tbk,  (void**)&L.ss,  (void**)&L.sbk,   (void**)&L.sr,  (void**)&L.sfi,
       (void**)&L.sne,  (void**)&L.sps, (void**)&L.sse,   (void**)&L.work, (void**)&L.trk,
-      (void**)&L.trk_save};
+      (void**)&L.trk_save, (void**)&L.hubs};
   give_back(h, ptrs);
   out_drop(h);
+  L.hubs_known = false;
 }
 
 // the kernels' arguments, and the refinable partition of the start partition
@@ -888,6 +926,7 @@ static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_tota
   a.sne = L.sne;
   a.sps = L.sps;
   a.sse = L.sse;
+  a.hubs = L.hubs;
   a.work = L.work;
   a.count = count_work_totals ? 1 : 0;
   a.ctl = h->ctl;
@@ -909,6 +948,11 @@ static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_tota
     BISIM_TRY_HIP(hipMemcpyAsync(L.be, L.bs, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
   hipLaunchKernelGGL(k_l_fill, dim3((unsigned)gi), dim3(kLT), 0, st, a);
   hipLaunchKernelGGL(k_l_zero_cnt, dim3((unsigned)gi), dim3(kLT), 0, st, a);
+  if (!L.hubs_known) {
+    hipLaunchKernelGGL(k_l_zero_u32, dim3(1), dim3(kLT), 0, st, L.hubs, 1u);
+    hipLaunchKernelGGL(k_l_hubs, dim3((unsigned)gi), dim3(kLT), 0, st, a);
+    L.hubs_known = true;
+  }
   BISIM_TRY_HIP(hipGetLastError());
   return BISIM_OK;
 }

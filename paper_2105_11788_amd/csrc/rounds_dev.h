@@ -1143,7 +1143,21 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       // ---- a splitter beyond the table: mark words per state
       ++nbig;
       const uint32_t cb = uniform_u32(sh.cb[0]), csz = uniform_u32(sh.csz0);
-      if (!dense && a.grid_edges && (uint64_t)csz * a.mean_deg >= a.grid_edges) {
+      bool grid = false;
+      if (!dense && a.grid_edges) {
+        grid = (uint64_t)csz * a.mean_deg >= a.grid_edges;
+        if (!grid) {  // few members, but they may be hubs: count
+          uint32_t edges = 0;
+          for (uint32_t i = tid; i < csz; i += WG)
+            edges += min((uint32_t)a.pin[cb + i], a.grid_edges);
+          if (tid == 0) sh.most = 0;
+          __syncthreads();
+          if (edges) atomicAdd(&sh.most, min(edges, a.grid_edges));
+          __syncthreads();
+          grid = uniform_u32(sh.most) >= a.grid_edges;
+        }
+      }
+      if (grid) {
         grid_C = C;  // its iteration is counted already
         if (track && wid == kWaves - 1) {  // the wave that took the entry
           wave_sync();

@@ -66,3 +66,29 @@ def test_sink_batch_load(B):
     print(f"[sink] batch load {st['t_pre_ms']:.1f} ms", flush=True)
     assert (got[0] == oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)[0]).all()
     assert st["t_pre_ms"] < 100  # (23 ms of them the load's atomics at the sink)
+
+
+@pytest.mark.parametrize("n,actions,loop", [(100_001, 10, False), (100_000, 10, True)])
+def test_sink_marked_by_the_grid(B, n, actions, loop):
+    """One state's in-transitions are spread over the grid, so a run is no
+    slower than engine 2's, whose wave takes them 64 at a time."""
+    L = sink(n, actions)
+    if loop:  # the sink has the others' actions: one block
+        L = gen.LTS(n, actions, *(np.concatenate([x, y]) for x, y in (
+            (L.src, np.zeros(actions, int)), (L.lab, np.arange(actions)),
+            (L.dst, np.zeros(actions, int)))))
+    dev = [B.DeviceArray.from_numpy(a, np.int32) for a in (L.src, L.lab, L.dst)]
+    out = B.DeviceArray(L.n, np.int32)
+    best = {}
+    with B.LTS(*dev, L.n, L.K, None) as h:
+        for engine in (3, 2):
+            h.set_option(B.OPT_ENGINE, engine)
+            h.run(out)
+            runs = [timed(lambda: h.run(out)) for _ in range(3)]
+            best[engine] = min(ms for _, ms in runs)
+            st = runs[0][0][1]
+            assert st.blocks == (1 if loop else 2) and st.iterations == (2 if loop else 3)
+            assert (out.numpy() == np.minimum(np.arange(n), 0 if loop else 1)).all()
+    print(f"[sink] {n} states, {L.m} transitions: engine 3 {best[3]:.2f} ms, 2 {best[2]:.2f}",
+          flush=True)
+    assert best[3] < 1.5 * best[2] + 1
