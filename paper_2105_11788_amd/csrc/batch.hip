@@ -52,9 +52,9 @@ struct bisim_batch {
   int32_t* sl = nullptr;
   int32_t *perm = nullptr, *pos = nullptr, *bs = nullptr, *be = nullptr, *cnt = nullptr,
           *fc = nullptr, *gc = nullptr, *tmp = nullptr, *rk = nullptr, *fi = nullptr,
-          *ob = nullptr, *nev = nullptr, *ltl = nullptr, *tlb = nullptr, *se = nullptr,
+          *ob = nullptr, *ltl = nullptr, *tlb = nullptr,
           *llo = nullptr, *lsz = nullptr;
-  uint64_t *sf = nullptr, *us = nullptr, *tmp64 = nullptr, *pin = nullptr;
+  uint64_t *us = nullptr, *tmp64 = nullptr, *pin = nullptr;
   uint8_t* trk = nullptr;
   uint32_t* iters_d = nullptr;  // [count]
   uint32_t* ctl_d = nullptr;    // [0] queue head, [1] error
@@ -96,9 +96,9 @@ struct BArgs {
   uint64_t *ub, *qb, *qs;
   int32_t* tl;
   int32_t* sl;
-  int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc, *tmp, *rk, *fi, *ob, *nev, *ltl, *tlb, *se, *llo,
+  int32_t *perm, *pos, *bs, *be, *cnt, *fc, *gc, *tmp, *rk, *fi, *ob, *ltl, *tlb, *llo,
       *lsz;
-  uint64_t *sf, *us, *tmp64, *pin;
+  uint64_t *us, *tmp64, *pin;
   uint32_t* out_ptr;  // transitions by source
   int32_t *out_dst, *out_ord;
   uint8_t* trk;
@@ -206,7 +206,6 @@ __global__ void k_batch_args(BArgs a, RoundsArgs<uint64_t>* __restrict__ out) {
   g.gc = a.gc + s0;
   g.nlb = a.nlb + s0;
   g.tmp64 = a.tmp64 + s0;
-  g.sf = a.sf + b0;
   g.ts = a.tl + s0;
   g.tb = a.tlb + s0;
   g.lb = a.ltl + s0;
@@ -216,9 +215,7 @@ __global__ void k_batch_args(BArgs a, RoundsArgs<uint64_t>* __restrict__ out) {
   g.sbk = a.ob + s0;
   g.sr = a.rk + s0;
   g.sfi = a.fi + s0;
-  g.sne = a.nev + s0;
   g.sps = a.tmp + s0;
-  g.sse = a.se + s0;
   g.ub = a.ub + b0;
   g.qb = a.qb + b0;
   g.us = a.us + b0;
@@ -300,8 +297,8 @@ void free_batch(bisim_batch* b) {
   void* ptrs[] = {b->n_off_d, b->bw_off_d, b->order_d, b->blk, b->mw,      b->nlb,  b->ub,
                   b->qb,      b->qs,       b->tl,      b->sl,  b->iters_d, b->ctl_d, b->perm,
                   b->pos,     b->bs,       b->be,      b->cnt, b->fc,      b->gc,    b->tmp,
-                  b->rk,      b->fi,       b->ltl,     b->sf,  b->us,      b->ob,    b->nev,
-                  b->tlb,     b->se,       b->tmp64,   b->work_d, b->llo, b->lsz,
+                  b->rk,      b->fi,       b->ltl,     b->us,  b->ob,
+                  b->tlb,     b->tmp64,   b->work_d, b->llo, b->lsz,
                   b->pin,     b->trk,      b->args_d};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -341,15 +338,12 @@ BArgs make_args(bisim_batch* b, int32_t* out) {
   a.rk = b->rk;
   a.fi = b->fi;
   a.ob = b->ob;
-  a.nev = b->nev;
   a.ltl = b->ltl;
   a.tlb = b->tlb;
-  a.se = b->se;
   a.llo = b->llo;
   a.lsz = b->lsz;
   a.tmp64 = b->tmp64;
   a.pin = b->pin;
-  a.sf = b->sf;
   a.us = b->us;
   a.out_ptr = b->u->lists.out_ptr;
   a.out_dst = b->u->lists.out_dst;
@@ -634,10 +628,10 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
         (st = dmalloc(&b->cnt, (size_t)N)) || (st = dmalloc(&b->fc, (size_t)N)) ||
         (st = dmalloc(&b->gc, (size_t)N)) || (st = dmalloc(&b->tmp, (size_t)N)) ||
         (st = dmalloc(&b->rk, (size_t)N)) || (st = dmalloc(&b->fi, (size_t)N)) ||
-        (st = dmalloc(&b->ltl, (size_t)N)) || (st = dmalloc(&b->sf, BW)) ||
-        (st = dmalloc(&b->ob, (size_t)N)) || (st = dmalloc(&b->nev, (size_t)N)) ||
+        (st = dmalloc(&b->ltl, (size_t)N)) ||
+        (st = dmalloc(&b->ob, (size_t)N)) ||
         (st = dmalloc(&b->us, BW)) || (st = dmalloc(&b->tlb, (size_t)N)) ||
-        (st = dmalloc(&b->se, (size_t)N)) || (st = dmalloc(&b->tmp64, (size_t)N)) ||
+        (st = dmalloc(&b->tmp64, (size_t)N)) ||
         (st = dmalloc(&b->pin, (size_t)N)) || (st = dmalloc(&b->trk, (size_t)N)) ||
         (st = dmalloc(&b->llo, (size_t)N)) || (st = dmalloc(&b->lsz, (size_t)N)) ||
         (st = dmalloc(&b->iters_d, count)) || (st = dmalloc(&b->ctl_d, 2)) ||

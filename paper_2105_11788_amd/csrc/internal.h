@@ -213,6 +213,7 @@ struct bisim_lists {
   uint8_t* trk = nullptr;
   uint32_t* trk_save = nullptr;
   uint32_t* hubs = nullptr;  // states of very many in-transitions
+  uint32_t nhubs = 0;
   bool hubs_known = false;
   // the captured graph of a chunk of iterations and the arguments it holds
   hipGraphExec_t gexec = nullptr;

@@ -72,7 +72,10 @@ constexpr int kPhases = 3;  // kernels per iteration
 // states of so many in-transitions are marked by the whole grid if there are
 // at most kHubCap of them (with more, waves have about as much each)
 constexpr uint32_t kHubDegree = 4096, kHubCap = 1024;
-constexpr uint32_t kManyMembers = 8192;
+constexpr uint32_t kManyMembers = 8192, kQueueMembers = 512;
+// mean in-degree from which the marks of a large splitter repeat.  The heavier
+// kernel costs others 2.6 us of 15 (planted quotient of 1.03M states, mean 8).
+constexpr uint32_t kRepeatDegree = 16;
 
 struct LArgs {
   uint32_t n;
@@ -101,6 +104,7 @@ struct LArgs {
   uint32_t lcap;
   uint32_t mpw;  // splitter members per wave and step of the mark kernel
   uint32_t* hubs;  // [1 + kHubCap] number of states of kHubDegree in-transitions, and these
+  uint32_t nhubs;  // their number, if the whole grid marks them
   int32_t *ts, *tbk;  // touched states and their blocks
   int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;  // split states (by list index)
   uint64_t* work;  // [8] totals when counting
@@ -179,6 +183,8 @@ __device__ __forceinline__ bool marks_differ(const LArgs& a, int32_t s, int32_t 
 // ---------------------------------------------------------------------------
 // M: select, mark
 // ---------------------------------------------------------------------------
+// kHeavy: for LTSs with hubs or of a high mean degree (mark_kernel)
+template <bool kHeavy>
 __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   const uint32_t done = a.ctl->state.v[1];
   const uint32_t k = iter_of(a, kofs);
@@ -193,7 +199,6 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   const bool lane_first = lane() < a.mpw && i_first < kWave;
   const uint32_t pf_lo = lane_first ? pc[4 + 2 * i_first] : 0u;
   const uint32_t pf_hi = lane_first ? pc[5 + 2 * i_first] : 0u;
-  const uint32_t hubs = a.hubs[0] <= kHubCap ? a.hubs[0] : 0u;  // (too many: as other members)
   if (idle(a, done)) return;
   const bool over = k + 1 > a.iter_cap;
   if (C0 == kNone || over) {  // the final pass, or the iteration cap
@@ -258,21 +263,25 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
     atomicAdd((unsigned long long*)&a.work[0], (unsigned long long)csz);
   }
   // one transition per lane with `valid`: mark its source's slot and touch it
-  // (wave-uniform call).  A large splitter's transitions often give a mark
-  // that is there already (100k states, 200 transitions each: 5.9 ms an
-  // iteration): it is read first, and whoever set it has touched the source.
-  const bool many = csz >= kManyMembers;
+  // (wave-uniform call).  Where states have many transitions, those of a large
+  // splitter often give a mark that is there already (100k states, 200
+  // transitions each: 5.9 ms an iteration): it is read first, and whoever set
+  // it has touched the source.
+  const bool many = kHeavy && csz >= kManyMembers;
   const auto visit = [&](bool valid, uint32_t edge) {
+    if (kHeavy && many) {
+      if (valid) {
+        const int32_t o = a.in_ord[edge];
+        valid = !((*mword(a, a.in_src[edge], o) >> (o & 63)) & 1ull);
+      }
+      if (__ballot(valid) == 0) return;
+    }
     bool first = false, lead = false;
-    int32_t s = 0, b = 0, o = 0;
+    int32_t s = 0, b = 0;
     uint32_t lo_ = 0, hi_ = 0;
     if (valid) {
       s = a.in_src[edge];
-      o = a.in_ord[edge];
-      if (many) valid = !((*mword(a, s, o) >> (o & 63)) & 1ull);
-    }
-    if (many && __ballot(valid) == 0) return;
-    if (valid) {
+      const int32_t o = a.in_ord[edge];
       // the source's block and, in case it leads that block, the block's
       // range are loaded beside the atomics (one round trip, not three)
       b = a.block[s];
@@ -285,7 +294,12 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
       // a touched leader of a one-state block has no untouched member
       lead = first && b == s && hi_ > lo_ + 1 && hi_ <= a.n;
     }
-    if (first) atomicAdd(&a.tcn[b], 1);
+    // the sources of a large splitter are members of large blocks, and would
+    // queue at their counts (1M states in 100 blocks 321 -> 147 us a kernel)
+    if (kHeavy || csz >= kQueueMembers)
+      (void)add_group(a.tcn, (uint32_t)b, first, group_of<8>((uint32_t)b, first));
+    else if (first)
+      atomicAdd(&a.tcn[b], 1);
     // list entries for first touches and for the listed block's member
     // segments (each with its absolute position range): both wave-aggregated
     // reservations are issued before either result is used
@@ -336,7 +350,7 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
         beg = (uint32_t)(x >> 32);
         deg = (uint32_t)x;
       }
-      if (hubs && deg >= kHubDegree) deg = 0;  // every wave's, below
+      if (kHeavy && deg >= kHubDegree && a.nhubs) deg = 0;  // every wave's, below
     }
     const uint32_t incl = wave_incl_scan_u32(deg);
     const uint32_t total = (uint32_t)__shfl((int)incl, kWave - 1, kWave);
@@ -354,8 +368,8 @@ __global__ void __launch_bounds__(kLT) k_l_mark(LArgs a, uint32_t kofs) {
   }
   // the hubs of C: their transitions over all waves (by the wave that has the
   // member, 64 at a time, a sink of 1M in-transitions took 21 ms)
-  for (uint32_t h0 = 0; h0 < hubs; h0 += kWave) {
-    const uint32_t h = h0 + lane() < hubs ? a.hubs[1 + h0 + lane()] : kNone;
+  for (uint32_t h0 = 0; kHeavy && h0 < a.nhubs; h0 += kWave) {
+    const uint32_t h = h0 + lane() < a.nhubs ? a.hubs[1 + h0 + lane()] : kNone;
     uint64_t mine = __ballot(h != kNone && (uint32_t)a.block[h != kNone ? h : 0] == C);
     while (mine) {
       const uint32_t s = lane_u32(h, (uint32_t)(__ffsll((unsigned long long)mine) - 1));
@@ -417,13 +431,10 @@ __global__ void __launch_bounds__(kLT) k_l_compare(LArgs a, uint32_t kofs) {
         b = a.tbk[i];
         sp = (b != s) && marks_differ(a, s, b);
       }
-      int32_t r = 0;
-      if (sp) {
-        atomicMax((unsigned long long*)&a.nlw[b],
-                  (unsigned long long)(epoch | (uint64_t)(kNone - (uint32_t)s)));
-        r = atomicAdd(&a.cnt[b], 1);
-        atomicOr((unsigned long long*)&a.sf[s >> 6], 1ull << (s & 63));
-      }
+      const Group g = group_of<8>((uint32_t)b, sp);
+      bid_min(a.nlw, (uint32_t)b, epoch, (uint32_t)s, sp, g);
+      const int32_t r = add_one(a.cnt, (uint32_t)b, sp, g);
+      if (sp) atomicOr((unsigned long long*)&a.sf[s >> 6], 1ull << (s & 63));
       const uint32_t si = reserve(nS, sp);
       if (sp && si < n) {
         a.ss[si] = s;
@@ -483,31 +494,45 @@ __global__ void __launch_bounds__(kLT) k_l_compare(LArgs a, uint32_t kofs) {
 // so the two steps that need every split state's bookkeeping in between take
 // one kernel, not two.  Every workgroup then clears touched states.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void relabel_one(const LArgs& a, uint32_t i) {
+// split state i (i < nS: there is one); wave-uniform call
+__device__ __forceinline__ void relabel_one(const LArgs& a, uint32_t i, uint32_t nS) {
   const uint32_t n = a.n;
-  const int32_t s = a.ss[i], b = a.sbk[i], r = a.sr[i];
-  const uint64_t nv = a.nlw[b];
-  const int32_t e = a.be[b], c = a.cnt[b], pv = a.pos[s];
-  const int32_t nl = (int32_t)(kNone - (uint32_t)nv);
-  a.block[s] = nl;
-  // rounds: a split part with different marks (they are cleared by a kernel
-  // of its own then)
-  if (a.gated && marks_differ(a, s, nl)) a.ctl->state.v[9] = 1;
-  const int32_t ne = e - c, q = ne + r;
-  int32_t fv = -1, uv = -1;
-  const bool ok = ne >= 0 && q >= ne && q < e && e <= (int32_t)n && pv >= 0 && pv < (int32_t)n;
-  if (ok) {
-    if (pv < ne) fv = atomicAdd(&a.fc[b], 1);
-    uv = a.perm[q];  // every tail position is examined once
-  } else {
-    a.ctl->state.v[4] = 1;  // never expected
+  const bool on = i < nS;
+  int32_t s = 0, b = 0, r = 0, e = 0, c = 0, pv = 0, nl = 0;
+  if (on) {
+    s = a.ss[i];
+    b = a.sbk[i];
+    r = a.sr[i];
+    const uint64_t nv = a.nlw[b];
+    e = a.be[b];
+    c = a.cnt[b];
+    pv = a.pos[s];
+    nl = (int32_t)(kNone - (uint32_t)nv);
+    a.block[s] = nl;
+    // rounds: a split part with different marks (they are cleared by a kernel
+    // of its own then)
+    if (a.gated && marks_differ(a, s, nl)) a.ctl->state.v[9] = 1;
   }
-  a.sfi[i] = fv;
-  a.sne[i] = ok ? ne : 0;
-  a.sps[i] = ok ? pv : 0;
-  a.sse[i] = (ok && nl == s) ? e : -1;
-  if (uv >= 0 && uv < (int32_t)n && !test_bit(a.sf, (uint32_t)uv)) {
-    const int32_t jj = atomicAdd(&a.gc[b], 1);
+  const int32_t ne = e - c, q = ne + r;
+  int32_t uv = -1;
+  const bool ok =
+      on && ne >= 0 && q >= ne && q < e && e <= (int32_t)n && pv >= 0 && pv < (int32_t)n;
+  if (ok) uv = a.perm[q];  // every tail position is examined once
+  else if (on) a.ctl->state.v[4] = 1;  // never expected
+  const bool front = ok && pv < ne;
+  const bool stays = uv >= 0 && uv < (int32_t)n && !test_bit(a.sf, (uint32_t)uv);
+  // (both counts are under way before either is waited for)
+  const Group gf = group_of((uint32_t)b, front), gs = group_of((uint32_t)b, stays);
+  const int32_t f0 = add_group(a.fc, (uint32_t)b, front, gf);
+  const int32_t j0 = add_group(a.gc, (uint32_t)b, stays, gs);
+  const int32_t fv = rank_in(f0, gf), jj = rank_in(j0, gs);
+  if (on) {
+    a.sfi[i] = front ? fv : -1;
+    a.sne[i] = ok ? ne : 0;
+    a.sps[i] = ok ? pv : 0;
+    a.sse[i] = (ok && nl == s) ? e : -1;
+  }
+  if (stays) {
     if (ne + jj < e)
       a.tmp64[ne + jj] = ((uint64_t)(uint32_t)uv << 32) | (uint32_t)q;
     else
@@ -590,14 +615,14 @@ __global__ void __launch_bounds__(kLT) k_l_split(LArgs a, uint32_t kofs) {
     count_work(a, 7, nS > 0 ? 1 : 0);
   }
   if (a.gated) {  // rounds: the swaps and the clearing are a kernel of their own
-    for (uint32_t i = p.gtid; i < nS; i += p.gthreads) relabel_one(a, i);
+    for (uint32_t i0 = p.gwave * kWave; i0 < nS; i0 += p.gthreads) relabel_one(a, i0 + lane(), nS);
     return;
   }
   // workgroup-uniform: the first R workgroups relabel, one split state per thread
   const uint32_t R = min((nS + kLT - 1) / kLT, gridDim.x);
   if (blockIdx.x < R) {
     count_work(a, 5, p.gtid == 0 ? nS : 0);
-    for (uint32_t i = p.gtid; i < nS; i += R * kLT) relabel_one(a, i);
+    for (uint32_t i0 = p.gwave * kWave; i0 < nS; i0 += R * kLT) relabel_one(a, i0 + lane(), nS);
     __threadfence();  // release this workgroup's bookkeeping
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -653,21 +678,78 @@ __global__ void k_l_zero(LArgs a) {
   if (p.gtid < 8) a.work[p.gtid] = 0;
   if (p.gtid < 2) a.pf[p.gtid * kPfWords + 3] = 0;
 }
-__global__ void k_l_count(LArgs a) {
-  const GPart p = gpart();
-  for (uint32_t s = p.gtid; s < a.n; s += p.gthreads) atomicAdd(&a.cnt[a.block[s]], 1);
+// One counter per block, added to by every state: first in a table of the
+// workgroup's kSetupRun states, then once per workgroup and block (a run of 5M
+// states in two blocks: 115 ms with an atomic per state, 2.1 with one per
+// wave, 0.4 so).
+constexpr uint32_t kSetupPer = 8, kSetupRun = kSetupPer * kLT, kSetupSlots = 1024;
+struct SetupTable {
+  uint32_t key[kSetupSlots], count[kSetupSlots];
+};
+// adds the states [r0, r0 + kSetupRun) to counter; rank[u]: the counter's value
+// before state r0 + u kLT + thread (workgroup-uniform call)
+__device__ __forceinline__ void setup_ranks(const LArgs& a, SetupTable& t, uint32_t r0,
+                                            int32_t* counter, uint32_t rank[kSetupPer]) {
+  for (uint32_t q = threadIdx.x; q < kSetupSlots; q += kLT) {
+    t.key[q] = kNone;
+    t.count[q] = 0;
+  }
+  __syncthreads();
+  uint32_t slot[kSetupPer];
+#pragma unroll
+  for (uint32_t u = 0; u < kSetupPer; ++u) {
+    const uint32_t s = r0 + u * kLT + threadIdx.x;
+    const bool on = s < a.n;
+    const uint32_t b = on ? (uint32_t)a.block[s] : 0u;
+    const Group g = group_of<1>(b, on);
+    uint32_t q = table_hash(b, 32 - 10);
+    if (on && lane() == g.lead) {
+      // (at most kSetupRun distinct keys: half of them may find the table full)
+      uint32_t probe = 0;
+      for (; probe < 32; ++probe, q = (q + 1) & (kSetupSlots - 1)) {
+        const uint32_t old = atomicCAS(&t.key[q], kNone, b);
+        if (old == kNone || old == b) break;
+      }
+      rank[u] = probe < 32 ? atomicAdd(&t.count[q], g.count)
+                           : (uint32_t)atomicAdd(&counter[b], (int32_t)g.count);
+      if (probe == 32) q = kNone;
+    }
+    rank[u] = (uint32_t)__shfl((int)rank[u], (int)g.lead, kWave) + g.below;
+    slot[u] = (uint32_t)__shfl((int)q, (int)g.lead, kWave);
+  }
+  __syncthreads();
+  for (uint32_t q = threadIdx.x; q < kSetupSlots; q += kLT)
+    if (t.key[q] != kNone) t.count[q] = (uint32_t)atomicAdd(&counter[t.key[q]], (int32_t)t.count[q]);
+  __syncthreads();
+#pragma unroll
+  for (uint32_t u = 0; u < kSetupPer; ++u)
+    if (slot[u] != kNone) rank[u] += t.count[slot[u]];
+  __syncthreads();
 }
-__global__ void k_l_fill(LArgs a) {
-  const GPart p = gpart();
-  for (uint32_t s = p.gtid; s < a.n; s += p.gthreads) {
-    const uint32_t q = (uint32_t)atomicAdd(&a.be[a.block[s]], 1);
-    if (q < a.n) {
-      a.perm[q] = (int32_t)s;
-      a.pos[s] = (int32_t)q;
-      const uint32_t e0 = a.in_ptr[s];
-      a.pin[q] = ((uint64_t)e0 << 32) | (a.in_ptr[s + 1] - e0);
-    } else {
-      a.ctl->state.v[4] = 1;  // never expected
+__global__ void __launch_bounds__(kLT) k_l_count(LArgs a) {
+  __shared__ SetupTable t;
+  for (uint64_t r = (uint64_t)blockIdx.x * kSetupRun; r < a.n; r += (uint64_t)gridDim.x * kSetupRun) {
+    uint32_t rank[kSetupPer];
+    setup_ranks(a, t, (uint32_t)r, a.cnt, rank);
+  }
+}
+__global__ void __launch_bounds__(kLT) k_l_fill(LArgs a) {
+  __shared__ SetupTable t;
+  for (uint64_t r = (uint64_t)blockIdx.x * kSetupRun; r < a.n; r += (uint64_t)gridDim.x * kSetupRun) {
+    uint32_t rank[kSetupPer];
+    setup_ranks(a, t, (uint32_t)r, a.be, rank);
+#pragma unroll
+    for (uint32_t u = 0; u < kSetupPer; ++u) {
+      const uint32_t s = (uint32_t)r + u * kLT + threadIdx.x, q = rank[u];
+      if (s >= a.n) continue;
+      if (q < a.n) {
+        a.perm[q] = (int32_t)s;
+        a.pos[s] = (int32_t)q;
+        const uint32_t e0 = a.in_ptr[s];
+        a.pin[q] = ((uint64_t)e0 << 32) | (a.in_ptr[s + 1] - e0);
+      } else {
+        a.ctl->state.v[4] = 1;  // never expected
+      }
     }
   }
 }
@@ -873,6 +955,11 @@ void lists_drop(bisim_lts* h) {
   L.hubs_known = false;
 }
 
+static void (*mark_kernel(const bisim_lts* h, const LArgs& a))(LArgs, uint32_t) {
+  const bool repeat = h->m >= (int64_t)kRepeatDegree * h->n;
+  return a.nhubs || repeat ? k_l_mark<true> : k_l_mark<false>;
+}
+
 // the kernels' arguments, and the refinable partition of the start partition
 static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_totals, bool fill,
                                 LArgs& a) {
@@ -940,19 +1027,25 @@ static bisim_status lists_setup(bisim_lts* h, uint32_t cap, bool count_work_tota
   int64_t gi = ((int64_t)n + kLT - 1) / kLT;
   gi = gi > cu * 8 ? cu * 8 : (gi < 1 ? 1 : gi);
   hipLaunchKernelGGL(k_l_zero, dim3((unsigned)gi), dim3(kLT), 0, st, a);
-  hipLaunchKernelGGL(k_l_count, dim3((unsigned)gi), dim3(kLT), 0, st, a);
+  int64_t gr = ((int64_t)n + kSetupRun - 1) / kSetupRun;
+  gr = gr > cu * 8 ? cu * 8 : (gr < 1 ? 1 : gr);
+  hipLaunchKernelGGL(k_l_count, dim3((unsigned)gr), dim3(kLT), 0, st, a);
   BISIM_TRY_HIP(hipGetLastError());
   BISIM_TRY(exclusive_scan_u32(reinterpret_cast<const uint32_t*>(L.cnt),
                                reinterpret_cast<uint32_t*>(L.bs), n, st));
   if (n > 0)
     BISIM_TRY_HIP(hipMemcpyAsync(L.be, L.bs, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
-  hipLaunchKernelGGL(k_l_fill, dim3((unsigned)gi), dim3(kLT), 0, st, a);
+  hipLaunchKernelGGL(k_l_fill, dim3((unsigned)gr), dim3(kLT), 0, st, a);
   hipLaunchKernelGGL(k_l_zero_cnt, dim3((unsigned)gi), dim3(kLT), 0, st, a);
   if (!L.hubs_known) {
     hipLaunchKernelGGL(k_l_zero_u32, dim3(1), dim3(kLT), 0, st, L.hubs, 1u);
     hipLaunchKernelGGL(k_l_hubs, dim3((unsigned)gi), dim3(kLT), 0, st, a);
+    BISIM_TRY_HIP(hipGetLastError());
+    BISIM_TRY_HIP(hipMemcpyAsync(&L.nhubs, L.hubs, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    BISIM_TRY_HIP(hipStreamSynchronize(st));
     L.hubs_known = true;
   }
+  a.nhubs = L.nhubs <= kHubCap ? L.nhubs : 0;
   BISIM_TRY_HIP(hipGetLastError());
   return BISIM_OK;
 }
@@ -966,6 +1059,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
   bisim_lists& L = h->lists;
   LArgs a;
   BISIM_TRY(lists_setup(h, cap, count_work_totals, true, a));
+  const auto mark = mark_kernel(h, a);
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   const int grid = h->grid > 0 ? h->grid : cu * 8;
   h->run_grid = grid;
@@ -1004,7 +1098,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
           if (!ends[kPhases - 1]) ends[kPhases - 1] = h->pev[8 * sampled.size()];
           carry = ends[kPhases - 1];
         }
-        go(k_l_mark, ends[0], k);
+        go(mark, ends[0], k);
         go(k_l_compare, ends[1], k);
         go(k_l_split, ends[2], k);
       }
@@ -1032,7 +1126,7 @@ bisim_status lists_loop(bisim_lts* h, uint32_t cap, bool count_work_totals) {
       hipGraph_t graph = nullptr;
       BISIM_TRY_HIP(hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal));
       for (uint32_t j = 0; j < kGraphIters; ++j) {
-        hipLaunchKernelGGL(k_l_mark, dim3(grid), dim3(kLT), 0, gs, a, j);
+        hipLaunchKernelGGL(mark, dim3(grid), dim3(kLT), 0, gs, a, j);
         hipLaunchKernelGGL(k_l_compare, dim3(grid), dim3(kLT), 0, gs, a, j);
         hipLaunchKernelGGL(k_l_split, dim3(grid), dim3(kLT), 0, gs, a, j);
       }
@@ -1151,7 +1245,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.iter_cap = cap;
   a.rcpp = rcpp ? 1 : 0;
   a.mean_deg = (uint32_t)(n ? (h->m + n - 1) / n : 1);
-  a.grid_edges = !rcpp && !start && h->m >= (int64_t)kGridEdges ? kGridEdges : 0;
+  a.grid_edges = !rcpp && !start && h->m + (int64_t)n >= (int64_t)kGridEdges ? kGridEdges : 0;
   a.in_ptr = h->in_ptr;
   a.in_src = h->in_src;
   a.in_ord = h->in_ord;
@@ -1167,7 +1261,6 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.gc = L.gc;
   a.nlb = h->nlw;
   a.tmp64 = L.tmp64;
-  a.sf = h->sb;
   a.ts = L.ts;
   a.tb = L.tbk;
   a.lb = L.lb;
@@ -1177,9 +1270,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.sbk = L.sbk;
   a.sr = L.sr;
   a.sfi = L.sfi;
-  a.sne = L.sne;
   a.sps = L.sps;
-  a.sse = L.sse;
   a.ub = h->ub;
   a.us = h->us;
   a.qb = l.qb;
@@ -1201,6 +1292,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   hipLaunchKernelGGL(kerns[0], dim3(1), dim3(kRWG), lds_bytes, st, a, h->ctl, L.pf, start,
                      lds_bytes);
   BISIM_TRY_HIP(hipGetLastError());
+  const auto mark = mark_kernel(h, l);
   uint64_t launched = 0;
   for (uint32_t reps = 1;;) {
     BISIM_TRY_HIP(hipMemcpyAsync(&h->ctl_host->state, &h->ctl->state, sizeof(Line),
@@ -1217,7 +1309,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
       continue;
     }
     for (uint32_t r = 0; r < reps; ++r) {
-      hipLaunchKernelGGL(k_l_mark, dim3(grid), dim3(kLT), 0, st, l, 0u);
+      hipLaunchKernelGGL(mark, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_compare, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_split, dim3(grid), dim3(kLT), 0, st, l, 0u);
       hipLaunchKernelGGL(k_l_move, dim3(grid), dim3(kLT), 0, st, l);

@@ -83,8 +83,12 @@ constexpr uint32_t kTrackLook = 256;  // rounds between two looks at the largest
 template <class MaskT, int kMode, bool kBm>
 constexpr uint32_t out_u() { return kMode != 2 ? 8 : sizeof(MaskT) == 4 && kBm ? 6 : 2; }
 constexpr uint32_t kListCap = 64;    // listed blocks kept in LDS
+constexpr uint32_t kWideCap = 8;     // blocks split by what stays, at a time
+// members of such blocks from which the iteration is the grid's
+constexpr uint32_t kGridMembers = 1u << 16;
 constexpr uint32_t kOwnBlock = 128;  // members up to which a wave takes a listed block alone
 constexpr uint32_t kScanU = 2;       // states or transitions in flight per thread
+constexpr uint32_t kWideU = 4;       // members of a wide block in flight per thread
 // transitions per thread and round
 template <int WG>
 constexpr uint32_t edges_per_thread() { return WG >= 512 ? 2 : 4; }
@@ -113,10 +117,10 @@ struct RoundsArgs {
   // used by splitters beyond the table, and by splits of more than WG states
   MaskT* mw;                              // zero between iterations
   int32_t *cnt, *fc, *gc;                 // zero between iterations
-  uint64_t *nlb, *tmp64, *sf;             // sf zero between iterations
+  uint64_t *nlb, *tmp64;
   int32_t *ts, *tb;                       // touched states and their blocks
   int32_t *lb, *llo, *lsz;                // listed blocks and their ranges
-  int32_t *ss, *sbk, *sr, *sfi, *sne, *sps, *sse;
+  int32_t *ss, *sbk, *sr, *sfi, *sps;
   // transitions by source, and per label its entry among the tracked ones plus
   // one (0: not tracked); null: no tracking
   uint32_t* out_ptr;
@@ -165,6 +169,11 @@ struct RoundsShared {
   uint8_t mc[WG];
   int32_t ss[small_split<WG>()], sb[small_split<WG>()];  // the first split states and their blocks
   uint32_t lb[kListCap], llo[kListCap], lsz[kListCap];   // the first listed blocks
+  // blocks whose touched leader has kSmall untouched members or more:
+  // candidate, block, first position, members
+  uint32_t wc[kWideCap], wb[kWideCap], wlo[kWideCap], wsz[kWideCap];
+  uint32_t nW;                      // such blocks found
+  uint32_t wmin, wstay, wfront, wback;  // of the one at hand
   uint32_t nc, np, mtot, etot, csz0, nT, tctr, bad;
   union {
     unsigned long long nSL;
@@ -259,6 +268,60 @@ __device__ __forceinline__ uint32_t list_push(uint32_t* counter, bool pred) {
   if ((int)lane() == leader) base = atomicAdd(counter, (uint32_t)__popcll(bal));
   base = lane_u32(base, (uint32_t)leader);
   return pred ? base + bits_below(bal) : kNone;
+}
+
+// Lanes with equal keys: for the first few keys of the wave, the lane that
+// speaks for this one, how many it speaks for, and how many of them are below
+// (every other lane speaks for itself).  Wave-uniform call.
+struct Group {
+  uint32_t lead, count, below;
+};
+template <int kKeys = 4>
+__device__ __forceinline__ Group group_of(uint32_t key, bool on) {
+  Group g{lane(), on ? 1u : 0u, 0u};
+  uint64_t todo = __ballot(on);
+  for (int k = 0; k < kKeys && todo; ++k) {
+    const uint32_t l = (uint32_t)(__ffsll((unsigned long long)todo) - 1);
+    const uint32_t first = lane_u32(key, l);
+    const bool mine = on && key == first;
+    const uint64_t same = __ballot(mine);
+    todo &= ~same;
+    if (__popcll(same) == 1) break;  // (keys that differ mostly differ all)
+    if (mine) g = {l, (uint32_t)__popcll(same), bits_below(same)};
+  }
+  return g;
+}
+// counter[key] += 1 per lane with `on`, by one atomic per group (the counter of
+// a large block otherwise takes 10 ns per state): the value before, on the
+// lanes that lead.  rank_in: the value before each lane's (wave-uniform call).
+__device__ __forceinline__ int32_t add_group(int32_t* counter, uint32_t key, bool on,
+                                             const Group& g) {
+  int32_t base = 0;
+  if (on && lane() == g.lead) base = atomicAdd(&counter[key], (int32_t)g.count);
+  return base;
+}
+__device__ __forceinline__ int32_t rank_in(int32_t base, const Group& g) {
+  return (int32_t)__shfl(base, (int)g.lead, kWave) + (int32_t)g.below;
+}
+__device__ __forceinline__ int32_t add_one(int32_t* counter, uint32_t key, bool on,
+                                           const Group& g) {
+  return rank_in(add_group(counter, key, on, g), g);
+}
+// word[key] = max(word[key], epoch | kNone - s) per lane with `on`, by one
+// atomic per group.  Wave-uniform call.
+__device__ __forceinline__ void bid_min(uint64_t* word, uint32_t key, uint64_t epoch, uint32_t s,
+                                        bool on, const Group& g) {
+  uint64_t leads = __ballot(on && lane() == g.lead && g.count > 1);
+  while (leads) {
+    const uint32_t l = (uint32_t)(__ffsll((unsigned long long)leads) - 1);
+    leads &= leads - 1;
+    const bool mine = on && g.lead == l;
+    const uint32_t least = wave_min_u32(mine ? s : kNone);
+    if (mine) s = least;
+  }
+  if (on && lane() == g.lead)
+    atomicMax((unsigned long long*)&word[key],
+              (unsigned long long)(epoch | (uint64_t)(kNone - s)));
 }
 
 // entry i of the split list and of the list of blocks: in LDS, beyond its
@@ -403,7 +466,6 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
     if (lane() == 0) {
       a.ub[q] = bits;
       a.qb[q] = bits;
-      a.sf[q] = 0;
     }
   }
   if (tid == 0) sh.bad = 0;
@@ -416,7 +478,11 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
       a.qs[q] = bits;
     }
   }
-  for (uint32_t s = tid; s < n; s += WG) atomicAdd(&a.cnt[a.blk[s]], 1);
+  for (uint32_t i0 = wid * kWave; i0 < n; i0 += WG) {
+    const uint32_t s = i0 + lane();
+    const uint32_t b = s < n ? (uint32_t)a.blk[s] : 0u;
+    (void)add_group(a.cnt, b, s < n, group_of(b, s < n));
+  }
   __syncthreads();
   {  // block ranges: exclusive prefix sums of the sizes in label order
     const uint32_t per = (n + WG - 1) / WG;
@@ -436,8 +502,11 @@ __device__ __forceinline__ bool rounds_setup(const RoundsArgs<MaskT>& a, RoundsS
     }
   }
   __syncthreads();
-  for (uint32_t s = tid; s < n; s += WG) {
-    const uint32_t p = (uint32_t)atomicAdd(&a.be[a.blk[s]], 1);
+  for (uint32_t i0 = wid * kWave; i0 < n; i0 += WG) {
+    const uint32_t s = i0 + lane();
+    const uint32_t b = s < n ? (uint32_t)a.blk[s] : 0u;
+    const uint32_t p = (uint32_t)add_one(a.be, b, s < n, group_of(b, s < n));
+    if (s >= n) continue;
     if (p >= n) {  // cannot happen with consistent counts; report, never write
       sh.bad = 1;
       continue;
@@ -741,6 +810,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
   const auto reset = [&]() {  // the first wave
     if (tid == 0) {
       sh.nS = sh.nL = sh.nT = 0;
+      sh.nW = 0;
       sh.tctr = 0;
       sh.fent = sh.ffresh = sh.mixed = sh.nself = 0;
     }
@@ -861,6 +931,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
     MaskT mv[EU], lmv[EU];  // a touched state's marks, its leader's
     bool part[EU];          // it leads a block with untouched members
     uint64_t split = 0;  // candidates that split something
+    uint32_t nwide = 0;  // wide blocks of all candidates
     if (np) {
       // ---- transitions: insert (candidate, source), collect its marks
       uint32_t eo[EU];
@@ -1005,11 +1076,25 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       for (uint32_t u = 0; u < EU; ++u) {
         part[u] = false;
         if (mv[u] == 0 || eb[u] != es[u]) continue;
-        part[u] = t_cnt[sl[u]] != sz[u];
-        if (part[u]) sh.unst[ek[u] >> kKeyBits] = 1;
+        const uint32_t untouched = sz[u] - t_cnt[sl[u]];
+        part[u] = untouched != 0;
+        if (!part[u]) continue;
+        const uint32_t c = ek[u] >> kKeyBits;
+        sh.unst[c] = 1;
+        if (__builtin_expect(untouched >= kSmall, 0)) {
+          const uint32_t i = atomicAdd(&sh.nW, 1u);
+          if (i < kWideCap) {
+            sh.wc[i] = c;
+            sh.wb[i] = es[u];
+            sh.wlo[i] = lo[u];
+            sh.wsz[i] = sz[u];
+          }
+        }
       }
       __syncthreads();
-      split = __ballot(lane() < np && sh.unst[lane() & (kCand - 1)] != 0);
+      const uint32_t unst = sh.unst[lane() & (kCand - 1)], v_nw = sh.nW;
+      split = __ballot(lane() < np && unst != 0);
+      nwide = min(uniform_u32(v_nw), kWideCap);
     }
     const uint32_t f = split ? (uint32_t)(__ffsll((unsigned long long)split) - 1) : np;
     // ---- verdicts, and the iterations that split nothing: every unstable
@@ -1084,6 +1169,17 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       return kRoundsGo;
     }
     want = kCand / 2;
+    // C's iteration (counted already) is carried out by the grid
+    const auto to_grid = [&]() -> uint32_t {
+      grid_C = C;
+      if (track && wid == kWaves - 1) {  // the wave that took the entry
+        wave_sync();
+        if (lane() == 0 && sh.ffresh) a.trk[C] = 0;
+      }
+      if (tid == 0) sh.nbig = nbig;
+      return kRoundsGrid;
+    };
+    uint32_t wides = 0;  // wide blocks that C splits
     // the members of the listed blocks that `is_split` says are split off
     const auto members = [&](const auto& is_split) {
       const uint32_t nL = uniform_u32(sh.nL);
@@ -1157,15 +1253,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           grid = uniform_u32(sh.most) >= a.grid_edges;
         }
       }
-      if (grid) {
-        grid_C = C;  // its iteration is counted already
-        if (track && wid == kWaves - 1) {  // the wave that took the entry
-          wave_sync();
-          if (lane() == 0 && sh.ffresh) a.trk[C] = 0;
-        }
-        if (tid == 0) sh.nbig = nbig;
-        return kRoundsGrid;
-      }
+      if (grid) return to_grid();
       count(tid == 0, kWMembers, csz);
       if (dense) {
         // mark words of all states in LDS.  Four members per thread are in
@@ -1318,10 +1406,24 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       // ---- the split states of C from the table: touched states that differ
       // from their leader, and the untouched members of blocks whose leader
       // was touched
+      // (those of wide blocks are not listed)
+      if (__builtin_expect(nwide != 0, 0)) {  // workgroup-uniform
+        const uint32_t w = lane() & (kWideCap - 1);
+        const bool its = lane() < nwide && sh.wc[w] == f;
+        wides = (uint32_t)__ballot(its);
+        const uint32_t z = wave_incl_scan_u32(its ? sh.wsz[w] : 0u);
+        if (a.grid_edges && lane_u32(z, kWave - 1) >= kGridMembers) {
+          clear_own();
+          return to_grid();
+        }
+      }
 #pragma unroll
       for (uint32_t u = 0; u < EU; ++u) {
         if ((wid + u * kWaves) * kWave >= E) continue;  // wave-uniform
-        const bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && mv[u] != 0;
+        bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && mv[u] != 0;
+        if (__builtin_expect(wides != 0, 0))
+          for (uint32_t w = wides; w; w &= w - 1)
+            mine = mine && eb[u] != sh.wb[__ffs((int)w) - 1];
         const bool sp = mine && es[u] != eb[u] && lmv[u] != mv[u];
         const bool pt = mine && part[u];
         const uint64_t sbal = __ballot(sp), pbal = __ballot(pt);
@@ -1344,6 +1446,101 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         const uint32_t x = table_find(t_key, tmask, tshift, (f << kKeyBits) | t);
         return x == kNone || t_mv[x] == 0;
       });
+      __syncthreads();
+    }
+    // ---- wide blocks: by far the most members are untouched, so the block is
+    // gone through twice, once for its smallest split state and the number of
+    // those that stay, once to relabel; the few that stay go to the front.  No
+    // member is listed (a block of 5,000 members 29 -> 11 us).
+    for (uint32_t w = wides; __builtin_expect(w != 0, 0); w &= w - 1) {
+      const uint32_t j = (uint32_t)__ffs((int)w) - 1;
+      const uint32_t b = uniform_u32(sh.wb[j]), l = uniform_u32(sh.wlo[j]), z = uniform_u32(sh.wsz[j]);
+      const uint32_t lx = table_find(t_key, tmask, tshift, (f << kKeyBits) | b);
+      const MaskT lm = lx != kNone ? t_mv[lx] : (MaskT)0;
+      const auto stays = [&](uint32_t s) {
+        const uint32_t x = table_find(t_key, tmask, tshift, (f << kKeyBits) | s);
+        return x != kNone && t_mv[x] == lm;
+      };
+      if (tid == 0) {
+        sh.wmin = kNone;
+        sh.wstay = sh.wfront = sh.wback = 0;
+      }
+      __syncthreads();
+      uint32_t least = kNone, kept = 0;
+      for (uint32_t i0 = wid * kWave; i0 < z; i0 += kWideU * WG) {
+        uint32_t v[kWideU];
+#pragma unroll
+        for (uint32_t u = 0; u < kWideU; ++u) {
+          const uint32_t i = i0 + u * WG + lane();
+          v[u] = i < z ? (uint32_t)a.perm[l + i] : kNone;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kWideU; ++u)
+          if (v[u] != kNone) {
+            if (stays(v[u])) ++kept;
+            else least = min(least, v[u]);
+          }
+      }
+      least = wave_min_u32(least);
+      kept = wave_incl_scan_u32(kept);
+      if (lane() == kWave - 1) {
+        atomicMin(&sh.wmin, least);
+        atomicAdd(&sh.wstay, kept);
+      }
+      __syncthreads();
+      const uint32_t nl = uniform_u32(sh.wmin), t = uniform_u32(sh.wstay);
+      if (nl >= n || t == 0 || t >= z) {  // never expected: the leader stays, some are untouched
+        if (tid == 0) sh.bad = 1;
+        __syncthreads();
+        continue;
+      }
+      for (uint32_t i0 = wid * kWave; i0 < z; i0 += kWideU * WG) {
+        uint32_t v[kWideU];
+#pragma unroll
+        for (uint32_t u = 0; u < kWideU; ++u) {
+          const uint32_t i = i0 + u * WG + lane();
+          v[u] = i < z ? (uint32_t)a.perm[l + i] : kNone;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kWideU; ++u) {
+          const uint32_t i = i0 + u * WG + lane();
+          const bool on = v[u] != kNone, st = on && stays(v[u]);
+          if (on && !st) a.blk[v[u]] = (int32_t)nl;
+          const uint32_t x = list_push(&sh.wfront, on && !st && i < t);
+          const uint32_t y = list_push(&sh.wback, st && i >= t);
+          if (x != kNone) a.sps[x] = (int32_t)(l + i);
+          if (y != kNone) a.sfi[y] = (int32_t)(l + i);
+        }
+      }
+      __syncthreads();
+      for (uint32_t i = tid; i < min(sh.wfront, sh.wback); i += WG) {
+        const uint32_t p = (uint32_t)a.sps[i], q = (uint32_t)a.sfi[i];
+        const uint32_t u = (uint32_t)a.perm[p], v = (uint32_t)a.perm[q];
+        const uint64_t xp = a.pin[p], xq = a.pin[q];
+        a.perm[p] = (int32_t)v;
+        a.pos[v] = (int32_t)p;
+        a.pin[p] = xq;
+        a.perm[q] = (int32_t)u;
+        a.pos[u] = (int32_t)q;
+        a.pin[q] = xp;
+      }
+      if (tid == 0) {
+        a.bs[nl] = (int32_t)(l + t);
+        a.be[nl] = (int32_t)(l + z);
+        a.be[b] = (int32_t)(l + t);
+        set2(b, nl);
+        count(true, kWBlocks, 1);
+        count(true, kWSplit, z - t);
+        count(true, kWVisits, z);
+        // neither the block nor C is tracked any longer, and C needs a verdict
+        // (its split parts may hold different marks)
+        if (track) {
+          a.trk[b] = 0;
+          a.trk[C] = 0;
+          sh.fent = 0;
+          if (!a.rcpp) label_set(Q, QS, C);
+        }
+      }
       __syncthreads();
     }
     if (__builtin_expect(big, 0)) {
@@ -1430,62 +1627,93 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         if (track) a.trk[C] = 0;
       }
       const uint64_t epoch = (uint64_t)sh.it << 32;  // this iteration's number
-      for (uint32_t i = tid; i < nS; i += WG) {
-        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
-        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
-        atomicMax((unsigned long long*)&a.nlb[b],
-                  (unsigned long long)(epoch | (uint64_t)(kNone - (uint32_t)s)));
-        a.sr[i] = atomicAdd(&a.cnt[b], 1);
-        atomicOr((unsigned long long*)&a.sf[(uint32_t)s >> 6], 1ull << (s & 63));
-      }
-      __syncthreads();
-      for (uint32_t i = tid; i < nS; i += WG) {
-        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
-        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
-        const int32_t r = a.sr[i];
-        const int32_t e = a.be[b], l = a.bs[b], ps = a.pos[s], c = a.cnt[b];
-        const int32_t nl = (int32_t)(kNone - (uint32_t)a.nlb[b]);
-        const int32_t ne = e - c, q = ne + r;
-        int32_t fv = -1;
-        const bool ok = l >= 0 && l < ne && q < e && e <= (int32_t)n && ps >= l && ps < e;
-        if (ok) {
-          a.blk[s] = nl;
-          if (ps < ne) fv = atomicAdd(&a.fc[b], 1);
-          const int32_t u = a.perm[q];  // every tail position is examined once
-          if (!test_bit(a.sf, (uint32_t)u)) {
-            const int32_t j = atomicAdd(&a.gc[b], 1);
-            if (ne + j < e) a.tmp64[ne + j] = ((uint64_t)(uint32_t)u << 32) | (uint32_t)q;
-            else sh.bad = 1;  // never expected
-          }
-        } else {
-          sh.bad = 1;  // never expected: the entry does nothing
+      const auto entry = [&](uint32_t i, uint32_t& s, uint32_t& b) {
+        const bool on = i < nS;
+        s = b = 0;
+        if (on) {
+          s = (uint32_t)(i < kSmall ? sh.ss[i] : a.ss[i]);
+          b = (uint32_t)(i < kSmall ? sh.sb[i] : a.sbk[i]);
         }
-        a.sfi[i] = fv;
-        a.sne[i] = ne;
-        a.sps[i] = ps;
-        a.sse[i] = (ok && nl == s) ? e : -1;
+        return on;
+      };
+      // the smallest split state of each block, and a rank for every one
+      for (uint32_t i0 = wid * kWave; i0 < nS; i0 += WG) {
+        uint32_t s, b;
+        const bool on = entry(i0 + lane(), s, b);
+        const Group g = group_of(b, on);
+        bid_min(a.nlb, b, epoch, s, on, g);
+        const int32_t r = add_one(a.cnt, b, on, g);
+        if (on) a.sr[i0 + lane()] = r;
+      }
+      __syncthreads();
+      // the new label; states in front of the tail are numbered
+      for (uint32_t i0 = wid * kWave; i0 < nS; i0 += WG) {
+        uint32_t s, b;
+        const bool on = entry(i0 + lane(), s, b);
+        int32_t e = 0, l = 0, ps = 0, c = 0;
+        if (on) {
+          e = a.be[b];
+          l = a.bs[b];
+          ps = a.pos[s];
+          c = a.cnt[b];
+          a.blk[s] = (int32_t)(kNone - (uint32_t)a.nlb[b]);
+        }
+        const int32_t ne = e - c;
+        const bool ok = on && l >= 0 && l < ne && ne < e && e <= (int32_t)n && ps >= l && ps < e;
+        if (on && !ok) sh.bad = 1;  // never expected: the entry does nothing
+        const bool front = ok && ps < ne;
+        const int32_t f = add_one(a.fc, b, front, group_of(b, front));
+        if (on) {
+          a.sfi[i0 + lane()] = front ? ne + f : -1;
+          a.sps[i0 + lane()] = ok ? ps : -1;
+        }
+      }
+      __syncthreads();
+      // the staying states of each tail
+      for (uint32_t i0 = wid * kWave; i0 < nS; i0 += WG) {
+        uint32_t s, b;
+        bool on = entry(i0 + lane(), s, b);
+        int32_t ne = 0, q = 0, e = 0;
+        uint32_t u = 0;
+        on = on && a.sps[i0 + lane()] >= 0;
+        if (on) {
+          e = a.be[b];
+          ne = e - a.cnt[b];
+          q = ne + a.sr[i0 + lane()];
+          on = q < e;
+          if (!on) sh.bad = 1;  // never expected
+        }
+        if (on) {
+          u = (uint32_t)a.perm[q];  // every tail position is examined once
+          on = (uint32_t)a.blk[u] == b;
+        }
+        const int32_t j = add_one(a.gc, b, on, group_of(b, on));
+        if (!on) continue;
+        if (ne + j < e) a.tmp64[ne + j] = ((uint64_t)u << 32) | (uint32_t)q;
+        else sh.bad = 1;  // never expected
       }
       __syncthreads();
       for (uint32_t i = tid; i < nS; i += WG) {
-        const int32_t s = i < kSmall ? sh.ss[i] : a.ss[i];
-        const int32_t b = i < kSmall ? sh.sb[i] : a.sbk[i];
-        const int32_t fv = a.sfi[i], ne = a.sne[i], ps = a.sps[i], e = a.sse[i];
-        if (fv >= 0) {
-          const uint64_t x = a.tmp64[ne + fv];
-          const int32_t q = (int32_t)(uint32_t)x, u = (int32_t)(x >> 32);
-          if (q >= ne && q < (int32_t)n && u >= 0 && u < (int32_t)n) {
+        uint32_t s, b;
+        (void)entry(i, s, b);
+        const int32_t x = a.sfi[i], ps = a.sps[i];
+        if (x >= 0) {
+          const uint64_t uq = a.tmp64[x];
+          const uint32_t q = (uint32_t)uq, u = (uint32_t)(uq >> 32);
+          if (q < n && u < n) {
             const uint64_t xq = a.pin[q], xp = a.pin[ps];
-            a.perm[ps] = u;
+            a.perm[ps] = (int32_t)u;
             a.pos[u] = ps;
             a.pin[ps] = xq;
-            a.perm[q] = s;
-            a.pos[s] = q;
+            a.perm[q] = (int32_t)s;
+            a.pos[s] = (int32_t)q;
             a.pin[q] = xp;
           } else {
             sh.bad = 1;  // never expected
           }
         }
-        if (e >= 0) {  // the new leader: one thread per split block
+        if (ps >= 0 && (uint32_t)a.blk[s] == s) {  // the new leader: one thread per split block
+          const int32_t e = a.be[b], ne = e - a.cnt[b];
           a.bs[s] = ne;
           a.be[s] = e;
           a.be[b] = ne;
@@ -1493,10 +1721,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           a.fc[b] = 0;
           a.gc[b] = 0;
           if (track) a.trk[b] = 0;
-          set2((uint32_t)b, (uint32_t)s);
+          set2(b, s);
           count(true, kWBlocks, 1);
         }
-        atomicAnd((unsigned long long*)&a.sf[(uint32_t)s >> 6], ~(1ull << (s & 63)));
       }
     }
     return kRoundsGo;

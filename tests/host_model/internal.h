@@ -138,6 +138,7 @@ inline T __shfl_xor(T v, int d, int w) {
   return __shfl(v, (lanes::g_current & 63) ^ d, w);
 }
 inline int __ffsll(unsigned long long v) { return __builtin_ffsll((long long)v); }
+inline int __ffs(int v) { return __builtin_ffs(v); }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 template <class T, class V>
 inline T atomicOr(T* p, V v) {
@@ -200,6 +201,12 @@ inline uint32_t wave_incl_scan_u32(uint32_t v) {
   uint32_t sum = 0;
   for (uint32_t i = 0; i <= lane(); ++i) sum += (uint32_t)all[i];
   return sum;
+}
+inline uint32_t wave_min_u32(uint32_t v) {
+  uint64_t all[64];
+  lanes::exchange(5, v, all);
+  for (int i = 0; i < 64; ++i) v = min(v, (uint32_t)all[i]);
+  return v;
 }
 inline bool test_bit(const uint64_t* words, uint32_t i) { return (words[i >> 6] >> (i & 63)) & 1ull; }
 }  // namespace bisim

@@ -39,13 +39,13 @@ uint32_t go(const Run& r) {
   a.in_src = r.in_src;
   a.in_ord = r.in_ord;
   int32_t** state[] = {&a.blk, &a.perm, &a.pos, &a.bs, &a.be, &a.cnt, &a.fc, &a.gc, &a.ts, &a.tb,
-                       &a.lb, &a.llo, &a.lsz, &a.ss, &a.sbk, &a.sr, &a.sfi, &a.sne, &a.sps, &a.sse};
+                       &a.lb, &a.llo, &a.lsz, &a.ss, &a.sbk, &a.sr, &a.sfi, &a.sps};
   for (int32_t** p : state) *p = (int32_t*)words(n, 4, kAny);
   a.pin = words(n, 8, kAny);
   a.nlb = words(n, 8, kAny);
   a.tmp64 = words(n, 8, kAny);
   a.mw = (MaskT*)words(n, sizeof(MaskT), kAny);
-  for (uint64_t** p : {&a.sf, &a.ub, &a.qb}) *p = words(nw, 8, kAny);
+  for (uint64_t** p : {&a.ub, &a.qb}) *p = words(nw, 8, kAny);
   for (uint64_t** p : {&a.us, &a.qs}) *p = words(nsw, 8, kAny);
   if (r.out_ptr) {
     a.trk = (uint8_t*)words(n, 1, kAny);

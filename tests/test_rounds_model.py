@@ -128,3 +128,38 @@ def test_each_in_transition_once(grouped, case, waves):
                   visits.ctypes.data_as(P))
     assert (visits[:m] == 1).all() and visits[m:].sum() == 0
     assert (target[:m] == np.repeat(np.arange(len(degree)), degree)).all()
+
+
+@pytest.fixture(scope="module")
+def shipped(tmp_path_factory):
+    return compiled(tmp_path_factory.mktemp("shipped"), {})
+
+
+def backward_chain(n):
+    return gen.LTS(n, 1, np.arange(1, n), np.zeros(n - 1, int), np.arange(n - 1))
+
+
+# blocks that lose more states than the tables of a split hold (128 here): all
+# but the leader, interleaved halves, several blocks at once
+LARGE = {
+    "backward-chain": lambda: backward_chain(420),
+    "backward-chain-permuted": lambda: gen.LTS(400, 1, *(
+        (lambda p, L: (p[L.src], L.lab, p[L.dst]))(np.random.default_rng(3).permutation(400),
+                                                    backward_chain(400)))),
+    "fat": lambda: gen.planted_quotient(6, 3.0, 2, seed=4, copies_hi=300),
+    "two-chains": lambda: gen.LTS(600, 2, np.arange(2, 600), np.zeros(598, int),
+                                  np.arange(598), np.arange(600) % 2),
+    "wide-marks": lambda: gen.random_lts(500, 700, 50, 5, init_blocks=2),
+    "halves": lambda: gen.LTS(602, 3, np.concatenate([np.arange(600), np.arange(600), [600, 601]]),
+                              np.concatenate([np.zeros(1200, int), [1, 2]]),
+                              np.concatenate([600 + np.arange(600) % 2, np.arange(600) // 2,
+                                              [600, 601]])),
+}
+
+
+# (the third budget holds neither the table nor the tables of a split)
+@pytest.mark.parametrize("lds,bitmaps,either", [(60000, True, False), (24000, True, True),
+                                                (3000, False, True)])
+@pytest.mark.parametrize("case", sorted(LARGE))
+def test_large_splits(shipped, case, lds, bitmaps, either):
+    check(shipped, LARGE[case](), lds=lds, bitmaps=bitmaps, either=either, seed=lds)
