@@ -146,9 +146,11 @@ const char* bisim_last_error(void);
  * bisim_set_option — per-handle settings.
  *   BISIM_OPT_ENGINE        0 = automatic (default: engine 3 for Algorithm 3
  *                           with the plain policy, and for Algorithm 2 up to
- *                           16,384 states; for the learned policy engine 1
- *                           with one workgroup up to 2,048 states (arrays in
- *                           LDS) and engine 2 above; engine 2 for traced,
+ *                           16,384 states and 131,072 transitions; for the
+ *                           learned policy engine 1 with one workgroup up to
+ *                           2,048 states (arrays in LDS; beyond 131,072
+ *                           transitions only with many blocks from the start)
+ *                           and engine 2 above; engine 2 for traced,
  *                           profiled or limited runs and states of more than
  *                           64 distinct actions; from 200,000 states
  *                           on, engine 3's grid is timed on the LTS's first

@@ -72,7 +72,7 @@ constexpr int kPhases = 3;  // kernels per iteration
 // states of so many in-transitions are marked by the whole grid if there are
 // at most kHubCap of them (with more, waves have about as much each)
 constexpr uint32_t kHubDegree = 4096, kHubCap = 1024;
-constexpr uint32_t kManyMembers = 8192, kQueueMembers = 512;
+constexpr uint32_t kManyMembers = 1024, kQueueMembers = 512;
 // mean in-degree from which the marks of a large splitter repeat.  The heavier
 // kernel costs others 2.6 us of 15 (planted quotient of 1.03M states, mean 8).
 constexpr uint32_t kRepeatDegree = 16;
@@ -784,6 +784,13 @@ constexpr uint32_t kSetupN = 16384;     // up to here the workgroup builds the m
 // (planted quotient of 1.03M states before tracking: 336 ms, with the
 // workgroup taking up to 8192 / 49152 transitions 444 / 937 ms).
 constexpr uint32_t kGridEdges = 2048;
+// While the mark words of all states fit LDS the workgroup takes 1.5 ns for a
+// transition, so its line is where those make up for the launches.  LTSs that
+// can have such splitters by much get their member lists from the grid at any
+// size (30 us).  (16,000 states, 2M / 8M transitions, 3 / 2 iterations: 2.85 /
+// 3.44 ms by the workgroup, 0.48 / 0.31 so; engine 2 0.91 / 3.10.)
+constexpr uint32_t kGridDense = 32768;
+constexpr int64_t kGridDenseM = 1 << 17;
 // LTSs with fewer transitions have no splitter worth tracking; up to the
 // second number the workgroup lays the transitions out by source itself, if
 // some block is large enough (10 us for 8000 transitions against 35 us for
@@ -1246,6 +1253,7 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
   a.rcpp = rcpp ? 1 : 0;
   a.mean_deg = (uint32_t)(n ? (h->m + n - 1) / n : 1);
   a.grid_edges = !rcpp && !start && h->m + (int64_t)n >= (int64_t)kGridEdges ? kGridEdges : 0;
+  a.grid_dense = a.grid_edges && h->m >= kGridDenseM ? kGridDense : 0;
   a.in_ptr = h->in_ptr;
   a.in_src = h->in_src;
   a.in_ord = h->in_ord;
@@ -1326,7 +1334,8 @@ static bisim_status rounds_launch(bisim_lts* h, const LArgs& l, const int32_t* s
 bisim_status rounds_run(bisim_lts* h, uint32_t cap, const int32_t* start, bool rcpp) {
   LArgs l;
   const uint32_t n = (uint32_t)h->n, nw = (n + 63) / 64;
-  const bool own = n <= kSetupN;
+  // (Algorithm 2 has no grid-wide iterations)
+  const bool own = n <= kSetupN && (rcpp || h->m < kGridDenseM);
   bisim_lists& L = h->lists;
   BISIM_TRY(lists_alloc(h));
   if (h->m >= kTrackMinM) {

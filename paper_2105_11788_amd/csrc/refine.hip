@@ -559,6 +559,14 @@ namespace {
 constexpr int32_t kTuneMinStates = 200000;  // smaller LTSs: no trials
 constexpr int32_t kRcppRoundsStates = 16384;
 constexpr int64_t kTuneIters = 96;          // iterations per trial
+// A workgroup that has no grid to turn to takes about 1 ns for each transition
+// of a splitter, and saves 10 us in each iteration: with more transitions than
+// this a run of few iterations is slower (Algorithm 2, 16,000 states, 2M
+// transitions, 3 iterations: 1.71 ms, engine 2 0.92).  Every block is a
+// splitter once, so a run of the learned policy with many blocks from the start
+// is ahead all the same (2,000 states and blocks, 200k transitions: 16 against
+// 38 ms).
+constexpr int64_t kOneWGTransitions = 1 << 17;
 
 std::string lts_tune_key(const bisim_lts* h) {
   hipDeviceProp_t p;
@@ -620,8 +628,9 @@ void lts_tune_store(const std::string& key, int engine, int grid, float us) {
 // against 256 ms).  Engine 2 for the learned policy, traced, capped and
 // profiled runs, states of more than 64 actions, and the allocation-free
 // entry point, whose region does not hold the member lists.  Algorithm 2
-// takes the rounds while its mark words fit one workgroup's LDS; beyond, a
-// large splitter would need the grid, whose kernels run Algorithm 3 only.
+// takes the rounds while its mark words fit one workgroup's LDS; beyond, and
+// for splitters of very many transitions, it would need the grid, whose
+// kernels run Algorithm 3 only.
 // From kTuneMinStates on the grid of the grid-wide iterations is the cached
 // choice for this device and size class, else the fastest of a few candidates
 // timed on the first kTuneIters iterations of this LTS (each timed twice, the
@@ -631,14 +640,15 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   *engine = 2;
   *grid = h->grid;
   const bool learned = h->policy == 1 && h->policy_w;
-  if (learned && h->n <= kLearnedWGStates && h->grid == 0 && h->profile_every == 0) {
+  if (learned && h->n <= kLearnedWGStates && h->grid == 0 && h->profile_every == 0 &&
+      (h->m <= kOneWGTransitions || h->pre_blocks >= (h->m >> 13))) {
     *engine = 1;
     *grid = 1;
     return BISIM_OK;
   }
   if (learned || h->iter_limit > 0 || arena_active() || !rounds_apply(h)) return BISIM_OK;
   if (h->algorithm == 2) {
-    if (h->n <= kRcppRoundsStates) *engine = 3;
+    if (h->n <= kRcppRoundsStates && h->m <= kOneWGTransitions) *engine = 3;
     return BISIM_OK;
   }
   if (h->n < kTuneMinStates || h->start_override) {

@@ -109,6 +109,7 @@ struct RoundsArgs {
   uint32_t iter_cap;
   uint32_t rcpp;        // Algorithm 2: one mark per state, C not re-marked
   uint32_t grid_edges;  // estimated in-transitions from which a splitter is left to the grid (0: never)
+  uint32_t grid_dense;  // the same while the mark words of all states fit LDS
   uint32_t mean_deg;    // mean in-degree, rounded up
   const uint32_t* in_ptr;
   const int32_t *in_src, *in_ord;
@@ -1240,7 +1241,9 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       ++nbig;
       const uint32_t cb = uniform_u32(sh.cb[0]), csz = uniform_u32(sh.csz0);
       bool grid = false;
-      if (!dense && a.grid_edges) {
+      if (dense) {
+        grid = a.grid_dense && (uint64_t)csz * a.mean_deg >= a.grid_dense;
+      } else if (a.grid_edges) {
         grid = (uint64_t)csz * a.mean_deg >= a.grid_edges;
         if (!grid) {  // few members, but they may be hubs: count
           uint32_t edges = 0;

@@ -115,3 +115,39 @@ def test_large_splits_in_a_batch(B, lds):
     for k, L in enumerate(insts):
         ref = oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst)
         assert (blocks[k] == ref["block"]).all() and its[k] == ref["iters"], sorted(SHAPES)[k]
+
+
+# many transitions per state, few iterations: (LTS, algorithm, learned policy)
+DENSE = {
+    "16k-2M": (lambda: gen.random_lts(16_000, 2_000_000, 1, 1, init_blocks=3), 3, False),
+    "16k-8M": (lambda: gen.random_lts(16_000, 8_000_000, 8, 1), 3, False),
+    "30k-8M": (lambda: gen.random_lts(30_000, 8_000_000, 1, 1, init_blocks=2), 3, False),
+    "100k-10M": (lambda: gen.random_lts(100_000, 10_000_000, 2, 1), 3, False),
+    "algorithm-2-16k-2M": (lambda: gen.kripke_uniform(16_000, 2_000_000, 1), 2, False),
+    "learned-2k-1M": (lambda: gen.kripke_uniform(2_000, 1_000_000, 1), 3, True),
+    "learned-2k-200k-64": (lambda: gen.random_lts(2_000, 200_000, 64, 1), 3, True),
+}
+
+
+@pytest.mark.parametrize("case", sorted(DENSE))
+def test_dense_no_slower_than_scans(B, case):
+    make, algorithm, learned = DENSE[case]
+    L = make()
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst, L.init)
+    dev = [None if a is None else B.DeviceArray.from_numpy(a, np.int32)
+           for a in (L.src, L.lab, L.dst, L.init)]
+    out = B.DeviceArray(L.n, np.int32)
+    with B.LTS(*dev[:3], L.n, L.K, dev[3]) as h:
+        h.set_option(B.OPT_ALGORITHM, algorithm)
+        w = B.MLP(B.POLICY_FEATURES, seed=1) if learned else None
+        if learned:
+            B.set_splitter_policy(h, B.POLICY_LEARNED, w)
+        h.run(out)
+        auto, st = best_of(h, out)
+        ran = h.run_config()
+        assert (out.numpy() == ks).all() and st.blocks == nb
+        h.set_option(B.OPT_ENGINE, 2)
+        scans, ref = best_of(h, out)
+        assert st.iterations == ref.iterations
+    print(f"[large splits] {case}: {auto:.2f} ms by {ran}, engine 2 {scans:.2f}", flush=True)
+    assert auto < 1.5 * scans + 0.3
