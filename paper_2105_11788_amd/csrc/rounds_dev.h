@@ -85,7 +85,7 @@ constexpr uint32_t out_u() { return kMode != 2 ? 8 : sizeof(MaskT) == 4 && kBm ?
 constexpr uint32_t kListCap = 64;    // listed blocks kept in LDS
 constexpr uint32_t kWideCap = 8;     // blocks split by what stays, at a time
 // members of such blocks from which the iteration is the grid's
-constexpr uint32_t kGridMembers = 1u << 16;
+constexpr uint32_t kGridMembers = 1u << 18;
 constexpr uint32_t kOwnBlock = 128;  // members up to which a wave takes a listed block alone
 constexpr uint32_t kScanU = 2;       // states or transitions in flight per thread
 constexpr uint32_t kWideU = 4;       // members of a wide block in flight per thread
@@ -1451,10 +1451,11 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       });
       __syncthreads();
     }
-    // ---- wide blocks: by far the most members are untouched, so the block is
-    // gone through twice, once for its smallest split state and the number of
-    // those that stay, once to relabel; the few that stay go to the front.  No
-    // member is listed (a block of 5,000 members 29 -> 11 us).
+    // ---- wide blocks: the members that stay are touched states of the table,
+    // each in a thread's hands, and by far the most members are untouched.  So
+    // the block is gone through twice, for its smallest split state and to
+    // relabel, and the few that stay get their label back and go to the front.
+    // No member is listed.
     for (uint32_t w = wides; __builtin_expect(w != 0, 0); w &= w - 1) {
       const uint32_t j = (uint32_t)__ffs((int)w) - 1;
       const uint32_t b = uniform_u32(sh.wb[j]), l = uniform_u32(sh.wlo[j]), z = uniform_u32(sh.wsz[j]);
@@ -1469,7 +1470,15 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         sh.wstay = sh.wfront = sh.wback = 0;
       }
       __syncthreads();
-      uint32_t least = kNone, kept = 0;
+      bool st[EU];
+      uint32_t kept = 0;
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        st[u] = sl[u] != kNone && (ek[u] >> kKeyBits) == f && eb[u] == b && mv[u] == lm;
+        kept += (uint32_t)__popcll(__ballot(st[u]));
+      }
+      if (lane() == 0 && kept) atomicAdd(&sh.wstay, kept);
+      // (only a member below the least one so far is looked up)
       for (uint32_t i0 = wid * kWave; i0 < z; i0 += kWideU * WG) {
         uint32_t v[kWideU];
 #pragma unroll
@@ -1477,18 +1486,14 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           const uint32_t i = i0 + u * WG + lane();
           v[u] = i < z ? (uint32_t)a.perm[l + i] : kNone;
         }
+        const uint32_t before = sh.wmin;
+        uint32_t least = before;
 #pragma unroll
         for (uint32_t u = 0; u < kWideU; ++u)
-          if (v[u] != kNone) {
-            if (stays(v[u])) ++kept;
-            else least = min(least, v[u]);
-          }
-      }
-      least = wave_min_u32(least);
-      kept = wave_incl_scan_u32(kept);
-      if (lane() == kWave - 1) {
-        atomicMin(&sh.wmin, least);
-        atomicAdd(&sh.wstay, kept);
+          if (v[u] < least && !stays(v[u])) least = v[u];
+        if (__ballot(least != before) == 0) continue;
+        least = wave_min_u32(least);
+        if (lane() == 0) atomicMin(&sh.wmin, least);
       }
       __syncthreads();
       const uint32_t nl = uniform_u32(sh.wmin), t = uniform_u32(sh.wstay);
@@ -1497,23 +1502,34 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         __syncthreads();
         continue;
       }
-      for (uint32_t i0 = wid * kWave; i0 < z; i0 += kWideU * WG) {
+      for (uint32_t i0 = tid; i0 < z; i0 += kWideU * WG) {
         uint32_t v[kWideU];
 #pragma unroll
         for (uint32_t u = 0; u < kWideU; ++u) {
-          const uint32_t i = i0 + u * WG + lane();
+          const uint32_t i = i0 + u * WG;
           v[u] = i < z ? (uint32_t)a.perm[l + i] : kNone;
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kWideU; ++u) {
-          const uint32_t i = i0 + u * WG + lane();
-          const bool on = v[u] != kNone, st = on && stays(v[u]);
-          if (on && !st) a.blk[v[u]] = (int32_t)nl;
-          const uint32_t x = list_push(&sh.wfront, on && !st && i < t);
-          const uint32_t y = list_push(&sh.wback, st && i >= t);
-          if (x != kNone) a.sps[x] = (int32_t)(l + i);
-          if (y != kNone) a.sfi[y] = (int32_t)(l + i);
+        for (uint32_t u = 0; u < kWideU; ++u)
+          if (v[u] != kNone) a.blk[v[u]] = (int32_t)nl;
+      }
+      __syncthreads();
+#pragma unroll
+      for (uint32_t u = 0; u < EU; ++u) {
+        if (__ballot(st[u]) == 0) continue;
+        uint32_t p = 0;
+        if (st[u]) {
+          a.blk[es[u]] = (int32_t)b;
+          p = (uint32_t)a.pos[es[u]];
         }
+        const uint32_t y = list_push(&sh.wback, st[u] && p >= l + t);
+        if (y != kNone) a.sfi[y] = (int32_t)p;
+      }
+      for (uint32_t i0 = wid * kWave; i0 < t; i0 += WG) {
+        const uint32_t i = i0 + lane();
+        const bool on = i < t && !stays((uint32_t)a.perm[l + i]);
+        const uint32_t x = list_push(&sh.wfront, on);
+        if (x != kNone) a.sps[x] = (int32_t)(l + i);
       }
       __syncthreads();
       for (uint32_t i = tid; i < min(sh.wfront, sh.wback); i += WG) {
