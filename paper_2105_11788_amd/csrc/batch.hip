@@ -38,6 +38,7 @@ struct bisim_batch {
   int device = 0, num_cu = 0;
   int lds_max = 0;
   bisim_lts* u = nullptr;  // the preprocessed union
+  bisim::Chunks mem;       // the device arrays below
   std::vector<int64_t> n_off;
   uint32_t* n_off_d = nullptr;  // [count+1]
   uint32_t* bw_off_d = nullptr; // [count+1] bitmap word offsets
@@ -279,12 +280,15 @@ __global__ void k_globalize(int32_t count, const uint32_t* __restrict__ n_off,
   if (bad) atomicOr(err, 1u);
 }
 
+// device memory from `mem` (an allocation of its own for each of the 40 arrays
+// was most of the load of a small batch)
 template <class T>
-bisim_status dmalloc(T** p, size_t count) {
+bisim_status dmalloc(Chunks& mem, hipStream_t s, T** p, size_t count) {
   *p = nullptr;
-  hipError_t e = hipMalloc((void**)p, sizeof(T) * (count ? count : 1));
+  const size_t bytes = sizeof(T) * (count ? count : 1);
+  const hipError_t e = mem.alloc((void**)p, bytes, s);
   if (e != hipSuccess) {
-    set_error("device allocation of %zu bytes failed: %s", sizeof(T) * count, hipGetErrorString(e));
+    set_error("device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
     return BISIM_E_NOMEM;
   }
   return BISIM_OK;
@@ -294,14 +298,8 @@ void free_batch(bisim_batch* b) {
   if (!b) return;
   if (b->stream) (void)hipStreamSynchronize(b->stream);
   if (b->gexec) (void)hipGraphExecDestroy(b->gexec);
-  void* ptrs[] = {b->n_off_d, b->bw_off_d, b->order_d, b->blk, b->mw,      b->nlb,  b->ub,
-                  b->qb,      b->qs,       b->tl,      b->sl,  b->iters_d, b->ctl_d, b->perm,
-                  b->pos,     b->bs,       b->be,      b->cnt, b->fc,      b->gc,    b->tmp,
-                  b->rk,      b->fi,       b->ltl,     b->us,  b->ob,
-                  b->tlb,     b->tmp64,   b->work_d, b->llo, b->lsz,
-                  b->pin,     b->trk,      b->args_d};
-  for (void* p : ptrs)
-    if (p) (void)hipFree(p);
+  b->mem.release(b->stream);
+  if (b->stream) (void)hipStreamSynchronize(b->stream);
   if (b->u) lts_destroy(b->u);
   if (b->ev0) (void)hipEventDestroy(b->ev0);
   if (b->ev1) (void)hipEventDestroy(b->ev1);
@@ -543,6 +541,7 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
   bisim_status st = BISIM_OK;
   int32_t *gsrc = nullptr, *gdst = nullptr, *ginit = nullptr, *Kd = nullptr;
   uint32_t *m_off_d = nullptr, *err = nullptr;
+  Chunks tmp;  // temporaries of loading
   do {
     hipError_t e = hipGetDevice(&b->device);
     if (e == hipSuccess)
@@ -573,11 +572,13 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
     std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
       return n_off[x + 1] - n_off[x] > n_off[y + 1] - n_off[y];
     });
-    if ((st = dmalloc(&b->n_off_d, count + 1)) || (st = dmalloc(&b->bw_off_d, count + 1)) ||
-        (st = dmalloc(&b->order_d, count)) || (st = dmalloc(&m_off_d, count + 1)) ||
-        (st = dmalloc(&Kd, count)) || (st = dmalloc(&err, 1)) ||
-        (st = dmalloc(&gsrc, (size_t)M)) || (st = dmalloc(&gdst, (size_t)M)) ||
-        (st = dmalloc(&ginit, (size_t)N)))
+    tmp.reserve(8 * (size_t)M + 4 * (size_t)N + 8 * (size_t)count + 8 * 256, s);
+    if ((st = dmalloc(b->mem, s, &b->n_off_d, count + 1)) ||
+        (st = dmalloc(b->mem, s, &b->bw_off_d, count + 1)) ||
+        (st = dmalloc(b->mem, s, &b->order_d, count)) ||
+        (st = dmalloc(tmp, s, &m_off_d, count + 1)) || (st = dmalloc(tmp, s, &Kd, count)) ||
+        (st = dmalloc(tmp, s, &err, 1)) || (st = dmalloc(tmp, s, &gsrc, (size_t)M)) ||
+        (st = dmalloc(tmp, s, &gdst, (size_t)M)) || (st = dmalloc(tmp, s, &ginit, (size_t)N)))
       break;
     e = hipMemcpyAsync(b->n_off_d, no.data(), 4 * (count + 1), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipMemcpyAsync(m_off_d, mo.data(), 4 * (count + 1), hipMemcpyHostToDevice, s);
@@ -619,23 +620,23 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
     // 32-bit mark words suffice when no state has more than 32 actions
     b->mask64 = Kmax > 32;
     const size_t BW = bo[count];
-    if ((st = dmalloc(&b->blk, (size_t)N)) || (st = dmalloc(&b->mw, (size_t)N)) ||
-        (st = dmalloc(&b->nlb, (size_t)N)) || (st = dmalloc(&b->ub, BW)) ||
-        (st = dmalloc(&b->qb, BW)) || (st = dmalloc(&b->qs, BW)) ||
-        (st = dmalloc(&b->tl, (size_t)N)) || (st = dmalloc(&b->sl, (size_t)N)) ||
-        (st = dmalloc(&b->perm, (size_t)N)) || (st = dmalloc(&b->pos, (size_t)N)) ||
-        (st = dmalloc(&b->bs, (size_t)N)) || (st = dmalloc(&b->be, (size_t)N)) ||
-        (st = dmalloc(&b->cnt, (size_t)N)) || (st = dmalloc(&b->fc, (size_t)N)) ||
-        (st = dmalloc(&b->gc, (size_t)N)) || (st = dmalloc(&b->tmp, (size_t)N)) ||
-        (st = dmalloc(&b->rk, (size_t)N)) || (st = dmalloc(&b->fi, (size_t)N)) ||
-        (st = dmalloc(&b->ltl, (size_t)N)) ||
-        (st = dmalloc(&b->ob, (size_t)N)) ||
-        (st = dmalloc(&b->us, BW)) || (st = dmalloc(&b->tlb, (size_t)N)) ||
-        (st = dmalloc(&b->tmp64, (size_t)N)) ||
-        (st = dmalloc(&b->pin, (size_t)N)) || (st = dmalloc(&b->trk, (size_t)N)) ||
-        (st = dmalloc(&b->llo, (size_t)N)) || (st = dmalloc(&b->lsz, (size_t)N)) ||
-        (st = dmalloc(&b->iters_d, count)) || (st = dmalloc(&b->ctl_d, 2)) ||
-        (st = dmalloc(&b->work_d, 16)) || (st = dmalloc(&b->args_d, (size_t)count)))
+    b->mem.reserve(105 * (size_t)N + 32 * BW +
+                       (size_t)count * (4 + sizeof(RoundsArgs<uint64_t>)) + 40 * 256,
+                   s);
+    int32_t** const state[] = {&b->blk, &b->tl,  &b->sl, &b->perm, &b->pos, &b->bs,
+                               &b->be,  &b->cnt, &b->fc, &b->gc,   &b->tmp, &b->rk,
+                               &b->fi,  &b->ltl, &b->ob, &b->tlb,  &b->llo, &b->lsz};
+    for (int32_t** p : state)
+      if (st == BISIM_OK) st = dmalloc(b->mem, s, p, (size_t)N);
+    if (st != BISIM_OK || (st = dmalloc(b->mem, s, &b->mw, (size_t)N)) ||
+        (st = dmalloc(b->mem, s, &b->nlb, (size_t)N)) ||
+        (st = dmalloc(b->mem, s, &b->tmp64, (size_t)N)) ||
+        (st = dmalloc(b->mem, s, &b->pin, (size_t)N)) ||
+        (st = dmalloc(b->mem, s, &b->trk, (size_t)N)) || (st = dmalloc(b->mem, s, &b->ub, BW)) ||
+        (st = dmalloc(b->mem, s, &b->qb, BW)) || (st = dmalloc(b->mem, s, &b->qs, BW)) ||
+        (st = dmalloc(b->mem, s, &b->us, BW)) || (st = dmalloc(b->mem, s, &b->iters_d, count)) ||
+        (st = dmalloc(b->mem, s, &b->ctl_d, 2)) || (st = dmalloc(b->mem, s, &b->work_d, 16)) ||
+        (st = dmalloc(b->mem, s, &b->args_d, (size_t)count)))
       break;
     st = by_source(b->u);
     if (st == BISIM_E_NOMEM) {  // no label is tracked then
@@ -658,12 +659,7 @@ bisim_status lts_batch_load(int32_t count, const int64_t* n_off, const int64_t* 
     }
     b->t_pre_ms = ms;
   } while (0);
-  if (gsrc) (void)hipFree(gsrc);
-  if (gdst) (void)hipFree(gdst);
-  if (ginit) (void)hipFree(ginit);
-  if (Kd) (void)hipFree(Kd);
-  if (m_off_d) (void)hipFree(m_off_d);
-  if (err) (void)hipFree(err);
+  tmp.release(b->stream);
   if (st != BISIM_OK) {
     free_batch(b);
     return st;
