@@ -86,12 +86,39 @@ __device__ __forceinline__ TileLds tile_stage(float* base, int per_wave,
   L.X = base + kParamFloats + (threadIdx.x / kWave) * per_wave;
   L.H1 = L.X + kTile * kS1;
   L.DZ = L.H1 + kTile * kS2;
-  for (int i = threadIdx.x; i < kMlpH * kMlpMaxF; i += kMT) {
-    const int j = i / kMlpMaxF, f = i % kMlpMaxF;
-    L.W1[j * kS1 + f] = f < F ? bf16_to_f(w[o.W1 + j * F + f]) : 0.f;
+  // 8 parameters a load (both matrices start at a multiple of 16 bytes): calls
+  // on a few rows are bound by this (one by one, and with the sums of waves
+  // without rows: a step on 1 row 69 us, now 54; forward 41.9, now 40.6)
+  const auto eight = [&](int64_t at, float v[8]) {
+    const uint4 x = *reinterpret_cast<const uint4*>(w + at);
+    const uint32_t q[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(q[i] << 16);
+      v[2 * i + 1] = __uint_as_float(q[i] & 0xFFFF0000u);
+    }
+  };
+  for (int i = threadIdx.x; i < kMlpH * kMlpH / 8; i += kMT) {
+    float v[8];
+    eight(o.W2 + 8 * i, v);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) L.W2[(i / (kMlpH / 8)) * kS2 + i % (kMlpH / 8) * 8 + e] = v[e];
   }
-  for (int i = threadIdx.x; i < kMlpH * kMlpH; i += kMT)
-    L.W2[(i / kMlpH) * kS2 + i % kMlpH] = bf16_to_f(w[o.W2 + i]);
+  for (int i = threadIdx.x; i < kMlpH * F / 8; i += kMT) {
+    float v[8];
+    eight(o.W1 + 8 * i, v);
+    int j = 8 * i / F, f = 8 * i % F;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      L.W1[j * kS1 + f] = v[e];
+      if (++f == F) {
+        f = 0;
+        ++j;
+      }
+    }
+  }
+  const int pad = kMlpMaxF - F;
+  for (int i = threadIdx.x; i < kMlpH * pad; i += kMT) L.W1[(i / pad) * kS1 + F + i % pad] = 0.f;
   if (threadIdx.x < kMlpH) {
     L.b1[threadIdx.x] = bf16_to_f(w[o.b1 + threadIdx.x]);
     L.b2[threadIdx.x] = bf16_to_f(w[o.b2 + threadIdx.x]);
@@ -302,7 +329,9 @@ __global__ void __launch_bounds__(kMT) k_mlp_backward(const uint16_t* __restrict
   }
   // the workgroup's waves in order
   const MlpOffsets o = mlp_offsets(F);
-  for (int q = 0; q < kMW; ++q) {
+  const int64_t tiles = (rows + kTile - 1) / kTile - (int64_t)blockIdx.x * kMW;
+  const int active = tiles < kMW ? (int)tiles : kMW;  // waves that had rows (the first ones)
+  for (int q = 0; q < active; ++q) {
     if (wv == q) {
       const auto add = [&](int64_t i, float v) { red[i] = q == 0 ? v : red[i] + v; };
 #pragma unroll
