@@ -151,10 +151,13 @@ const char* bisim_last_error(void);
  *                           2,048 states (arrays in LDS; beyond 131,072
  *                           transitions only with many blocks from the start)
  *                           and engine 2 above; engine 2 for traced,
- *                           profiled or limited runs and states of more than
- *                           64 distinct actions; from 200,000 states
- *                           on, engine 3's grid is timed on the LTS's first
- *                           iterations once per device and size class and
+ *                           profiled or limited runs and, below 200,000
+ *                           states, for states of more than 64 distinct
+ *                           actions; from 200,000 states on, engine 3's grid
+ *                           (with more than 64 actions or 2^27 states the
+ *                           faster of engines 2 and 3 as well) is timed on the
+ *                           LTS's first iterations once per device and size
+ *                           class and
  *                           cached in the file BISIM_TUNE_CACHE, else
  *                           $HOME/.cache/bisim_tune.txt), 1 = one cooperative persistent
  *                           launch per fixpoint (grid barriers between

@@ -568,7 +568,7 @@ constexpr int64_t kTuneIters = 96;          // iterations per trial
 // 38 ms).
 constexpr int64_t kOneWGTransitions = 1 << 17;
 
-std::string lts_tune_key(const bisim_lts* h) {
+std::string lts_tune_key(const bisim_lts* h, bool rounds) {
   hipDeviceProp_t p;
   std::string arch = "gpu";
   if (hipGetDeviceProperties(&p, h->device) == hipSuccess) arch = p.gcnArchName;
@@ -578,8 +578,8 @@ std::string lts_tune_key(const bisim_lts* h) {
   for (int64_t v = h->n; v > 1; v >>= 1) ++ln;
   for (int64_t v = h->m; v > 1; v >>= 1) ++lm;
   char buf[256];
-  snprintf(buf, sizeof buf, "lts_rounds_%s_cu%d_n%d_m%d_u%d", arch.c_str(), h->num_cu, ln, lm,
-           h->uniform);
+  snprintf(buf, sizeof buf, "lts_%s%s_cu%d_n%d_m%d_u%d", rounds ? "rounds_" : "", arch.c_str(),
+           h->num_cu, ln, lm, h->uniform);
   return buf;
 }
 
@@ -624,17 +624,18 @@ void lts_tune_store(const std::string& key, int engine, int grid, float us) {
 
 // Engine and grid of an automatic run.  Engine 3 (rounds) for Algorithm 3
 // with the plain policy: it carries out one iteration where engine 2 carries
-// out eight, and is ahead from 5 states on (uniform LTS of 20k states: 35 ms
+// out eight, and is ahead from 5 states on (uniform LTS of 20k states: 25 ms
 // against 256 ms).  Engine 2 for the learned policy, traced, capped and
-// profiled runs, states of more than 64 actions, and the allocation-free
-// entry point, whose region does not hold the member lists.  Algorithm 2
-// takes the rounds while its mark words fit one workgroup's LDS; beyond, and
-// for splitters of very many transitions, it would need the grid, whose
-// kernels run Algorithm 3 only.
+// profiled runs, and the allocation-free entry point, whose region does not
+// hold the member lists.  Algorithm 2 takes the rounds while its mark words
+// fit one workgroup's LDS; beyond, and for splitters of very many transitions,
+// it would need the grid, whose kernels run Algorithm 3 only.
 // From kTuneMinStates on the grid of the grid-wide iterations is the cached
 // choice for this device and size class, else the fastest of a few candidates
 // timed on the first kTuneIters iterations of this LTS (each timed twice, the
-// second kept).
+// second kept).  What the rounds do not take (states of more than 64 actions,
+// 2^27 states and more, counted runs) goes in lock step, by engine 2 below
+// kTuneMinStates and from there on by the engine and grid so found.
 static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   const int cu = h->num_cu > 0 ? h->num_cu : 1;
   *engine = 2;
@@ -646,16 +647,19 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
     *grid = 1;
     return BISIM_OK;
   }
-  if (learned || h->iter_limit > 0 || arena_active() || !rounds_apply(h)) return BISIM_OK;
+  if (learned || h->iter_limit > 0 || arena_active()) return BISIM_OK;
+  const bool rounds = rounds_apply(h);
   if (h->algorithm == 2) {
-    if (h->n <= kRcppRoundsStates && h->m <= kOneWGTransitions) *engine = 3;
+    if (rounds && h->n <= kRcppRoundsStates && h->m <= kOneWGTransitions) *engine = 3;
     return BISIM_OK;
   }
   if (h->n < kTuneMinStates || h->start_override) {
-    *engine = 3;
+    if (rounds) *engine = 3;
     return BISIM_OK;
   }
-  const std::string key = lts_tune_key(h);
+  if (!rounds && (h->trace_cap > 0 || h->first_splitter >= 0 || h->profile_every > 0))
+    return BISIM_OK;
+  const std::string key = lts_tune_key(h, rounds);
   int e = 0, g = 0;
   if (lts_tune_lookup(key, &e, &g)) {
     *engine = e;
@@ -665,7 +669,10 @@ static bisim_status choose_engine(bisim_lts* h, int* engine, int* grid) {
   struct Cand {
     int engine, grid;
   };
-  const Cand cands[] = {{3, cu * 4}, {3, cu * 8}};
+  // (in lock step either engine may be the faster one)
+  const std::vector<Cand> cands =
+      rounds ? std::vector<Cand>{{3, cu * 4}, {3, cu * 8}}
+             : std::vector<Cand>{{2, cu * 4}, {2, cu * 8}, {2, cu * 16}, {3, cu * 4}, {3, cu * 8}};
   const int saved_engine = h->engine, saved_grid = h->grid;
   const int64_t saved_limit = h->iter_limit;
   float best = 1e30f;

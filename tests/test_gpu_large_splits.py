@@ -151,3 +151,24 @@ def test_dense_no_slower_than_scans(B, case):
         assert st.iterations == ref.iterations
     print(f"[large splits] {case}: {auto:.2f} ms by {ran}, engine 2 {scans:.2f}", flush=True)
     assert auto < 1.5 * scans + 0.3
+
+
+def test_many_actions_choose_between_the_engines(B, monkeypatch, tmp_path):
+    """States of more than 64 actions go in lock step: from 200,000 states on
+    engines 2 and 3 are both timed on the first iterations, once."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("BISIM_TUNE_CACHE", str(cache))
+    L = gen.uniform_lts(2000, 3.0, 90, seed=6)
+    hub = np.arange(80)  # one state with 80 actions, and others without any
+    L = gen.LTS(300_000, 90, np.concatenate([L.src, np.zeros(80, int)]),
+                np.concatenate([L.lab, hub]), np.concatenate([L.dst, hub * 97 % L.n]))
+    ks, nb = oracle.ks_coarsest(L.n, L.K, L.src, L.lab, L.dst)
+    dev = [B.DeviceArray.from_numpy(a, np.int32) for a in (L.src, L.lab, L.dst)]
+    with B.LTS(*dev, L.n, L.K, None) as h:
+        for _ in range(2):
+            out, st = h.run()
+            assert (out.numpy() == ks).all() and st.blocks == nb
+            engine, grid = h.run_config()
+            chosen = [x.split() for x in cache.read_text().splitlines()]
+            assert len(chosen) == 1 and chosen[0][1:3] == [str(engine), str(grid)]
+            assert chosen[0][0].startswith("lts_") and "rounds" not in chosen[0][0]
