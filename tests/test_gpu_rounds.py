@@ -186,3 +186,17 @@ def test_batch_rounds_default_workgroup(B, lds):
     for k, L in enumerate(insts):
         ref = oracle.alg3_trace(L.n, L.K, L.src, L.lab, L.dst, L.init)
         assert (blocks[k] == ref["block"]).all() and its[k] == ref["iters"], (k, L.name)
+
+
+@pytest.mark.parametrize("lds", [0, 1024, 1 << 14, 40000])
+def test_mixed_batch_default_workgroup(B, lds):
+    """Uneven instances, empty ones among them, at the default 1024 threads."""
+    from test_gpu_batch import mixed_instances, check as check_batch
+    insts = mixed_instances()
+    with B.Batch(insts) as b:
+        b.set_option(B.BOPT_LDS_LIMIT, lds)
+        b.set_option(B.BOPT_GRID, 7)
+        out, its, st = b.run()
+        blocks = b.split(out.numpy())
+    assert st["workgroup_size"] == 1024
+    check_batch(B, insts, blocks, its)
