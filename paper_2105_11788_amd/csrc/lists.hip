@@ -682,7 +682,7 @@ __global__ void k_l_zero(LArgs a) {
 // workgroup's kSetupRun states, then once per workgroup and block (a run of 5M
 // states in two blocks: 115 ms with an atomic per state, 2.1 with one per
 // wave, 0.4 so).
-constexpr uint32_t kSetupPer = 8, kSetupRun = kSetupPer * kLT, kSetupSlots = 1024;
+constexpr uint32_t kSetupPer = 4, kSetupRun = kSetupPer * kLT, kSetupSlots = 1024;
 struct SetupTable {
   uint32_t key[kSetupSlots], count[kSetupSlots];
 };

@@ -88,7 +88,9 @@ constexpr uint32_t kWideCap = 8;     // blocks split by what stays, at a time
 constexpr uint32_t kGridMembers = 1u << 18;
 constexpr uint32_t kOwnBlock = 128;  // members up to which a wave takes a listed block alone
 constexpr uint32_t kScanU = 2;       // states or transitions in flight per thread
-constexpr uint32_t kWideU = 4;       // members of a wide block in flight per thread
+// members of a wide block in flight per thread
+template <int kMode, bool kBm>
+constexpr uint32_t wide_u() { return kMode == 2 && !kBm ? 2 : 4; }
 // transitions per thread and round
 template <int WG>
 constexpr uint32_t edges_per_thread() { return WG >= 512 ? 2 : 4; }
@@ -626,7 +628,7 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
   };
   // split tables (LDS that does not hold them: the global path), then the table
   constexpr uint32_t kSmall = small_split<WG>(), kB = 2u * kSmall, kBShift = 32 - log2_u32(kB);
-  constexpr uint32_t kOutU = out_u<MaskT, kMode, kBm>();
+  constexpr uint32_t kOutU = out_u<MaskT, kMode, kBm>(), kWideU = wide_u<kMode, kBm>();
   constexpr uint32_t EU = edges_per_thread<WG>(), kChunks = EU * WG / kWave;
   static_assert(kChunks <= kWave && kWaves >= 2, "one chunk of transitions per lane");
   const bool small_ok = split_bytes<WG>() + table_bytes<MaskT>(256) <= rbytes;
@@ -1424,9 +1426,17 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       for (uint32_t u = 0; u < EU; ++u) {
         if ((wid + u * kWaves) * kWave >= E) continue;  // wave-uniform
         bool mine = sl[u] != kNone && (ek[u] >> kKeyBits) == f && mv[u] != 0;
-        if (__builtin_expect(wides != 0, 0))
-          for (uint32_t w = wides; w; w &= w - 1)
-            mine = mine && eb[u] != sh.wb[__ffs((int)w) - 1];
+        if (__builtin_expect(wides != 0, 0)) {
+          bool wide = false;
+          for (uint32_t w = wides; w; w &= w - 1) wide |= eb[u] == sh.wb[__ffs((int)w) - 1];
+          wide = wide && mine;
+          const uint32_t i = list_push(&sh.nT, wide && lmv[u] == mv[u]);  // it stays
+          if (i != kNone) {
+            a.ts[i] = (int32_t)es[u];
+            a.tb[i] = (int32_t)eb[u];
+          }
+          mine = mine && !wide;
+        }
         const bool sp = mine && es[u] != eb[u] && lmv[u] != mv[u];
         const bool pt = mine && part[u];
         const uint64_t sbal = __ballot(sp), pbal = __ballot(pt);
@@ -1451,11 +1461,10 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
       });
       __syncthreads();
     }
-    // ---- wide blocks: the members that stay are touched states of the table,
-    // each in a thread's hands, and by far the most members are untouched.  So
-    // the block is gone through twice, for its smallest split state and to
-    // relabel, and the few that stay get their label back and go to the front.
-    // No member is listed.
+    // ---- wide blocks: the members that stay are touched states, and listed;
+    // by far the most members are untouched.  So the block is gone through
+    // twice, for its smallest split state and to relabel, and the few that stay
+    // get their label back and go to the front.
     for (uint32_t w = wides; __builtin_expect(w != 0, 0); w &= w - 1) {
       const uint32_t j = (uint32_t)__ffs((int)w) - 1;
       const uint32_t b = uniform_u32(sh.wb[j]), l = uniform_u32(sh.wlo[j]), z = uniform_u32(sh.wsz[j]);
@@ -1470,13 +1479,11 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
         sh.wstay = sh.wfront = sh.wback = 0;
       }
       __syncthreads();
-      bool st[EU];
+      const uint32_t nT = uniform_u32(sh.nT);
       uint32_t kept = 0;
-#pragma unroll
-      for (uint32_t u = 0; u < EU; ++u) {
-        st[u] = sl[u] != kNone && (ek[u] >> kKeyBits) == f && eb[u] == b && mv[u] == lm;
-        kept += (uint32_t)__popcll(__ballot(st[u]));
-      }
+      for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG)
+        kept += (uint32_t)__popcll(
+            __ballot(i0 + lane() < nT && (uint32_t)a.tb[min(i0 + lane(), nT - 1)] == b));
       if (lane() == 0 && kept) atomicAdd(&sh.wstay, kept);
       // (only a member below the least one so far is looked up)
       for (uint32_t i0 = wid * kWave; i0 < z; i0 += kWideU * WG) {
@@ -1514,15 +1521,16 @@ __device__ __forceinline__ uint32_t rounds_loop(const RoundsArgs<MaskT>& a, Roun
           if (v[u] != kNone) a.blk[v[u]] = (int32_t)nl;
       }
       __syncthreads();
-#pragma unroll
-      for (uint32_t u = 0; u < EU; ++u) {
-        if (__ballot(st[u]) == 0) continue;
+      for (uint32_t i0 = wid * kWave; i0 < nT; i0 += WG) {
+        const uint32_t i = min(i0 + lane(), nT - 1);
+        const bool on = i0 + lane() < nT && (uint32_t)a.tb[i] == b;
         uint32_t p = 0;
-        if (st[u]) {
-          a.blk[es[u]] = (int32_t)b;
-          p = (uint32_t)a.pos[es[u]];
+        if (on) {
+          const uint32_t s = (uint32_t)a.ts[i];
+          a.blk[s] = (int32_t)b;
+          p = (uint32_t)a.pos[s];
         }
-        const uint32_t y = list_push(&sh.wback, st[u] && p >= l + t);
+        const uint32_t y = list_push(&sh.wback, on && p >= l + t);
         if (y != kNone) a.sfi[y] = (int32_t)p;
       }
       for (uint32_t i0 = wid * kWave; i0 < t; i0 += WG) {
