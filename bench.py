@@ -156,10 +156,41 @@ def lists_bytes(n: int, iters: int, w: dict):
     return [mark / it, comp / it, spl / it]
 
 
-def batch_bytes(sizes, st, mask_bytes: int):
+def rounds_bytes(sizes, st, mask_bytes: int):
     """Bytes the batched kernel moves in one launch, from its work totals
-    (st["work"], per tier) and a byte model of its global-memory loads,
-    stores and atomics (an atomic counts its read and its write):
+    (st["work"], over both size classes: all instances are refined the same
+    way) and a byte model of its global-memory loads and stores:
+      per state      108 + mask at set-up and at the end (start and result
+                     label, block id, counters and bids cleared, member counts
+                     and places by one add per wave and block, range ends, the
+                     member list with positions and in-transition ranges, mark
+                     word cleared, tracked entry)
+      per member     8 (in-transition range) of a label marked
+      per transition 20 into it (source, action rank, the source's block and
+                     the range it would lead)
+      per member     4 visited for being untouched
+      per split state 68 (position, the block's range, the state in its tail
+                     place with its in-transition range, the label; then the
+                     swap of two states with their ranges, counted for every
+                     split state though only those in front of the tail swap)
+      per new block  12 (ranges)
+    Label bitmaps, marks and the tables of a split are in LDS and count
+    nothing; nor do the transitions by source that a tracked label's lost
+    states are looked up in, which the totals do not name."""
+    w0, w1 = (np.asarray(w, np.float64) for w in st["work"])
+    n = float(np.sum(sizes))
+    members, transitions = w0[1] + w1[1], w0[2] + w1[2]
+    visited, split, blocks = w1[5], w0[5] + w1[6], w1[7]
+    return (108.0 + mask_bytes) * n + 8.0 * members + 20.0 * transitions + 4.0 * visited \
+        + 68.0 * split + 12.0 * blocks
+
+
+def batch_bytes(sizes, st, mask_bytes: int):
+    """Bytes of a batched kernel that goes one iteration at a time, with a tier
+    of instances held in LDS and one of member lists, from its work totals
+    (st["work"], per tier) and a byte model of its global-memory loads, stores
+    and atomics (an atomic counts its read and its write); the library's kernel
+    goes by rounds (rounds_bytes):
       both tiers   8 per state (preprocessed label in, result out)
       LDS tier     per iteration only the in-transitions of the splitter
                    leave LDS: 8 per splitter member (in_ptr pair) + 8 per
@@ -649,7 +680,7 @@ def form_batched(bisim, gen, args):
     ms = (time.perf_counter() - t0) * 1000.0 / args.steps
     work = float(sum(x.m * int(i) for x, i in zip(insts, its)))
     mask_bytes = 8 if max(x.K for x in insts) > 32 else 4
-    moved = batch_bytes([x.n for x in insts], st, mask_bytes)
+    moved = rounds_bytes([x.n for x in insts], st, mask_bytes)
     kern_ms = float(np.mean(alg))
     achieved = moved / (kern_ms * 1e-3) / 1e9
     copy_gbs = bisim.copy_bandwidth(1 << 30)
@@ -701,17 +732,17 @@ def form_batched(bisim, gen, args):
                     "traffic": stored_traffic("k_batch", cfg["workload"]),
                     "bytes_per_launch": moved,
                     "bytes_definition": "bytes the batched kernel moves per launch: the byte "
-                                        "model of its global loads, stores and atomics "
-                                        "(bench.py batch_bytes) times its work totals per "
-                                        "tier (splitters marked, also those decided ahead of "
-                                        "their turn); LDS-resident state counts nothing",
+                                        "model of its global loads and stores (bench.py "
+                                        "rounds_bytes) times its work totals (splitters "
+                                        "marked, also those decided ahead of their turn); "
+                                        "bitmaps, marks and split tables in LDS count nothing",
                     "kernel_ms": kern_ms,
                     "measured_copy_GBs": copy_gbs,
-                    "work_totals": {"lds_tier": st["work"][0], "member_list_tier": st["work"][1]},
+                    "work_totals": {"within_lds_budget": st["work"][0], "others": st["work"][1]},
                     "note": "one launch refines every instance; its time is the critical path "
-                            "of the slowest instance (one workgroup, one dependent chain of "
-                            "global-memory round trips per phase), so the kernel is latency-"
-                            "bound and moves little data per second",
+                            "of the slowest instance (one workgroup, whose rounds are chains "
+                            "of dependent trips to the L2 and to memory), so the kernel is "
+                            "latency-bound and moves little data per second",
                 },
                 "plain_one_by_one_estimate_s": plain_est_ms / 1000.0,
                 "speedup_vs_plain": plain_est_ms / ms,
