@@ -245,7 +245,8 @@ __global__ void __launch_bounds__(kPT) k_persistent(Args a) {
 // takes 8 us per iteration against 20 with four kernels (11 with the arrays in
 // global memory); the scans over all states make the kernels faster from about
 // 4000 states on.
-constexpr int kLW = 512;  // (1024 threads: the same time, with registers spilled)
+constexpr int kLW = 512;  // (1024 threads: the same time, and far more than these 12 bytes of
+                          // scratch a lane)
 constexpr int32_t kLearnedWGStates = 2048;
 
 // bytes of the LDS arrays for n states, after the network's weights
