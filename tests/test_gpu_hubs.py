@@ -92,3 +92,20 @@ def test_sink_marked_by_the_grid(B, n, actions, loop):
     print(f"[sink] {n} states, {L.m} transitions: engine 3 {best[3]:.2f} ms, 2 {best[2]:.2f}",
           flush=True)
     assert best[3] < 1.5 * best[2] + 1
+
+
+def test_sink_signature_rounds(B):
+    """The targets of the transitions are written by all waves: one lane takes
+    25 ns for each of a sink's, 0.25 s here; the rounds' sorts and hash tables
+    are a few passes over 10M transitions, below 10 ms at a tenth of the
+    memory's rate."""
+    L = sink(1_000_001, 10)
+    dev = [B.DeviceArray.from_numpy(a, np.int32) for a in (L.src, L.lab, L.dst)]
+    out = B.DeviceArray(L.n, np.int32)
+    with B.LTS(*dev, L.n, L.K, None) as h:
+        h.set_option(B.OPT_ALGORITHM, B.ALGORITHM_SIGNATURE)
+        h.run(out)
+        runs = [timed(lambda: h.run(out))[1] for _ in range(3)]
+    print(f"[sink] signature rounds {min(runs):.1f} ms", flush=True)
+    assert (out.numpy() == np.minimum(np.arange(L.n), 1)).all()
+    assert min(runs) < 100
