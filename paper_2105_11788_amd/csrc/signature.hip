@@ -64,7 +64,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
        i += (int64_t)gridDim.x * blockDim.x)
 
 // (a lane per target took 25 ns for each in-transition of a sink: signature
-// rounds of 1M transitions to one state 25.5 ms, of 10M 253; now 0.3 and 0.9)
+// rounds of 1M transitions to one state 25-28 ms, of 10M 253; now 0.3 and 0.9)
 __global__ void k_targets(int32_t n, const uint32_t* __restrict__ in_ptr,
                           int32_t* __restrict__ tgt) {
   const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) / kWave;
